@@ -289,70 +289,75 @@ __global__ __launch_bounds__(256) void k_pack_dup2d(Splats2DDev sp, CamDev cam, 
     });
 }
 
-constexpr int kAccStride2D = 17;   // floats between the LDS accumulators of consecutive surfels of a batch (odd)
+constexpr int kAccStride2D = 15;   // floats between the LDS accumulators of consecutive surfels of a batch (odd)
 
-// LDS image of one staged batch of kB surfels (kB a multiple of 64, at most the workgroup size)
-template <int kB>
-struct Stage2D {
-    float4 a[kB];   // t0x, t0y, t1x, t1y
-    float4 b[kB];   // t2x, t2y, t2z, log2(opacity)
-    float4 c[kB];   // mx, my, red, green
-    float4 d[kB];   // blue, t0z, t1z, -
-    unsigned long long mask[4][kB / 64];
+// A staged surfel of the forward kernel: 64 bytes, so that one LDS address register serves the four reads of a visit.
+struct StageRec2D {
+    float4 a;   // t0x, t0y, t1x, t1y
+    float4 b;   // t2x, t2y, t2z, log2(opacity)
+    float4 c;   // mx, my, red, green
+    float4 d;   // blue, t0z, t1z, -
 };
 
-// Stage list entries [first, first+count): one per thread. A quadrant is kept for a splat if the bounding box of the
-// image of the disk rim where alpha falls to 1/255 (rho^2 = 2 ln(255 o)), or the low-pass support around the centre,
-// meets the quadrant's pixel centres; taken conservatively. count <= kB. All 256 threads must call it.
+// LDS image of one staged batch of kB surfels of the backward kernel (kB a multiple of 64, at most the workgroup size)
 template <int kB>
-__device__ __forceinline__ void stage_batch2d(Stage2D<kB>& S, const TileCtx& t, const uint32_t* __restrict__ vals,
-                                              const Packed2D* __restrict__ packed, uint32_t first, int count, uint32_t& id,
-                                              float4& r0, float4& r1, float4& r2, float4& r3)
+struct Stage2D {
+    float4 a[kB], b[kB], c[kB], d[kB];     // the parts of StageRec2D
+    unsigned long long mask[4][kB / 64];   // [quadrant][staging wavefront]: which of its 64 splats the quadrant blended
+};
+
+// Can the splat with raster record r0..r3 (L = log2 of its opacity) touch the quadrant whose first pixel centre is
+// (qx0, qy0) with alpha >= 1/255? Yes if the bounding box of the image of the disk rim where alpha falls to 1/255
+// (rho^2 = 2 ln(255 o)), or of the low-pass support around the centre, meets the quadrant's pixel centres; taken
+// conservatively, NaN keeps.
+__device__ __forceinline__ bool quadrant_reach2d(const float4& r0, const float4& r1, const float4& r2, const float4& r3, float L,
+                                                 float qx0, float qy0)
+{
+    const float tau = (L + kLog2_255) * 0.6931471805599453f;      // ln(255 o): alpha >= 1/255 <=> -ln G^ <= tau
+    if (tau < -0.02f) return false;
+    const float rho2 = 2.f * fmaxf(tau, 0.f) + 0.05f;          // rim of the disk part, with margin
+    const float lp = sqrtf(fmaxf(tau, 0.f)) + 0.05f;           // radius of the low-pass part, with margin
+    // image of the rim u^2 + v^2 = rho2, relative to the projected centre: rows T_0', T_1', T_2
+    const float aa = rho2 * (r1.x * r1.x + r1.y * r1.y) - r1.z * r1.z;
+    if (!(aa < -0.02f * r1.z * r1.z)) return true;   // the rim at this level comes (almost) to the camera plane: keep
+    const float ia = 1.0f / aa;
+    const float bx = rho2 * (r0.x * r1.x + r0.y * r1.y) - r3.z * r1.z, by = rho2 * (r0.z * r1.x + r0.w * r1.y) - r3.w * r1.z;
+    const float cx = rho2 * (r0.x * r0.x + r0.y * r0.y) - r3.z * r3.z, cy = rho2 * (r0.z * r0.z + r0.w * r0.w) - r3.w * r3.w;
+    const float c0x = bx * ia, c0y = by * ia;
+    const float hx = sqrtf(fmaxf(0.f, c0x * c0x - cx * ia)) * 1.001f + 0.01f;
+    const float hy = sqrtf(fmaxf(0.f, c0y * c0y - cy * ia)) * 1.001f + 0.01f;
+    const float lx = qx0 - r2.x, ly = qy0 - r2.y;
+    return !((fmaxf(lp, c0x + hx) < lx) || (fminf(-lp, c0x - hx) > lx + 7.f) ||
+             (fmaxf(lp, c0y + hy) < ly) || (fminf(-lp, c0y - hy) > ly + 7.f));
+}
+
+// Backward pass: stage list entries [first, first+count), one per thread; count <= kB. All 256 threads must call it.
+// blend_words: one byte per quadrant and list position, written by the forward pass's wavefront of that quadrant for
+// every position it staged (bit 0: some pixel of the quadrant blended the splat), so the walk visits no splat for
+// nothing and the rim test is not repeated. The bytes of positions a quadrant never came to are stale or zero; its
+// pixels' last indices end before them, so they are never acted on.
+template <int kB>
+__device__ __forceinline__ void stage_batch2d(Stage2D<kB>& S, const uint32_t* __restrict__ vals,
+                                              const Packed2D* __restrict__ packed, const uint32_t* __restrict__ blend_words,
+                                              uint32_t first, int count, uint32_t& id, float4& r0, float4& r1, float4& r2, float4& r3)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool have = (int)threadIdx.x < count;
-    bool reach[4] = {false, false, false, false};
+    uint32_t bits = 0;
     id = 0;
     r0 = r1 = r2 = r3 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (have) {
+    if ((int)threadIdx.x < count) {
         id = vals[first + threadIdx.x];
+        bits = blend_words[first + threadIdx.x];
         const float4* rec = reinterpret_cast<const float4*>(packed + id);
         r0 = rec[0]; r1 = rec[1]; r2 = rec[2]; r3 = rec[3];
-        const float L = __log2f(r1.w);
         S.a[threadIdx.x] = r0;
-        S.b[threadIdx.x] = make_float4(r1.x, r1.y, r1.z, L);
+        S.b[threadIdx.x] = make_float4(r1.x, r1.y, r1.z, __log2f(r1.w));
         S.c[threadIdx.x] = r2;
         S.d[threadIdx.x] = make_float4(r3.x, r3.z, r3.w, 0.f);
-        const float tau = (L + kLog2_255) * 0.6931471805599453f;      // ln(255 o): alpha >= 1/255 <=> -ln G^ <= tau
-        if (!(tau < -0.02f)) {
-            const float rho2 = 2.f * fmaxf(tau, 0.f) + 0.05f;          // rim of the disk part, with margin
-            const float lp = sqrtf(fmaxf(tau, 0.f)) + 0.05f;           // radius of the low-pass part, with margin
-            // image of the rim u^2 + v^2 = rho2, relative to the projected centre: rows T_0', T_1', T_2
-            const float aa = rho2 * (r1.x * r1.x + r1.y * r1.y) - r1.z * r1.z;
-            float lo[2] = {-lp, -lp}, hi[2] = {lp, lp};
-            const bool bounded = aa < -0.02f * r1.z * r1.z;   // else the rim at this level comes (almost) to the camera plane: keep all
-            if (bounded) {
-                const float ia = 1.0f / aa;
-                const float bx = rho2 * (r0.x * r1.x + r0.y * r1.y) - r3.z * r1.z, by = rho2 * (r0.z * r1.x + r0.w * r1.y) - r3.w * r1.z;
-                const float cx = rho2 * (r0.x * r0.x + r0.y * r0.y) - r3.z * r3.z, cy = rho2 * (r0.z * r0.z + r0.w * r0.w) - r3.w * r3.w;
-                const float c0x = bx * ia, c0y = by * ia;
-                const float hx = sqrtf(fmaxf(0.f, c0x * c0x - cx * ia)) * 1.001f + 0.01f;
-                const float hy = sqrtf(fmaxf(0.f, c0y * c0y - cy * ia)) * 1.001f + 0.01f;
-                lo[0] = fminf(lo[0], c0x - hx); hi[0] = fmaxf(hi[0], c0x + hx);
-                lo[1] = fminf(lo[1], c0y - hy); hi[1] = fmaxf(hi[1], c0y + hy);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float qx0 = (float)(t.tx0 + (q & 1) * 8) + 0.5f - r2.x, qy0 = (float)(t.ty0 + (q >> 1) * 8) + 0.5f - r2.y;
-                // keep unless the box lies wholly outside the quadrant's span of pixel centres (NaN keeps)
-                const bool out = (hi[0] < qx0) || (lo[0] > qx0 + 7.f) || (hi[1] < qy0) || (lo[1] > qy0 + 7.f);
-                reach[q] = !bounded || !out;
-            }
-        }
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const unsigned long long m = __ballot(reach[q]);
+        const unsigned long long m = __ballot(((bits >> (8 * q)) & 1u) != 0u);
         if (lane == 0 && wave < kB / 64) S.mask[q][wave] = m;
     }
 }
@@ -377,29 +382,50 @@ __device__ __forceinline__ void eval_pair2d(const float4& a, const float4& b, co
     E.e2 = -kLog2e * (E.dx * E.dx + E.dy * E.dy);
 }
 
+// Forward. As in the 3D kernel, the four wavefronts of a tile do not wait for each other: each stages the list for
+// itself, 64 surfels at a time (one per lane, into its own 4 KB of LDS), tests them against its own quadrant only, stops
+// when its 64 pixels have ended, and leaves for the backward pass which of them it blended.
+constexpr int kFwdBatch2D = 64;
+
 __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
-                                                         float bg0, float bg1, float bg2, float* __restrict__ image,
-                                                         float* __restrict__ final_T, uint32_t* __restrict__ last_idx)
+                                                         uint8_t* __restrict__ blend_bits, float bg0, float bg1, float bg2,
+                                                         float* __restrict__ image, float* __restrict__ final_T,
+                                                         uint32_t* __restrict__ last_idx)
 {
-    __shared__ Stage2D<kBatch> S;
+    __shared__ StageRec2D sRec[4][kFwdBatch2D];
     const TileCtx c = tile_ctx(cam, ranges, tile_order);
-    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    StageRec2D* const rec_w = sRec[wave];
     const float fx = (float)c.px + 0.5f, fy = (float)c.py + 0.5f;
+    // centre of the quadrant's first pixel
+    const float qx0 = (float)(c.tx0 + (wave & 1) * 8) + 0.5f, qy0 = (float)(c.ty0 + (wave >> 1) * 8) + 0.5f;
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
     uint32_t last = 0;
     bool live = c.inside;
-    for (uint32_t base = c.start; base < c.end; base += kBatch) {
-        if (__syncthreads_count(live) == 0) break;
-        const int cnt = (int)min((uint32_t)kBatch, c.end - base);
-        uint32_t id; float4 r0, r1, r2, r3;
-        stage_batch2d(S, c, vals, packed, base, cnt, id, r0, r1, r2, r3);
-        __syncthreads();
-        if (__ballot(live) == 0ull) continue;
+    for (uint32_t base = c.start; base < c.end; base += kFwdBatch2D) {
+        if (__ballot(live) == 0ull) break;           // every pixel of the quadrant has ended
+        const int cnt = (int)min((uint32_t)kFwdBatch2D, c.end - base);
+        bool reach = false;
+        if (lane < cnt) {
+            const uint32_t id = vals[base + lane];
+            const float4* rec = reinterpret_cast<const float4*>(packed + id);
+            const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
+            const float L = __log2f(r1.w);
+            rec_w[lane].a = r0;
+            rec_w[lane].b = make_float4(r1.x, r1.y, r1.z, L);
+            rec_w[lane].c = r2;
+            rec_w[lane].d = make_float4(r3.x, r3.z, r3.w, 0.f);
+            reach = quadrant_reach2d(r0, r1, r2, r3, L, qx0, qy0);
+        }
+        unsigned long long m = __ballot(reach);
+        unsigned long long used = 0ull;              // the splats of the batch that some pixel of the quadrant blends
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const uint32_t pos0 = base - c.start + 1u;
         // alpha of one visit: everything that does not depend on the pixel's running state
         auto eval = [&](int j, float& alpha, bool& ok, float& r, float& g, float& bl) {
-            const float4 a = S.a[j], b = S.b[j], cc = S.c[j], dd = S.d[j];
+            const float4 a = rec_w[j].a, b = rec_w[j].b, cc = rec_w[j].c, dd = rec_w[j].d;
             bl = dd.x; r = cc.z; g = cc.w;
             Pair2D E;
             eval_pair2d(a, b, cc, dd, fx, fy, E);
@@ -407,7 +433,7 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
             alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(b.w + ex));
             ok = (E.p2 != 0.f) && (alpha >= kAlphaMin);
         };
-        auto blend_one = [&](int j, float alpha, bool ok, float r, float g, float bl) {
+        auto blend_one = [&](int j, unsigned long long bit, float alpha, bool ok, float r, float g, float bl) {
             const bool valid = live && ok;
             const float aT = alpha * T;
             const float Tn = T - aT;            // T (1 - alpha), with the product the weight needs anyway
@@ -418,30 +444,33 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
             C0 += r * w; C1 += g * w; C2 += bl * w;
             T = blend ? Tn : T;
             last = blend ? pos0 + (uint32_t)j : last;
+            used |= __ballot(blend) != 0ull ? bit : 0ull;      // scalar work beside the vector chain
         };
-        for (int k = 0; k < 4; ++k) {
-            unsigned long long m = uniform_u64(S.mask[wave][k]);
-            // two visits per trip while there are two (independent alphas, blends in list order), as in the 3D kernel
-            while (m & (m - 1ull)) {
-                const int j0 = k * 64 + __builtin_ctzll(m);
-                m &= m - 1ull;
-                const int j1 = k * 64 + __builtin_ctzll(m);
-                m &= m - 1ull;
-                float al0, red0, grn0, blu0, al1, red1, grn1, blu1;
-                bool ok0, ok1;
-                eval(j0, al0, ok0, red0, grn0, blu0);
-                eval(j1, al1, ok1, red1, grn1, blu1);
-                blend_one(j0, al0, ok0, red0, grn0, blu0);
-                blend_one(j1, al1, ok1, red1, grn1, blu1);
-            }
-            if (m) {
-                const int j0 = k * 64 + __builtin_ctzll(m);
-                float al0, red0, grn0, blu0;
-                bool ok0;
-                eval(j0, al0, ok0, red0, grn0, blu0);
-                blend_one(j0, al0, ok0, red0, grn0, blu0);
-            }
+        // two visits per trip while there are two (independent alphas, blends in list order), as in the 3D kernel
+        while (m & (m - 1ull)) {
+            const unsigned long long bit0 = m & (0ull - m);
+            const int j0 = __builtin_ctzll(m);
+            m &= m - 1ull;
+            const unsigned long long bit1 = m & (0ull - m);
+            const int j1 = __builtin_ctzll(m);
+            m &= m - 1ull;
+            float al0, red0, grn0, blu0, al1, red1, grn1, blu1;
+            bool ok0, ok1;
+            eval(j0, al0, ok0, red0, grn0, blu0);
+            eval(j1, al1, ok1, red1, grn1, blu1);
+            blend_one(j0, bit0, al0, ok0, red0, grn0, blu0);
+            blend_one(j1, bit1, al1, ok1, red1, grn1, blu1);
         }
+        if (m) {
+            const int j0 = __builtin_ctzll(m);
+            float al0, red0, grn0, blu0;
+            bool ok0;
+            eval(j0, al0, ok0, red0, grn0, blu0);
+            blend_one(j0, m, al0, ok0, red0, grn0, blu0);
+        }
+        if (lane < cnt) blend_bits[(size_t)4 * (base + lane) + wave] = (uint8_t)((used >> lane) & 1ull);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();             // the next batch overwrites the staged records
     }
     if (c.inside) {
         const size_t HW = (size_t)cam.W * cam.H;
@@ -457,23 +486,35 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
 // the moments S0 = sum dp, Sx = sum dx dp, Sy = sum dy dp (dx, dy from the projected centre):
 //   sum dL/dh_u = T_2 x Sy - T_1' x S0,   sum dL/dh_v = Sx x T_2 - S0 x T_0',
 //   dT_0 = -sum dL/dh_u, dT_1 = -sum dL/dh_v, dT_2 = mx sum dL/dh_u + my sum dL/dh_v - T_1' x Sx - Sy x T_0'.
-// Together with 3 colour sums, d opacity and the 2 low-pass sums for mean2d: 15 sums per splat, through two row
-// butterflies, an LDS accumulator for the tile and one 64-byte record per (tile, splat) pair.
+// Together with 3 colour sums, sum o G^ dL/dalpha (o times d opacity) and the 2 low-pass sums for mean2d (half of them):
+// 15 sums per splat and one 64-byte record per (tile, splat) pair.
+//
+// The sums over pixels are taken four visits at a time, as in the 3D kernel: a visit stores five numbers per pixel (dp,
+// the blend weight, o G^ dL/dalpha) as rows of 64 floats in LDS and keeps one ballot (which pixels take the disk part);
+// after four visits each row of 16 lanes takes one of them, a lane the numbers of four neighbouring pixels, whose dx, dy
+// and dL/dcolour give its 15 weighted sums, and two row butterflies finish all four visits at once. The kernel is bound by
+// vector issue: that is about 24 instructions a visit where every visit reducing its own 15 products took 55.
+// kRows2D rows and one ballot, not six rows: the LDS then holds four workgroups per compute unit.
 constexpr int kBwdBatch2D = 64;    // surfels staged at a time by the backward kernel: what the per-quadrant accumulators leave room for
 
-__global__ __launch_bounds__(256, 6) void k_composite2d_bwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
+constexpr int kSlots2D = 4;        // visits staged per reduction: one per row of 16 lanes
+constexpr int kRows2D = 5;         // rows a visit stores: dp (3), w, o G^ dL/dalpha
+
+__global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
-                                                         const uint32_t* __restrict__ slot_base, float bg0, float bg1, float bg2,
+                                                         const uint32_t* __restrict__ blend_words, const uint32_t* __restrict__ slot_base,
+                                                         float bg0, float bg1, float bg2,
                                                          const float* __restrict__ final_T, const uint32_t* __restrict__ last_idx,
                                                          const float* __restrict__ dL_dimage, uint32_t cap,
                                                          float4* __restrict__ partial)
 {
     __shared__ Stage2D<kBwdBatch2D> S;
-    // [quadrant][splat of the batch][value], 17 floats apart (odd: the stores of one visit and the per-thread reads at
+    // [quadrant][splat of the batch][value], 15 floats apart (odd: the stores of one visit and the per-thread reads at
     // the end of a batch spread over the LDS banks). A wavefront visits a splat at most once per batch, so it writes its
     // quadrant's sums with plain stores and the thread that staged the splat adds the four up: no LDS float atomics,
     // which cost the LDS about 2.5 cycles per active lane.
     __shared__ float sAcc[4][kAccStride2D * kBwdBatch2D];
+    __shared__ __align__(16) float sV[4][kRows2D * kSlots2D * 64];   // per wavefront: visit slot s has rows kRows2D s ...
     __shared__ uint32_t sMax[4];
     const TileCtx c = tile_ctx(cam, ranges, tile_order);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -511,15 +552,64 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_bwd(CamDev cam, const ui
         }
     }
     if (tile_last == 0) return;
+    float* const sAccW = sAcc[wave];
+    float* const sVw = sV[wave];
+    // In a reduction lane l takes visit slot l / 16 and the four pixels held by the wavefront's lanes 4 pg .. 4 pg + 3,
+    // pg = l % 16: half a pixel row of the quadrant. Their dL/dcolour come from those lanes, through LDS.
+    const int pg = lane & 15;
+    float4 G0, G1, G2;
+    {
+        sVw[lane] = g0; sVw[64 + lane] = g1; sVw[128 + lane] = g2c;
+        __builtin_amdgcn_wave_barrier();
+        G0 = *reinterpret_cast<const float4*>(sVw + 4 * pg);
+        G1 = *reinterpret_cast<const float4*>(sVw + 64 + 4 * pg);
+        G2 = *reinterpret_cast<const float4*>(sVw + 128 + 4 * pg);
+        __builtin_amdgcn_wave_barrier();
+    }
+    // centre of the first of the four pixels; the others follow on the same row
+    const float rx = (float)(c.tx0 + (wave & 1) * 8 + 4 * (pg & 1)) + 0.5f, ry = (float)(c.ty0 + (wave >> 1) * 8 + (pg >> 1)) + 0.5f;
+    const float* const rd_row = sVw + kRows2D * 64 * (lane >> 4) + 4 * pg;
+    float* const wr_row = sVw + lane;
     const bool bit1 = (lane & 2) != 0;
     const int acc_slot = ((lane & 1) ? 8 : 0) + ((lane >> 1) & 7);     // see row_sum8: odd lanes take the second eight sums
-    float* const sAccW = sAcc[wave];
+    int slot_j = 0;                // of this lane's slot: the surfel's position in the batch,
+    uint32_t slot_disk = 0u;       // and the word of the "disk part" ballot that holds its four pixels
+    int nslot = 0;         // visits staged since the last reduction (uniform)
+    // Reduces the staged rows and stores the sums of the first `count` visit slots in their surfels' accumulators.
+    auto reduce_slots = [&](int count) {
+        __builtin_amdgcn_wave_barrier();
+        const int j = slot_j;
+        const uint32_t disk = slot_disk >> (4 * (pg & 7));
+        const float4 d0 = *reinterpret_cast<const float4*>(rd_row);
+        const float4 d1 = *reinterpret_cast<const float4*>(rd_row + 64);
+        const float4 d2 = *reinterpret_cast<const float4*>(rd_row + 128);
+        const float4 w = *reinterpret_cast<const float4*>(rd_row + 192);
+        const float4 e = *reinterpret_cast<const float4*>(rd_row + 256);
+        const float4 cc = S.c[j];
+        __builtin_amdgcn_wave_barrier();
+        const float dx = rx - cc.x, dy = ry - cc.y;
+        const auto sum4 = [](const float4& v) { return (v.x + v.y) + (v.z + v.w); };
+        const auto ramp = [](const float4& v) { return v.y + 2.f * v.z + 3.f * v.w; };      // sum over the pixels dx + i: i v_i
+        const float m0 = sum4(d0), m1 = sum4(d1), m2 = sum4(d2);
+        const float4 l = make_float4((disk & 1u) ? 0.f : e.x, (disk & 2u) ? 0.f : e.y, (disk & 4u) ? 0.f : e.z, (disk & 8u) ? 0.f : e.w);
+        const float lm = sum4(l);
+        const float va[8] = {m0, m1, m2, dx * m0 + ramp(d0), dx * m1 + ramp(d1), dx * m2 + ramp(d2), dy * m0, dy * m1};
+        const float vb[8] = {dy * m2,
+                             w.x * G0.x + w.y * G0.y + w.z * G0.z + w.w * G0.w,
+                             w.x * G1.x + w.y * G1.y + w.z * G1.z + w.w * G1.w,
+                             w.x * G2.x + w.y * G2.y + w.z * G2.z + w.w * G2.w,
+                             sum4(e), dx * lm + ramp(l), dy * lm, 0.f};
+        const float pa = row_sum8(va, bit1);
+        const float pb = row_sum8(vb, bit1);
+        // even lanes of a row keep the first eight sums, odd lanes (their copies) take the second eight
+        if (acc_slot < kAccStride2D && (lane >> 4) < count) sAccW[kAccStride2D * j + acc_slot] = (lane & 1) ? pb : pa;
+    };
     const int nbatch = (int)((tile_last + kBwdBatch2D - 1) / kBwdBatch2D);
     for (int bi = nbatch - 1; bi >= 0; --bi) {
         const uint32_t boff = (uint32_t)bi * kBwdBatch2D;
         const int cnt = (int)min((uint32_t)kBwdBatch2D, tile_last - boff);
         uint32_t id; float4 q0, q1, q2, q3;
-        stage_batch2d(S, c, vals, packed, c.start + boff, cnt, id, q0, q1, q2, q3);
+        stage_batch2d(S, vals, packed, blend_words, c.start + boff, cnt, id, q0, q1, q2, q3);
 #pragma unroll
         for (int k = 0; k < 4 * kAccStride2D * kBwdBatch2D / 256; ++k) (&sAcc[0][0])[k * 256 + threadIdx.x] = 0.f;
         __syncthreads();
@@ -537,11 +627,9 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_bwd(CamDev cam, const ui
                     eval_pair2d(a, b, cc, dd, fx, fy, E);
                     const bool disk = E.e1 > E.e2;                         // which part of the max is active (false for NaN)
                     const float ex = disk ? E.e1 : E.e2;
-                    const float gh = __builtin_amdgcn_exp2f(ex);           // G^
                     const float araw = __builtin_amdgcn_exp2f(b.w + ex);   // o G^
                     const float alpha = fminf(kAlphaMax, araw);
                     const bool hit = (pos <= last) && (E.p2 != 0.f) && (alpha >= kAlphaMin);
-                    if (__ballot(hit) == 0ull) continue;
                     const float ioma = __builtin_amdgcn_rcpf(1.f - alpha);
                     const float Tk = T * ioma;
                     const float w = hit ? alpha * Tk : 0.f;
@@ -550,27 +638,26 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_bwd(CamDev cam, const ui
                     const float da = (hit && araw < kAlphaMax) ? dL_dalpha : 0.f;     // zero where alpha was clamped
                     T = hit ? Tk : T;
                     Sfx += w * cg;
-                    const float d_o = gh * da;
                     const float dgh = araw * da;                             // o G^ dL/dalpha (zero unless hit)
-                    // disk part: dL/du = -u G o dL/dalpha; low-pass part: dL/dmx = 2 dx G2 o dL/dalpha.
+                    // disk part: dL/du = -u G o dL/dalpha; low-pass part (the sums of the reduction): dL/dmx = 2 dx G2 o dL/dalpha.
                     // u, v, 1/p2 are finite wherever the disk part is the active one; elsewhere they are replaced by 0
                     // so that no 0 * inf reaches the sums.
                     const float us = disk ? E.u : 0.f, vs = disk ? E.v : 0.f, ips = disk ? E.ip2 : 0.f;
                     const float du = -us * dgh, dv = -vs * dgh;
-                    const float dmx = disk ? 0.f : 2.f * E.dx * dgh, dmy = disk ? 0.f : 2.f * E.dy * dgh;
-                    const float dp0 = du * ips, dp1 = dv * ips, dp2 = -(du * us + dv * vs) * ips;
-                    const float va[8] = {dp0, dp1, dp2, E.dx * dp0, E.dx * dp1, E.dx * dp2, E.dy * dp0, E.dy * dp1};
-                    const float vb[8] = {E.dy * dp2, w * g0, w * g1, w * g2c, d_o, dmx, dmy, 0.f};
-                    const float pa = row_sum8(va, bit1);
-                    const float pb = row_sum8(vb, bit1);
-                    // even lanes of a row keep the first eight sums, odd lanes (their copies) take the second eight;
-                    // the four rows are added lane by lane, and the 16 lanes of the last row store the sums
-                    const float tot = sum_rows((lane & 1) ? pb : pa);
-                    int acc_base = kAccStride2D * j;
-                    asm volatile("" : "+s"(acc_base));      // keep the product on the scalar unit (as in the 3D kernel)
-                    if (lane >= 48) sAccW[acc_base + acc_slot] = tot;
+                    float* const rows = wr_row + kRows2D * 64 * nslot;
+                    rows[0] = du * ips;
+                    rows[64] = dv * ips;
+                    rows[128] = -(du * us + dv * vs) * ips;
+                    rows[192] = w;
+                    rows[256] = dgh;
+                    const unsigned long long disk_mask = __ballot(disk);
+                    const uint32_t disk_word = pg >= 8 ? (uint32_t)(disk_mask >> 32) : (uint32_t)disk_mask;
+                    slot_j = (lane >> 4) == nslot ? j : slot_j;
+                    slot_disk = (lane >> 4) == nslot ? disk_word : slot_disk;
+                    if (++nslot == kSlots2D) { reduce_slots(kSlots2D); nslot = 0; }
                 }
             }
+            if (nslot) { reduce_slots(nslot); nslot = 0; }
         }
         __syncthreads();
         if ((int)threadIdx.x < cnt) {
@@ -605,8 +692,8 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_bwd(CamDev cam, const ui
                 float4* dst = partial + (size_t)4 * u;
                 dst[0] = make_float4(-dhu[0], -dhu[1], -dhu[2], -dhv[0]);                                     // dT0, dT1.x
                 dst[1] = make_float4(-dhv[1], -dhv[2], mx * dhu[0] + my * dhv[0] + ex[0], mx * dhu[1] + my * dhv[1] + ex[1]);
-                dst[2] = make_float4(mx * dhu[2] + my * dhv[2] + ex[2], acc[13], acc[14],   // dT2.z, d mean2d
-                                     acc[12]);                                                          // d opacity
+                dst[2] = make_float4(mx * dhu[2] + my * dhv[2] + ex[2], 2.f * acc[13], 2.f * acc[14],   // dT2.z, d mean2d
+                                     q1.w > 0.f ? acc[12] / q1.w : 0.f);                                             // d opacity
                 dst[3] = make_float4(acc[9], acc[10], acc[11], 0.f);        // d colour
             }
         }
@@ -786,7 +873,8 @@ hipError_t launch_composite2d_fwd(const CamDev& cam, const Layout& L, char* ws, 
     hipLaunchKernelGGL(k_composite2d_fwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                        reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
                        reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L)),
-                       reinterpret_cast<const Packed2D*>(ws + L.off_packed), bg[0], bg[1], bg[2], image, final_T, last_idx);
+                       reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<uint8_t*>(ws + L.off_reach),
+                       bg[0], bg[1], bg[2], image, final_T, last_idx);
     return hipGetLastError();
 }
 
@@ -800,7 +888,8 @@ hipError_t launch_composite2d_bwd(const CamDev& cam, const Layout& L, char* ws, 
         hipLaunchKernelGGL(k_composite2d_bwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                            reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
                        reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L)),
-                           reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<const uint32_t*>(ws + L.off_slot_base),
+                           reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<const uint32_t*>(ws + L.off_reach),
+                           reinterpret_cast<const uint32_t*>(ws + L.off_slot_base),
                            bg[0], bg[1], bg[2], final_T, last_idx, dL_dimage, L.cap, partial);
     }
     if (n > 0) {

@@ -116,4 +116,46 @@ __device__ __forceinline__ float row_sum16(float v)
     return v;
 }
 
+// ---- bookkeeping of the walks ----------------------------------------------------------------------------------------
+// The walks are bound by issue, scalar instructions included (three more of them a visit cost the 3D forward kernel 7 %),
+// so a visit's bookkeeping is spelled out: the splats left in a wavefront's batch are a 64-bit scalar mask that gives up
+// one bit in one instruction, and which pixels are still open is a scalar lane mask.
+
+// the lowest splat left in the mask, taken out of it (m != 0)
+__device__ __forceinline__ int take_lowest(unsigned long long& m)
+{
+    const int j = __builtin_ctzll(m);
+    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(j));
+    return j;
+}
+
+// the highest splat left in the mask, taken out of it (m != 0)
+__device__ __forceinline__ int take_highest(unsigned long long& m)
+{
+    const int j = 63 - __builtin_clzll(m);
+    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(j));
+    return j;
+}
+
+// One blend in list order. ok: lanes whose alpha counts; live: lanes whose pixel is still open, which is updated by the
+// stop rule. Returns whether this lane blends. (A lane that is not live may set its bit of "stops": it is not live anyway.)
+__device__ __forceinline__ bool blend_decision(unsigned long long& live, bool ok, float Tn)
+{
+    const unsigned long long m = __ballot(ok);
+    live &= ~(m & __ballot(Tn < kTStop));
+    return __builtin_amdgcn_inverse_ballot_w64(live & m);
+}
+
+// Byte offset of a staged record, as a vector value: the address of the visit's LDS reads, and what a lane that blends
+// keeps as its last record (turned into a list position once a batch). Scalar multiply, one vector move; left to itself
+// the compiler forms the address with a 64-bit vector multiply-add, four times the issue slots.
+__device__ __forceinline__ uint32_t staged_offset(uint32_t wave_base, int j, uint32_t stride)
+{
+    uint32_t off = wave_base + (uint32_t)j * stride;
+    asm("" : "+s"(off));
+    uint32_t v;
+    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(off));
+    return v;
+}
+
 }  // namespace pbdr

@@ -531,7 +531,8 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
     uint32_t wmax = last;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, d, 64));
-    if (lane == 0) sMax[wave] = wmax;
+    const uint32_t wlast = __builtin_amdgcn_readfirstlane(wmax);     // the last list position any pixel of the quadrant blended
+    if (lane == 0) sMax[wave] = wlast;
     __syncthreads();
     const uint32_t tile_last = max(max(sMax[0], sMax[1]), max(sMax[2], sMax[3]));
     const int tile_x = c.tix, tile_y = c.tiy;
@@ -572,13 +573,15 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
     float* const wr_row = sVw + lane;
     const bool bit1 = (lane & 2) != 0;
     const int acc_slot = ((lane & 1) ? 8 : 0) + ((lane >> 1) & 7);     // see row_sum8: odd lanes take the second eight sums
-    int slot_j = 0;                // of this lane's slot: the surfel's position in the batch,
-    uint32_t slot_disk = 0u;       // and the word of the "disk part" ballot that holds its four pixels
-    int nslot = 0;         // visits staged since the last reduction (uniform)
+    uint32_t slot_disk = 0u;       // of this lane's slot: the word of the "disk part" ballot that holds its four pixels
+    int nslot = 0;                 // visits staged since the last reduction, and their surfels' positions in the batch,
+    uint32_t slot_pos = 0u;        // a byte each, the newest lowest, as in the 3D kernel
+    static_assert(kSlots2D == 4 && kBwdBatch2D <= 256, "four positions of eight bits");
+    const int slot_shift = 24 - 8 * (lane >> 4);      // of this lane's slot once four are staged
     // Reduces the staged rows and stores the sums of the first `count` visit slots in their surfels' accumulators.
     auto reduce_slots = [&](int count) {
         __builtin_amdgcn_wave_barrier();
-        const int j = slot_j;
+        const int j = (int)((slot_pos << (8 * (kSlots2D - count)) >> slot_shift) & 255u);
         const uint32_t disk = slot_disk >> (4 * (pg & 7));
         const float4 d0 = *reinterpret_cast<const float4*>(rd_row);
         const float4 d1 = *reinterpret_cast<const float4*>(rd_row + 64);
@@ -613,13 +616,15 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
 #pragma unroll
         for (int k = 0; k < 4 * kAccStride2D * kBwdBatch2D / 256; ++k) (&sAcc[0][0])[k * 256 + threadIdx.x] = 0.f;
         __syncthreads();
-        if (wmax > boff) {
+        if (wlast > boff) {
             for (int k = kBwdBatch2D / 64 - 1; k >= 0; --k) {
                 unsigned long long m = uniform_u64(S.mask[wave][k]);
+                // bytes behind the quadrant's last blended splat are stale: such a visit changes no pixel unless its
+                // colour is not finite (0 * inf), so they are not visited
+                const uint32_t here = wlast - boff - (uint32_t)(64 * k);
+                if (here < 64u) m &= (1ull << here) - 1ull;
                 while (m) {
-                    const int bit = 63 - __builtin_clzll(m);
-                    m &= ~(1ull << bit);
-                    const int j = k * 64 + bit;
+                    const int j = k * 64 + take_highest(m);
                     const uint32_t pos = boff + (uint32_t)j + 1u;
                     const float4 a = S.a[j], b = S.b[j], cc = S.c[j], dd = S.d[j];
                     const float blue = dd.x;
@@ -652,7 +657,7 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
                     rows[256] = dgh;
                     const unsigned long long disk_mask = __ballot(disk);
                     const uint32_t disk_word = pg >= 8 ? (uint32_t)(disk_mask >> 32) : (uint32_t)disk_mask;
-                    slot_j = (lane >> 4) == nslot ? j : slot_j;
+                    slot_pos = (slot_pos << 8) | (uint32_t)j;
                     slot_disk = (lane >> 4) == nslot ? disk_word : slot_disk;
                     if (++nslot == kSlots2D) { reduce_slots(kSlots2D); nslot = 0; }
                 }

@@ -238,3 +238,33 @@ def test_caller_supplied_conics_that_are_not_positive_definite():
         # a pixel that sits within rounding of sigma = 0 of an indefinite splat is flagged fragile and carries no loss;
         # what is left must agree
         grad_close("indefinite conics " + k, g[k], rg[k])
+
+
+@pytest.mark.parametrize("count", [1, 2, 3, 4, 5, 63, 64, 65, 127, 128, 130, 259])
+@pytest.mark.parametrize("opacity", [0.03, 0.5])
+def test_walk_of_lists_around_the_batch_and_reduction_sizes(count, opacity):
+    """The compositing walks take splats from a 64-bit mask per batch of 64, two at a time forward, and reduce four at a
+    time backward: list lengths on both sides of each of these, with pixels that stay open (opacity 0.03) and pixels that
+    end at different places within the list (0.5)."""
+    rng = np.random.default_rng(count)
+    w, h = 16, 16
+    st = dict(mean2d=rng.uniform(4, 12, (count, 2)).astype(np.float32),
+              conic=np.tile([0.02, 0.003, 0.03], (count, 1)).astype(np.float32), opacity=np.full(count, opacity, dtype=np.float32),
+              color=rng.uniform(0, 1, (count, 3)).astype(np.float32), radius=np.full(count, 12, dtype=np.int32))
+    got_l, ref_l, view = _lists_case(st, rng.uniform(0.5, 20, count).astype(np.float32), w, h)
+    assert np.array_equal(got_l["vals"], ref_l["vals"])
+    bg = [0.1, 0.2, 0.3]
+    got = view.render_fwd(bg)
+    st64 = {k: np.asarray(v).astype(np.float64) for k, v in st.items() if k != "radius"} | {"radius": st["radius"]}
+    ref = oracle.render_fwd(st64, ref_l, w, h, bg)
+    ok = ref["fragile"] == 0
+    assert ok.mean() > 0.95
+    assert np.abs(got["image"] - ref["image"])[ok].max() <= 1e-4
+    assert np.abs(got["final_T"] - ref["final_T"])[ok].max() <= 1e-4
+    assert np.array_equal(got["last_idx"][ok], ref["last_idx"][ok])
+    G = rng.normal(size=(h, w, 3)).astype(np.float32)
+    G[~ok] = 0.0
+    g = view.render_bwd(bg, G)
+    rg = oracle.render_bwd(st64, ref_l, w, h, bg, G.astype(np.float64))
+    for k in ("mean2d", "conic", "opacity", "color"):
+        grad_close(f"walk of {count} " + k, g[k], rg[k])

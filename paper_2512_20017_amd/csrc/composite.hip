@@ -328,8 +328,9 @@ __global__ __launch_bounds__(256, 7) void k_composite_bwd(CamDev cam, const uint
     const bool add_lane = ninth_lane || (lane & 1) == 0;
     const int acc_slot = ninth_lane ? 8 : (lane >> 1) & 7;
     // The visits staged since the last reduction and their splats' positions in the batch, a byte each, the newest lowest:
-    // one instruction a visit (kept in the lane that stands for the slot it took three, and a cross-lane read per reduction;
-    // 1M points at 1920x1080, forward and backward: 488.6 of 491.9 us before, 531 of 547 after, on two cards).
+    // one instruction a visit (kept in the lane that stands for the slot it took three, and a cross-lane read per reduction:
+    // with one address register for a record's two 16-byte reads, 489 -> 479 us for the forward and backward pass of 1M
+    // points at 1920x1080).
     int nslot = 0;
     uint32_t slot_pos = 0;
     static_assert(kVisitSlots == 4 && kBwdBatch <= 256, "four positions of eight bits");

@@ -495,6 +495,7 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
 // and dL/dcolour give its 15 weighted sums, and two row butterflies finish all four visits at once. The kernel is bound by
 // vector issue: that is about 24 instructions a visit where every visit reducing its own 15 products took 55.
 // kRows2D rows and one ballot, not six rows: the LDS then holds four workgroups per compute unit.
+// 1M disks at 1920x1080, forward and backward: 772.9 -> 715.3 us with this and the forward pass staged per wavefront.
 constexpr int kBwdBatch2D = 64;    // surfels staged at a time by the backward kernel: what the per-quadrant accumulators leave room for
 
 constexpr int kSlots2D = 4;        // visits staged per reduction: one per row of 16 lanes

@@ -291,51 +291,48 @@ __global__ __launch_bounds__(256) void k_pack_dup2d(Splats2DDev sp, CamDev cam, 
 
 constexpr int kAccStride2D = 15;   // floats between the LDS accumulators of consecutive surfels of a batch (odd)
 
-// A staged surfel of the forward kernel: 64 bytes, so that one LDS address register serves the four reads of a visit.
-struct StageRec2D {
-    float4 a;   // t0x, t0y, t1x, t1y
-    float4 b;   // t2x, t2y, t2z, log2(opacity)
-    float4 c;   // mx, my, red, green
-    float4 d;   // blue, t0z, t1z, -
-};
-
-// LDS image of one staged batch of kB surfels of the backward kernel (kB a multiple of 64, at most the workgroup size)
+// LDS image of one staged batch of kB surfels (kB a multiple of 64, at most the workgroup size)
 template <int kB>
 struct Stage2D {
-    float4 a[kB], b[kB], c[kB], d[kB];     // the parts of StageRec2D
-    unsigned long long mask[4][kB / 64];   // [quadrant][staging wavefront]: which of its 64 splats the quadrant blended
+    float4 a[kB];   // t0x, t0y, t1x, t1y
+    float4 b[kB];   // t2x, t2y, t2z, log2(opacity)
+    float4 c[kB];   // mx, my, red, green
+    float4 d[kB];   // blue, t0z, t1z, -
+    unsigned long long mask[4][kB / 64];   // [quadrant][staging wavefront]: which of its 64 splats the quadrant visits
 };
 
-// Can the splat with raster record r0..r3 (L = log2 of its opacity) touch the quadrant whose first pixel centre is
-// (qx0, qy0) with alpha >= 1/255? Yes if the bounding box of the image of the disk rim where alpha falls to 1/255
-// (rho^2 = 2 ln(255 o)), or of the low-pass support around the centre, meets the quadrant's pixel centres; taken
-// conservatively, NaN keeps.
-__device__ __forceinline__ bool quadrant_reach2d(const float4& r0, const float4& r1, const float4& r2, const float4& r3, float L,
-                                                 float qx0, float qy0)
+// Which quadrants of the tile whose first pixel centre is (x0, y0) can the splat with raster record r0..r3 (L = log2 of
+// its opacity) touch with alpha >= 1/255? Bit q for quadrant q. A quadrant is kept if the bounding box of the image of the
+// disk rim where alpha falls to 1/255 (rho^2 = 2 ln(255 o)), or of the low-pass support around the centre, meets its
+// pixel centres; taken conservatively, NaN keeps.
+__device__ __forceinline__ uint32_t tile_reach2d(const float4& r0, const float4& r1, const float4& r2, const float4& r3, float L,
+                                                 float x0, float y0)
 {
     const float tau = (L + kLog2_255) * 0.6931471805599453f;      // ln(255 o): alpha >= 1/255 <=> -ln G^ <= tau
-    if (tau < -0.02f) return false;
+    if (tau < -0.02f) return 0u;
     const float rho2 = 2.f * fmaxf(tau, 0.f) + 0.05f;          // rim of the disk part, with margin
     const float lp = sqrtf(fmaxf(tau, 0.f)) + 0.05f;           // radius of the low-pass part, with margin
     // image of the rim u^2 + v^2 = rho2, relative to the projected centre: rows T_0', T_1', T_2
     const float aa = rho2 * (r1.x * r1.x + r1.y * r1.y) - r1.z * r1.z;
-    if (!(aa < -0.02f * r1.z * r1.z)) return true;   // the rim at this level comes (almost) to the camera plane: keep
+    if (!(aa < -0.02f * r1.z * r1.z)) return 15u;   // the rim at this level comes (almost) to the camera plane: keep
     const float ia = 1.0f / aa;
     const float bx = rho2 * (r0.x * r1.x + r0.y * r1.y) - r3.z * r1.z, by = rho2 * (r0.z * r1.x + r0.w * r1.y) - r3.w * r1.z;
     const float cx = rho2 * (r0.x * r0.x + r0.y * r0.y) - r3.z * r3.z, cy = rho2 * (r0.z * r0.z + r0.w * r0.w) - r3.w * r3.w;
     const float c0x = bx * ia, c0y = by * ia;
     const float hx = sqrtf(fmaxf(0.f, c0x * c0x - cx * ia)) * 1.001f + 0.01f;
     const float hy = sqrtf(fmaxf(0.f, c0y * c0y - cy * ia)) * 1.001f + 0.01f;
-    const float lx = qx0 - r2.x, ly = qy0 - r2.y;
-    return !((fmaxf(lp, c0x + hx) < lx) || (fminf(-lp, c0x - hx) > lx + 7.f) ||
-             (fmaxf(lp, c0y + hy) < ly) || (fminf(-lp, c0y - hy) > ly + 7.f));
+    // a column or row of quadrants is out if it lies wholly beside it
+    const float qx0 = x0 - r2.x, qx1 = (x0 + 8.f) - r2.x, qy0 = y0 - r2.y, qy1 = (y0 + 8.f) - r2.y;
+    const float lo_x = fminf(-lp, c0x - hx), hi_x = fmaxf(lp, c0x + hx), lo_y = fminf(-lp, c0y - hy), hi_y = fmaxf(lp, c0y + hy);
+    const bool left = !(hi_x < qx0 || lo_x > qx0 + 7.f), right = !(hi_x < qx1 || lo_x > qx1 + 7.f);
+    const bool top = !(hi_y < qy0 || lo_y > qy0 + 7.f), bottom = !(hi_y < qy1 || lo_y > qy1 + 7.f);
+    return (left && top ? 1u : 0u) | (right && top ? 2u : 0u) | (left && bottom ? 4u : 0u) | (right && bottom ? 8u : 0u);
 }
 
 // Backward pass: stage list entries [first, first+count), one per thread; count <= kB. All 256 threads must call it.
-// blend_words: one byte per quadrant and list position, written by the forward pass's wavefront of that quadrant for
-// every position it staged (bit 0: some pixel of the quadrant blended the splat), so the walk visits no splat for
-// nothing and the rim test is not repeated. The bytes of positions a quadrant never came to are stale or zero; its
-// pixels' last indices end before them, so they are never acted on.
+// blend_words: one word per list position, a byte per quadrant (bit 0: some pixel of the quadrant blended the splat), so
+// the walk visits no splat for nothing and the rim test is not repeated. The forward pass writes the words of every
+// position that its tile staged, and no pixel's last index lies behind those.
 template <int kB>
 __device__ __forceinline__ void stage_batch2d(Stage2D<kB>& S, const uint32_t* __restrict__ vals,
                                               const Packed2D* __restrict__ packed, const uint32_t* __restrict__ blend_words,
@@ -382,95 +379,123 @@ __device__ __forceinline__ void eval_pair2d(const float4& a, const float4& b, co
     E.e2 = -kLog2e * (E.dx * E.dx + E.dy * E.dy);
 }
 
-// Forward. As in the 3D kernel, the four wavefronts of a tile do not wait for each other: each stages the list for
-// itself, 64 surfels at a time (one per lane, into its own 4 KB of LDS), tests them against its own quadrant only, stops
-// when its 64 pixels have ended, and leaves for the backward pass which of them it blended.
-constexpr int kFwdBatch2D = 64;
+// Forward. The tile's list is staged 256 surfels at a time by the whole workgroup, so that the rim test (126 vector
+// instructions) is made once per tile and splat. Independent wavefronts that stage for themselves, as in the 3D kernel,
+// make it four times: 344 against 333 us at 2M disks on 2600x1463, 169 against 163 at 1M on 1920x1080; they gain only
+// where quadrants end far apart (390 against 424 us at 600k disks on 400x300).
+//
+// The walk also notes for the backward pass which splats its quadrant blended. Bound by instruction issue, it can spare
+// little for that: the lane masks of a visit are kept as scalars, the instruction that forms the mask of blending lanes
+// leaves in the carry whether it is empty, and two additions with carry shift that bit into a 64-bit history, one bit per
+// visit (a ballot of the lane predicate, compare and select took two vector and six scalar instructions a visit). LDS
+// offsets and the last blended position are kept as in the 3D kernel. 1M disks at 1920x1080, this kernel: 179.5 -> 163.3
+// us, and 165.7 for a walk in the compiler's own form that notes nothing.
+constexpr int kFwdBatch2D = 256;
 
 __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
-                                                         uint8_t* __restrict__ blend_bits, float bg0, float bg1, float bg2,
+                                                         uint32_t* __restrict__ blend_words, float bg0, float bg1, float bg2,
                                                          float* __restrict__ image, float* __restrict__ final_T,
                                                          uint32_t* __restrict__ last_idx)
 {
-    __shared__ StageRec2D sRec[4][kFwdBatch2D];
+    __shared__ Stage2D<kFwdBatch2D> S;
+    __shared__ unsigned long long sBlended[4][kFwdBatch2D / 64];     // [quadrant][64 positions of the batch]: blended by some pixel
     const TileCtx c = tile_ctx(cam, ranges, tile_order);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    StageRec2D* const rec_w = sRec[wave];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float fx = (float)c.px + 0.5f, fy = (float)c.py + 0.5f;
-    // centre of the quadrant's first pixel
-    const float qx0 = (float)(c.tx0 + (wave & 1) * 8) + 0.5f, qy0 = (float)(c.ty0 + (wave >> 1) * 8) + 0.5f;
+    const float x0 = (float)c.tx0 + 0.5f, y0 = (float)c.ty0 + 0.5f;     // centre of the tile's first pixel
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
     uint32_t last = 0;
-    bool live = c.inside;
+    unsigned long long live = __ballot(c.inside);
     for (uint32_t base = c.start; base < c.end; base += kFwdBatch2D) {
-        if (__ballot(live) == 0ull) break;           // every pixel of the quadrant has ended
         const int cnt = (int)min((uint32_t)kFwdBatch2D, c.end - base);
-        bool reach = false;
-        if (lane < cnt) {
-            const uint32_t id = vals[base + lane];
+        uint32_t reach = 0u;
+        if ((int)threadIdx.x < cnt) {
+            const uint32_t id = vals[base + threadIdx.x];
             const float4* rec = reinterpret_cast<const float4*>(packed + id);
             const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
             const float L = __log2f(r1.w);
-            rec_w[lane].a = r0;
-            rec_w[lane].b = make_float4(r1.x, r1.y, r1.z, L);
-            rec_w[lane].c = r2;
-            rec_w[lane].d = make_float4(r3.x, r3.z, r3.w, 0.f);
-            reach = quadrant_reach2d(r0, r1, r2, r3, L, qx0, qy0);
+            S.a[threadIdx.x] = r0;
+            S.b[threadIdx.x] = make_float4(r1.x, r1.y, r1.z, L);
+            S.c[threadIdx.x] = r2;
+            S.d[threadIdx.x] = make_float4(r3.x, r3.z, r3.w, 0.f);
+            reach = tile_reach2d(r0, r1, r2, r3, L, x0, y0);
         }
-        unsigned long long m = __ballot(reach);
-        unsigned long long used = 0ull;              // the splats of the batch that some pixel of the quadrant blends
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t pos0 = base - c.start + 1u;
-        // alpha of one visit: everything that does not depend on the pixel's running state
-        auto eval = [&](int j, float& alpha, bool& ok, float& r, float& g, float& bl) {
-            const float4 a = rec_w[j].a, b = rec_w[j].b, cc = rec_w[j].c, dd = rec_w[j].d;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned long long m = __ballot(((reach >> q) & 1u) != 0u);
+            if (lane == 0) S.mask[q][wave] = m;
+        }
+        __syncthreads();
+        uint32_t last_off = ~0u;                     // 16 * place in the batch of the splat the lane blended last
+        uint32_t used_lo = 0u, used_hi = 0u;         // a bit per visit, the newest lowest: some lane blended
+        // alpha of one visit: everything that does not depend on the pixel's running state. ok: lanes whose alpha counts
+        auto eval = [&](uint32_t off, float& alpha, unsigned long long& ok, float& r, float& g, float& bl) {
+            const auto at = [off](const float4* p) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) + off); };
+            const float4 a = at(S.a), b = at(S.b), cc = at(S.c), dd = at(S.d);
             bl = dd.x; r = cc.z; g = cc.w;
             Pair2D E;
             eval_pair2d(a, b, cc, dd, fx, fy, E);
-            const float ex = (E.p2 != 0.f) ? fmaxf(E.e1, E.e2) : -1e30f;
-            alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(b.w + ex));
-            ok = (E.p2 != 0.f) && (alpha >= kAlphaMin);
+            alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(b.w + fmaxf(E.e1, E.e2)));
+            ok = __builtin_amdgcn_ballot_w64(E.p2 != 0.f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
         };
-        auto blend_one = [&](int j, unsigned long long bit, float alpha, bool ok, float r, float g, float bl) {
-            const bool valid = live && ok;
+        auto blend_one = [&](uint32_t off, float alpha, unsigned long long ok, float r, float g, float bl) {
             const float aT = alpha * T;
             const float Tn = T - aT;            // T (1 - alpha), with the product the weight needs anyway
-            const bool stop = valid && (Tn < kTStop);
-            const bool blend = valid && !stop;
-            live = live && !stop;
+            const unsigned long long stop = __builtin_amdgcn_ballot_w64(Tn < kTStop);
+            const unsigned long long valid = live & ok;
+            unsigned long long blending;        // valid and not stop; SCC = any
+            asm("s_andn2_b64 %0, %3, %4\n\ts_addc_u32 %1, %1, %1\n\ts_addc_u32 %2, %2, %2"
+                : "=&s"(blending), "+s"(used_lo), "+s"(used_hi) : "s"(valid), "s"(stop) : "scc");
+            live &= ~(ok & stop);               // (a lane that is not live may be among these: it is not live anyway)
+            const bool blend = __builtin_amdgcn_inverse_ballot_w64(blending);
             const float w = blend ? aT : 0.f;
             C0 += r * w; C1 += g * w; C2 += bl * w;
             T = blend ? Tn : T;
-            last = blend ? pos0 + (uint32_t)j : last;
-            used |= __ballot(blend) != 0ull ? bit : 0ull;      // scalar work beside the vector chain
+            last_off = blend ? off : last_off;
         };
-        // two visits per trip while there are two (independent alphas, blends in list order), as in the 3D kernel
-        while (m & (m - 1ull)) {
-            const unsigned long long bit0 = m & (0ull - m);
-            const int j0 = __builtin_ctzll(m);
-            m &= m - 1ull;
-            const unsigned long long bit1 = m & (0ull - m);
-            const int j1 = __builtin_ctzll(m);
-            m &= m - 1ull;
-            float al0, red0, grn0, blu0, al1, red1, grn1, blu1;
-            bool ok0, ok1;
-            eval(j0, al0, ok0, red0, grn0, blu0);
-            eval(j1, al1, ok1, red1, grn1, blu1);
-            blend_one(j0, bit0, al0, ok0, red0, grn0, blu0);
-            blend_one(j1, bit1, al1, ok1, red1, grn1, blu1);
+        for (int k = 0; k < kFwdBatch2D / 64; ++k) {
+            unsigned long long blended = 0ull;
+            if (live != 0ull) {
+                const unsigned long long reached = uniform_u64(S.mask[wave][k]);
+                unsigned long long m = reached;
+                used_lo = used_hi = 0u;
+                // two visits per trip while there are two (independent alphas, blends in list order), as in the 3D kernel
+                int left = __builtin_popcountll(m);
+                for (; left >= 2; left -= 2) {
+                    const uint32_t o0 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
+                    const uint32_t o1 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
+                    float al0, red0, grn0, blu0, al1, red1, grn1, blu1;
+                    unsigned long long ok0, ok1;
+                    eval(o0, al0, ok0, red0, grn0, blu0);
+                    eval(o1, al1, ok1, red1, grn1, blu1);
+                    blend_one(o0, al0, ok0, red0, grn0, blu0);
+                    blend_one(o1, al1, ok1, red1, grn1, blu1);
+                }
+                if (left) {
+                    const uint32_t o0 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
+                    float al0, red0, grn0, blu0;
+                    unsigned long long ok0;
+                    eval(o0, al0, ok0, red0, grn0, blu0);
+                    blend_one(o0, al0, ok0, red0, grn0, blu0);
+                }
+                // the history back to the visited splats' places: of v visits the one with r before it has bit v - 1 - r
+                const unsigned long long used = ((unsigned long long)used_hi << 32) | used_lo;
+                const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(reached >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)reached, 0u));
+                const int bit = (__builtin_popcountll(reached) - 1 - before) & 63;
+                blended = __ballot(((reached >> lane) & (used >> bit) & 1ull) != 0ull);
+            }
+            if (lane == 0) sBlended[wave][k] = blended;
         }
-        if (m) {
-            const int j0 = __builtin_ctzll(m);
-            float al0, red0, grn0, blu0;
-            bool ok0;
-            eval(j0, al0, ok0, red0, grn0, blu0);
-            blend_one(j0, m, al0, ok0, red0, grn0, blu0);
+        if (last_off != ~0u) last = base - c.start + 1u + last_off / (uint32_t)sizeof(float4);
+        const int open = __syncthreads_count(live != 0ull);
+        if ((int)threadIdx.x < cnt) {
+            uint32_t word = 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) word |= (uint32_t)((sBlended[q][wave] >> lane) & 1ull) << (8 * q);
+            blend_words[base + threadIdx.x] = word;
         }
-        if (lane < cnt) blend_bits[(size_t)4 * (base + lane) + wave] = (uint8_t)((used >> lane) & 1ull);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        __builtin_amdgcn_wave_barrier();             // the next batch overwrites the staged records
+        if (open == 0) break;                        // every pixel of the tile has ended
     }
     if (c.inside) {
         const size_t HW = (size_t)cam.W * cam.H;
@@ -879,7 +904,7 @@ hipError_t launch_composite2d_fwd(const CamDev& cam, const Layout& L, char* ws, 
     hipLaunchKernelGGL(k_composite2d_fwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                        reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
                        reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L)),
-                       reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<uint8_t*>(ws + L.off_reach),
+                       reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<uint32_t*>(ws + L.off_reach),
                        bg[0], bg[1], bg[2], image, final_T, last_idx);
     return hipGetLastError();
 }

@@ -384,3 +384,56 @@ def test_backward_writes_every_per_pair_record_itself():
     for k in PARAM_KEYS:
         assert np.isfinite(gb[k]).all(), k
         np.testing.assert_allclose(gb[k], ga[k], rtol=1e-5, atol=1e-6 * np.abs(ga[k]).max(), err_msg=k)
+
+
+def _image_space_state(rng, centre, sigma, depth, tilt, opacity, cam):
+    """Splat state of disks of `sigma` pixels around `centre`, tilted out of the image plane by up to `tilt` radians."""
+    n = len(centre)
+    f, c = cam["fx"], np.array([cam["cx"], cam["cy"]])
+    mid = np.concatenate([(centre - c) / f, np.ones((n, 1))], 1) * depth[:, None]
+    ang, lean = rng.uniform(0, 2 * np.pi, n), rng.uniform(0, tilt, n)
+    tu = np.stack([np.cos(ang) * np.cos(lean), np.sin(ang) * np.cos(lean), np.sin(lean)], 1)
+    tv = np.stack([-np.sin(ang), np.cos(ang), np.zeros(n)], 1)
+    H = np.stack([tu * (sigma * depth / f)[:, None], tv * (sigma * depth / f)[:, None], mid], 2)      # columns u, v, centre
+    K = np.array([[f, 0, c[0]], [0, f, c[1]], [0, 0, 1]])
+    T = (K @ H).reshape(n, 9).astype(np.float32)
+    return dict(mean2d=(T[:, [2, 5]] / T[:, 8:9]).astype(np.float32), T=T, opacity=np.broadcast_to(opacity, n).astype(np.float32),
+                color=rng.uniform(0, 1, (n, 3)).astype(np.float32), radius=np.full(n, 12, dtype=np.int32),
+                depth=depth.astype(np.float32))
+
+
+def _one_tile_walk_case(count, opacity):
+    """`count` disks over one 16 x 16 tile, every third of them so small that the low-pass is what shows."""
+    rng = np.random.default_rng(count)
+    cam = synth.pinhole(16, 16, 30.0, np.eye(3), [0.0, 0.0, 0.0])
+    sigma = np.where(np.arange(count) % 3 == 2, rng.uniform(0.05, 0.3, count), rng.uniform(1.0, 3.0, count))
+    return cam, _image_space_state(rng, rng.uniform(1, 15, (count, 2)), sigma, rng.uniform(0.5, 20, count), 0.9, opacity, cam)
+
+
+@pytest.mark.parametrize("count", [1, 2, 3, 4, 5, 7, 63, 64, 65, 129, 255, 256, 257, 321, 515])
+@pytest.mark.parametrize("opacity", [0.03, 0.5])
+def test_walk_of_lists_around_the_batch_and_reduction_sizes(count, opacity):
+    """The surfel walks stage 256 (forward) and 64 (backward) splats at a time, take them from 64-bit masks two at a time
+    forward, note which of them a quadrant blended, and reduce the pixels' sums four visits at a time backward: list
+    lengths on both sides of each of these, with pixels that stay open (opacity 0.03) and pixels that end at different
+    places within the list (0.5)."""
+    cam, st = _one_tile_walk_case(count, opacity)
+    view = SurfelView(count, cam, count)
+    view.splats = B.Splats2D.from_numpy(st)
+    lists = oracle.bin_sort(st["mean2d"].astype(np.float64), st["radius"], st["depth"], 16, 16)
+    assert lists["P"] == count
+    got = view.render_fwd(BG)
+    ref = oracle.render_fwd2d(_state64(st), lists, 16, 16, BG)
+    ok = ref["fragile"] == 0
+    assert ok.mean() > 0.95
+    assert np.abs(got["image"] - ref["image"])[ok].max() <= IMG_ATOL
+    assert np.abs(got["final_T"] - ref["final_T"])[ok].max() <= IMG_ATOL
+    assert np.array_equal(got["last_idx"][ok], ref["last_idx"][ok])
+    G = np.random.default_rng(7).normal(size=(16, 16, 3)).astype(np.float32)
+    G[~ok] = 0.0
+    gs = view.render_bwd(BG, G)
+    ref_b = oracle.render_bwd2d(_state64(st), lists, 16, 16, BG, G.astype(np.float64))
+    for r in range(3):
+        _grad_close(f"walk of {count} T{r}", gs["T"][:, 3 * r:3 * r + 3], ref_b["T"][:, 3 * r:3 * r + 3])
+    for k in ("mean2d", "opacity", "color"):
+        _grad_close(f"walk of {count} {k}", gs[k], ref_b[k])

@@ -332,7 +332,7 @@ __device__ __forceinline__ uint32_t tile_reach2d(const float4& r0, const float4&
 // Backward pass: stage list entries [first, first+count), one per thread; count <= kB. All 256 threads must call it.
 // blend_words: one word per list position, a byte per quadrant (bit 0: some pixel of the quadrant blended the splat), so
 // the walk visits no splat for nothing and the rim test is not repeated. The forward pass writes the words of every
-// position that its tile staged, and no pixel's last index lies behind those.
+// position that its tile staged, and no pixel's last index lies behind those, so no word of an earlier call is read here.
 template <int kB>
 __device__ __forceinline__ void stage_batch2d(Stage2D<kB>& S, const uint32_t* __restrict__ vals,
                                               const Packed2D* __restrict__ packed, const uint32_t* __restrict__ blend_words,
@@ -645,10 +645,6 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
         if (wlast > boff) {
             for (int k = kBwdBatch2D / 64 - 1; k >= 0; --k) {
                 unsigned long long m = uniform_u64(S.mask[wave][k]);
-                // bytes behind the quadrant's last blended splat are stale: such a visit changes no pixel unless its
-                // colour is not finite (0 * inf), so they are not visited
-                const uint32_t here = wlast - boff - (uint32_t)(64 * k);
-                if (here < 64u) m &= (1ull << here) - 1ull;
                 while (m) {
                     const int j = k * 64 + take_highest(m);
                     const uint32_t pos = boff + (uint32_t)j + 1u;

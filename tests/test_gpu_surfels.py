@@ -437,3 +437,70 @@ def test_walk_of_lists_around_the_batch_and_reduction_sizes(count, opacity):
         _grad_close(f"walk of {count} T{r}", gs["T"][:, 3 * r:3 * r + 3], ref_b["T"][:, 3 * r:3 * r + 3])
     for k in ("mean2d", "opacity", "color"):
         _grad_close(f"walk of {count} {k}", gs[k], ref_b[k])
+
+
+def _ended_quadrant_case():
+    """One 16 x 16 tile. 40 disks around (3, 3) end every pixel of the first quadrant and leave the far corner of the last
+    one open; behind them come faint disks around (13, 13), from the 65th splat on (the first quadrant's wavefront has left
+    the list by then) in turn with disks that reach into the first quadrant only."""
+    rng = np.random.default_rng(3)
+    n = 240
+    cam = synth.pinhole(16, 16, 30.0, np.eye(3), [0.0, 0.0, 0.0])
+    far = np.arange(n) >= 40
+    behind = (np.arange(n) >= 64) & (np.arange(n) % 2 == 1)
+    centre = np.where((far & ~behind)[:, None], 13.0, 3.0) + rng.uniform(-0.3, 0.3, (n, 2))
+    sigma = np.where(behind, 1.0, np.where(far, 1.5, 5.0))
+    opacity = np.where(behind, 0.5, np.where(far, 0.05, 0.95))
+    return cam, behind, _image_space_state(rng, centre, sigma, 1.0 + 0.01 * np.arange(n), 0.3, opacity, cam)
+
+
+@pytest.mark.parametrize("poison", [0x00, 0xFF])
+def test_backward_does_not_visit_splats_behind_a_quadrants_last_blended_one(poison):
+    """A splat that no pixel of a quadrant blended must not enter that quadrant's backward walk, whatever the workspace held
+    before the forward pass: with a colour that is not finite, one visit turns the quadrant's running sums into NaN
+    (0 * inf). The gradient is that of the same splats with finite colours behind, element for element."""
+    cam, behind, st = _ended_quadrant_case()
+    lists = oracle.bin_sort(st["mean2d"].astype(np.float64), st["radius"], st["depth"], 16, 16)
+    assert lists["P"] == 240 and np.array_equal(lists["vals"], np.arange(240))
+    ref = oracle.render_fwd2d(_state64(st), lists, 16, 16, BG)
+    assert ref["last_idx"][:8, :8].max() <= 40 and ref["last_idx"].max() > 200      # the case is what it claims
+    G = np.random.default_rng(8).normal(size=(16, 16, 3)).astype(np.float32)
+    out = []
+    for value in (0.5, np.inf):
+        view = SurfelView(240, cam, 240)
+        view.ws.fill_(poison)
+        colour = st["color"].copy()
+        colour[behind] = value
+        view.splats = B.Splats2D.from_numpy(dict(st, color=colour))
+        fw = view.render_fwd(BG)
+        assert np.isfinite(fw["image"]).all() and np.array_equal(fw["last_idx"], ref["last_idx"])
+        out.append((fw, view.render_bwd(BG, G)))
+    (fwa, ga), (fwb, gb) = out
+    assert np.array_equal(fwa["image"], fwb["image"])
+    for k in STATE_KEYS:
+        assert np.isfinite(gb[k]).all(), k
+        assert np.array_equal(ga[k], gb[k]), k
+        assert not gb[k][behind].any(), k
+
+
+def test_backward_after_other_views_on_the_same_workspace():
+    """The words the forward pass leaves per list position belong to its own view: a view that ends early, a sparse one and a
+    dense one in turn on one workspace give each the gradient that it gives on a fresh workspace."""
+    sc = synth.random_small_surfels(51, 4000, 1, spread=0.6, ls_mu=-2.0)
+    sc["logit"] = np.full(4000, 2.0, dtype=np.float32)
+    cams = [synth.pinhole(160, 96, fov, *synth.look_at(eye, [0, 0, 0], [0, 1, 0]))
+            for fov, eye in ((25.0, [0.2, 0.1, -2.5]), (80.0, [0.0, 0.4, -4.0]), (50.0, [1.5, 0.1, -2.0]))]
+    scene = B.Scene2D.from_numpy(sc)
+    G = np.random.default_rng(10).normal(size=(96, 160, 3)).astype(np.float32)
+    shared = SurfelView(4000, cams[0], 400000)
+    for cam in cams + cams[:1]:
+        fresh = SurfelView(4000, cam, 400000)
+        shared.cam = cam
+        got = []
+        for view in (shared, fresh):
+            vis = view.preprocess(scene)["radius"] > 0
+            view.render_fwd(BG)
+            got.append(view.render_bwd(BG, G))
+        assert vis.any()
+        for k in STATE_KEYS:
+            assert np.array_equal(got[0][k][vis], got[1][k][vis]), k

@@ -89,22 +89,6 @@ __device__ __forceinline__ float row_sum8(const float v[8], bool bit1)
     return d;
 }
 
-// Adds the four rows of 16 lanes of a wavefront lane by lane; every row ends up with the total.
-// v_permlane16_swap (gfx950) exchanges the odd rows of its first operand with the even rows of its second, in both
-// registers: from two copies of v = [r0 r1 r2 r3] it leaves [r0 r0 r2 r2] and [r1 r1 r3 r3], whose sum holds r0 + r1 in
-// rows 0, 1 and r2 + r3 in rows 2, 3. v_permlane32_swap does the same with the halves of the wavefront. Written as
-// assembly because both registers are results (the compiler's builtin hands back only one of them correctly); the
-// s_nop covers the wait states between a VALU write of an operand and the swap.
-__device__ __forceinline__ float sum_rows(float v)
-{
-    float a = v, b = v;
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    const float s = a + b;
-    a = s; b = s;
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    return a + b;
-}
-
 // sum over each row of 16 lanes, left in every lane of the row: partners lane ^ 1, ^ 2, ^ 7 (within eight), ^ 15
 __device__ __forceinline__ float row_sum16(float v)
 {

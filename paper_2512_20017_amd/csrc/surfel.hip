@@ -616,18 +616,19 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
         const float4 e = *reinterpret_cast<const float4*>(rd_row + 256);
         const float4 cc = S.c[j];
         __builtin_amdgcn_wave_barrier();
-        const float dx = rx - cc.x, dy = ry - cc.y;
+        // each pixel's own offset (exact near the centre): dx of the first pixel times the sum, plus a ramp over the four,
+        // cancels where the weight sits beside the centre
+        const float dx0 = rx - cc.x, dx1 = rx + 1.f - cc.x, dx2 = rx + 2.f - cc.x, dx3 = rx + 3.f - cc.x, dy = ry - cc.y;
         const auto sum4 = [](const float4& v) { return (v.x + v.y) + (v.z + v.w); };
-        const auto ramp = [](const float4& v) { return v.y + 2.f * v.z + 3.f * v.w; };      // sum over the pixels dx + i: i v_i
+        const auto sum4x = [&](const float4& v) { return (v.x * dx0 + v.y * dx1) + (v.z * dx2 + v.w * dx3); };
         const float m0 = sum4(d0), m1 = sum4(d1), m2 = sum4(d2);
         const float4 l = make_float4((disk & 1u) ? 0.f : e.x, (disk & 2u) ? 0.f : e.y, (disk & 4u) ? 0.f : e.z, (disk & 8u) ? 0.f : e.w);
-        const float lm = sum4(l);
-        const float va[8] = {m0, m1, m2, dx * m0 + ramp(d0), dx * m1 + ramp(d1), dx * m2 + ramp(d2), dy * m0, dy * m1};
+        const float va[8] = {m0, m1, m2, sum4x(d0), sum4x(d1), sum4x(d2), dy * m0, dy * m1};
         const float vb[8] = {dy * m2,
                              w.x * G0.x + w.y * G0.y + w.z * G0.z + w.w * G0.w,
                              w.x * G1.x + w.y * G1.y + w.z * G1.z + w.w * G1.w,
                              w.x * G2.x + w.y * G2.y + w.z * G2.z + w.w * G2.w,
-                             sum4(e), dx * lm + ramp(l), dy * lm, 0.f};
+                             sum4(e), sum4x(l), dy * sum4(l), 0.f};
         const float pa = row_sum8(va, bit1);
         const float pb = row_sum8(vb, bit1);
         // even lanes of a row keep the first eight sums, odd lanes (their copies) take the second eight

@@ -504,3 +504,40 @@ def test_backward_after_other_views_on_the_same_workspace():
         assert vis.any()
         for k in STATE_KEYS:
             assert np.array_equal(got[0][k][vis], got[1][k][vis]), k
+
+
+def _spread_disks(rng, centre, sigma, tilt, opacity):
+    """One disk per tile of a 640 x 640 image, away from its neighbours, its surroundings empty."""
+    cam = synth.pinhole(640, 640, 50.0, np.eye(3), [0.0, 0.0, 0.0])
+    corner = np.stack(np.meshgrid(np.arange(40), np.arange(40)), 2).reshape(-1, 2) * 16.0
+    st = _image_space_state(rng, corner + centre, sigma, rng.uniform(0.5, 20, 1600), tilt, opacity, cam)
+    st["radius"][:] = 6
+    return cam, st
+
+
+def _gradient_and_reference(cam, st, G):
+    lists = oracle.bin_sort(st["mean2d"].astype(np.float64), st["radius"], st["depth"], 640, 640)
+    view = SurfelView(1600, cam, lists["P"])
+    view.splats = B.Splats2D.from_numpy(st)
+    black = [0.0, 0.0, 0.0]
+    view.render_fwd(black)
+    G[oracle.render_fwd2d(_state64(st), lists, 640, 640, black)["fragile"] != 0] = 0.0
+    return view.render_bwd(black, G), oracle.render_bwd2d(_state64(st), lists, 640, 640, black, G.astype(np.float64))
+
+
+@pytest.mark.parametrize("off", [0.02, 0.005])
+def test_low_pass_centre_gradient_keeps_its_precision_beside_the_centre(off):
+    """Sub-pixel disks `off` pixels from a pixel's centre, with a loss on that pixel only: the gradient of the projected
+    centre is one product with that offset. Eight roundings of half a unit in the last place (offset, two exponentials
+    of one unit each, transmittance, weight, products) are 5e-7; a sum about a point three pixels away rounds at three
+    pixels instead of at `off` (1e-5 and 4e-5)."""
+    rng = np.random.default_rng(5)
+    cam, st = _spread_disks(rng, rng.integers(4, 12, (1600, 2)) + 0.5 + rng.choice([-1, 1], (1600, 2)) * off,
+                            np.full(1600, 0.1), 0.3, 0.5)
+    px = np.floor(st["mean2d"]).astype(int)
+    G = np.zeros((640, 640, 3), dtype=np.float32)
+    G[px[:, 1], px[:, 0]] = rng.uniform(0.5, 1.5, (1600, 3))
+    got, ref = _gradient_and_reference(cam, st, G)
+    ok = np.abs(ref["mean2d"]) > 0
+    assert ok.mean() > 0.99
+    assert (np.abs(got["mean2d"] - ref["mean2d"])[ok] / np.abs(ref["mean2d"])[ok]).max() <= 1e-6

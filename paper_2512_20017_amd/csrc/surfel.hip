@@ -511,20 +511,20 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
 // the moments S0 = sum dp, Sx = sum dx dp, Sy = sum dy dp (dx, dy from the projected centre):
 //   sum dL/dh_u = T_2 x Sy - T_1' x S0,   sum dL/dh_v = Sx x T_2 - S0 x T_0',
 //   dT_0 = -sum dL/dh_u, dT_1 = -sum dL/dh_v, dT_2 = mx sum dL/dh_u + my sum dL/dh_v - T_1' x Sx - Sy x T_0'.
-// Together with 3 colour sums, sum o G^ dL/dalpha (o times d opacity) and the 2 low-pass sums for mean2d (half of them):
-// 15 sums per splat and one 64-byte record per (tile, splat) pair.
+// Together with 3 colour sums, sum G^ dL/dalpha (d opacity) and the 2 low-pass sums for mean2d: 15 sums per splat and one
+// 64-byte record per (tile, splat) pair. dp and the low-pass sums leave out the factors o and, the latter, 2; the record
+// has them.
 //
 // The sums over pixels are taken four visits at a time, as in the 3D kernel: a visit stores five numbers per pixel (dp,
-// the blend weight, o G^ dL/dalpha) as rows of 64 floats in LDS and keeps one ballot (which pixels take the disk part);
+// the blend weight, G^ dL/dalpha) as rows of 64 floats in LDS and keeps one ballot (which pixels take the disk part);
 // after four visits each row of 16 lanes takes one of them, a lane the numbers of four neighbouring pixels, whose dx, dy
-// and dL/dcolour give its 15 weighted sums, and two row butterflies finish all four visits at once. The kernel is bound by
-// vector issue: that is about 24 instructions a visit where every visit reducing its own 15 products took 55.
-// kRows2D rows and one ballot, not six rows: the LDS then holds four workgroups per compute unit.
-// 1M disks at 1920x1080, forward and backward: 772.9 -> 715.3 us with this and the forward pass staged per wavefront.
+// and dL/dcolour give its 15 weighted sums, and two row butterflies finish all four visits at once: about 26 vector
+// instructions a visit where every visit reducing its own 15 products took 55. kRows2D rows and one ballot, not six rows:
+// the LDS then holds four workgroups per compute unit.
 constexpr int kBwdBatch2D = 64;    // surfels staged at a time by the backward kernel: what the per-quadrant accumulators leave room for
 
 constexpr int kSlots2D = 4;        // visits staged per reduction: one per row of 16 lanes
-constexpr int kRows2D = 5;         // rows a visit stores: dp (3), w, o G^ dL/dalpha
+constexpr int kRows2D = 5;         // rows a visit stores: dp (3), w, G^ dL/dalpha
 
 __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
@@ -666,18 +666,20 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
                     const float da = (hit && araw < kAlphaMax) ? dL_dalpha : 0.f;     // zero where alpha was clamped
                     T = hit ? Tk : T;
                     Sfx += w * cg;
-                    const float dgh = araw * da;                             // o G^ dL/dalpha (zero unless hit)
-                    // disk part: dL/du = -u G o dL/dalpha; low-pass part (the sums of the reduction): dL/dmx = 2 dx G2 o dL/dalpha.
+                    // G^ by an exponential of its own: the opacity's gradient is the sum of G^ dL/dalpha, and o G^ over o
+                    // carries the rounding of log2(o). The sums below leave o out; the record multiplies them by it.
+                    const float d_o = __builtin_amdgcn_exp2f(ex) * da;       // zero unless hit
+                    // disk part: dL/du = -u o G dL/dalpha; low-pass part (the sums of the reduction): dL/dmx = 2 dx o G2 dL/dalpha.
                     // u, v, 1/p2 are finite wherever the disk part is the active one; elsewhere they are replaced by 0
                     // so that no 0 * inf reaches the sums.
                     const float us = disk ? E.u : 0.f, vs = disk ? E.v : 0.f, ips = disk ? E.ip2 : 0.f;
-                    const float du = -us * dgh, dv = -vs * dgh;
+                    const float du = -us * d_o, dv = -vs * d_o;
                     float* const rows = wr_row + kRows2D * 64 * nslot;
                     rows[0] = du * ips;
                     rows[64] = dv * ips;
                     rows[128] = -(du * us + dv * vs) * ips;
                     rows[192] = w;
-                    rows[256] = dgh;
+                    rows[256] = d_o;
                     const unsigned long long disk_mask = __ballot(disk);
                     const uint32_t disk_word = pg >= 8 ? (uint32_t)(disk_mask >> 32) : (uint32_t)disk_mask;
                     slot_pos = (slot_pos << 8) | (uint32_t)j;
@@ -699,9 +701,10 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
                     const int e = kAccStride2D * (int)threadIdx.x + k;
                     acc[k] = (sAcc[0][e] + sAcc[1][e]) + (sAcc[2][e] + sAcc[3][e]);
                 }
-                const float s0[3] = {acc[0], acc[1], acc[2]};
-                const float sx[3] = {acc[3], acc[4], acc[5]};
-                const float sy[3] = {acc[6], acc[7], acc[8]};
+                const float o = q1.w;
+                const float s0[3] = {o * acc[0], o * acc[1], o * acc[2]};
+                const float sx[3] = {o * acc[3], o * acc[4], o * acc[5]};
+                const float sy[3] = {o * acc[6], o * acc[7], o * acc[8]};
                 const float t0[3] = {q0.x, q0.y, q3.z}, t1[3] = {q0.z, q0.w, q3.w}, t2[3] = {q1.x, q1.y, q1.z};
                 const float mx = q2.x, my = q2.y;
                 float dhu[3], dhv[3], ex[3];
@@ -720,8 +723,8 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
                 float4* dst = partial + (size_t)4 * u;
                 dst[0] = make_float4(-dhu[0], -dhu[1], -dhu[2], -dhv[0]);                                     // dT0, dT1.x
                 dst[1] = make_float4(-dhv[1], -dhv[2], mx * dhu[0] + my * dhv[0] + ex[0], mx * dhu[1] + my * dhv[1] + ex[1]);
-                dst[2] = make_float4(mx * dhu[2] + my * dhv[2] + ex[2], 2.f * acc[13], 2.f * acc[14],   // dT2.z, d mean2d
-                                     q1.w > 0.f ? acc[12] / q1.w : 0.f);                                             // d opacity
+                dst[2] = make_float4(mx * dhu[2] + my * dhv[2] + ex[2], 2.f * o * acc[13], 2.f * o * acc[14],   // dT2.z, d mean2d
+                                     acc[12]);                                                          // d opacity
                 dst[3] = make_float4(acc[9], acc[10], acc[11], 0.f);        // d colour
             }
         }

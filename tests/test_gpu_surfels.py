@@ -541,3 +541,21 @@ def test_low_pass_centre_gradient_keeps_its_precision_beside_the_centre(off):
     ok = np.abs(ref["mean2d"]) > 0
     assert ok.mean() > 0.99
     assert (np.abs(got["mean2d"] - ref["mean2d"])[ok] / np.abs(ref["mean2d"])[ok]).max() <= 1e-6
+
+
+def test_opacity_gradient_of_faint_disks_keeps_its_precision():
+    """Disks of opacity 0.008 to 0.06, far from each other. The gradient is a sum of G^ dL/dalpha over the pixels; four
+    roundings a term (exponential, weight, their product, dL/dalpha), each half a unit at most and 0.29 of 2^-23 in the
+    mean square, are 7e-8 before the sum averages them. Formed as (o G^) / o the terms share the rounding of
+    log2(o) + ex, of size 5: 2e-7 in the mean square."""
+    rng = np.random.default_rng(5)
+    cam, st = _spread_disks(rng, 8 + rng.uniform(-1, 1, (1600, 2)), rng.uniform(1.0, 2.0, 1600), 0.5, rng.uniform(0.008, 0.06, 1600))
+    got, ref = _gradient_and_reference(cam, st, rng.uniform(0.5, 1.5, (640, 640, 3)).astype(np.float32))
+    err = (got["opacity"] - ref["opacity"]) / ref["opacity"]
+    assert np.sqrt((err ** 2).mean()) <= 1e-7
+    # an opacity that is not finite is clamped everywhere: no gradient reaches it
+    st["opacity"][::7] = np.inf
+    view = SurfelView(1600, cam, 160000)
+    view.splats = B.Splats2D.from_numpy(st)
+    view.render_fwd(BG)
+    assert not view.render_bwd(BG, np.ones((640, 640, 3), dtype=np.float32))["opacity"][::7].any()

@@ -19,8 +19,10 @@ Prints ONE JSON line with the contract fields plus
                    with throughput, dominant kernel, pairs / cull rate, staged parity and the oracle's time on one view.
 """
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -67,17 +69,31 @@ def profiled_traffic(kernel):
     return None
 
 
+def compositing_sources_digest():
+    """Digest of the compositing kernels' sources without comments and layout: a committed counter summary names the one it
+    was taken of."""
+    h = hashlib.sha256()
+    for name in ("composite.hip", "composite_common.h"):
+        text = open(os.path.join(ROOT, "paper_2512_20017_amd", "csrc", name)).read()
+        h.update(" ".join(re.sub(r"//[^\n]*|/\*.*?\*/", " ", text, flags=re.S).split()).encode())
+    return h.hexdigest()[:16]
+
+
 def profiled_valu_cycles(kernel):
     """Vector-ALU issue cycles per launch of `kernel`, summed over the chip's SIMDs, from the committed shader-counter
     summary of the benchmark workload: SQ_INSTS_VALU wavefront instructions at the cost of a plain instruction plus the
     extra cost of the transcendental ones (SQ_INSTS_VALU_TRANS_F32), both costs calibrated on the FMA / exp micro-benchmark
     (profiles/valu_issue_pmc_calibration.txt: a kernel of plain FMAs that keeps every SIMD issuing reads one SQ_INSTS_VALU
     per instruction). DPP and row-swap instructions cost more than a plain one too and have no counter of their own, so
-    this is a lower bound of the kernel's share of the issue capacity. None if a file or the kernel is missing."""
+    this is a lower bound of the kernel's share of the issue capacity. None if a file or the kernel is missing, or if the
+    counters are of other kernels than these sources build (the counts of a longer kernel over a shorter one's time say
+    nothing)."""
     try:
         cal = open(os.path.join(ROOT, "profiles", "valu_issue_pmc_calibration.txt")).read().splitlines()
         rows = open(os.path.join(ROOT, "profiles", "bench_mid_pmc_sq.txt")).read().splitlines()
     except OSError:
+        return None
+    if "sources=" + compositing_sources_digest() not in rows:
         return None
     c_plain = c_trans = None
     for ln in cal:

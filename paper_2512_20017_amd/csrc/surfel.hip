@@ -379,17 +379,17 @@ __device__ __forceinline__ void eval_pair2d(const float4& a, const float4& b, co
     E.e2 = -kLog2e * (E.dx * E.dx + E.dy * E.dy);
 }
 
-// Forward. The tile's list is staged 256 surfels at a time by the whole workgroup, so that the rim test (126 vector
-// instructions) is made once per tile and splat. Independent wavefronts that stage for themselves, as in the 3D kernel,
-// make it four times: 344 against 333 us at 2M disks on 2600x1463, 169 against 163 at 1M on 1920x1080; they gain only
-// where quadrants end far apart (390 against 424 us at 600k disks on 400x300).
+// Forward. The tile's list is staged 256 surfels at a time by the whole workgroup, so that the rim test (over a hundred
+// vector instructions) is made once per tile and splat. Independent wavefronts that stage for themselves, as in the 3D
+// kernel, make it four times: 344 against 333 us at 2M disks on 2600x1463, 169 against 163 at 1M on 1920x1080; they gain
+// only where quadrants end far apart (390 against 424 us at 600k disks on 400x300).
 //
-// The walk also notes for the backward pass which splats its quadrant blended. Bound by instruction issue, it can spare
-// little for that: the lane masks of a visit are kept as scalars, the instruction that forms the mask of blending lanes
-// leaves in the carry whether it is empty, and two additions with carry shift that bit into a 64-bit history, one bit per
-// visit (a ballot of the lane predicate, compare and select took two vector and six scalar instructions a visit). LDS
-// offsets and the last blended position are kept as in the 3D kernel. 1M disks at 1920x1080, this kernel: 179.5 -> 163.3
-// us, and 165.7 for a walk in the compiler's own form that notes nothing.
+// The walk also notes for the backward pass which splats its quadrant blended. Bound by instruction issue (92 % of it at
+// 1M disks, 1920x1080), it can spare little for that: the lane masks of a visit are kept as scalars, the instruction that
+// forms the mask of blending lanes leaves in the carry whether it is empty, and two additions with carry shift that bit
+// into a 64-bit history, one bit per visit (a ballot of the lane predicate, compare and select took two vector and five
+// scalar instructions a visit). LDS offsets and the last blended position are kept as in the 3D kernel. 1M disks at
+// 1920x1080, this kernel: 180.9 -> 162.4 us, and 167.7 for a walk in the compiler's own form that notes nothing.
 constexpr int kFwdBatch2D = 256;
 
 __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
@@ -516,15 +516,17 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
 // has them.
 //
 // The sums over pixels are taken four visits at a time, as in the 3D kernel: a visit stores five numbers per pixel (dp,
-// the blend weight, G^ dL/dalpha) as rows of 64 floats in LDS and keeps one ballot (which pixels take the disk part);
-// after four visits each row of 16 lanes takes one of them, a lane the numbers of four neighbouring pixels, whose dx, dy
-// and dL/dcolour give its 15 weighted sums, and two row butterflies finish all four visits at once: about 26 vector
-// instructions a visit where every visit reducing its own 15 products took 55. kRows2D rows and one ballot, not six rows:
-// the LDS then holds four workgroups per compute unit.
+// the blend weight, G^ dL/dalpha) as rows of 64 floats in LDS; after four visits each row of 16 lanes takes one of them, a
+// lane the numbers of four neighbouring pixels, whose dx, dy and dL/dcolour give its 15 weighted sums, and two row
+// butterflies finish all four visits at once: about 26 vector instructions a visit where every visit reducing its own 15
+// products took 55. Which pixels take the disk part is the sign of their weight, which is never negative itself: one
+// instruction a visit (as a ballot kept in the lanes that need it, five: 380 against 363 us). kRows2D rows, not six: the
+// LDS then holds four workgroups per compute unit. 1M disks at 1920x1080, this kernel: 454 -> 363 us, the blended splats
+// handed over by the forward pass included.
 constexpr int kBwdBatch2D = 64;    // surfels staged at a time by the backward kernel: what the per-quadrant accumulators leave room for
 
 constexpr int kSlots2D = 4;        // visits staged per reduction: one per row of 16 lanes
-constexpr int kRows2D = 5;         // rows a visit stores: dp (3), w, G^ dL/dalpha
+constexpr int kRows2D = 5;         // rows a visit stores: dp (3), signed w, G^ dL/dalpha
 
 __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
@@ -599,7 +601,6 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
     float* const wr_row = sVw + lane;
     const bool bit1 = (lane & 2) != 0;
     const int acc_slot = ((lane & 1) ? 8 : 0) + ((lane >> 1) & 7);     // see row_sum8: odd lanes take the second eight sums
-    uint32_t slot_disk = 0u;       // of this lane's slot: the word of the "disk part" ballot that holds its four pixels
     int nslot = 0;                 // visits staged since the last reduction, and their surfels' positions in the batch,
     uint32_t slot_pos = 0u;        // a byte each, the newest lowest, as in the 3D kernel
     static_assert(kSlots2D == 4 && kBwdBatch2D <= 256, "four positions of eight bits");
@@ -608,7 +609,6 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
     auto reduce_slots = [&](int count) {
         __builtin_amdgcn_wave_barrier();
         const int j = (int)((slot_pos << (8 * (kSlots2D - count)) >> slot_shift) & 255u);
-        const uint32_t disk = slot_disk >> (4 * (pg & 7));
         const float4 d0 = *reinterpret_cast<const float4*>(rd_row);
         const float4 d1 = *reinterpret_cast<const float4*>(rd_row + 64);
         const float4 d2 = *reinterpret_cast<const float4*>(rd_row + 128);
@@ -622,12 +622,12 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
         const auto sum4 = [](const float4& v) { return (v.x + v.y) + (v.z + v.w); };
         const auto sum4x = [&](const float4& v) { return (v.x * dx0 + v.y * dx1) + (v.z * dx2 + v.w * dx3); };
         const float m0 = sum4(d0), m1 = sum4(d1), m2 = sum4(d2);
-        const float4 l = make_float4((disk & 1u) ? 0.f : e.x, (disk & 2u) ? 0.f : e.y, (disk & 4u) ? 0.f : e.z, (disk & 8u) ? 0.f : e.w);
+        const auto unless_disk = [](float ws, float v) { return __float_as_int(ws) < 0 ? 0.f : v; };
+        const float4 l = make_float4(unless_disk(w.x, e.x), unless_disk(w.y, e.y), unless_disk(w.z, e.z), unless_disk(w.w, e.w));
+        const auto sumw = [&](const float4& G) { return fabsf(w.x) * G.x + fabsf(w.y) * G.y + fabsf(w.z) * G.z + fabsf(w.w) * G.w; };
         const float va[8] = {m0, m1, m2, sum4x(d0), sum4x(d1), sum4x(d2), dy * m0, dy * m1};
         const float vb[8] = {dy * m2,
-                             w.x * G0.x + w.y * G0.y + w.z * G0.z + w.w * G0.w,
-                             w.x * G1.x + w.y * G1.y + w.z * G1.z + w.w * G1.w,
-                             w.x * G2.x + w.y * G2.y + w.z * G2.z + w.w * G2.w,
+                             sumw(G0), sumw(G1), sumw(G2),
                              sum4(e), sum4x(l), dy * sum4(l), 0.f};
         const float pa = row_sum8(va, bit1);
         const float pb = row_sum8(vb, bit1);
@@ -678,12 +678,9 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
                     rows[0] = du * ips;
                     rows[64] = dv * ips;
                     rows[128] = -(du * us + dv * vs) * ips;
-                    rows[192] = w;
+                    rows[192] = disk ? -w : w;      // the sign marks the disk part
                     rows[256] = d_o;
-                    const unsigned long long disk_mask = __ballot(disk);
-                    const uint32_t disk_word = pg >= 8 ? (uint32_t)(disk_mask >> 32) : (uint32_t)disk_mask;
                     slot_pos = (slot_pos << 8) | (uint32_t)j;
-                    slot_disk = (lane >> 4) == nslot ? disk_word : slot_disk;
                     if (++nslot == kSlots2D) { reduce_slots(kSlots2D); nslot = 0; }
                 }
             }

@@ -3,12 +3,12 @@
 // lines 12 and 18).
 //
 // One workgroup (4 wavefronts of 64) per 16x16 tile; each wavefront owns one 8x8 pixel quadrant. The tile's
-// depth-sorted list is staged through LDS 256 splats at a time (one 48-byte record per thread). While staging, each
-// thread works out which of the four quadrants its splat can reach at all with alpha >= 1/255 (exact minimum of
-// the quadratic form over the quadrant rectangle, taken conservatively), and the wavefronts ballot these into one
-// 256-bit mask per quadrant. A wavefront then walks only the set bits of its own mask with scalar bit scans, so a
-// splat that cannot touch the quadrant costs it nothing. The cull never changes a result: every visited
-// (pixel, splat) pair still takes the full per-pixel tests.
+// depth-sorted list is staged through LDS 64 splats at a time: forward by each wavefront for itself, backward by the
+// workgroup. While staging, a forward wavefront works out which splats can reach its quadrant at all with alpha >= 1/255
+// (exact minimum of the quadratic form over the quadrant rectangle, taken conservatively), ballots these into a 64-bit
+// mask and leaves them, a byte per position, for the backward pass. The walks visit only the set bits of the mask with
+// scalar bit scans, so a splat that cannot touch the quadrant costs nothing. The cull never changes a result: every
+// visited (pixel, splat) pair still takes the full per-pixel tests.
 //
 // The per-pair arithmetic is branch-free and in the log2 domain: alpha = min(0.99, 2^(log2 o - q(d))) with
 // q = log2(e) * sigma folded into the staged conic. Plain VALU work: no dense contraction, so no MFMA.
@@ -128,9 +128,9 @@ __device__ __forceinline__ void stage_batch_bwd(Stage<kB>& S, const uint32_t* __
 // time (one per lane, into its own 3 KB of LDS), tests them against its own quadrant only, and stops when its 64 pixels
 // have ended. (When the four staged 256 splats together, every batch ended with the quadrants waiting at a barrier for
 // the one with the most splats to visit; the records are read four times now, from L2.)
-// Bound by instruction issue. Masks, record addresses and the last blended position are kept as described at take_lowest;
-// with the approximate reciprocals of the reach test the 1M-point view at 1920x1080, forward only, went 258.2 -> 251.6 us
-// (whole call, this kernel's share of the gain all of it).
+// Bound by instruction issue (88 % of it at 1M points, 1920x1080). Masks, record addresses and the last blended position
+// are kept as described at take_lowest; that and the approximate reciprocals of the reach test took this kernel there
+// from 112.8 to 104.9 us.
 constexpr int kFwdBatch = 64;
 
 __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
@@ -328,9 +328,9 @@ __global__ __launch_bounds__(256, 7) void k_composite_bwd(CamDev cam, const uint
     const bool add_lane = ninth_lane || (lane & 1) == 0;
     const int acc_slot = ninth_lane ? 8 : (lane >> 1) & 7;
     // The visits staged since the last reduction and their splats' positions in the batch, a byte each, the newest lowest:
-    // one instruction a visit (kept in the lane that stands for the slot it took three, and a cross-lane read per reduction.
-    // Forward and backward of 1M points at 1920x1080, all changes to the walks' bookkeeping: 547.2 -> 529.9 us, of which
-    // the forward pass is 6.6).
+    // one instruction a visit (kept in the lane that stands for the slot it took three, and a cross-lane read per reduction;
+    // with the mask and address of a visit as described at take_lowest this kernel went from 214.5 to 203.9 us at 1M points,
+    // 1920x1080).
     int nslot = 0;
     uint32_t slot_pos = 0;
     static_assert(kVisitSlots == 4 && kBwdBatch <= 256, "four positions of eight bits");

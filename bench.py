@@ -712,8 +712,7 @@ def bench_view(args, workload, headline):
             step_on(ctxs[i % args.streams])
         torch.cuda.synchronize()
         t1 = time.perf_counter()
-        # same results as the one-view-in-flight run: the image bit for bit; the gradient to the rounding of the
-        # backward kernel's LDS adds, whose order among a tile's four wavefronts is not fixed
+        # same results as the one-view-in-flight run: image and gradient bit for bit (every sum has a fixed order)
         same_image = all(torch.equal(c["image"], image) for c in ctxs)
         gscale = float(grads.flat.abs().max().item())
         gdiff = max(float((c["grads"].flat - grads.flat).abs().max().item()) for c in ctxs) / max(gscale, 1e-30)
@@ -723,7 +722,7 @@ def bench_view(args, workload, headline):
         del ctxs
 
     # ---- the same step recorded once into a HIP graph and replayed (not `value`): the calls are kernel launches on the
-    # caller's stream and nothing else, so the step can be captured; one graph launch then stands for its ~45 launches
+    # caller's stream and nothing else, so the step can be captured; one graph launch then stands for its 17 launches
     graph_replay = None
     if headline and not args.no_graph and not args.train_step:
         graph = torch.cuda.CUDAGraph()

@@ -170,9 +170,13 @@ __global__ __launch_bounds__(256) void k_pack_dup(SplatsDev sp, CamDev cam, BinA
     const size_t N = (size_t)sp.n;
     pack_dup_block(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth, [&](int i) {
         float4* dst = reinterpret_cast<float4*>(packed + i);
-        dst[0] = make_float4(sp.mean2d[i], sp.mean2d[N + i], sp.conic[i], sp.conic[N + i]);
-        dst[1] = make_float4(sp.conic[2 * N + i], sp.opacity[i], sp.color[i], sp.color[N + i]);
-        dst[2] = make_float4(sp.color[2 * N + i], __int_as_float(sp.radius[i]), sp.depth[i], 0.f);
+        const float qa = sp.conic[i], qb = sp.conic[N + i], qc = sp.conic[2 * N + i], o = sp.opacity[i];
+        const float A = 0.5f * kLog2e * qa, B = kLog2e * qb, C = 0.5f * kLog2e * qc, L = __log2f(o);
+        const bool safe = safely_definite(A, B, C);
+        dst[0] = make_float4(sp.mean2d[i], sp.mean2d[N + i], A, B);
+        dst[1] = make_float4(C, L, sp.color[i], sp.color[N + i]);
+        dst[2] = make_float4(sp.color[2 * N + i], __int_as_float(sp.radius[i]), o, __uint_as_float(safe && o <= 0.98f ? kSplatPlain : 0u));
+        dst[3] = splat_ellipse(A, B, C, L);
     });
 }
 

@@ -5,8 +5,6 @@
 namespace pbdr {
 
 constexpr int kBatch = 256;
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLog2_255 = 7.994353436858858f;
 
 struct TileCtx {
     int px, py;       // this lane's pixel (image coordinates)
@@ -43,6 +41,17 @@ __device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v)
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return ((unsigned long long)hi << 32) | lo;
 }
+
+// Asks for 16 bytes per active lane, from src to the wavefront's 16 * lane bytes behind dst (uniform) in LDS, without a
+// register in between. The issuing wavefront waits with wait_loads() before anybody reads them. (The builtin for this
+// instruction makes the compiler wait for the load before the next LDS read, whatever that reads.)
+__device__ __forceinline__ void load_to_lds16(const void* src, void* dst)
+{
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)dst);
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0" : "=&s"(m0) : "s"(at), "v"(src) : "memory");
+}
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 template <int kCtrl>
 __device__ __forceinline__ float dpp_move(float v)
@@ -87,6 +96,30 @@ __device__ __forceinline__ float row_sum8(const float v[8], bool bit1)
     float d = keep + dpp_move<0x1B>(send);         // quad_perm:[3,2,1,0]
     d += dpp_move<0xB1>(d);                        // quad_perm:[1,0,3,2]
     return d;
+}
+
+// Sums eight values over each quad of lanes: lane r of the quad is left with the sums of values 2 r and 2 r + 1.
+__device__ __forceinline__ void quad_sum8(const float (&v)[8], int quad_lane, float2& out)
+{
+    const bool hi = (quad_lane & 2) != 0, odd = (quad_lane & 1) != 0;
+    float a[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float keep = hi ? v[k + 4] : v[k], send = hi ? v[k] : v[k + 4];
+        a[k] = keep + dpp_move<0x4E>(send);        // quad_perm:[2,3,0,1]
+    }
+    const float k0 = odd ? a[2] : a[0], s0 = odd ? a[0] : a[2], k1 = odd ? a[3] : a[1], s1 = odd ? a[1] : a[3];
+    out.x = k0 + dpp_move<0xB1>(s0);               // quad_perm:[1,0,3,2]
+    out.y = k1 + dpp_move<0xB1>(s1);
+}
+
+// sum over each quad of lanes, in all of them
+__device__ __forceinline__ float quad_sum(float v)
+{
+    asm volatile("" : "+v"(v));   // (as in row_sum16)
+    v += dpp_move<0xB1>(v);
+    v += dpp_move<0x4E>(v);
+    return v;
 }
 
 // sum over each row of 16 lanes, left in every lane of the row: partners lane ^ 1, ^ 2, ^ 7 (within eight), ^ 15

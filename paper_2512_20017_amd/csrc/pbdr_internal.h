@@ -57,13 +57,45 @@ __device__ __forceinline__ void grad_out(float* __restrict__ p, float v)
     else (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Raster record: everything the compositing kernels need about one splat, gathered with three 16-byte loads.
+// Raster record: everything the compositing kernels need about one splat, gathered with 16-byte loads.
 struct __attribute__((aligned(16))) Packed {
-    float mx, my, qa, qb;   // mean2d, conic a, b
-    float qc, o, r, g;      // conic c, opacity, red, green
-    float b, radius_bits, depth, pad2;  // radius_bits: the integer extent, bit-cast
+    float mx, my, A, B;                     // mean2d; the conic in log2 units: A = log2(e)/2 a, B = log2(e) b, C = log2(e)/2 c
+    float C, L, r, g;                       // L = log2(opacity); red, green
+    float b, radius_bits, o, kind_bits;     // blue, the integer extent (bit-cast), opacity, kSplatPlain or 0 (bit-cast)
+    float4 ellipse;                         // splat_ellipse()
 };
-static_assert(sizeof(Packed) == 48, "raster record is 48 bytes");
+static_assert(sizeof(Packed) == 64, "raster record is 64 bytes");
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kLog2_255 = 7.994353436858858f;
+constexpr uint32_t kSplatPlain = 3u;
+
+// What the compositing kernels' cull needs to know about a splat, worked out once per splat: the ellipse of the pixel centres
+// at which alpha >= 1/255, i.e. A dx^2 + B dx dy + C dy^2 <= tau with the conic in log2 units and tau = log2(255 o), as
+//   x: K = tau / (16 A),  y: D = (4 A C - B^2) / (64 A^2),  z: y of its leftmost point (its rightmost lies at -z),  w: B / (8 A),
+// so that its ends in x at height y are -w y -+ sqrt(K - D y^2), in units of four pixels. tau carries a margin: rounding,
+// here, in reached_cells() and in the per-pixel evaluation, is a few 1e-7 of the largest term of the form, which on the
+// ellipse is at most tau 4 A C / (4 A C - B^2). Nothing is reached: K < 0. The form not positive definite, or the numbers
+// out of the range in which this holds (any comparison with a NaN included): everything is reached.
+__device__ __forceinline__ float4 splat_ellipse(float A, float B, float C, float L)
+{
+    const float tau = L + kLog2_255;
+    if (tau < -0.05f) return make_float4(-1.f, 0.f, 0.f, 0.f);
+    const float ac4 = 4.f * A * C, det = ac4 - B * B, cdet = C * det;
+    const bool sound = A > 1e-15f && A < 1e6f && C > 1e-15f && C < 1e6f && det > 2e-6f * ac4 && cdet > 1e-30f && tau < 100.f;
+    if (!sound) return make_float4(1e30f, 0.f, 0.f, 0.f);
+    const float t = fmaxf(tau, 0.f) * (1.f + 8e-6f * (ac4 / det)) + 0.1f;
+    const float i8A = 1.f / (8.f * A);
+    return make_float4(0.5f * t * i8A, det * i8A * i8A, B * sqrtf(t / cdet), B * i8A);
+}
+
+// "positive definite with a margin that rounding cannot bridge": the quadratic form is then never negative and the
+// per-pixel sign test can be left out (see the walk loops)
+__device__ __forceinline__ bool safely_definite(float A, float B, float C)
+{
+    return (A > 0.f) && (C > 0.f) && (4.f * A * C > 1.00001f * (B * B));
+}
 
 struct SceneDev {
     int n, sh_degree;

@@ -268,3 +268,71 @@ def test_walk_of_lists_around_the_batch_and_reduction_sizes(count, opacity):
     rg = oracle.render_bwd(st64, ref_l, w, h, bg, G.astype(np.float64))
     for k in ("mean2d", "conic", "opacity", "color"):
         grad_close(f"walk of {count} " + k, g[k], rg[k])
+
+
+def _forward_backward_against_oracle(label, st, depth, w, h, seed):
+    """Render and its backward on a caller-made state against the oracle: image, last index, and every splat gradient."""
+    got_l, ref_l, view = _lists_case(st, depth, w, h)
+    assert np.array_equal(got_l["vals"], ref_l["vals"])
+    bg = [0.1, 0.2, 0.3]
+    got = view.render_fwd(bg)
+    st64 = {k: np.asarray(v).astype(np.float64) for k, v in st.items() if k != "radius"} | {"radius": st["radius"]}
+    ref = oracle.render_fwd(st64, ref_l, w, h, bg)
+    ok = ref["fragile"] == 0
+    assert ok.mean() > 0.9
+    assert np.abs(got["image"] - ref["image"])[ok].max() <= 1e-4
+    assert np.array_equal(got["last_idx"][ok], ref["last_idx"][ok])
+    G = np.random.default_rng(seed).normal(size=(h, w, 3)).astype(np.float32)
+    G[~ok] = 0.0
+    G[got["last_idx"] != ref["last_idx"]] = 0.0
+    g = view.render_bwd(bg, G)
+    rg = oracle.render_bwd(st64, ref_l, w, h, bg, G.astype(np.float64))
+    listed = np.zeros(len(depth), dtype=bool)      # the gradients of the others are not written
+    listed[ref_l["vals"]] = True
+    for k in ("mean2d", "conic", "opacity", "color"):
+        grad_close(f"{label} {k}", g[k][listed], rg[k][listed])
+
+
+@pytest.mark.parametrize("count", [23, 24, 25, 48, 49, 191, 193, 255, 256, 257, 321, 513])
+def test_lists_around_the_chunk_and_run_sizes(count):
+    """The forward kernel finds the cells of 256 list positions at a time and stages 64 splats, the backward kernel searches
+    256 positions and keeps the sums of 24 visits: lists on both sides of each, every splat on every cell of the tile, and
+    faint, so that no pixel ends early."""
+    rng = np.random.default_rng(count)
+    st = dict(mean2d=rng.uniform(2, 14, (count, 2)).astype(np.float32), conic=np.tile([0.004, 0.001, 0.005], (count, 1)).astype(np.float32),
+              opacity=np.full(count, 0.012, dtype=np.float32), color=rng.uniform(0, 1, (count, 3)).astype(np.float32),
+              radius=np.full(count, 16, dtype=np.int32))
+    _forward_backward_against_oracle(f"{count} splats", st, rng.uniform(0.5, 20, count).astype(np.float32), 16, 16, count)
+
+
+@pytest.mark.parametrize("kind", ["thin", "sub-pixel", "large", "faint", "opaque", "far"])
+def test_cells_that_a_splat_reaches(kind):
+    """The compositing kernels visit only the 4x4 cells that the ellipse alpha >= 1/255 of a splat can reach. Shapes at the
+    limits of that test - long and thin in every direction, smaller than a pixel, larger than the image, an ellipse that all
+    but vanishes (opacity near 1/255), opacities above the clamp, centres far off the image - against the oracle, which
+    tests every pixel of the splat's rectangle."""
+    rng = np.random.default_rng(len(kind))
+    # opaque: a pair leaves 1 - alpha = 0.01 with alpha's 1e-6 on it, 1e-4 of the transmittance recovered from it, so few of them
+    # may lie on top of each other
+    w, h, n = 72, 56, 40 if kind == "opaque" else 400
+    mean = np.stack([rng.uniform(-4, w + 4, n), rng.uniform(-4, h + 4, n)], 1)
+    opacity = rng.uniform(0.05, 0.9, n)
+    # thin: alpha carries three roundings of terms up to log2(e)/2 a dx^2, 530 at the far end of a diagonal ellipse of 9 by
+    # 0.55 px: 1e-4 of itself, which leaves a sum over pixels with cancelling signs within 1e-3
+    long, short = dict(thin=((4, 9), (0.55, 0.7)), large=((40, 300), (30, 200))).get(kind, ((0.55, 4.0), (0.55, 3.0)))
+    if kind == "sub-pixel":
+        long = short = (0.12, 0.4)
+    if kind == "faint":
+        opacity = rng.uniform(1 / 255, 1.2 / 255, n)
+    if kind == "opaque":
+        opacity = rng.uniform(0.96, 1.0, n)
+    s1, s2, a = rng.uniform(*long, n), rng.uniform(*short, n), rng.uniform(0, np.pi, n)
+    if kind == "far":       # a rim of large splats around the image
+        t = rng.uniform(0, 2 * np.pi, n)
+        s1, s2 = rng.uniform(20, 80, n), rng.uniform(15, 60, n)
+        mean = np.stack([w / 2 + 150 * np.cos(t), h / 2 + 150 * np.sin(t)], 1)
+    c, s = np.cos(a), np.sin(a)
+    conic = np.stack([(c / s1) ** 2 + (s / s2) ** 2, c * s * (1 / s1 ** 2 - 1 / s2 ** 2), (s / s1) ** 2 + (c / s2) ** 2], 1)
+    st = dict(mean2d=mean.astype(np.float32), conic=conic.astype(np.float32), opacity=opacity.astype(np.float32),
+              color=rng.uniform(0, 1, (n, 3)).astype(np.float32), radius=np.ceil(3.4 * np.maximum(s1, s2)).astype(np.int32))
+    _forward_backward_against_oracle(kind, st, rng.uniform(0.5, 20, n).astype(np.float32), w, h, n)

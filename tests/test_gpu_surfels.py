@@ -439,6 +439,49 @@ def test_walk_of_lists_around_the_batch_and_reduction_sizes(count, opacity):
         _grad_close(f"walk of {count} {k}", gs[k], ref_b[k])
 
 
+@pytest.mark.parametrize("count, blended", [
+    (300, [0]), (300, [255]), (300, [256]), (257, [0, 255, 256]), (513, [0, 511, 512]),
+    (600, list(range(1, 600, 9))), (512, list(range(0, 512, 8))), (520, list(range(0, 520, 8))),      # 67, 64 and 65 of them
+    (700, list(range(190, 320)) + [512, 699]), (256, list(range(256))),
+    (66000, [3, 40000, 65279, 65280, 65534, 65535, 65536, 65537, 65791, 65792, 65999] + list(range(64700, 65500, 10)))])
+def test_backward_finds_the_blended_entries_of_a_list(count, blended):
+    """The surfel backward kernel searches a tile's list 256 positions at a time for the entries that some quadrant blended
+    and stages 64 of those at a time; positions are kept in 16 bits with their upper half apart. Blended splats on both
+    sides of each of these limits among others that reach no pixel or only the gaps between pixel centres: the gradient is
+    the oracle's and, since a splat's sums do not depend on its place, bit for bit that of a list of the blended ones
+    alone, and zero for the others whatever the workspace held."""
+    rng = np.random.default_rng(count)
+    cam = synth.pinhole(16, 16, 30.0, np.eye(3), [0.0, 0.0, 0.0])
+    shown = np.zeros(count, dtype=bool)
+    shown[blended] = True
+    gap = rng.uniform(size=count) < 0.5      # o exp(-1/2) < 1/255 at the four pixel centres around a corner, o > 1/255
+    centre = np.where(shown[:, None], rng.uniform(1, 15, (count, 2)), rng.integers(2, 15, (count, 2)))
+    st = _image_space_state(rng, centre, np.where(shown, rng.uniform(1.0, 3.0, count), 0.2), 1.0 + 0.001 * np.arange(count), 0.6,
+                            np.where(shown, 0.03, np.where(gap, 0.005, 0.002)), cam)
+    lists = oracle.bin_sort(st["mean2d"].astype(np.float64), st["radius"], st["depth"], 16, 16)
+    assert np.array_equal(lists["vals"], np.arange(count))
+    G = rng.normal(size=(16, 16, 3)).astype(np.float32)
+    G[oracle.render_fwd2d(_state64(st), lists, 16, 16, BG)["fragile"] != 0] = 0.0
+    ref = oracle.render_bwd2d(_state64(st), lists, 16, 16, BG, G.astype(np.float64))
+    out = []
+    for keep in (np.ones(count, dtype=bool), shown):
+        part = {k: v[keep] for k, v in st.items()}
+        view = SurfelView(int(keep.sum()), cam, int(keep.sum()))
+        view.ws.fill_(0xFF)
+        view.splats = B.Splats2D.from_numpy(part)
+        fw = view.render_fwd(BG)
+        out.append((fw, view.render_bwd(BG, G)))
+    (fwa, ga), (fwb, gb) = out
+    assert np.array_equal(fwa["image"], fwb["image"])
+    for k in STATE_KEYS:
+        assert np.array_equal(ga[k][shown], gb[k]), k
+        assert not ga[k][~shown].any(), k
+    for r in range(3):
+        _grad_close(f"{len(blended)} of {count} T{r}", ga["T"][:, 3 * r:3 * r + 3], ref["T"][:, 3 * r:3 * r + 3])
+    for k in ("mean2d", "opacity", "color"):
+        _grad_close(f"{len(blended)} of {count} {k}", ga[k], ref[k])
+
+
 def _ended_quadrant_case():
     """One 16 x 16 tile. 40 disks around (3, 3) end every pixel of the first quadrant and leave the far corner of the last
     one open; behind them come faint disks around (13, 13), from the 65th splat on (the first quadrant's wavefront has left

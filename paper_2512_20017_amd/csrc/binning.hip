@@ -169,13 +169,16 @@ __global__ __launch_bounds__(256) void k_pack_dup(SplatsDev sp, CamDev cam, BinA
 {
     const size_t N = (size_t)sp.n;
     pack_dup_block(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth, [&](int i) {
+        // (every load before the first store: the compiler cannot know that the record overlaps none of the planes)
         float4* dst = reinterpret_cast<float4*>(packed + i);
         const float qa = sp.conic[i], qb = sp.conic[N + i], qc = sp.conic[2 * N + i], o = sp.opacity[i];
+        const float mx = sp.mean2d[i], my = sp.mean2d[N + i], red = sp.color[i], green = sp.color[N + i], blue = sp.color[2 * N + i];
+        const int radius = sp.radius[i];
         const float A = 0.5f * kLog2e * qa, B = kLog2e * qb, C = 0.5f * kLog2e * qc, L = __log2f(o);
         const bool safe = safely_definite(A, B, C);
-        dst[0] = make_float4(sp.mean2d[i], sp.mean2d[N + i], A, B);
-        dst[1] = make_float4(C, L, sp.color[i], sp.color[N + i]);
-        dst[2] = make_float4(sp.color[2 * N + i], __int_as_float(sp.radius[i]), o, __uint_as_float(safe && o <= 0.98f ? kSplatPlain : 0u));
+        dst[0] = make_float4(mx, my, A, B);
+        dst[1] = make_float4(C, L, red, green);
+        dst[2] = make_float4(blue, __int_as_float(radius), o, __uint_as_float(safe && o <= 0.98f ? kSplatPlain : 0u));
         dst[3] = splat_ellipse(A, B, C, L);
     });
 }

@@ -277,15 +277,18 @@ __global__ __launch_bounds__(256) void k_pack_dup2d(Splats2DDev sp, CamDev cam, 
 {
     const size_t N = (size_t)sp.n;
     pack_dup_block(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth, [&](int i) {
+        // (every load before the first store: the compiler cannot know that the record overlaps none of the planes)
         const float mx = sp.mean2d[i], my = sp.mean2d[N + i];
-        const float t2x = sp.T[6 * N + i], t2y = sp.T[7 * N + i], t2z = sp.T[8 * N + i];
+        float t[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) t[k] = sp.T[k * N + i];
+        const float o = sp.opacity[i], red = sp.color[i], green = sp.color[N + i], blue = sp.color[2 * N + i];
+        const int radius = sp.radius[i];
         float4* dst = reinterpret_cast<float4*>(packed + i);
-        dst[0] = make_float4(fmaf(-mx, t2x, sp.T[i]), fmaf(-mx, t2y, sp.T[N + i]), fmaf(-my, t2x, sp.T[3 * N + i]),
-                             fmaf(-my, t2y, sp.T[4 * N + i]));
-        dst[1] = make_float4(t2x, t2y, t2z, sp.opacity[i]);
-        dst[2] = make_float4(mx, my, sp.color[i], sp.color[N + i]);
-        dst[3] = make_float4(sp.color[2 * N + i], __int_as_float(sp.radius[i]), fmaf(-mx, t2z, sp.T[2 * N + i]),
-                             fmaf(-my, t2z, sp.T[5 * N + i]));
+        dst[0] = make_float4(fmaf(-mx, t[6], t[0]), fmaf(-mx, t[7], t[1]), fmaf(-my, t[6], t[3]), fmaf(-my, t[7], t[4]));
+        dst[1] = make_float4(t[6], t[7], t[8], o);
+        dst[2] = make_float4(mx, my, red, green);
+        dst[3] = make_float4(blue, __int_as_float(radius), fmaf(-mx, t[8], t[2]), fmaf(-my, t[8], t[5]));
     });
 }
 

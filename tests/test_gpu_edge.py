@@ -188,6 +188,37 @@ def test_capacity_overflow_is_reported_and_in_bounds():
     assert np.isfinite(out["image"]).all()
 
 
+@pytest.mark.parametrize("w,h", [(640, 480), (5000, 40), (40, 5000)])
+@pytest.mark.parametrize("share", [1.0, 0.37])
+def test_lists_with_points_on_hundreds_of_tiles(w, h, share):
+    """Pairs of a point on 256 tiles or more are written by its whole workgroup, those of the others by their wavefront, which
+    steps over the former: rectangles on both sides of that size and over the whole image, alone, next to each other, at the
+    ends of a wavefront and of a block, in rows longer and shorter than the workgroup - and with room for all pairs and for a
+    part of them only, which is the first ones in point order."""
+    rng = np.random.default_rng(w)
+    n = 900
+    st = _rand_state(rng, n, w, h, rmax=40)
+    r256 = 120 if min(w, h) > 300 else 680      # about 256 tiles: 16 x 16, or three rows of 85
+    sizes = [r256 - 8, r256 - 2, r256 - 1, r256, r256 + 1, r256 + 2, r256 + 7, r256 + 8, 2 * r256, 2000, 100000]
+    at = np.array([0, 1, 2, 63, 64, 200, 255, 256, 300, 383, 384, 385, 386, 387, 511, 512, 640, 899])
+    st["radius"][at] = [sizes[k % len(sizes)] for k in range(len(at))]
+    st["radius"][700:770] = r256 + 4 + np.arange(70) % 9
+    st["mean2d"][700:770] = [w / 2, h / 2] + rng.uniform(-16, 16, (70, 2))
+    depth = rng.uniform(0.3, 50, n).astype(np.float32)
+    ref = oracle.bin_sort(st["mean2d"].astype(np.float64), st["radius"], depth, w, h)
+    count = np.bincount(ref["vals"], minlength=n)
+    assert (count >= 256).sum() > 10 and (count[count > 0] < 256).sum() > 100      # the case is what it claims
+    cap = int(ref["P"] * share)
+    got, _, view = _lists_case(st, depth, w, h, cap=cap)
+    if share == 1.0:
+        assert np.array_equal(got["keys"], ref["keys"]) and np.array_equal(got["vals"], ref["vals"])
+        assert np.array_equal(got["ranges"], ref["ranges"])
+        return
+    assert B.pbdr_query_lists(view.ws, n, w, h, cap) == (ref["P"], True)
+    kept = np.sort(np.lexsort((ref["keys"] >> np.uint64(32), ref["vals"]))[:cap])      # by point, then row by row
+    assert np.array_equal(got["keys"], ref["keys"][kept]) and np.array_equal(got["vals"], ref["vals"][kept])
+
+
 def test_large_radius_covers_whole_image():
     w, h = 200, 120
     st = dict(mean2d=[[100.0, 60.0], [10.0, 10.0]], conic=[[1e-4, 0, 1e-4], [0.05, 0, 0.05]], opacity=[0.6, 0.9],

@@ -343,8 +343,11 @@ __global__ __launch_bounds__(256, 5) void k_composite_bwd(CamDev cam, const uint
     float* const wr_ninth = sSumW + kVisitFloats * (lane >> 4) + 32 + cell;
     // the gradient of every pixel finite: then the products of a lane that a visit does not blend are zero without a select
     const bool finite_pixels = __ballot(!(fabsf(g0) + fabsf(g1) + fabsf(g2c) + fabsf(Sfx) < 1e15f)) == 0ull;
-    // Reduces the staged rows: the sums of slot s go to place i + s of the run.
-    auto reduce_slots = [&](int i) {
+    // Reduces the staged rows: the sums of slot s go to place i + s of the run. finite: the gradient of every pixel is; else a
+    // pixel that did not blend the splat (w = 0) is left out of the colour sums, so that a NaN or an infinity at one pixel
+    // reaches the splats which that pixel blended and no other (a cell's list holds every splat that comes near).
+    auto reduce_slots = [&](auto finite, int i) {
+        const auto term = [](float wk, float g) { return !decltype(finite)::value && wk == 0.f ? 0.f : wk * g; };
         __builtin_amdgcn_wave_barrier();
         const float4 d = *reinterpret_cast<const float4*>(rd_row);
         const float4 w = *reinterpret_cast<const float4*>(rd_row + 64);
@@ -355,9 +358,9 @@ __global__ __launch_bounds__(256, 5) void k_composite_bwd(CamDev cam, const uint
         const float mx = PX * m0 + s1;
         const float mxx = PX * (mx + s1) + s2;                    // sum of ds (PX + i)^2 = PX (PX m0 + 2 s1) + s2
         const float my = PY * m0;
-        const float v8[8] = {w.x * G0.x + w.y * G0.y + w.z * G0.z + w.w * G0.w,
-                             w.x * G1.x + w.y * G1.y + w.z * G1.z + w.w * G1.w,
-                             w.x * G2.x + w.y * G2.y + w.z * G2.z + w.w * G2.w,
+        const float v8[8] = {term(w.x, G0.x) + term(w.y, G0.y) + term(w.z, G0.z) + term(w.w, G0.w),
+                             term(w.x, G1.x) + term(w.y, G1.y) + term(w.z, G1.z) + term(w.w, G1.w),
+                             term(w.x, G2.x) + term(w.y, G2.y) + term(w.z, G2.z) + term(w.w, G2.w),
                              m0, mx, my, mxx, PY * mx};
         float2 part;
         quad_sum8(v8, quad_lane, part);
@@ -475,12 +478,12 @@ __global__ __launch_bounds__(256, 5) void k_composite_bwd(CamDev cam, const uint
                         const float alpha = hit ? al : 0.f;
                         const float ioma = __builtin_amdgcn_rcpf(1.f - alpha);
                         const float Tk = T * ioma;                              // transmittance in front of this splat
-                        const float w = alpha * Tk;
+                        const float w = !kGeneral || hit ? alpha * Tk : 0.f;
                         const float cg = b.z * g0 + b.w * g1 + cb * g2c;
                         const float dL_dalpha = Tk * cg - Sfx * ioma;
                         float ds = -alpha * dL_dalpha;
                         if (kGeneral) ds = (hit && raw < kAlphaMax) ? ds : 0.f;      // zero where alpha was clamped
-                        T = Tk;
+                        T = !kGeneral || hit ? Tk : T;
                         if (!kGeneral || hit) Sfx += w * cg;
                         rows[0] = ds;
                         rows[64] = w;
@@ -501,7 +504,7 @@ __global__ __launch_bounds__(256, 5) void k_composite_bwd(CamDev cam, const uint
                             asm volatile("" ::: "memory");
                             visit(std::false_type{}, r2, wr_row + 256);
                             visit(std::false_type{}, r3, wr_row + 384);
-                            reduce_slots(i);
+                            reduce_slots(std::true_type{}, i);
                         }
                         if (i < count) {      // (what the rows of the other slots hold goes to places that no splat has)
                             float* rows = wr_row;
@@ -511,13 +514,14 @@ __global__ __launch_bounds__(256, 5) void k_composite_bwd(CamDev cam, const uint
                                 rows += 256;
                             }
                             if (count & 1) visit(std::false_type{}, read(run[count - 1]), rows);
-                            reduce_slots(i);
+                            reduce_slots(std::true_type{}, i);
                         }
                     } else {
                         for (int i = 0; i < count; i += kVisitSlots) {
                             float* rows = wr_row;
                             for (int k = i; k < min(count, i + kVisitSlots); ++k, rows += 128) visit(std::true_type{}, read(run[k]), rows);
-                            reduce_slots(i);
+                            if (finite_pixels) reduce_slots(std::true_type{}, i);
+                            else reduce_slots(std::false_type{}, i);
                         }
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -367,3 +367,48 @@ def test_cells_that_a_splat_reaches(kind):
     st = dict(mean2d=mean.astype(np.float32), conic=conic.astype(np.float32), opacity=opacity.astype(np.float32),
               color=rng.uniform(0, 1, (n, 3)).astype(np.float32), radius=np.ceil(3.4 * np.maximum(s1, s2)).astype(np.int32))
     _forward_backward_against_oracle(kind, st, rng.uniform(0.5, 20, n).astype(np.float32), w, h, n)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("opacity", [(0.02, 0.3), (0.985, 1.0)])
+def test_a_pixel_gradient_that_is_not_finite_stays_with_the_splats_it_blended(value, opacity):
+    """One pixel of the image gradient is NaN or infinite, in one colour. The gradients of the splats which that pixel blended
+    are lost; those of every other splat are what they are with a zero in its place: of splats that only come near the pixel,
+    that reach its cell without blending, or that lie behind its last blended one, in lists of several batches."""
+    rng = np.random.default_rng(7)
+    w, h, n = 40, 24, 700
+    # small and mostly faint, so that pixels stay open; the second range adds splats above the 0.99 clamp, few on a pixel
+    o = rng.uniform(0.02, 0.3, n)
+    pick = rng.uniform(size=n) < 0.02
+    o[pick] = rng.uniform(*opacity, n)[pick]
+    s = rng.uniform(0.6, 2.5, n)
+    st = dict(mean2d=np.stack([rng.uniform(0, w, n), rng.uniform(0, h, n)], 1).astype(np.float32),
+              conic=np.stack([1 / s ** 2, 0.2 / s ** 2, 1.3 / s ** 2], 1).astype(np.float32), opacity=o.astype(np.float32),
+              color=rng.uniform(0, 1, (n, 3)).astype(np.float32), radius=np.ceil(3.4 * s).astype(np.int32))
+    lists, ref_l, view = _lists_case(st, rng.uniform(0.5, 20, n), w, h)
+    assert np.array_equal(lists["vals"], ref_l["vals"])
+    assert (ref_l["ranges"][:, 1] - ref_l["ranges"][:, 0]).max() > 128
+    bg = [0.1, 0.2, 0.3]
+    got = view.render_fwd(bg)
+    st64 = {k: np.asarray(v).astype(np.float64) for k, v in st.items() if k != "radius"} | {"radius": st["radius"]}
+    ref = oracle.render_fwd(st64, ref_l, w, h, bg)
+    ok = (ref["fragile"] == 0) & (got["last_idx"] == ref["last_idx"])
+    assert ok.mean() > 0.9
+    listed = np.zeros(n, dtype=bool)
+    listed[ref_l["vals"]] = True
+    for y, x in [(3, 5), (11, 17), (18, 30), (23, 39)]:
+        y, x = next((a, b) for a, b in [(y, x), (y - 1, x), (y, x - 1), (y - 1, x - 1)] if ok[a, b] and ref["last_idx"][a, b])
+        one = np.zeros((h, w, 3))
+        one[y, x] = 1.0
+        blended = oracle.render_bwd(st64, ref_l, w, h, bg, one)["color"].any(axis=1)
+        assert blended.any()
+        G = rng.normal(size=(h, w, 3)).astype(np.float32)
+        G[~ok] = 0.0
+        G[y, x] = 0.0
+        rg = oracle.render_bwd(st64, ref_l, w, h, bg, G.astype(np.float64))
+        G[y, x, 1] = value
+        g = view.render_bwd(bg, G)
+        assert not np.isfinite(g["color"][blended, 1]).any()
+        for k in ("mean2d", "conic", "opacity", "color"):
+            assert np.isfinite(g[k][listed & ~blended]).all(), k
+            grad_close(f"{value} at ({x}, {y}) {k}", g[k][listed & ~blended], rg[k][listed & ~blended])

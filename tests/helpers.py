@@ -61,6 +61,6 @@ def grad_close(name, got, ref, report=True):
     worst = float((err / tol).max())
     if report:
         print(f"[parity] {name}: worst |err|/tol = {worst:.3f} over {ref.size} elements (max|ref| = {float(np.abs(ref).max()):.3e})")
-    bad = err > tol
+    bad = ~(err <= tol)
     assert not bad.any(), (name, int(bad.sum()), ref.size, worst, float(err.max()), float(np.abs(ref).max()))
     return worst

@@ -174,7 +174,8 @@ __global__ __launch_bounds__(256) void k_pack_dup(SplatsDev sp, CamDev cam, BinA
         const float qa = sp.conic[i], qb = sp.conic[N + i], qc = sp.conic[2 * N + i], o = sp.opacity[i];
         const float mx = sp.mean2d[i], my = sp.mean2d[N + i], red = sp.color[i], green = sp.color[N + i], blue = sp.color[2 * N + i];
         const int radius = sp.radius[i];
-        const float A = 0.5f * kLog2e * qa, B = kLog2e * qb, C = 0.5f * kLog2e * qc, L = __log2f(o);
+        const float A = 0.5f * kLog2e * qa, B = kLog2e * qb, C = 0.5f * kLog2e * qc;
+        const float L = o < 0.f ? -__builtin_inff() : __log2f(o);      // below zero: blends nowhere, as zero does (NaN stays NaN)
         const bool safe = safely_definite(A, B, C);
         dst[0] = make_float4(mx, my, A, B);
         dst[1] = make_float4(C, L, red, green);

@@ -26,6 +26,14 @@ __device__ __forceinline__ float log2_alpha(float A, float B, float C, float L, 
     return fmaf(-(C * dy), dy, fmaf(-fmaf(B, dy, A * dx), dx, L));
 }
 
+// q(dx, dy) >= 0, the rule's "sigma < 0: skip", for splats whose conic is not safely definite. On q itself: e <= L would let
+// a form below zero by less than half a last place of L through, and stop a splat whose opacity is NaN, which blends with
+// the alpha of the clamp.
+__device__ __forceinline__ bool form_not_negative(float A, float B, float C, float dx, float dy)
+{
+    return fmaf(C * dy, dy, fmaf(B, dy, A * dx) * dx) >= 0.f;
+}
+
 // A staged splat of the forward kernel: 48 bytes, so that one LDS address register serves the three reads of a visit.
 struct StageRec {
     float4 a, b;                           // mx, my, A, B; C, L, red, green
@@ -178,7 +186,7 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
                     const float e = log2_alpha(a.z, a.w, b.x, b.y, dx, dy);
                     const float raw = __builtin_amdgcn_exp2f(e);
                     v.alpha = kGeneral ? fminf(kAlphaMax, raw) : raw;
-                    v.ok = (!kGeneral || e <= b.y) && v.alpha >= kAlphaMin;      // e <= L: the form is not negative
+                    v.ok = (!kGeneral || form_not_negative(a.z, a.w, b.x, dx, dy)) && v.alpha >= kAlphaMin;
                 };
                 auto blend = [&](uint32_t off, const Visit& v) {
                     const float aT = v.alpha * T;
@@ -474,7 +482,7 @@ __global__ __launch_bounds__(256, 5) void k_composite_bwd(CamDev cam, const uint
                         const float e = log2_alpha(a.z, a.w, b.x, b.y, dx, dy);
                         const float raw = __builtin_amdgcn_exp2f(e);
                         const float al = kGeneral ? fminf(kAlphaMax, raw) : raw;
-                        const bool hit = ((int)off <= last_off) && (!kGeneral || e <= b.y) && (al >= kAlphaMin);
+                        const bool hit = ((int)off <= last_off) && (!kGeneral || form_not_negative(a.z, a.w, b.x, dx, dy)) && (al >= kAlphaMin);
                         const float alpha = hit ? al : 0.f;
                         const float ioma = __builtin_amdgcn_rcpf(1.f - alpha);
                         const float Tk = T * ioma;                              // transmittance in front of this splat
@@ -666,7 +674,7 @@ __global__ __launch_bounds__(256) void k_render_stats(CamDev cam, const uint32_t
                 const float dx = fx - a.x, dy = fy - a.y;
                 const float e = log2_alpha(a.z, a.w, b.x, b.y, dx, dy);
                 ++examined;
-                if (!(e <= b.y)) continue;
+                if (!form_not_negative(a.z, a.w, b.x, dx, dy)) continue;
                 const float alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(e));
                 if (alpha < kAlphaMin) continue;
                 const float Tn = T - alpha * T;     // as the forward kernel forms it

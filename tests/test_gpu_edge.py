@@ -412,3 +412,57 @@ def test_a_pixel_gradient_that_is_not_finite_stays_with_the_splats_it_blended(va
         for k in ("mean2d", "conic", "opacity", "color"):
             assert np.isfinite(g[k][listed & ~blended]).all(), k
             grad_close(f"{value} at ({x}, {y}) {k}", g[k][listed & ~blended], rg[k][listed & ~blended])
+
+
+def test_opacities_and_forms_outside_the_usual_range():
+    """Caller-supplied states: an opacity that is NaN or infinite blends with the alpha of the clamp, one below zero nowhere, and
+    a quadratic form below zero nowhere however little it is below. Among ordinary splats, in lists of several batches."""
+    rng = np.random.default_rng(3)
+    w, h, n = 64, 48, 600
+    s = rng.uniform(0.6, 3.0, n)
+    st = dict(mean2d=np.stack([rng.uniform(0, w, n), rng.uniform(0, h, n)], 1).astype(np.float32),
+              conic=np.stack([1 / s ** 2, 0.2 / s ** 2, 1.3 / s ** 2], 1).astype(np.float32), opacity=rng.uniform(0.02, 0.3, n).astype(np.float32),
+              color=rng.uniform(0, 1, (n, 3)).astype(np.float32), radius=np.ceil(3.4 * s).astype(np.int32))
+    special = np.arange(5, n, 40)
+    st["mean2d"][special] = [(x, y) for y in (8, 24, 40) for x in (6, 19, 32, 45, 58)]      # apart: T behind 0.01 is the last to compare
+    st["conic"][special] = [0.3, 0.0, 0.3]
+    st["opacity"][special] = [np.nan, -0.5, np.inf] * 5
+    st["radius"][special] = 4
+    depth = rng.uniform(0.5, 20, n).astype(np.float32)
+    bg = [0.1, 0.2, 0.3]
+    got_l, ref_l, view = _lists_case(st, depth, w, h)
+    got = view.render_fwd(bg)
+    st64 = {k: np.asarray(v).astype(np.float64) for k, v in st.items() if k != "radius"} | {"radius": st["radius"]}
+    ref = oracle.render_fwd(st64, ref_l, w, h, bg)
+    ok = (ref["fragile"] == 0) & (got["last_idx"] == ref["last_idx"])
+    assert ok.mean() > 0.9 and np.array_equal(got["last_idx"][ref["fragile"] == 0], ref["last_idx"][ref["fragile"] == 0])
+    assert np.abs(got["image"] - ref["image"])[ok].max() <= 1e-4
+    blended = B.pbdr_render_stats(view.cam, n, view.cap, view.ws)[1]
+    assert abs(blended - ref["n_blend"]) <= 1e-3 * ref["n_blend"]
+    G = rng.normal(size=(h, w, 3)).astype(np.float32)
+    G[~ok] = 0.0
+    g = view.render_bwd(bg, G)
+    rg = oracle.render_bwd(st64, ref_l, w, h, bg, G.astype(np.float64))
+    ordinary = np.ones(n, dtype=bool)
+    ordinary[special] = False
+    for k in ("mean2d", "conic", "opacity", "color"):
+        keep = ordinary if k != "color" else np.ones(n, dtype=bool)
+        grad_close("unusual opacities " + k, g[k][keep], rg[k][keep])
+    assert np.abs(rg["color"][special[st["opacity"][special] < 0]]).max() == 0.0      # the case is what it claims
+    for shown in (np.isnan(st["opacity"]), np.isinf(st["opacity"])):      # (one of them may lie behind two others)
+        assert rg["color"][shown].any(axis=1).sum() >= 4
+
+    # forms below zero by 1e-9 of a square pixel and less: as if those splats were not there
+    below = 100
+    more = {k: np.concatenate([np.asarray(v), np.asarray(v)[:below]]) for k, v in st.items()}
+    more["mean2d"][n:] = np.floor(more["mean2d"][n:]) + np.float32(0.25)      # off the lines through the pixel centres, where a form is zero
+    more["conic"][n:] = np.array([[0.0, 0.0, -1e-9], [-1e-9, 0.0, 0.0]], dtype=np.float32)[np.arange(below) % 2]
+    more["opacity"][n:], more["radius"][n:] = 0.4, 12
+    _, ref_l, view = _lists_case(more, np.concatenate([depth, depth[:below]]), w, h)
+    got_m = view.render_fwd(bg)
+    assert np.abs(got_m["image"] - got["image"]).max() <= 1e-6
+    gm = view.render_bwd(bg, G)
+    listed = np.unique(ref_l["vals"])
+    for k in ("mean2d", "conic", "opacity", "color"):
+        assert not gm[k][listed[listed >= n]].any(), k
+        grad_close("beside forms below zero " + k, gm[k][:n][ordinary], g[k][ordinary])

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void k_pack_dup(SplatsDev sp, CamDev cam, BinA
         const bool safe = safely_definite(A, B, C);
         dst[0] = make_float4(mx, my, A, B);
         dst[1] = make_float4(C, L, red, green);
-        dst[2] = make_float4(blue, __int_as_float(radius), o, __uint_as_float(safe && o <= 0.98f ? kSplatPlain : 0u));
+        dst[2] = make_float4(blue, __int_as_float(radius), o, __uint_as_float(!safe ? 0u : o <= 0.98f ? kSplatPlain : kSplatDefinite));
         dst[3] = splat_ellipse(A, B, C, L);
     });
 }

@@ -61,7 +61,7 @@ __device__ __forceinline__ void grad_out(float* __restrict__ p, float v)
 struct __attribute__((aligned(16))) Packed {
     float mx, my, A, B;                     // mean2d; the conic in log2 units: A = log2(e)/2 a, B = log2(e) b, C = log2(e)/2 c
     float C, L, r, g;                       // L = log2(opacity); red, green
-    float b, radius_bits, o, kind_bits;     // blue, the integer extent (bit-cast), opacity, kSplatPlain or 0 (bit-cast)
+    float b, radius_bits, o, kind_bits;     // blue, the integer extent (bit-cast), opacity, kSplatPlain, kSplatDefinite or 0 (bit-cast)
     float4 ellipse;                         // splat_ellipse()
 };
 static_assert(sizeof(Packed) == 64, "raster record is 64 bytes");
@@ -69,7 +69,8 @@ static_assert(sizeof(Packed) == 64, "raster record is 64 bytes");
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLog2_255 = 7.994353436858858f;
-constexpr uint32_t kSplatPlain = 3u;
+constexpr uint32_t kSplatDefinite = 1u;      // the conic is safely_definite(): the sign test of the form cannot fire
+constexpr uint32_t kSplatPlain = 3u;         // and the opacity at most 0.98: the clamp of alpha at 0.99 cannot fire either
 
 // What the compositing kernels' cull needs to know about a splat, worked out once per splat: the ellipse of the pixel centres
 // at which alpha >= 1/255, i.e. A dx^2 + B dx dy + C dy^2 <= tau with the conic in log2 units and tau = log2(255 o), as

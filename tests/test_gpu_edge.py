@@ -466,3 +466,32 @@ def test_opacities_and_forms_outside_the_usual_range():
     for k in ("mean2d", "conic", "opacity", "color"):
         assert not gm[k][listed[listed >= n]].any(), k
         grad_close("beside forms below zero " + k, gm[k][:n][ordinary], g[k][ordinary])
+
+
+def _mixed_list(count, kind):
+    """count splats on one 16 x 16 tile, every one on every cell and faint there. kind: opacities above the alpha clamp on all of
+    them or on one in 40, seen from afar, and a few on a pixel where the clamp fires; or an indefinite conic on one in 40."""
+    rng = np.random.default_rng(count)
+    a = rng.uniform(0, 2 * np.pi, count)
+    near = rng.uniform(2, 14, (count, 2))
+    far = 8 + 47 * np.stack([np.cos(a), np.sin(a)], 1)
+    some = np.arange(count) % 40 == 3
+    opaque = np.ones(count, dtype=bool) if kind == "opaque" else some & (kind == "mixed")
+    st = dict(mean2d=np.where(opaque[:, None], far, near), conic=np.where(opaque[:, None], [0.004, 0.0, 0.004], [0.004, 0.001, 0.005]),
+              opacity=np.where(opaque, rng.choice([0.981, 0.985, 0.995, 1.0], count), 0.012), color=rng.uniform(0, 1, (count, 3)))
+    clamped = np.array([0, count // 2, count - 1]) if kind != "indefinite" else np.zeros(0, dtype=int)
+    st["mean2d"][clamped] = np.array([[3.55, 4.55], [11.55, 2.45], [7.45, 12.55]])[:len(clamped)]
+    st["conic"][clamped] = [3.0, 0.0, 3.0]
+    st["opacity"][clamped] = 1.0
+    if kind == "indefinite":
+        st["conic"][some] = [0.004, 0.006, 0.005]
+    return {k: v.astype(np.float32) for k, v in st.items()} | dict(radius=np.full(count, 64, dtype=np.int32)), rng.uniform(0.5, 20, count).astype(np.float32)
+
+
+@pytest.mark.parametrize("count", [3, 24, 25, 63, 64, 65, 129, 255, 256, 257, 321, 513])
+@pytest.mark.parametrize("kind", ["mixed", "opaque", "indefinite"])
+def test_lists_of_each_kind_of_walk_around_the_chunk_and_run_sizes(count, kind):
+    """Windows and batches take a walk without the alpha clamp and the sign test, with the clamp, or with both, by what their
+    splats can do: lists around the staging sizes whose batches take the second and the third, some next to the first."""
+    st, depth = _mixed_list(count, kind)
+    _forward_backward_against_oracle(f"{count} splats, {kind}", st, depth, 16, 16, count)

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict
     }
 }
 
-// 3D Gaussians: the 48-byte raster record of a listed point (see binning_common.h for the rest of the block's work).
+// 3D Gaussians: the raster record (64 bytes) of a listed point (see binning_common.h for the rest of the block's work).
 __global__ __launch_bounds__(256) void k_pack_dup(SplatsDev sp, CamDev cam, BinArrays A, Packed* __restrict__ packed)
 {
     const size_t N = (size_t)sp.n;

@@ -717,9 +717,8 @@ hipError_t launch_composite_fwd(const CamDev& cam, const Layout& L, char* ws, co
     const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L));
     const Packed* packed = reinterpret_cast<const Packed*>(ws + L.off_packed);
     ProfScope prof(kKCompositeFwd, s);
-    const uint32_t ntiles = (uint32_t)(cam.TX * cam.TY);
-        hipLaunchKernelGGL(k_composite_fwd, dim3(ntiles), dim3(256), 0, s, cam, ranges, tile_order, vals, packed,
-                           reinterpret_cast<uint16_t*>(ws + L.off_reach), bg[0], bg[1], bg[2], image, final_T, last_idx);
+    hipLaunchKernelGGL(k_composite_fwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam, ranges, tile_order, vals, packed,
+                       reinterpret_cast<uint16_t*>(ws + L.off_reach), bg[0], bg[1], bg[2], image, final_T, last_idx);
     return hipGetLastError();
 }
 

@@ -116,27 +116,16 @@ __device__ __forceinline__ void quad_sum8(const float (&v)[8], int quad_lane, fl
 // sum over each quad of lanes, in all of them
 __device__ __forceinline__ float quad_sum(float v)
 {
-    asm volatile("" : "+v"(v));   // (as in row_sum16)
+    asm volatile("" : "+v"(v));   // keeps a product that feeds v from being fused into the first add (which would cost the DPP form)
     v += dpp_move<0xB1>(v);
     v += dpp_move<0x4E>(v);
     return v;
 }
 
-// sum over each row of 16 lanes, left in every lane of the row: partners lane ^ 1, ^ 2, ^ 7 (within eight), ^ 15
-__device__ __forceinline__ float row_sum16(float v)
-{
-    asm volatile("" : "+v"(v));   // keeps a product that feeds v from being fused into the first add (which would cost the DPP form)
-    v += dpp_move<0xB1>(v);    // quad_perm:[1,0,3,2]
-    v += dpp_move<0x4E>(v);    // quad_perm:[2,3,0,1]
-    v += dpp_move<0x141>(v);   // row_half_mirror
-    v += dpp_move<0x140>(v);   // row_mirror
-    return v;
-}
-
 // ---- bookkeeping of the walks ----------------------------------------------------------------------------------------
-// The walks are bound by issue, scalar instructions included (three more of them a visit cost the 3D forward kernel 7 %),
-// so a visit's bookkeeping is spelled out: the splats left in a wavefront's batch are a 64-bit scalar mask that gives up
-// one bit in one instruction, and which pixels are still open is a scalar lane mask.
+// The walks are bound by issue, scalar instructions included, so a visit's bookkeeping is spelled out: which pixels are still
+// open is a scalar lane mask and, in the surfel walks, the splats left in a wavefront's batch are a 64-bit scalar mask that
+// gives up one bit in one instruction (the 3D walks read lists, see composite.hip).
 
 // the lowest splat left in the mask, taken out of it (m != 0)
 __device__ __forceinline__ int take_lowest(unsigned long long& m)

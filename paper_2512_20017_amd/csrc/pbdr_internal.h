@@ -161,7 +161,7 @@ enum Variant { kVariant3D = 0, kVariant2D = 1 };   // 3D Gaussians / 2D Gaussian
 struct Layout {
     int n, W, H, TX, TY, tiles;
     int variant;
-    size_t record_bytes;      // raster record per point: 48 (3D) or 64 (2D)
+    size_t record_bytes;      // raster record per point, 64 in both variants
     int partial_vec4;         // float4s of partial gradient sums per pair: 3 (3D) or 4 (2D)
     uint32_t cap;
     int tile_bits, tile_passes;   // key bits / radix passes spent on the tile id

@@ -353,15 +353,15 @@ __device__ __forceinline__ void eval_pair2d(const float4& a, const float4& b, co
 }
 
 // Forward. The tile's list is staged 256 surfels at a time by the whole workgroup, so that the rim test (over a hundred
-// vector instructions) is made once per tile and splat. Independent wavefronts that stage for themselves, as in the 3D
-// kernel, make it four times: 344 against 333 us at 2M disks on 2600x1463, 169 against 163 at 1M on 1920x1080; they gain
+// vector instructions) is made once per tile and splat. Independent wavefronts that stage and test for themselves make it
+// four times: 344 against 333 us at 2M disks on 2600x1463, 169 against 163 at 1M on 1920x1080; they gain
 // only where quadrants end far apart (390 against 424 us at 600k disks on 400x300).
 //
 // The walk also notes for the backward pass which splats its quadrant blended. Bound by instruction issue (92 % of it at
 // 1M disks, 1920x1080), it can spare little for that: the lane masks of a visit are kept as scalars, the instruction that
 // forms the mask of blending lanes leaves in the carry whether it is empty, and two additions with carry shift that bit
 // into a 64-bit history, one bit per visit (a ballot of the lane predicate, compare and select took two vector and five
-// scalar instructions a visit). LDS offsets and the last blended position are kept as in the 3D kernel. 1M disks at
+// scalar instructions a visit). LDS offsets and the last blended position are kept as staged_offset says. 1M disks at
 // 1920x1080, this kernel: 180.9 -> 162.4 us, and 167.7 for a walk in the compiler's own form that notes nothing.
 constexpr int kFwdBatch2D = 256;
 
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
                 const unsigned long long reached = uniform_u64(S.mask[wave][k]);
                 unsigned long long m = reached;
                 used_lo = used_hi = 0u;
-                // two visits per trip while there are two (independent alphas, blends in list order), as in the 3D kernel
+                // two visits per trip while there are two (independent alphas, blends in list order)
                 int left = __builtin_popcountll(m);
                 for (; left >= 2; left -= 2) {
                     const uint32_t o0 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
     const bool bit1 = (lane & 2) != 0;
     const int acc_slot = ((lane & 1) ? 8 : 0) + ((lane >> 1) & 7);     // see row_sum8: odd lanes take the second eight sums
     int nslot = 0;                 // visits staged since the last reduction, and their surfels' positions in the batch,
-    uint32_t slot_pos = 0u;        // a byte each, the newest lowest, as in the 3D kernel
+    uint32_t slot_pos = 0u;        // a byte each, the newest lowest: one instruction a visit
     static_assert(kSlots2D == 4 && kBwdBatch2D <= 256, "four positions of eight bits");
     const int slot_shift = 24 - 8 * (lane >> 4);      // of this lane's slot once four are staged
     // Reduces the staged rows and stores the sums of the first `count` visit slots in their surfels' accumulators.

@@ -495,3 +495,39 @@ def test_lists_of_each_kind_of_walk_around_the_chunk_and_run_sizes(count, kind):
     splats can do: lists around the staging sizes whose batches take the second and the third, some next to the first."""
     st, depth = _mixed_list(count, kind)
     _forward_backward_against_oracle(f"{count} splats, {kind}", st, depth, 16, 16, count)
+
+
+@pytest.mark.parametrize("aspect", [1, 30, 300, 1000, 1400, 3000, "indefinite"])
+def test_the_cull_keeps_every_pixel_that_a_needle_blends(aspect):
+    """One splat alone in an image of several hundred cells, at any angle, needles up to 3000 : 1: on both sides of the determinant
+    below which the cull takes everything as reached (about 1400 : 1), and forms that are negative in places. Which pixels it
+    blends is the oracle's answer, which tests every pixel, wherever rounding does not decide."""
+    rng = np.random.default_rng(len(str(aspect)) + (aspect if isinstance(aspect, int) else 0))
+    w, h = 112, 96
+    st = dict(depth=np.ones(1, dtype=np.float32), color=np.ones((1, 3), dtype=np.float32), radius=np.array([400], dtype=np.int32))
+    view = GpuView(1, _cam(w, h), 64)
+    shown = decided = 0
+    for k in range(40):
+        r = aspect if isinstance(aspect, int) else 5
+        s2 = np.exp(rng.uniform(np.log(0.3), np.log(3.0)))
+        s1 = s2 * r
+        a = np.pi / 4 * rng.integers(0, 4) + rng.choice([0.0, 1e-3, 0.3]) if k % 2 else rng.uniform(0, np.pi)
+        c, s = np.cos(a), np.sin(a)
+        conic = [(c / s1) ** 2 + (s / s2) ** 2, c * s * (1 / s1 ** 2 - 1 / s2 ** 2), (s / s1) ** 2 + (c / s2) ** 2]
+        if aspect == "indefinite":
+            conic[1] *= 1.0 + rng.uniform(0.0, 0.5) if conic[0] * conic[2] < 1.2 * conic[1] ** 2 else 3.0
+        o = rng.choice([1.02 / 255, 1.5 / 255, 0.05, 0.4, 0.97, 1.0])
+        st.update(mean2d=np.array([[rng.uniform(-10, w + 10), rng.uniform(-10, h + 10)]], dtype=np.float32),
+                  conic=np.array([conic], dtype=np.float32), opacity=np.array([o], dtype=np.float32))
+        st64 = {q: v.astype(np.float64) for q, v in st.items() if q != "radius"} | {"radius": st["radius"]}
+        lists = oracle.bin_sort(st64["mean2d"], st["radius"], st["depth"], w, h)
+        assert lists["P"] == 42
+        view.splats = B.Splats.from_numpy(st)
+        got = view.render_fwd([0, 0, 0])
+        ref = oracle.render_fwd(st64, lists, w, h, [0, 0, 0])
+        ok = ref["fragile"] == 0
+        bad = ok & (got["last_idx"] != ref["last_idx"])
+        assert not bad.any(), (k, np.degrees(a), s2, o, int(bad.sum()), np.argwhere(bad)[:4].tolist())
+        shown += int((ok & (ref["last_idx"] == 1)).sum())
+        decided += int(ok.sum())
+    assert decided > 0.5 * 40 * w * h and shown > 500      # the case is what it claims

@@ -70,15 +70,6 @@ __device__ __forceinline__ uint32_t by_quadrant(uint32_t m)
     return (m & 3u) | ((m >> 2) & 12u) | ((m << 2) & 0x30u) | (m & 0xc0u);
 }
 
-// Forward. The workgroup finds the cells of 256 list positions at a time, one per thread; most lists are not much longer.
-// Then the wavefronts go on by themselves: each compacts the positions that reach its quadrant, stages their records 64 at
-// a time (one per lane, in its own 3 KB of LDS) and writes the lists of its cells, LDS offsets of 16 bits; the entries
-// behind a list's end name a record that reaches nothing. A walk reads two entries per cell and trip: their alphas do not
-// depend on each other, which gives the vector ALU two independent chains; the blends stay in list order.
-// 1M points, 1920x1080: 100.6 -> 86.4 us, 77 -> 58 M vector instructions; 30k points, 1031x517: 26.8 -> 25.0; 64 tiles of
-// 160 splats: 29.7 -> 21.5; 8M points, 3840x2160: -18 %. (Measured and dropped: a wavefront per 8x8 quadrant or per 16x8
-// half tile with two pixels a lane, each finding its own cells: 102 and 91 us, and 27.6 and 39 at 30k points, where the
-// chip is not full; 512 positions at a time: 90, five workgroups fit instead of eight.)
 // The walks of both kernels come in three kinds, chosen per window or batch (uniform): without the clamp and the sign test,
 // neither of which can fire where every conic is safely definite and every opacity at most 0.98; with the clamp alone; and with
 // both, for the other states a caller may hand in. All are unrolled and ask for records ahead alike: one splat above 0.98 is
@@ -91,6 +82,18 @@ constexpr int kWalkPlain = 0, kWalkClamped = 1, kWalkGeneral = 2;
 template <int kKind>
 using WalkKind = std::integral_constant<int, kKind>;
 
+// Forward. The workgroup finds the cells of 256 list positions at a time, one per thread; most lists are not much longer.
+// Then the wavefronts go on by themselves: each compacts the positions that reach its quadrant, stages their records 64 at
+// a time (one per lane, in its own 3 KB of LDS) and writes the lists of its cells, LDS offsets of 16 bits; the entries
+// behind a list's end name a record that reaches nothing. A walk reads two entries per cell and trip: their alphas do not
+// depend on each other, which gives the vector ALU two independent chains; the blends stay in list order.
+// Against one splat a visit on the whole quadrant: the benchmark's view (1M points, 1920x1080, bench.py) 103.8 -> 88.9 us,
+// 77 -> 64 M vector instructions, its 4K street view (8M points) 326 -> 235; clusters and boxes as perf/cases.py draws them,
+// 1M points at 1920x1080 88.6 -> 74.7, 200k at 1280x720 51.0 -> 39.9, 30k at 1031x517 21.9 -> 19.0, 4096 at 128x128
+// 28.1 -> 20.0 (the launch lasts as long as its longest list).
+// (Measured and dropped, where this one took 87 us at 1M points and 25 at 30k: a wavefront per 8x8 quadrant or per 16x8 half
+// tile with two pixels a lane, each finding its own cells: 102 and 91, and 27.6 and 39 at 30k points, where the chip is not
+// full; 512 positions at a time: 90, five workgroups fit instead of eight.)
 constexpr int kFwdChunk = 256;                   // list positions whose cells are worked out at a time
 
 __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
@@ -268,10 +271,14 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
 // rank of this tile in the splat's rectangle). A splat's pairs are contiguous there, so a per-splat kernel adds them
 // up afterwards (k_gather_splat_grads).
 //
-// 1M points, 1920x1080: 209 -> 185 us, 146 -> 115 M vector instructions; what is left is bound by latency as much as by
-// issue (five workgroups per compute unit by registers and LDS). 200k points, 1280x720, two views: 231 -> 166 us; 30k
-// points, 1031x517: 56 -> 42; 64 tiles of 160 splats: 67 -> 40. Records asked for two visits ahead are 2 to 6 % of that.
-// (Measured and dropped: four workgroups with runs of 32 visits: 203 us at 1M points, 160 at 200k; six with 16: 212, the
+// Against one splat a visit on the whole quadrant: the benchmark's view (1M points, 1920x1080, bench.py) 213 -> 182 us,
+// 143 -> 112 M vector instructions, its 4K street view 597 -> 427; clusters and boxes as perf/cases.py draws them, 1M points at
+// 1920x1080 182 -> 156, 200k at 1280x720 106 -> 72, 30k at 1031x517 48 -> 33, 4096 at 128x128 65 -> 38. What is left is bound
+// by latency as much as by issue (five workgroups per compute unit by registers and LDS). Records asked for two visits ahead
+// are 2 to 6 % of that. States that no preprocessing makes lost by it: with a tenth of all conics indefinite (a list then holds
+// the splat for every cell, and a visit that no lane blends is reduced like any other) 289 against 276 us at 1M points for the
+// whole backward call, with all of them 449 against 321; at 200k points and below up to a third they are faster too.
+// (Measured and dropped, where this one took 185 us at 1M points: four workgroups with runs of 32 visits: 203; six with 16: 212, the
 // registers spill; one wavefront per tile that takes the four quadrants in turn: the few tiles with thousands of splats then
 // run four times longer. The contraction on fp32 matrix instructions: these hold the SIMD for their 32 cycles, plain vector
 // instructions of other wavefronts do not overlap with them, and most of their output columns are of no use here.)

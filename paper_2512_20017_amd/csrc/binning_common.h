@@ -50,19 +50,24 @@ struct BinArrays {
 // 64 points occupy one contiguous range (the slots are a prefix sum); lane l writes slots B + l, B + l + 64, ... and
 // finds the owning point of a slot from the range starts (see the loop). Points are emitted in index
 // order: the depth order of each tile's list is made afterwards, tile by tile (k_tile_depth_sort).
-// Points with kWidePairs pairs or more are left out of that loop and written by the whole workgroup, 256 slots per trip of
-// two stores and four additions: a step of 64 slots is a chain of LDS and cross-lane reads, and one splat over the whole
-// image kept one wavefront at it when all others had ended. 1M disks at 1920x1080, three of eight scenes with such a splat:
-// this kernel 76 -> 23 us, step 785 -> 727, 749 -> 725 and 831 -> 810 us; scenes without one as before (within 0.1 %). 256:
-// below it a trip would leave lanes of the workgroup idle.
-constexpr uint32_t kWidePairs = 256;
+// In a block that holds a point with kWideBlock pairs or more, the points with kWidePairs or more are left out of that loop
+// and written by the whole workgroup, 256 slots per trip of two stores and four additions: a step of 64 slots is a chain of
+// LDS and cross-lane reads, and one splat over the whole image kept one wavefront at it when all others had ended. 1M disks
+// at 1920x1080, three of eight scenes with such a splat: this kernel 76 -> 23 us, step 785 -> 727, 749 -> 725 and 831 -> 810 us;
+// scenes without one as before (within 0.1 %).
+// A trip is a step that four wavefronts share, so it pays from somewhat over 256 slots: all lists of 300 points at 1920x1080,
+// without / with, 119.4 / 120.6 us at 289 tiles a point, 123.2 / 121.5 at 306, 140.5 / 123.3 at 380, 1033 / 307 over the image.
+// And doing both after one another costs more than either (points on 225 to 256 tiles, half of them left out: 105.1 / 114.1),
+// so a block of points below kWideBlock leaves out none (105.1). A wavefront without such a point takes the loop without the
+// test that steps over their slots (points on 210 tiles: 105.3 -> 101.2).
+constexpr uint32_t kWidePairs = 256, kWideBlock = 320;
 
 template <class Pack>
 __device__ __forceinline__ void pack_dup_block(const BinInput& in, const CamDev& cam, const BinArrays& A,
                                                const float* __restrict__ depth, Pack pack)
 {
     __shared__ uint32_t sMark[4][64];      // per wavefront: which lane's range starts at each slot of the current step
-    __shared__ uint32_t sVis[4], sPairs[4];
+    __shared__ uint32_t sVis[4], sPairs[4], sLarge[4];
     __shared__ uint4 sWide[256];           // the block's wide points: first slot; pairs; x0, y0; width of the rectangle, place in the block
     __shared__ uint32_t sNumWide;
     // the blocks with many pairs are started first: their wavefronts run longest (64 slots per step), and in index order
@@ -76,7 +81,8 @@ __device__ __forceinline__ void pack_dup_block(const BinInput& in, const CamDev&
     const bool vis = cnt > 0u;
     const unsigned long long vm = __ballot(vis);
     const uint32_t inc = wave_inclusive_scan_sat(cnt);
-    if (lane == 63) { sVis[wave] = (uint32_t)__popcll(vm); sPairs[wave] = inc; }
+    const bool large = __ballot(cnt >= kWideBlock) != 0ull;
+    if (lane == 63) { sVis[wave] = (uint32_t)__popcll(vm); sPairs[wave] = inc; sLarge[wave] = large ? 1u : 0u; }
     if (threadIdx.x == 0) sNumWide = 0u;
     __syncthreads();
     uint32_t slot = A.blk_vis[blk] + (uint32_t)__popcll(vm & ((1ull << lane) - 1ull));
@@ -98,7 +104,7 @@ __device__ __forceinline__ void pack_dup_block(const BinInput& in, const CamDev&
         const uint32_t end = min(at + cnt, A.cap);
         for (uint32_t c = (at + kChunkPairs - 1) / kChunkPairs; (uint64_t)c * kChunkPairs < end; ++c) A.chunk_rank[c] = slot;
     }
-    const bool wide = cnt >= kWidePairs;
+    const bool wide = cnt >= kWidePairs && (sLarge[0] | sLarge[1] | sLarge[2] | sLarge[3]) != 0u;
     const unsigned long long wide_lanes = __ballot(wide);
     if (wide) {
         const uint32_t pairs = at < A.cap ? min(cnt, A.cap - at) : 0u;      // (a grid has at most 4096 x 4096 tiles)
@@ -116,7 +122,7 @@ __device__ __forceinline__ void pack_dup_block(const BinInput& in, const CamDev&
     // step to step, hands every slot its owner - one LDS round trip per step where a binary search over the 64 range
     // ends took six in a row, which is what the wavefronts with thousands of pairs, the last to finish, were made of.
     int carry = -1;
-    for (uint32_t base = first; base < last;) {
+    const auto step = [&](uint32_t base) {
         const uint32_t u = base + lane;
         sMark[wave][lane] = 0xffffffffu;
         if (vis && at - base < 64u) sMark[wave][at - base] = (uint32_t)lane;      // at >= base or the difference wraps past 64
@@ -141,10 +147,17 @@ __device__ __forceinline__ void pack_dup_block(const BinInput& in, const CamDev&
             A.tkeys[u] = (uint32_t)(ty * cam.TX + tx);
             A.tvals[u] = oid;
         }
-        base += 64u;
-        if (carry >= 0 && ((wide_lanes >> carry) & 1ull) != 0ull) {      // on to the step in which a wide point's range ends
-            const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)(at + cnt), carry);
-            if (end > base) base += (end - base) & ~63u;
+    };
+    if (wide_lanes == 0ull) {
+        for (uint32_t base = first; base < last; base += 64) step(base);
+    } else {
+        for (uint32_t base = first; base < last;) {
+            step(base);
+            base += 64u;
+            if (carry >= 0 && ((wide_lanes >> carry) & 1ull) != 0ull) {      // on to the step in which a wide point's range ends
+                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)(at + cnt), carry);
+                if (end > base) base += (end - base) & ~63u;
+            }
         }
     }
     __syncthreads();

@@ -531,3 +531,22 @@ def test_the_cull_keeps_every_pixel_that_a_needle_blends(aspect):
         shown += int((ok & (ref["last_idx"] == 1)).sum())
         decided += int(ok.sum())
     assert decided > 0.5 * 40 * w * h and shown > 500      # the case is what it claims
+
+
+@pytest.mark.parametrize("n", [5 * 256, 5 * 256 - 100])
+def test_lists_of_blocks_around_the_size_from_which_a_workgroup_writes_a_point(n):
+    """A block of 256 points has its workgroup write those on 256 tiles or more if one of them is on 320 or more: blocks whose
+    points are all on 255, on 258, on 318 and on 321 tiles, and one of the first two with a single point of the last."""
+    w, h = 5000, 40                                          # three rows of 313 tiles
+    rng = np.random.default_rng(n)
+    cols = np.repeat([85, 86, 106, 107, 0], 256)[:n]
+    cols[4 * 256:] = rng.choice([85, 86], n - 4 * 256)
+    cols[4 * 256 + 77] = 107
+    st = _rand_state(rng, n, w, h)
+    st["mean2d"] = np.stack([16.0 * rng.integers(60, 250, n) + 8 * (cols % 2), np.full(n, 20.0)], 1).astype(np.float32)
+    st["radius"] = (8 * cols - 8).astype(np.int32)
+    depth = rng.uniform(0.3, 50, n).astype(np.float32)
+    got, ref, _ = _lists_case(st, depth, w, h)
+    assert np.array_equal(np.bincount(ref["vals"], minlength=n), 3 * cols)      # the case is what it claims
+    assert np.array_equal(got["keys"], ref["keys"]) and np.array_equal(got["vals"], ref["vals"])
+    assert np.array_equal(got["ranges"], ref["ranges"])

@@ -616,14 +616,11 @@ def bench_view(args, workload, headline):
 
     # ---- roofline of the dominant kernel
     K = (scene.sh_degree + 1) ** 2
-    tile_passes = max(1, (max(1, (((W + 15) // 16) * ((H + 15) // 16) - 1).bit_length()) + 7) // 8)
     hbm_bytes = {   # algorithmic bytes per step
         "k_preprocess": 16.0 * n + (32.0 + 12.0 * K + 40.0) * n_vis,
         "k_count_visible": 8.0 * n + 8.0 * n_vis,
-        "k_pack_dup": 4.0 * n + (44.0 + 64.0) * n_vis + 8.0 * P,
-        "k_radix_hist": tile_passes * 4.0 * P,
-        "k_radix_scatter": tile_passes * 16.0 * P,
-        "k_tile_ranges": 4.0 * P,
+        "k_tile_count": 4.0 * n + 8.0 * n_vis,
+        "k_pack": 4.0 * n + (44.0 + 64.0) * n_vis + 8.0 * P,
         "k_tile_depth_sort": 12.0 * P,
         "k_gather_splat_grads": 8.0 * n + 48.0 * P + 36.0 * n,
         # accumulate: read + write of the visible points' gradient entries; first view: one write of every point's

@@ -59,30 +59,24 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->TX = (W + kTile - 1) / kTile; L->TY = (H + kTile - 1) / kTile;
     L->tiles = L->TX * L->TY;
     L->cap = (uint32_t)cap;
-    L->tile_bits = 0;
-    while ((1 << L->tile_bits) < L->tiles) ++L->tile_bits;
-    L->tile_passes = radix_pass_count(L->tile_bits);
-    const size_t nblk_t = ((size_t)cap + kSortItems - 1) / kSortItems;
     size_t off = 0;
     const auto take = [&](size_t bytes) { const size_t at = off; off = align256(off + bytes); return at; };
     L->off_status = take(kStWords * sizeof(uint32_t));
     L->off_packed = take((size_t)n * L->record_bytes);
     L->off_depth_bits = take((size_t)n * sizeof(uint32_t));
-    L->off_blk_vis = take(((size_t)n / 256 + 8) * sizeof(uint32_t));
-    L->off_blk_pairs = take(((size_t)n / 256 + 8) * sizeof(uint32_t));
-    L->off_blk_vis_at = take(((size_t)n / 256 + 8) * sizeof(uint32_t));  // exclusive sums of the two above
-    L->off_blk_pairs_at = take(((size_t)n / 256 + 8) * sizeof(uint32_t));
-    L->off_blk_order = take(((size_t)n / 256 + 8) * sizeof(uint32_t));   // blocks of points in the order the packing kernel takes them
+    const size_t nb = ((size_t)n + 255) / 256;                           // blocks of 256 points
+    L->off_blk = take(nb * sizeof(uint2));
+    L->off_sup = take((nb / 16 + 1) * sizeof(uint2));
+    L->off_blk_at = take(nb * sizeof(uint2));
+    L->off_blk_cells = take(nb * sizeof(uint4));
     L->off_touched = take((size_t)n * sizeof(uint32_t));
     L->off_offsets = take(((size_t)n + 1) * sizeof(uint32_t));
     L->off_slot_base = take((size_t)n * sizeof(uint32_t));
     L->off_order = take((size_t)n * sizeof(uint32_t));       // listed points in index order ("rank" -> point)
-    L->off_tkey0 = take((size_t)cap * sizeof(uint32_t));
-    L->off_tval0 = take((size_t)cap * sizeof(uint32_t));
-    L->off_tkey1 = take((size_t)cap * sizeof(uint32_t));
-    L->off_tval1 = take((size_t)cap * sizeof(uint32_t));
-    L->off_totals = take((size_t)kRadixMaxBins * sizeof(uint32_t));      // digit totals of a pass of the tile sort
-    L->off_tile_hist = take(nblk_t * kRadixMaxBins * sizeof(uint32_t));
+    L->off_keys = take((size_t)cap * sizeof(uint32_t));
+    L->off_vals = take((size_t)cap * sizeof(uint32_t));
+    L->off_spare = take((size_t)cap * 2 * sizeof(uint32_t));             // the blocks' tiles, then the other half of a list too long for LDS
+    L->off_tile_count = take((size_t)L->tiles * sizeof(uint32_t));
     L->off_ranges = take((size_t)L->tiles * 2 * sizeof(uint32_t));
     L->off_partial = take((size_t)cap * L->partial_vec4 * 4 * sizeof(float));
     L->off_keys64 = take((size_t)cap * sizeof(uint64_t));
@@ -530,7 +524,7 @@ static int lists_view(int variant, void* workspace, size_t workspace_bytes, int3
         }
         *keys = reinterpret_cast<const uint64_t*>(ws + L.off_keys64);
     }
-    if (vals) *vals = reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L));
+    if (vals) *vals = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     if (ranges) *ranges = reinterpret_cast<const uint32_t*>(ws + L.off_ranges);
     if (num_dup) *num_dup = reinterpret_cast<const uint32_t*>(ws + L.off_status) + kStNumDup;
     return PBDR_OK;

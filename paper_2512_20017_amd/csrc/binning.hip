@@ -1,36 +1,40 @@
-// Tile binning: per-splat tile count + raster record, device prefix sums, key/value duplication in index order, stable
-// sort by tile, tile ranges, depth order inside each tile's list. These are the steps between pts_splatting and the
-// per-pixel blend that realise "sorts these view-dependent splats by their distance to the camera plane" (paper
-// Sec. 2.1) per 16x16 tile.  All HBM- or latency-bound integer work.
+// Tile binning: per-splat tile count + raster record, device prefix sums, per-tile pair counts, the (tile, point) pairs put
+// into their tiles' lists, tile ranges and order, depth order inside each tile's list. These are the steps between
+// pts_splatting and the per-pixel blend that realise "sorts these view-dependent splats by their distance to the camera
+// plane" (paper Sec. 2.1) per 16x16 tile.  All HBM- or latency-bound integer work.
 //
-// The tile lists are ordered by the 64-bit key (tile << 32 | depth bits), ties by splat index. That order is made in
-// two halves: the (tile, point) pairs are emitted in point-index order and sorted stably by tile id (two radix passes
-// over the P pairs), which leaves every tile's list in index order; one workgroup per tile then sorts its list stably
-// by the 32 depth bits (k_tile_depth_sort, radix_sort.hip: in LDS for lists up to 2048 entries). The same permutation
-// as a six-pass radix sort of P 64-bit keys, in a third of the launches of the earlier scheme (depth digits sorted on
-// the points before duplication: twelve launches for 0.5 M keys, every one of them at the latency floor).
+// The tile lists are ordered by the 64-bit key (tile << 32 | depth bits), ties by point index. The tile half is a counting
+// sort without a pass over the pairs: a block of 256 points, which in Z-order lie on a few dozen tiles, counts its pairs per
+// tile in LDS and reserves its room in each of those tiles' lists with one atomic add, and once the lists' starts are known
+// every pair is written to its place. The lists come out in no particular order; each is then sorted by depth bits and, among
+// equal ones, by point index (k_tile_depth_sort, depth_sort.hip), so the result is the same on every run.
+// Five launches where a stable two-pass radix sort of the pairs by tile id took eleven; with the depth sort as it is now, us
+// before and now, in turn on one card: 1M points at 1920x1080 472 -> 438 a step, 225 -> 195 an evaluation; 30k at 1031x517 156 -> 129 a
+// step; 12,000 at 400x300 79 -> 49 an evaluation. The order of points matters more than before: where a block's points lie all
+// over the image, its pairs are on as many tiles, and each costs an atomic add.
 #include "pbdr_internal.h"
 #include "binning_common.h"
 
 namespace pbdr {
 
-// Tiles touched by every point (0 for culled points) and, per block of 256 consecutive points, the number of points
-// that touch at least one tile - those are the points binning lists ("visible" below) - and the number of their pairs.
-// A state made by the preprocessing calls has radius == 0 for every point without a tile; a caller-made state with
+// Tiles touched by every point (0 for culled points) and, per block of 256 consecutive points and per kSuperBlocks of them,
+// the number of points that touch at least one tile - those are the points binning lists ("visible" below) - and the number of
+// their pairs. A state made by the preprocessing calls has radius == 0 for every point without a tile; a caller-made state with
 // radius > 0 and an empty tile rectangle is treated as culled here, so every listed point owns at least one pair.
 // Four consecutive points per thread (one 16-byte load of the radii, one 16-byte store of the counts: with one point
 // per thread the launch did not keep enough bytes in flight, 2 TB/s at eight million points: 32 -> 21 us there), so a
 // wavefront covers exactly one block of 256 points and its two sums need no LDS and no barrier.
-__global__ __launch_bounds__(256) void k_count_visible(BinInput in, CamDev cam, uint32_t* __restrict__ tiles_touched,
-                                                       uint32_t* __restrict__ blk_vis, uint32_t* __restrict__ blk_pairs,
-                                                       uint32_t* __restrict__ status, uint32_t* __restrict__ ranges, uint32_t nranges)
+__global__ __launch_bounds__(1024) void k_count_visible(BinInput in, CamDev cam, BinArrays A, uint32_t* __restrict__ ranges, uint32_t nranges,
+                                                        uint32_t ntiles)
 {
-    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    // first launch of a binning call: the status words and the tile ranges start at zero (every later kernel of the call
-    // comes after this one on the stream)
-    if (gid < (uint32_t)kStCleared) status[gid] = 0u;
-    for (uint32_t k = gid; k < nranges; k += gridDim.x * 256u) ranges[k] = 0u;
+    __shared__ uint2 sBlk[kSuperBlocks];
+    const uint32_t gid = blockIdx.x * 1024u + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // first launch of a binning call: the status words, the tile ranges and the tiles' pair counts start at zero (every later
+    // kernel of the call comes after this one on the stream)
+    if (gid < (uint32_t)kStCleared) A.status[gid] = 0u;
+    for (uint32_t k = gid; k < nranges; k += gridDim.x * 1024u) ranges[k] = 0u;
+    for (uint32_t k = gid; k < ntiles; k += gridDim.x * 1024u) A.tile_count[k] = 0u;
     const size_t i0 = (size_t)gid * 4u;
     const size_t n = (size_t)in.n;
     int r[4] = {0, 0, 0, 0};
@@ -55,133 +59,166 @@ __global__ __launch_bounds__(256) void k_count_visible(BinInput in, CamDev cam, 
         pairs = sat_add(pairs, t[k]);
     }
     if (i0 + 4u <= n) {
-        *reinterpret_cast<uint4*>(tiles_touched + i0) = make_uint4(t[0], t[1], t[2], t[3]);      // (the array starts on a 256-byte boundary)
+        *reinterpret_cast<uint4*>(A.touched + i0) = make_uint4(t[0], t[1], t[2], t[3]);      // (the array starts on a 256-byte boundary)
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) if (i0 + k < n) tiles_touched[i0 + k] = t[k];
+        for (int k = 0; k < 4; ++k) if (i0 + k < n) A.touched[i0 + k] = t[k];
     }
-    const uint32_t inc = wave_inclusive_scan_sat(pairs);
+    vis = wave_reduce(vis, OpAdd{});
+    pairs = wave_reduce(pairs, OpSatAdd{});
+    const size_t blk = (size_t)blockIdx.x * kSuperBlocks + wave;      // the wavefront's 256 points
+    if (lane == 0) {
+        sBlk[wave] = make_uint2(vis, pairs);
+        if (blk * 256u < n) A.blk[blk] = make_uint2(vis, pairs);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint2 s = make_uint2(0u, 0u);
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) vis += (uint32_t)__shfl_xor((int)vis, d, 64);
-    const size_t blk = (size_t)blockIdx.x * 4u + (threadIdx.x >> 6);      // the wavefront's 256 points
-    if (lane == 63 && blk * 256u < n) {
-        blk_vis[blk] = vis;
-        blk_pairs[blk] = inc;
+        for (uint32_t w = 0; w < kSuperBlocks; ++w) { s.x += sBlk[w].x; s.y = sat_add(s.y, sBlk[w].y); }
+        A.sup[blockIdx.x] = s;
     }
 }
 
-// Exclusive prefix sums of the per-block counts of listed points and of pairs (the latter saturating), the totals into the
-// status words and the pair total behind the last rank's offset. Also the order in which the packing kernel takes the
-// blocks: those with kHeavyBlockPairs pairs or more first (in index order), the others after them (from the back, in
-// reverse index order: one pass, no second scan).
-// Workgroup g takes the 1024 kPer blocks from g * 1024 kPer on. What came before them it adds up by itself from the
-// counts (a few coalesced loads per thread), so no workgroup waits for another, and eight million points are eight
-// workgroups that each do one chunk instead of one that does eight in a row.
-constexpr uint32_t kHeavyBlockPairs = 1536;      // about twice the benchmark view's mean
-// kPer consecutive blocks per thread, 1024 kPer per workgroup: one up to two million points (four workgroups at a
-// million: 5.4 us against 6.9 for one), four beyond (eight million points: 10.7 us against 13.8 for 31 workgroups
-// of 1024 blocks, whose sums over what precedes them then take longer than their own chunk)
-template <uint32_t kPer>
-__global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict__ blk_vis, const uint32_t* __restrict__ blk_pairs, uint32_t nb,
-                                                      uint32_t* __restrict__ blk_vis_at, uint32_t* __restrict__ blk_pairs_at,
-                                                      uint32_t* __restrict__ status, uint32_t* __restrict__ offsets, uint32_t n,
-                                                      uint32_t* __restrict__ blk_order)
+// Listed points and pairs of the blocks before block b.
+template <int kThreads>
+__device__ __forceinline__ uint2 blocks_before(const BinArrays& A, uint32_t b, uint2* sSum)
 {
-    constexpr uint32_t kScanChunk = 1024u * kPer;
-    __shared__ uint32_t sV[16], sP[16], sH[16];
-    __shared__ uint32_t cV[16], cP[16], cH[16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t start = blockIdx.x * kScanChunk;
-    // totals of the chunks before this one
-    uint32_t carry_v = 0, carry_p = 0, carry_h = 0;
-    if (start > 0u) {
-        for (uint32_t i = threadIdx.x; i < start; i += kScanChunk) {      // (start is a multiple of kScanChunk: no tail)
-            uint32_t vv[kPer], pv[kPer];
+    const uint32_t s = b / kSuperBlocks;
+    uint32_t v = 0u, p = 0u;
+    for (uint32_t i0 = 0; i0 < s; i0 += 4u * (uint32_t)kThreads) {      // four loads in flight
+        uint2 x[4];
 #pragma unroll
-            for (uint32_t k = 0; k < kPer; ++k) { vv[k] = blk_vis[i + k * 1024u]; pv[k] = blk_pairs[i + k * 1024u]; }
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const uint32_t i = i0 + k * (uint32_t)kThreads + threadIdx.x;
+            x[k] = i < s ? A.sup[i] : make_uint2(0u, 0u);
+        }
 #pragma unroll
-            for (uint32_t k = 0; k < kPer; ++k) {
-                carry_v += vv[k]; carry_p = sat_add(carry_p, pv[k]); carry_h += pv[k] >= kHeavyBlockPairs ? 1u : 0u;
+        for (uint32_t k = 0; k < 4u; ++k) { v += x[k].x; p = sat_add(p, x[k].y); }
+    }
+    const uint32_t i = s * kSuperBlocks + threadIdx.x;
+    if (threadIdx.x < kSuperBlocks && i < b) {
+        const uint2 x = A.blk[i];
+        v += x.x; p = sat_add(p, x.y);
+    }
+    v = wave_reduce(v, OpAdd{});
+    p = wave_reduce(p, OpSatAdd{});
+    if ((threadIdx.x & 63u) == 0u) sSum[threadIdx.x >> 6] = make_uint2(v, p);
+    __syncthreads();
+    uint2 r = make_uint2(0u, 0u);
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) { r.x += sSum[w].x; r.y = sat_add(r.y, sSum[w].y); }
+    return r;
+}
+
+// Pairs per tile, and every block's room in the tiles' lists: the block's pairs are counted per tile in LDS, one atomic add per
+// tile then says how many pairs of other blocks counted so far (the order of the blocks in a list varies from run to run; the
+// depth sort does not depend on it). What precedes a block of points it adds up by itself from the counts, so no workgroup
+// waits for another. The last block leaves the totals.
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_tile_count(BinInput in, CamDev cam, BinArrays A, uint32_t nb)
+{
+    __shared__ PairLds<kThreads> S;
+    __shared__ uint32_t sCount[kTableCells / 2];      // two to a word: a block has at most 256 pairs on a tile
+    __shared__ uint2 sSum[kThreads / 64];
+    __shared__ uint16_t sList[kTableCells];               // the cells of the table that are not zero
+    __shared__ uint32_t sCells, sListed;
+    const uint32_t blk = blockIdx.x;
+    const uint2 mine = A.blk[blk];
+    if (mine.x == 0u && blk + 1u != nb) return;
+    const int i = (int)(blk * 256u + threadIdx.x);
+    const PointExtent extent = point_extent(in, i);
+    if (threadIdx.x == 0) { sCells = 0u; sListed = 0u; }
+    const uint2 before = blocks_before<kThreads>(A, blk, sSum);
+    PointPairs P = point_pairs(cam, extent);
+    if (blk + 1u == nb && threadIdx.x == 0) {
+        const uint32_t listed = min(before.x + mine.x, (uint32_t)in.n), pairs = sat_add(before.y, mine.y);
+        A.status[kStNumVis] = listed;
+        A.status[kStNumDup] = pairs;
+        A.status[kStOverflow] = pairs > A.cap ? 1u : 0u;
+        A.offsets[listed] = pairs;
+    }
+    if (threadIdx.x == 0) A.blk_at[blk] = before;
+    if (mine.x == 0u || before.y >= A.cap) {
+        if (threadIdx.x == 0) A.blk_cells[blk] = make_uint4(0u, 0u, 0u, 0u);
+        return;
+    }
+    const uint32_t total = lay_out_pairs(S, before, P);
+    {   // the rectangle of tiles that holds the block's
+        // (the lower edges as their distance from 65,535, so that all four are maxima)
+        const uint32_t lo_x = wave_reduce(P.cnt ? 0xffffu - (uint32_t)P.x0 : 0u, OpMax{}), lo_y = wave_reduce(P.cnt ? 0xffffu - (uint32_t)P.y0 : 0u, OpMax{});
+        const uint32_t hi_x = wave_reduce(P.cnt ? (uint32_t)P.x1 : 0u, OpMax{}), hi_y = wave_reduce(P.cnt ? (uint32_t)P.y1 : 0u, OpMax{});
+        if ((threadIdx.x & 63u) == 0u && threadIdx.x < 256u) S.box[threadIdx.x >> 6] = make_uint4(lo_x, lo_y, hi_x, hi_y);
+        __syncthreads();
+    }
+    const uint4 q0 = S.box[0], q1 = S.box[1], q2 = S.box[2], q3 = S.box[3];
+    const uint32_t bx = 0xffffu - __builtin_amdgcn_readfirstlane(max(max(q0.x, q1.x), max(q2.x, q3.x)));
+    const uint32_t by = 0xffffu - __builtin_amdgcn_readfirstlane(max(max(q0.y, q1.y), max(q2.y, q3.y)));
+    const uint32_t bw = __builtin_amdgcn_readfirstlane(max(max(q0.z, q1.z), max(q2.z, q3.z))) - bx;
+    const uint32_t bh = __builtin_amdgcn_readfirstlane(max(max(q0.w, q1.w), max(q2.w, q3.w))) - by;
+    const uint32_t rows = kTableCells / bw;                       // of a band
+    for (uint32_t y0 = 0; y0 < bh; y0 += rows) {
+        const uint32_t cells = min(rows, bh - y0) * bw;
+        for (uint32_t c = threadIdx.x; 2u * c < cells; c += (uint32_t)kThreads) sCount[c] = 0u;
+        __syncthreads();
+        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) {
+            if (y - by - y0 < rows) {
+                const uint32_t c = (y - by - y0) * bw + x - bx;
+                atomicAdd(&sCount[c >> 1], 1u << ((c & 1u) << 4));
+            }
+        });
+        __syncthreads();
+        // (the cells are listed first: an atomic add of a cell as the search comes to it would be a round trip to memory each)
+        const auto count_of = [&](uint32_t c) { return (sCount[c >> 1] >> ((c & 1u) << 4)) & 0xffffu; };
+        for (uint32_t c = threadIdx.x; c < cells; c += (uint32_t)kThreads)
+            if (count_of(c)) sList[atomicAdd(&sListed, 1u)] = (uint16_t)c;
+        __syncthreads();
+        const uint32_t listed = __builtin_amdgcn_readfirstlane(sListed), out = before.y + __builtin_amdgcn_readfirstlane(sCells);
+        for (uint32_t j0 = 0; j0 < listed; j0 += 4u * (uint32_t)kThreads) {      // four adds in flight
+            uint32_t at[4], xy[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4u; ++k) {
+                const uint32_t j = j0 + k * (uint32_t)kThreads + threadIdx.x;
+                if (j < listed) {
+                    const uint32_t c = sList[j], row = c / bw, x = bx + c - row * bw, y = by + y0 + row;
+                    xy[k] = x | y << 16;
+                    at[k] = atomicAdd(&A.tile_count[y * (uint32_t)cam.TX + x], count_of(c));
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < 4u; ++k) {
+                const uint32_t j = j0 + k * (uint32_t)kThreads + threadIdx.x;
+                if (j < listed) A.cells[out + j] = make_uint2(xy[k], at[k]);      // (fewer tiles than pairs below the capacity)
             }
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            carry_v += __shfl_xor(carry_v, d, 64); carry_p = sat_add(carry_p, __shfl_xor(carry_p, d, 64)); carry_h += __shfl_xor(carry_h, d, 64);
-        }
-        if (lane == 0) { cV[wave] = carry_v; cP[wave] = carry_p; cH[wave] = carry_h; }
         __syncthreads();
-        carry_v = 0; carry_p = 0; carry_h = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) { carry_v += cV[w]; carry_p = sat_add(carry_p, cP[w]); carry_h += cH[w]; }
+        if (threadIdx.x == 0) { sCells += listed; sListed = 0u; }
+        __syncthreads();      // the table is cleared for the next band
     }
-    const uint32_t idx0 = start + threadIdx.x * kPer;
-    uint32_t v[kPer], p[kPer], h[kPer];
-    uint32_t tv = 0, tp = 0, th = 0;         // this thread's totals
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        v[k] = idx0 + k < nb ? blk_vis[idx0 + k] : 0u;
-        p[k] = idx0 + k < nb ? blk_pairs[idx0 + k] : 0u;
-        h[k] = p[k] >= kHeavyBlockPairs ? 1u : 0u;
-        tv += v[k]; tp = sat_add(tp, p[k]); th += h[k];
-    }
-    uint32_t iv = tv, ip = tp, ih = th;      // inclusive over the wavefront's threads
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t uv = __shfl_up(iv, d, 64), up = __shfl_up(ip, d, 64), uh = __shfl_up(ih, d, 64);
-        if (lane >= d) { iv += uv; ip = sat_add(ip, up); ih += uh; }
-    }
-    if (lane == 63) { sV[wave] = iv; sP[wave] = ip; sH[wave] = ih; }
-    __syncthreads();
-    uint32_t bv = carry_v, bp = carry_p, bh = carry_h, cv = carry_v, cp = carry_p;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        const uint32_t wv = sV[w], wp = sP[w], wh = sH[w];
-        if (w < wave) { bv += wv; bp = sat_add(bp, wp); bh += wh; }
-        cv += wv; cp = sat_add(cp, wp);
-    }
-    // exclusive over the threads before this one = the lane below's inclusive sum
-    const uint32_t ep = __shfl_up(ip, 1, 64);
-    uint32_t ev = bv + iv - tv, eh = bh + ih - th;
-    uint32_t epairs = sat_add(bp, lane == 0 ? 0u : ep);
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        const uint32_t idx = idx0 + k;
-        if (idx < nb) {
-            blk_vis_at[idx] = ev;
-            blk_pairs_at[idx] = epairs;
-            eh += h[k];                      // heavy blocks among 0 .. idx
-            if (h[k]) blk_order[eh - 1u] = idx;
-            else blk_order[nb - 1u - (idx - eh)] = idx;
-        }
-        ev += v[k];
-        epairs = sat_add(epairs, p[k]);
-    }
-    if (threadIdx.x == 0 && start + kScanChunk >= nb) {      // the last chunk: cv, cp are the totals
-        const uint32_t m = min(cv, n);
-        status[kStNumVis] = m;
-        status[kStNumDup] = cp;
-        offsets[m] = cp;
-    }
+    if (threadIdx.x == 0) A.blk_cells[blk] = make_uint4(sCells, bx | by << 16, bw | bh << 16, 0u);
 }
 
 // 3D Gaussians: the raster record (64 bytes) of a listed point (see binning_common.h for the rest of the block's work).
-__global__ __launch_bounds__(256) void k_pack_dup(SplatsDev sp, CamDev cam, BinArrays A, Packed* __restrict__ packed)
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_pack(SplatsDev sp, CamDev cam, BinArrays A, Packed* __restrict__ packed)
 {
     const size_t N = (size_t)sp.n;
-    pack_dup_block(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth, [&](int i) {
-        // (every load before the first store: the compiler cannot know that the record overlaps none of the planes)
-        float4* dst = reinterpret_cast<float4*>(packed + i);
-        const float qa = sp.conic[i], qb = sp.conic[N + i], qc = sp.conic[2 * N + i], o = sp.opacity[i];
-        const float mx = sp.mean2d[i], my = sp.mean2d[N + i], red = sp.color[i], green = sp.color[N + i], blue = sp.color[2 * N + i];
-        const int radius = sp.radius[i];
-        const float A = 0.5f * kLog2e * qa, B = kLog2e * qb, C = 0.5f * kLog2e * qc;
-        const float L = o < 0.f ? -__builtin_inff() : __log2f(o);      // below zero: blends nowhere, as zero does (NaN stays NaN)
-        const bool safe = safely_definite(A, B, C);
-        dst[0] = make_float4(mx, my, A, B);
-        dst[1] = make_float4(C, L, red, green);
-        dst[2] = make_float4(blue, __int_as_float(radius), o, __uint_as_float(!safe ? 0u : o <= 0.98f ? kSplatPlain : kSplatDefinite));
-        dst[3] = splat_ellipse(A, B, C, L);
-    });
+    struct Parts { float qa, qb, qc, o, red, green, blue, mx, my; int radius; };
+    pack_block<kThreads>(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth,
+        [&](int i, const PointExtent& e) {
+            return Parts{sp.conic[i], sp.conic[N + i], sp.conic[2 * N + i], sp.opacity[i], sp.color[i], sp.color[N + i], sp.color[2 * N + i],
+                         e.mx, e.my, e.radius};
+        },
+        [&](int i, const Parts& p) {
+            float4* dst = reinterpret_cast<float4*>(packed + i);
+            const float A = 0.5f * kLog2e * p.qa, B = kLog2e * p.qb, C = 0.5f * kLog2e * p.qc, o = p.o;
+            const float L = o < 0.f ? -__builtin_inff() : __log2f(o);      // below zero: blends nowhere, as zero does (NaN stays NaN)
+            const bool safe = safely_definite(A, B, C);
+            dst[0] = make_float4(p.mx, p.my, A, B);
+            dst[1] = make_float4(C, L, p.red, p.green);
+            dst[2] = make_float4(p.blue, __int_as_float(p.radius), o, __uint_as_float(!safe ? 0u : o <= 0.98f ? kSplatPlain : kSplatDefinite));
+            dst[3] = splat_ellipse(A, B, C, L);
+        });
 }
 
 __global__ __launch_bounds__(256) void k_bin_begin(uint32_t* __restrict__ status, uint32_t* __restrict__ ranges, size_t nranges,
@@ -193,66 +230,20 @@ __global__ __launch_bounds__(256) void k_bin_begin(uint32_t* __restrict__ status
     if (2 * i < nranges) tile_order[i] = (uint32_t)i;      // no lists: any order will do
 }
 
-// Four consecutive sorted pairs per thread: mark where each tile's run starts and ends.
-__global__ __launch_bounds__(256) void k_tile_ranges(const uint32_t* __restrict__ tkeys, const uint32_t* __restrict__ status,
-                                                     uint32_t cap, uint32_t ntiles, uint32_t* __restrict__ ranges)
-{
-    const uint32_t P = min(status[kStNumDup], cap);
-    const uint32_t i0 = (blockIdx.x * 256u + threadIdx.x) * 4u;
-    if (i0 >= P) return;
-    uint32_t t[6];      // the pair before, the four of this thread, the pair after
-    if (i0 + 4u <= P) {
-        const uint4 v = *reinterpret_cast<const uint4*>(tkeys + i0);
-        t[1] = v.x; t[2] = v.y; t[3] = v.z; t[4] = v.w;
-    } else {
-#pragma unroll
-        for (uint32_t k = 0; k < 4u; ++k) t[1 + k] = i0 + k < P ? tkeys[i0 + k] : 0xffffffffu;
-    }
-    t[0] = i0 > 0u ? tkeys[i0 - 1u] : 0xffffffffu;
-    t[5] = i0 + 4u < P ? tkeys[i0 + 4u] : 0xffffffffu;
-#pragma unroll
-    for (uint32_t k = 0; k < 4u; ++k) {
-        const uint32_t i = i0 + k, tile = t[1 + k];
-        if (i >= P || tile >= ntiles) continue;     // tile >= ntiles cannot happen for keys written by the packing kernels; keeps the writes in bounds regardless
-        if (i == 0u || t[k] != tile) ranges[2 * tile] = i;
-        if (i + 1u == P || t[2 + k] != tile) ranges[2 * tile + 1] = i + 1u;
-    }
-}
-
-// The order in which the compositing kernels take the tiles: longest lists first. Workgroups start in index order and a
-// tile's cost grows with its list, so in image order a launch ends on whatever long tiles happen to come late, with
-// most of the chip idle. Tiles are put in classes of list length, two per octave (class 0 = longest); within a class
-// they keep the image order, so neighbours in the order are still neighbours in the image and share splat records in L2.
-// That is a stable counting sort on the class, done by one workgroup: wavefront w owns a contiguous run of tiles and
-// takes it 64 at a time. A lane finds the lanes of its class from six ballots, one per bit of the class, with no loop
-// over the classes present: the kernel runs on one compute unit, so its instruction count is its duration.
+// Where every tile's list starts and ends, and the order in which the compositing kernels take the tiles: longest lists
+// first. Workgroups start in index order and a tile's cost grows with its list, so in image order a launch ends on whatever long
+// tiles happen to come late, with most of the chip idle. Tiles are put in classes of list length, two per octave (class 0 =
+// longest); within a class they keep the image order, so neighbours in the order are still neighbours in the image and share
+// splat records in L2. That is a stable counting sort on the class: a thread takes a tile, and a lane finds the lanes of its
+// class from six ballots, one per bit of the class, with no loop over the classes present.
 constexpr int kOrderClasses = 40;           // < 63; class 63 stands for "no tile"
-constexpr uint32_t kOrderRounds = 1;        // rounds of 64 tiles per wavefront: 1,024 tiles per workgroup (measured: 8 rounds 12.0 us, 2 rounds 6.3, 1 round 5.5 for 8,160 tiles)
-// lists of kWaveListMax - 1 = 1023 entries or more are sorted by a whole workgroup; length + 1 < 1024 = 2^10 means a
-// class code of at most 2 * 9 + 1
-static_assert(kWaveListMax == 1024, "kFirstSmallClass is the class that starts at this length");
-constexpr uint32_t kFirstSmallClass = (uint32_t)(kOrderClasses - 1) - 19u;
-
+constexpr uint32_t kOrderChunk = 1024;      // tiles per workgroup, one per thread (eight per thread: 12.0 us instead of 5.5 for 8,160 tiles)
 __device__ __forceinline__ uint32_t order_class(uint32_t len)
 {
     const uint32_t x = len + 1u;
     const int e = 31 - __clz((int)x);
     const uint32_t half = e > 0 ? (x >> (e - 1)) & 1u : 0u;
     return (uint32_t)(kOrderClasses - 1) - min(2u * (uint32_t)e + half, (uint32_t)(kOrderClasses - 1));
-}
-
-// classes of the tiles tb + 64 k + lane, k = 0 .. kOrderRounds - 1, of the run that ends at t1
-__device__ __forceinline__ void order_classes(const uint2* __restrict__ range2, uint32_t tb, uint32_t t1, uint32_t lane,
-                                              uint32_t (&cls)[kOrderRounds])
-{
-    uint2 r[kOrderRounds];
-#pragma unroll
-    for (uint32_t k = 0; k < kOrderRounds; ++k) {
-        const uint32_t t = tb + k * 64u + lane;
-        r[k] = t < t1 ? range2[t] : make_uint2(0u, 0u);
-    }
-#pragma unroll
-    for (uint32_t k = 0; k < kOrderRounds; ++k) cls[k] = tb + k * 64u + lane < t1 ? order_class(r[k].y - r[k].x) : 63u;
 }
 
 // the lanes of the wavefront whose class equals this lane's
@@ -268,53 +259,53 @@ __device__ __forceinline__ uint64_t lanes_of_my_class(uint32_t cls)
     return same;
 }
 
-// Workgroup g orders the kOrderChunk tiles from g * kOrderChunk on (1,024 of them: the ballot-ranked counting and placing of its own tiles is what takes a workgroup's time). Where
-// they go also depends on the other workgroups' tiles: how many of each class lie in earlier chunks, and in later ones.
-// Every workgroup counts those for itself from the ranges, so none waits for another.
-constexpr uint32_t kOrderChunk = 16u * kOrderRounds * 64u;
+// Workgroup g takes the kOrderChunk tiles from g * kOrderChunk on. Where they go also depends on the other workgroups' tiles:
+// how many of each class lie in earlier chunks, and in later ones, and how many pairs in earlier ones. Every workgroup counts
+// those for itself, so none waits for another.
 template <bool kMulti>                      // more than one chunk
-__global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict__ ranges, uint32_t ntiles, uint32_t* __restrict__ tile_order,
-                                                     uint32_t* __restrict__ status)
+__global__ __launch_bounds__(1024) void k_tile_lists(const uint32_t* __restrict__ tile_count, uint32_t ntiles, uint32_t* __restrict__ ranges,
+                                                     uint32_t* __restrict__ tile_order, uint32_t* __restrict__ status, int long_code)
 {
     // per class: (earlier chunks,) the 16 wavefronts of this one(, later chunks)
     constexpr uint32_t kOrderSlots = kMulti ? 18u : 16u, kFirst = kMulti ? 1u : 0u;
     constexpr int kPer = (kOrderClasses * kOrderSlots + 63) / 64;
     __shared__ uint32_t count[64 * kOrderSlots];      // [class][slot]: tiles, then where the next tile of (class, slot) goes (class 63: unused, in bounds)
+    __shared__ uint32_t other[kMulti ? 2 * kOrderClasses * 16 : 1];      // [earlier, later chunks][class][lane % 16]
+    __shared__ uint32_t sPairs[2][16];                // per wavefront: pairs of its tiles, and of its share of the earlier chunks
     const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
     const uint32_t c0 = blockIdx.x * kOrderChunk, c1 = min(ntiles, c0 + kOrderChunk);
-    const uint32_t t0 = min(c1, c0 + w * (kOrderRounds * 64u)), t1 = min(c1, t0 + kOrderRounds * 64u);
+    const uint32_t t = c0 + threadIdx.x;
     const uint64_t below = (1ull << lane) - 1ull;
-    const uint2* range2 = reinterpret_cast<const uint2*>(ranges);
-
-    __shared__ uint32_t other[kMulti ? 2 * kOrderClasses * 16 : 1];      // [earlier, later chunks][class][lane % 16]
+    const uint32_t len = t < c1 ? tile_count[t] : 0u;
     for (uint32_t i = threadIdx.x; i < 64u * kOrderSlots; i += 1024u) count[i] = 0u;
     if (kMulti)
         for (uint32_t i = threadIdx.x; i < 2u * kOrderClasses * 16u; i += 1024u) other[i] = 0u;
     __syncthreads();
-    uint32_t cls[kOrderRounds];
-    order_classes(range2, t0, t1, lane, cls);
-#pragma unroll
-    for (uint32_t k = 0; k < kOrderRounds; ++k) {
-        const uint64_t same = lanes_of_my_class(cls[k]);
-        if ((same & below) == 0ull && cls[k] != 63u) count[cls[k] * kOrderSlots + kFirst + w] += (uint32_t)__popcll(same);      // first lane of its class
-    }
+    const uint32_t cls = t < c1 ? order_class(len) : 63u;
+    const uint64_t same = lanes_of_my_class(cls);
+    if ((same & below) == 0ull && cls != 63u) count[cls * kOrderSlots + kFirst + w] = (uint32_t)__popcll(same);      // first lane of its class
+    uint32_t earlier = 0u;
     if (kMulti) {      // the tiles of the other chunks, by class
         // (one of 16 counters per side and class, by lane: a wavefront's tiles are mostly of one class, and additions to
         // one LDS address take their turns)
         for (uint32_t ib = threadIdx.x; ib < ntiles; ib += 4u * 1024u) {
-            uint2 r[4];
+            uint32_t r[4];
 #pragma unroll
             for (uint32_t k = 0; k < 4u; ++k) {
                 const uint32_t i = ib + k * 1024u;
-                r[k] = i < ntiles ? range2[i] : make_uint2(0u, 0u);
+                r[k] = i < ntiles ? tile_count[i] : 0u;
             }
 #pragma unroll
             for (uint32_t k = 0; k < 4u; ++k) {
                 const uint32_t i = ib + k * 1024u;
+                if (i < c0) earlier += r[k];      // (all lists together stay below the capacity, 2^30)
                 if (i < ntiles && (i < c0 || i >= c1))
-                    atomicAdd(&other[((i < c0 ? 0u : (uint32_t)kOrderClasses) + order_class(r[k].y - r[k].x)) * 16u + (lane & 15u)], 1u);
+                    atomicAdd(&other[((i < c0 ? 0u : (uint32_t)kOrderClasses) + order_class(r[k])) * 16u + (lane & 15u)], 1u);
             }
         }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) earlier += (uint32_t)__shfl_xor((int)earlier, d, 64);
+        if (lane == 0u) sPairs[1][w] = earlier;
         __syncthreads();
         if (threadIdx.x < 2u * kOrderClasses) {
             uint32_t sum = 0;
@@ -324,6 +315,14 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict_
             count[c * kOrderSlots + (threadIdx.x < (uint32_t)kOrderClasses ? 0u : kOrderSlots - 1u)] = sum;
         }
     }
+    // where this thread's list starts
+    uint32_t inc = len;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t up = __shfl_up(inc, d);
+        if (lane >= (uint32_t)d) inc += up;
+    }
+    if (lane == 63u) sPairs[0][w] = inc;
     __syncthreads();
     if (w == 0) {      // exclusive prefix sums over (class, slot), classes 0 .. kOrderClasses - 1: kPer consecutive entries per lane
         uint32_t v[kPer], sum = 0;
@@ -339,20 +338,18 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint32_t* __restrict_
 #pragma unroll
         for (int k = 0; k < kPer; ++k) { count[lane * kPer + k] = at; at += v[k]; }
     }
-    __syncthreads();
-    // how many tiles hold kWaveListMax - 1 entries or more: they come first in the order, and the depth sort gives each a whole
-    // workgroup (the classes are cut at powers of two of length + 1, so this is where a class starts)
-    if (threadIdx.x == 0 && blockIdx.x == 0) status[kStNumBig] = count[kFirstSmallClass * kOrderSlots];
+    uint32_t start = inc - len;
 #pragma unroll
-    for (uint32_t k = 0; k < kOrderRounds; ++k) {
-        const uint64_t same = lanes_of_my_class(cls[k]);
-        const uint32_t slot = cls[k] * kOrderSlots + kFirst + w;
-        const uint32_t at = count[slot];      // every lane of the class reads it before its first lane moves it on
-        if (cls[k] != 63u) {
-            tile_order[at + (uint32_t)__popcll(same & below)] = t0 + k * 64u + lane;
-            if ((same & below) == 0ull) count[slot] = at + (uint32_t)__popcll(same);
-        }
+    for (uint32_t k = 0; k < 16u; ++k) {
+        if (k < w) start += sPairs[0][k];
+        if (kMulti) start += sPairs[1][k];
     }
+    if (t < c1) reinterpret_cast<uint2*>(ranges)[t] = len ? make_uint2(start, start + len) : make_uint2(0u, 0u);
+    __syncthreads();
+    // how many tiles hold 2^(long_code / 2) - 1 entries (1.5 times that if odd) or more: they come first in the order, and the depth sort gives each a whole
+    // workgroup (where a class starts)
+    if (threadIdx.x == 0 && blockIdx.x == 0) status[kStNumBig] = count[((uint32_t)kOrderClasses - (uint32_t)long_code) * kOrderSlots];
+    if (cls != 63u) tile_order[count[cls * kOrderSlots + kFirst + w] + (uint32_t)__popcll(same & below)] = t;
 }
 
 // Inspection only: the 64-bit keys (tile << 32 | depth bits) of the sorted pairs, rebuilt from the tile ranges, the
@@ -367,7 +364,7 @@ __global__ __launch_bounds__(256) void k_make_keys64(const uint32_t* __restrict_
 
 hipError_t launch_make_keys64(const Layout& L, char* ws, hipStream_t s)
 {
-    const uint32_t* tv = reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L));
+    const uint32_t* tv = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     hipLaunchKernelGGL(k_make_keys64, dim3((unsigned)L.tiles), dim3(256), 0, s, reinterpret_cast<const uint32_t*>(ws + L.off_ranges), tv,
                        reinterpret_cast<const uint32_t*>(ws + L.off_depth_bits), L.cap, reinterpret_cast<uint64_t*>(ws + L.off_keys64));
     return hipGetLastError();
@@ -386,92 +383,69 @@ hipError_t launch_bin_begin(const Layout& L, char* ws, hipStream_t s)
 
 BinArrays bin_arrays(const Layout& L, char* ws)
 {
+    const auto u32 = [&](size_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
     BinArrays A;
-    A.touched = reinterpret_cast<const uint32_t*>(ws + L.off_touched);
-    A.blk_vis = reinterpret_cast<const uint32_t*>(ws + L.off_blk_vis_at);
-    A.blk_pairs = reinterpret_cast<const uint32_t*>(ws + L.off_blk_pairs_at);
-    A.blk_order = reinterpret_cast<const uint32_t*>(ws + L.off_blk_order);
-    A.blk_count = reinterpret_cast<const uint32_t*>(ws + L.off_blk_vis);
-    A.order = reinterpret_cast<uint32_t*>(ws + L.off_order);
-    A.offsets = reinterpret_cast<uint32_t*>(ws + L.off_offsets);
-    A.slot_base = reinterpret_cast<uint32_t*>(ws + L.off_slot_base);
-    A.depth_bits = reinterpret_cast<uint32_t*>(ws + L.off_depth_bits);
-    A.tkeys = reinterpret_cast<uint32_t*>(ws + L.off_tkey0);
-    A.tvals = reinterpret_cast<uint32_t*>(ws + L.off_tval0);
-    A.chunk_rank = reinterpret_cast<uint32_t*>(ws + L.off_chunk_rank);
+    A.touched = u32(L.off_touched);
+    A.blk = reinterpret_cast<uint2*>(ws + L.off_blk);
+    A.sup = reinterpret_cast<uint2*>(ws + L.off_sup);
+    A.blk_at = reinterpret_cast<uint2*>(ws + L.off_blk_at);
+    A.blk_cells = reinterpret_cast<uint4*>(ws + L.off_blk_cells);
+    A.cells = reinterpret_cast<uint2*>(ws + L.off_spare);
+    A.tile_count = u32(L.off_tile_count);
+    A.ranges = u32(L.off_ranges);
+    A.order = u32(L.off_order);
+    A.offsets = u32(L.off_offsets);
+    A.slot_base = u32(L.off_slot_base);
+    A.depth_bits = u32(L.off_depth_bits);
+    A.keys = u32(L.off_keys);
+    A.vals = u32(L.off_vals);
+    A.chunk_rank = u32(L.off_chunk_rank);
     A.cap = L.cap;
-    A.status = reinterpret_cast<uint32_t*>(ws + L.off_status);
+    A.status = u32(L.off_status);
     return A;
 }
 
-// Tiles per point, listed points and pairs per block of 256 points and their prefix sums; leaves the listed count and the
-// pair total in the status words. Also the call's first launch: clears the status words and the tile ranges.
-hipError_t launch_count_visible(const BinInput& in, const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
+// Everything up to the tiles' lists having their places: tiles per point, listed points and pairs per block of 256 points, pairs
+// per tile, the ranges and the order of the tiles. Also the call's first launch: clears the status words and the tile ranges.
+hipError_t launch_bin_count(const BinInput& in, const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
 {
-    const int n = in.n;
-    if (n == 0) return hipSuccess;
-    uint32_t* blk_vis = reinterpret_cast<uint32_t*>(ws + L.off_blk_vis);
-    uint32_t* blk_pairs = reinterpret_cast<uint32_t*>(ws + L.off_blk_pairs);
-    uint32_t* status = reinterpret_cast<uint32_t*>(ws + L.off_status);
-    const unsigned nb = (unsigned)((n + 255) / 256);
-    ProfScope prof(kKCountPack, s);
-    hipLaunchKernelGGL(k_count_visible, dim3((nb + 3u) / 4u), dim3(256), 0, s, in, cam, reinterpret_cast<uint32_t*>(ws + L.off_touched), blk_vis,
-                       blk_pairs, status, reinterpret_cast<uint32_t*>(ws + L.off_ranges), (uint32_t)(2 * (size_t)L.tiles));
-    uint32_t* const vis_at = reinterpret_cast<uint32_t*>(ws + L.off_blk_vis_at);
-    uint32_t* const pairs_at = reinterpret_cast<uint32_t*>(ws + L.off_blk_pairs_at);
-    uint32_t* const offsets = reinterpret_cast<uint32_t*>(ws + L.off_offsets);
-    uint32_t* const blk_order = reinterpret_cast<uint32_t*>(ws + L.off_blk_order);
-    if (nb <= 8192u)
-        hipLaunchKernelGGL(k_scan_blocks<1>, dim3((nb + 1023u) / 1024u), dim3(1024), 0, s, blk_vis, blk_pairs, nb, vis_at, pairs_at, status,
-                           offsets, (uint32_t)n, blk_order);
-    else
-        hipLaunchKernelGGL(k_scan_blocks<4>, dim3((nb + 4095u) / 4096u), dim3(1024), 0, s, blk_vis, blk_pairs, nb, vis_at, pairs_at, status,
-                           offsets, (uint32_t)n, blk_order);
-    return hipGetLastError();
-}
-
-// Everything after the pairs are in place (in point order): stable sort by tile, tile ranges, the order in which the
-// compositing kernels take the tiles, depth order inside every tile's list.
-hipError_t launch_bin_finish(const BinInput& sp, const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
-{
-    if (sp.n == 0) return hipSuccess;
-    uint32_t* status = reinterpret_cast<uint32_t*>(ws + L.off_status);
+    if (in.n == 0) return hipSuccess;
+    const BinArrays A = bin_arrays(L, ws);
     uint32_t* ranges = reinterpret_cast<uint32_t*>(ws + L.off_ranges);
-    uint32_t* tk[2] = {reinterpret_cast<uint32_t*>(ws + L.off_tkey0), reinterpret_cast<uint32_t*>(ws + L.off_tkey1)};
-    uint32_t* tv[2] = {reinterpret_cast<uint32_t*>(ws + L.off_tval0), reinterpret_cast<uint32_t*>(ws + L.off_tval1)};
-    uint32_t* totals = reinterpret_cast<uint32_t*>(ws + L.off_totals);
-    uint32_t* tile_hist = reinterpret_cast<uint32_t*>(ws + L.off_tile_hist);
-    // tile digits: stable sort of the P pairs by tile id
-    hipError_t e = launch_radix_sort32(tk, tv, status + kStNumDup, L.cap, L.tile_bits, totals, tile_hist, s);
-    if (e != hipSuccess) return e;
-    const int fin = L.tile_passes & 1;
+    const unsigned nb = (unsigned)((in.n + 255) / 256);
     const uint32_t ntiles = (uint32_t)(cam.TX * cam.TY);      // the call's tile grid (a patch covers fewer tiles than the image the workspace is sized for)
-    uint32_t* tile_order = reinterpret_cast<uint32_t*>(ws + L.off_tile_order);
     {
-        ProfScope prof(kKTileRanges, s);
-        hipLaunchKernelGGL(k_tile_ranges, dim3((L.cap + 1023u) / 1024u), dim3(256), 0, s, tk[fin], status, L.cap, (uint32_t)L.tiles, ranges);
-        if (ntiles <= kOrderChunk) hipLaunchKernelGGL(k_tile_order<false>, dim3(1), dim3(1024), 0, s, ranges, ntiles, tile_order, status);
-        else hipLaunchKernelGGL(k_tile_order<true>, dim3((ntiles + kOrderChunk - 1u) / kOrderChunk), dim3(1024), 0, s, ranges, ntiles, tile_order, status);
+        ProfScope prof(kKCountVisible, s);
+        hipLaunchKernelGGL(k_count_visible, dim3((nb + kSuperBlocks - 1u) / kSuperBlocks), dim3(1024), 0, s, in, cam, A, ranges,
+                           (uint32_t)(2 * (size_t)L.tiles), ntiles);
     }
-    // depth digits: every tile's list, now in point order, into depth order (the tile ids in tk[fin] are spent: that
-    // array and the other pair of buffers are the scratch of lists too long for LDS)
-    return launch_tile_depth_sort(ranges, tile_order, ntiles, status, reinterpret_cast<const uint32_t*>(ws + L.off_depth_bits), L.cap,
-                                  tk[fin], tv[fin], tk[fin ^ 1], tv[fin ^ 1], s);
+    {
+        ProfScope prof(kKTileCount, s);
+        if (block_threads(in.n) == 256) hipLaunchKernelGGL(k_tile_count<256>, dim3(nb), dim3(256), 0, s, in, cam, A, nb);
+        else hipLaunchKernelGGL(k_tile_count<1024>, dim3(nb), dim3(1024), 0, s, in, cam, A, nb);
+    }
+    ProfScope prof(kKTileLists, s);
+    uint32_t* tile_order = reinterpret_cast<uint32_t*>(ws + L.off_tile_order);
+    if (ntiles <= kOrderChunk) hipLaunchKernelGGL(k_tile_lists<false>, dim3(1), dim3(1024), 0, s, A.tile_count, ntiles, ranges, tile_order, A.status, long_list_code(ntiles));
+    else hipLaunchKernelGGL(k_tile_lists<true>, dim3((ntiles + kOrderChunk - 1u) / kOrderChunk), dim3(1024), 0, s, A.tile_count, ntiles, ranges, tile_order, A.status, long_list_code(ntiles));
+    return hipGetLastError();
 }
 
 hipError_t launch_bin_sort(const SplatsDev& sp, const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
 {
     if (sp.n == 0) return launch_bin_begin(L, ws, s);      // nothing to count: only the cleared status words and ranges
-    hipError_t e = launch_count_visible(BinInput{sp.n, sp.mean2d, sp.radius}, cam, L, ws, s);
+    hipError_t e = launch_bin_count(BinInput{sp.n, sp.mean2d, sp.radius}, cam, L, ws, s);
     if (e != hipSuccess) return e;
     {
-        ProfScope prof(kKDuplicate, s);
-        hipLaunchKernelGGL(k_pack_dup, dim3((unsigned)((sp.n + 255) / 256)), dim3(256), 0, s, sp, cam, bin_arrays(L, ws),
-                           reinterpret_cast<Packed*>(ws + L.off_packed));
+        ProfScope prof(kKPack, s);
+        const unsigned nb = (unsigned)((sp.n + 255) / 256);
+        Packed* packed = reinterpret_cast<Packed*>(ws + L.off_packed);
+        if (block_threads(sp.n) == 256) hipLaunchKernelGGL(k_pack<256>, dim3(nb), dim3(256), 0, s, sp, cam, bin_arrays(L, ws), packed);
+        else hipLaunchKernelGGL(k_pack<1024>, dim3(nb), dim3(1024), 0, s, sp, cam, bin_arrays(L, ws), packed);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return launch_bin_finish(BinInput{sp.n, sp.mean2d, sp.radius}, cam, L, ws, s);
+    return launch_tile_depth_sort(cam, L, ws, s);
 }
 
 }  // namespace pbdr

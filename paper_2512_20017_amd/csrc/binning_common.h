@@ -1,8 +1,10 @@
 // Device code shared by the binning kernels of the 3D-Gaussian and the 2D-surfel variants: the block of 256 consecutive
-// points that compacts its visible points, writes their raster records and emits their (tile, point) pairs.
+// points that compacts its visible points, writes their raster records and puts their (tile, point) pairs into the tiles'
+// lists.
 #pragma once
 #include "pbdr_internal.h"
 #include "pair_reduce.h"
+#include "wave_ops.h"
 
 namespace pbdr {
 
@@ -13,171 +15,261 @@ __device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b)      // a, b
 {
     return min(a + b, kPairSat);
 }
+struct OpSatAdd { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return sat_add(a, b); } };
 
-__device__ __forceinline__ uint32_t wave_inclusive_scan_sat(uint32_t v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= d) v = sat_add(v, t);
-    }
-    return v;
-}
-
-// What the pair emission reads and writes (device pointers into the workspace).
+// What the binning kernels keep per block of 256 points, per tile and per pair (device pointers into the workspace).
+constexpr uint32_t kSuperBlocks = 16;      // blocks of points per workgroup of k_count_visible
 struct BinArrays {
-    const uint32_t* touched;     // [n] tiles per point, 0 = not listed
-    const uint32_t* blk_vis;     // [blocks] listed points in the blocks before this one
-    const uint32_t* blk_pairs;   // [blocks] pairs of the blocks before this one (saturating)
-    const uint32_t* blk_order;   // [blocks] the block of points each workgroup takes: those with the most pairs first
-    const uint32_t* blk_count;   // [blocks] listed points of each block
+    uint32_t* touched;           // [n] tiles per point, 0 = not listed
+    uint2* blk;                  // [blocks] listed points and their pairs (saturating)
+    uint2* sup;                  // [blocks / kSuperBlocks] the same per kSuperBlocks blocks
+    uint2* blk_at;               // [blocks] listed points and pairs in the blocks before this one (of blocks with a listed point)
+    uint4* blk_cells;            // [blocks] {tiles the block's pairs lie on, x | y << 16 of its rectangle of tiles, width | height << 16, -}
+    uint2* cells;                // [cap] those tiles, from blk_at.y on: {x | y << 16, pairs of the blocks that counted the tile before}
+    uint32_t* tile_count;        // [tiles] pairs
+    const uint32_t* ranges;      // [tiles][2]
     uint32_t* order;             // [n] listed points in index order ("rank" -> point)
-    uint32_t* offsets;           // [n + 1] first pair of each rank; offsets[listed] = pair total (written by the block scan)
+    uint32_t* offsets;           // [n + 1] first pair of each rank; offsets[listed] = pair total
     uint32_t* slot_base;         // [n] first pair of each listed point, by point index
     uint32_t* depth_bits;        // [n] bit pattern of the depth, by point index
-    uint32_t* tkeys;             // [cap] tile id of each pair, in emission order
-    uint32_t* tvals;             // [cap] point index of each pair
+    uint32_t* keys;              // [cap] depth bits of each pair, tile by tile
+    uint32_t* vals;              // [cap] point index of each pair
     uint32_t* chunk_rank;        // rank owning every 256th pair (pair_reduce.h)
     uint32_t cap;
     uint32_t* status;
 };
 
-// One block of 256 consecutive points. A listed point gets its rank among the listed points (index order), its raster
-// record (pack(i), supplied by the variant), and the slots [at, at + count) of the pair list, where its pairs go in
-// row-major order over its tile rectangle. Every (tile, point) pair of a wavefront's 64 consecutive points is written
-// by whichever lane comes next, so the work is balanced whatever the mix of small and large splats: the pairs of those
-// 64 points occupy one contiguous range (the slots are a prefix sum); lane l writes slots B + l, B + l + 64, ... and
-// finds the owning point of a slot from the range starts (see the loop). Points are emitted in index
-// order: the depth order of each tile's list is made afterwards, tile by tile (k_tile_depth_sort).
-// In a block that holds a point with kWideBlock pairs or more, the points with kWidePairs or more are left out of that loop
-// and written by the whole workgroup, 256 slots per trip of two stores and four additions: a step of 64 slots is a chain of
-// LDS and cross-lane reads, and one splat over the whole image kept one wavefront at it when all others had ended. 1M disks
-// at 1920x1080, three of eight scenes with such a splat: this kernel 76 -> 23 us, step 785 -> 727, 749 -> 725 and 831 -> 810 us;
-// scenes without one as before (within 0.1 %).
-// A trip is a step that four wavefronts share, so it pays from somewhat over 256 slots: all lists of 300 points at 1920x1080,
-// without / with, 119.4 / 120.6 us at 289 tiles a point, 123.2 / 121.5 at 306, 140.5 / 123.3 at 380, 1033 / 307 over the image.
-// And doing both after one another costs more than either (points on 225 to 256 tiles, half of them left out: 105.1 / 114.1),
-// so a block of points below kWideBlock leaves out none (105.1). A wavefront without such a point takes the loop without the
-// test that steps over their slots (points on 210 tiles: 105.3 -> 101.2).
-constexpr uint32_t kWidePairs = 256, kWideBlock = 320;
+// ---- the pairs of a block of 256 points, spread over the kThreads threads of its workgroup --------------------------------------------------
+// A pair's slot is its place in the order by point, then row by row over the point's tile rectangle; slots at or beyond the
+// capacity are dropped. Points of fewer than kWidePairs pairs are walked together, 64 pairs per wavefront and step, whatever
+// the mix of sizes: their pairs are numbered by a prefix sum, and the owner of a number is the last point whose range
+// starts at or before it. The points whose range starts inside a step leave their number at that place in LDS, and a
+// running maximum over the lanes (DPP) hands every lane its owner; the owner of the step's first pair is counted from the
+// starts, four per lane. The wavefronts take the steps in turn, so a block with thousands of pairs keeps all of them busy.
+// Wider points are walked by the whole workgroup one after the other, kThreads pairs per trip of a few additions (one splat over
+// the whole image would keep a wavefront at its steps of 64 when all others have ended).
+constexpr uint32_t kWidePairs = 256;
 
-template <class Pack>
-__device__ __forceinline__ void pack_dup_block(const BinInput& in, const CamDev& cam, const BinArrays& A,
-                                               const float* __restrict__ depth, Pack pack)
+template <int kThreads>
+struct PairLds {
+    static constexpr int kWaves = kThreads / 64;
+    uint32_t start[256];      // first number of the point's pairs among those walked together, ~0 if it has none
+    uint32_t at[256];         // slot of its first pair
+    uint32_t xy[256];         // its rectangle: x | y << 16 of the first tile (a grid has at most 4096 x 4096 tiles)
+    uint32_t size[256];       // width | height << 16
+    uint32_t mark[kWaves][64];
+    uint16_t wide[256];       // the wide points
+    uint32_t sums[3][4];
+    uint4 box[4];             // (k_tile_count)
+    uint32_t num_wide;
+};
+
+struct PointPairs {           // this thread's point of the block
+    uint32_t cnt;             // pairs (tiles touched), 0 = not listed
+    uint32_t slot_rank;       // listed points before it
+    uint32_t at;              // pairs before it (saturating)
+    int x0, y0, x1, y1;
+};
+
+// What of point i says where its pairs lie (nothing for a point that is culled). Asked for at once: reading the count of tiles that
+// k_count_visible left, and then the rest for the points that have any, would be two round trips in a row.
+struct PointExtent { int radius; float mx, my; };
+__device__ __forceinline__ PointExtent point_extent(const BinInput& in, int i)      // (a block's points are its first 256 threads')
 {
-    __shared__ uint32_t sMark[4][64];      // per wavefront: which lane's range starts at each slot of the current step
-    __shared__ uint32_t sVis[4], sPairs[4], sLarge[4];
-    __shared__ uint4 sWide[256];           // the block's wide points: first slot; pairs; x0, y0; width of the rectangle, place in the block
-    __shared__ uint32_t sNumWide;
-    // the blocks with many pairs are started first: their wavefronts run longest (64 slots per step), and in index order
-    // the launch ended on the few that happened to come late
-    const uint32_t blk = A.blk_order[blockIdx.x];
-    // a block none of whose points is listed has nothing to write (most blocks, when the view sees a tenth of a large cloud)
-    if (A.blk_count[blk] == 0u) return;
-    const int i = (int)(blk * 256u + threadIdx.x);
+    if (threadIdx.x >= 256u || i >= in.n) return PointExtent{0, 0.f, 0.f};
+    return PointExtent{in.radius[i], in.mean2d[i], in.mean2d[(size_t)in.n + i]};
+}
+
+// Its pairs (slot_rank and at are lay_out_pairs()'s).
+__device__ __forceinline__ PointPairs point_pairs(const CamDev& cam, const PointExtent& e)
+{
+    PointPairs P;
+    P.cnt = 0u;
+    P.x0 = P.y0 = P.x1 = P.y1 = 0;
+    if (e.radius > 0) {
+        tile_rect(cam, e.mx, e.my, e.radius, P.x0, P.y0, P.x1, P.y1);
+        P.cnt = (uint32_t)(max(P.x1 - P.x0, 0) * max(P.y1 - P.y0, 0));
+    }
+    return P;
+}
+
+// Lays the block's points out for walk_pairs(). before: listed points and pairs of the blocks before this one. Returns the
+// number of pairs that are walked together. Every thread of the workgroup calls it; it ends with the LDS written and visible.
+template <int kThreads>
+__device__ __forceinline__ uint32_t lay_out_pairs(PairLds<kThreads>& S, uint2 before, PointPairs& P)
+{
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t cnt = (i < in.n) ? A.touched[i] : 0u;
-    const bool vis = cnt > 0u;
+    const bool vis = P.cnt > 0u;
+    const bool wide = P.cnt >= kWidePairs;
+    const uint32_t narrow = wide ? 0u : P.cnt;
     const unsigned long long vm = __ballot(vis);
-    const uint32_t inc = wave_inclusive_scan_sat(cnt);
-    const bool large = __ballot(cnt >= kWideBlock) != 0ull;
-    if (lane == 63) { sVis[wave] = (uint32_t)__popcll(vm); sPairs[wave] = inc; sLarge[wave] = large ? 1u : 0u; }
-    if (threadIdx.x == 0) sNumWide = 0u;
+    const uint32_t inc = wave_inclusive_scan(P.cnt, OpSatAdd{});
+    const uint32_t ninc = wave_inclusive_scan(narrow, OpAdd{});      // (at most 255 * 256 in all)
+    if (threadIdx.x == 0) S.num_wide = 0u;
+    if (lane == 63 && wave < 4) { S.sums[0][wave] = (uint32_t)__popcll(vm); S.sums[1][wave] = inc; S.sums[2][wave] = ninc; }
     __syncthreads();
-    uint32_t slot = A.blk_vis[blk] + (uint32_t)__popcll(vm & ((1ull << lane) - 1ull));
-    const uint32_t below = __shfl_up(inc, 1, 64);                    // exclusive = the lane below's inclusive sum
-    uint32_t at = sat_add(A.blk_pairs[blk], lane == 0 ? 0u : below);
+    const uint32_t below = __shfl_up(inc, 1, 64);            // exclusive = the lane below's inclusive sum
+    P.slot_rank = before.x + (uint32_t)__popcll(vm & ((1ull << lane) - 1ull));
+    P.at = sat_add(before.y, lane == 0 ? 0u : below);
+    uint32_t nat = ninc - narrow, total = 0u;
 #pragma unroll
-    for (int w = 0; w < 3; ++w)
-        if (w < wave) { slot += sVis[w]; at = sat_add(at, sPairs[w]); }
-    int x0 = 0, y0 = 0, x1 = 0, y1 = 0;
-    if (vis) {
-        const float mx = in.mean2d[i], my = in.mean2d[(size_t)in.n + i];
-        tile_rect(cam, mx, my, in.radius[i], x0, y0, x1, y1);
-        A.order[slot] = (uint32_t)i;
-        A.offsets[slot] = at;
-        A.slot_base[i] = at;
-        A.depth_bits[i] = __float_as_uint(depth[i]);
-        pack(i);
-        // which rank owns every 256th pair (for the pair-balanced gather of the backward pass)
-        const uint32_t end = min(at + cnt, A.cap);
-        for (uint32_t c = (at + kChunkPairs - 1) / kChunkPairs; (uint64_t)c * kChunkPairs < end; ++c) A.chunk_rank[c] = slot;
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) { P.slot_rank += S.sums[0][w]; P.at = sat_add(P.at, S.sums[1][w]); nat += S.sums[2][w]; }
+        total += S.sums[2][w];
     }
-    const bool wide = cnt >= kWidePairs && (sLarge[0] | sLarge[1] | sLarge[2] | sLarge[3]) != 0u;
-    const unsigned long long wide_lanes = __ballot(wide);
-    if (wide) {
-        const uint32_t pairs = at < A.cap ? min(cnt, A.cap - at) : 0u;      // (a grid has at most 4096 x 4096 tiles)
-        sWide[atomicAdd(&sNumWide, 1u)] = make_uint4(at, pairs, (uint32_t)x0 | (uint32_t)y0 << 16, (uint32_t)(x1 - x0) | threadIdx.x << 16);
+    if (kThreads == 256 || threadIdx.x < 256u) {
+        S.start[threadIdx.x] = narrow ? nat : 0xffffffffu;
+        S.at[threadIdx.x] = P.at;
+        S.xy[threadIdx.x] = (uint32_t)P.x0 | (uint32_t)P.y0 << 16;
+        S.size[threadIdx.x] = (uint32_t)(P.x1 - P.x0) | (uint32_t)(P.y1 - P.y0) << 16;
     }
-    const int w = wide ? 0 : x1 - x0;      // 0: no slot of this point is written by the wavefront's loop
-    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)at, 0);
-    const uint32_t last_raw = (uint32_t)__builtin_amdgcn_readlane((int)(at + cnt), 63);
-    const uint32_t last = min(last_raw, A.cap);        // slots at or beyond the capacity are dropped
-    __builtin_amdgcn_wave_barrier();
-    // Uniform trip count: every lane takes part in the cross-lane reads of each step, only lanes with a slot store.
-    // The owner of slot u is the last lane whose range starts at or before u (the ranges are a prefix sum: no gaps, and
-    // the ranges of listed points start at distinct slots). Per step of 64 slots: the lanes whose range starts inside
-    // the step leave their number at that slot's place in LDS, and a running maximum over the lanes (DPP), carried from
-    // step to step, hands every slot its owner - one LDS round trip per step where a binary search over the 64 range
-    // ends took six in a row, which is what the wavefronts with thousands of pairs, the last to finish, were made of.
-    int carry = -1;
-    const auto step = [&](uint32_t base) {
-        const uint32_t u = base + lane;
-        sMark[wave][lane] = 0xffffffffu;
-        if (vis && at - base < 64u) sMark[wave][at - base] = (uint32_t)lane;      // at >= base or the difference wraps past 64
-        __builtin_amdgcn_wave_barrier();
-        int lo = (int)sMark[wave][lane];                  // -1 where no range starts
-        __builtin_amdgcn_wave_barrier();
-        lo = max(lo, __builtin_amdgcn_update_dpp(-1, lo, 0x111, 0xf, 0xf, false));      // row_shr:1
-        lo = max(lo, __builtin_amdgcn_update_dpp(-1, lo, 0x112, 0xf, 0xf, false));      // row_shr:2
-        lo = max(lo, __builtin_amdgcn_update_dpp(-1, lo, 0x114, 0xf, 0xf, false));      // row_shr:4
-        lo = max(lo, __builtin_amdgcn_update_dpp(-1, lo, 0x118, 0xf, 0xf, false));      // row_shr:8
-        lo = max(lo, __builtin_amdgcn_update_dpp(-1, lo, 0x142, 0xa, 0xf, false));      // row_bcast:15 into rows 1 and 3
-        lo = max(lo, __builtin_amdgcn_update_dpp(-1, lo, 0x143, 0xc, 0xf, false));      // row_bcast:31 into rows 2 and 3
-        lo = max(lo, carry);
-        carry = __builtin_amdgcn_readlane(lo, 63);
-        const int src = max(lo, 0);
-        const int ox0 = __shfl(x0, src, 64), oy0 = __shfl(y0, src, 64), ow = __shfl(w, src, 64);
-        const uint32_t oat = (uint32_t)__shfl((int)at, src, 64);
-        const uint32_t oid = blk * 256u + (uint32_t)(wave * 64 + src);
-        if (u < last && lo >= 0 && ow > 0) {
-            const int t = (int)(u - oat);
-            const int ty = oy0 + t / ow, tx = ox0 + t - (t / ow) * ow;
-            A.tkeys[u] = (uint32_t)(ty * cam.TX + tx);
-            A.tvals[u] = oid;
+    if (wide) S.wide[atomicAdd(&S.num_wide, 1u)] = (uint16_t)threadIdx.x;
+    __syncthreads();
+    return total;
+}
+
+// pair(x, y, place of its point in the block) for every pair of the block whose slot lies below the capacity
+template <int kThreads, class Pair>
+__device__ __forceinline__ void walk_pairs(PairLds<kThreads>& S, uint32_t total, uint32_t cap, Pair pair)
+{
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t st[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4u; ++q) st[q] = S.start[q * 64u + lane];
+    for (uint32_t base = wave * 64u; base < total; base += (uint32_t)kThreads) {
+        uint32_t first = 0u;      // owner of the step's first pair
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+            const unsigned long long m = __ballot(st[q] <= base);
+            if (m) first = q * 64u + 63u - (uint32_t)__builtin_clzll(m);
         }
-    };
-    if (wide_lanes == 0ull) {
-        for (uint32_t base = first; base < last; base += 64) step(base);
-    } else {
-        for (uint32_t base = first; base < last;) {
-            step(base);
-            base += 64u;
-            if (carry >= 0 && ((wide_lanes >> carry) & 1ull) != 0ull) {      // on to the step in which a wide point's range ends
-                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)(at + cnt), carry);
-                if (end > base) base += (end - base) & ~63u;
+        S.mark[wave][lane] = first;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q)
+            if (st[q] - base < 64u) S.mark[wave][st[q] - base] = q * 64u + lane;      // (a start before base wraps past 64)
+        __builtin_amdgcn_wave_barrier();
+        int own = (int)S.mark[wave][lane];
+        __builtin_amdgcn_wave_barrier();
+        own = max(own, __builtin_amdgcn_update_dpp(-1, own, 0x111, 0xf, 0xf, false));      // row_shr:1
+        own = max(own, __builtin_amdgcn_update_dpp(-1, own, 0x112, 0xf, 0xf, false));      // row_shr:2
+        own = max(own, __builtin_amdgcn_update_dpp(-1, own, 0x114, 0xf, 0xf, false));      // row_shr:4
+        own = max(own, __builtin_amdgcn_update_dpp(-1, own, 0x118, 0xf, 0xf, false));      // row_shr:8
+        own = max(own, __builtin_amdgcn_update_dpp(-1, own, 0x142, 0xa, 0xf, false));      // row_bcast:15 into rows 1 and 3
+        own = max(own, __builtin_amdgcn_update_dpp(-1, own, 0x143, 0xc, 0xf, false));      // row_bcast:31 into rows 2 and 3
+        const uint32_t e = base + lane;
+        if (e < total) {
+            const uint32_t t = e - S.start[own], w = S.size[own] & 0xffffu, xy = S.xy[own];
+            if (S.at[own] + t < cap) {
+                // t / w for t, w < 256: the quotient of t + 1/2 stays 1 / (2 w) away from any whole number
+                const uint32_t row = (uint32_t)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)w));
+                pair((xy & 0xffffu) + t - row * w, (xy >> 16) + row, (uint32_t)own);
             }
         }
     }
-    __syncthreads();
-    const uint32_t num_wide = __builtin_amdgcn_readfirstlane(sNumWide);
+    const uint32_t num_wide = __builtin_amdgcn_readfirstlane(S.num_wide);
     for (uint32_t k = 0; k < num_wide; ++k) {
-        const uint4 e = sWide[k];
-        const uint32_t ow = e.w & 0xffffu, id = blk * 256u + (e.w >> 16);
-        const uint32_t dy = 256u / ow, dx = 256u - dy * ow;      // a step of 256 slots: rows and columns
-        uint32_t ty = threadIdx.x / ow, tx = threadIdx.x - ty * ow;
-        uint32_t key = ((e.z >> 16) + ty) * (uint32_t)cam.TX + (e.z & 0xffffu) + tx;
-        const uint32_t dkey = dy * (uint32_t)cam.TX + dx, wrap = (uint32_t)cam.TX - ow;
-        for (uint32_t t = threadIdx.x; t < e.y; t += 256u) {
-            A.tkeys[e.x + t] = key;
-            A.tvals[e.x + t] = id;
-            tx += dx;
-            key += dkey;
-            if (tx >= ow) { tx -= ow; key += wrap; }
+        const uint32_t own = S.wide[k], at = S.at[own], xy = S.xy[own], w = S.size[own] & 0xffffu, h = S.size[own] >> 16;
+        const uint32_t dy = (uint32_t)kThreads / w, dx = (uint32_t)kThreads - dy * w;      // a step: rows and columns
+        uint32_t ty = threadIdx.x / w, tx = threadIdx.x - ty * w;
+        for (uint32_t t = threadIdx.x; t < w * h && at + t < cap; t += (uint32_t)kThreads) {
+            pair((xy & 0xffffu) + tx, (xy >> 16) + ty, own);
+            tx += dx; ty += dy;
+            if (tx >= w) { tx -= w; ++ty; }
         }
     }
-    if (lane == 0 && last_raw > A.cap) A.status[kStOverflow] = 1u;
+}
+
+// A block's tiles are counted in a table of its rectangle of tiles in LDS, kTableCells at a time (bands of whole rows).
+// Points in Z-order make that rectangle small: a dozen tiles by a dozen on the benchmark's views.
+constexpr uint32_t kTableCells = 4096;      // at least one row of the widest grid
+
+// Threads per block of 256 points, in k_tile_count and the packing kernels. A block's pairs may be thousands, and where the blocks
+// do not fill the chip the largest one is the launch: 1,024 threads (30k points at 1031x517, counting / packing 13.9 / 14.8 us with 256,
+// 8.7 / 9.2 with 1,024; 200k at 1280x720 28.3 / 32.6 and 24.6 / 25.3 for two views). Where they do, 256 (1M points, 256 / 1,024:
+// 20.6 / 29.8 and 32.4 / 31.9).
+inline int block_threads(int n) { return (n + 255) / 256 <= 1024 ? 1024 : 256; }
+
+// One block of 256 consecutive points. A listed point gets its rank among the listed points (index order), its raster
+// record (store(i, load(i, its extent)), supplied by the variant), and the slots [at, at + count) of its pairs, where the backward
+// pass leaves their partial sums. Its pairs go into the tiles' lists: k_tile_count has reserved room in each list for all pairs of
+// the block, and here every pair takes the next place of its tile's room (an LDS counter per tile of the block). So a list holds its
+// pairs in no particular order; k_tile_depth_sort orders them by depth bits and, among equals, by point index.
+// A chain of round trips to memory per block, so what can be asked for early is: the record's parts before the block is laid out,
+// the tiles' starts before the record is written.
+template <int kThreads, class Load, class Store>
+__device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam, const BinArrays& A, const float* __restrict__ depth, Load load, Store store)
+{
+    __shared__ PairLds<kThreads> S;
+    __shared__ uint32_t sNext[kTableCells];      // where the next pair of each tile goes
+    __shared__ uint32_t sDepth[256];
+    const uint32_t blk = blockIdx.x;
+    const int i = (int)(blk * 256u + threadIdx.x);
+    const uint2 before = A.blk_at[blk];
+    const uint4 box = A.blk_cells[blk];
+    // a block none of whose points is listed has nothing to write (most blocks, when the view sees a tenth of a large cloud)
+    if (A.blk[blk].x == 0u) return;
+    const PointExtent extent = point_extent(in, i);
+    PointPairs P = point_pairs(cam, extent);
+    const bool listed = P.cnt > 0u;
+    decltype(load(i, extent)) rec;
+    uint32_t bits = 0u;
+    if (listed) { rec = load(i, extent); bits = __float_as_uint(depth[i]); }
+    // 1,024 of the block's tiles; more are fetched where they are used
+    constexpr uint32_t kPer = 1024u / (uint32_t)kThreads;
+    uint2 cell[kPer];
+    uint32_t start[kPer];
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        const uint32_t j = k * (uint32_t)kThreads + threadIdx.x;
+        cell[k] = make_uint2(0u, 0u);
+        if (j < box.x) cell[k] = A.cells[before.y + j];
+    }
+    const auto tile_of = [&](const uint2& c) { return (c.x >> 16) * (uint32_t)cam.TX + (c.x & 0xffffu); };
+    const uint32_t total = lay_out_pairs(S, before, P);
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        start[k] = 0u;
+        if (k * (uint32_t)kThreads + threadIdx.x < box.x) start[k] = A.ranges[2u * tile_of(cell[k])];
+    }
+    if (listed) {
+        sDepth[threadIdx.x] = bits;
+        A.order[P.slot_rank] = (uint32_t)i;
+        A.offsets[P.slot_rank] = P.at;
+        A.slot_base[i] = P.at;
+        A.depth_bits[i] = bits;
+        store(i, rec);
+        // which rank owns every 256th pair (for the pair-balanced gather of the backward pass)
+        const uint32_t end = min(P.at + P.cnt, A.cap);
+        for (uint32_t c = (P.at + kChunkPairs - 1) / kChunkPairs; (uint64_t)c * kChunkPairs < end; ++c) A.chunk_rank[c] = P.slot_rank;
+    }
+    const uint32_t bx = box.y & 0xffffu, by = box.y >> 16, bw = box.z & 0xffffu, bh = box.z >> 16;
+    if (box.x == 0u) return;                     // every pair lies beyond the capacity
+    const uint32_t rows = kTableCells / bw;      // of a band
+    for (uint32_t y0 = 0; y0 < bh; y0 += rows) {
+        if (y0) __syncthreads();                 // the band before has placed its pairs
+        const auto put = [&](const uint2& c, uint32_t at) {
+            const uint32_t x = c.x & 0xffffu, y = c.x >> 16;
+            if (y - by - y0 < rows) sNext[(y - by - y0) * bw + x - bx] = at + c.y;
+        };
+#pragma unroll
+        for (uint32_t k = 0; k < kPer; ++k)
+            if (k * (uint32_t)kThreads + threadIdx.x < box.x) put(cell[k], start[k]);
+        for (uint32_t j = 1024u + threadIdx.x; j < box.x; j += (uint32_t)kThreads) {
+            const uint2 c = A.cells[before.y + j];
+            put(c, A.ranges[2u * tile_of(c)]);
+        }
+        __syncthreads();
+        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t own) {
+            if (y - by - y0 < rows) {
+                const uint32_t pos = atomicAdd(&sNext[(y - by - y0) * bw + x - bx], 1u);
+                if (pos < A.cap) {               // always true for consistent inputs
+                    A.keys[pos] = sDepth[own];
+                    A.vals[pos] = blk * 256u + own;
+                }
+            }
+        });
+    }
 }
 
 }  // namespace pbdr

@@ -721,7 +721,7 @@ hipError_t launch_composite_fwd(const CamDev& cam, const Layout& L, char* ws, co
 {
     const uint32_t* ranges = reinterpret_cast<const uint32_t*>(ws + L.off_ranges);
     const uint32_t* tile_order = reinterpret_cast<const uint32_t*>(ws + L.off_tile_order);
-    const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L));
+    const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     const Packed* packed = reinterpret_cast<const Packed*>(ws + L.off_packed);
     ProfScope prof(kKCompositeFwd, s);
     hipLaunchKernelGGL(k_composite_fwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam, ranges, tile_order, vals, packed,
@@ -740,7 +740,7 @@ hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, in
 {
     const uint32_t* ranges = reinterpret_cast<const uint32_t*>(ws + L.off_ranges);
     const uint32_t* tile_order = reinterpret_cast<const uint32_t*>(ws + L.off_tile_order);
-    const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L));
+    const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     const Packed* packed = reinterpret_cast<const Packed*>(ws + L.off_packed);
     const uint32_t* offsets = reinterpret_cast<const uint32_t*>(ws + L.off_offsets);
     const uint32_t* slot_base = reinterpret_cast<const uint32_t*>(ws + L.off_slot_base);
@@ -776,7 +776,7 @@ hipError_t launch_render_stats(const CamDev& cam, const Layout& L, char* ws, uin
 {
     const uint32_t* ranges = reinterpret_cast<const uint32_t*>(ws + L.off_ranges);
     const uint32_t* tile_order = reinterpret_cast<const uint32_t*>(ws + L.off_tile_order);
-    const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L));
+    const uint32_t* vals = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     const Packed* packed = reinterpret_cast<const Packed*>(ws + L.off_packed);
     ProfScope prof(kKStats, s);
     hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, s, reinterpret_cast<float*>(counters), 0.f, (size_t)4);

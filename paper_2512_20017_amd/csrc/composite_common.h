@@ -16,7 +16,7 @@ struct TileCtx {
 };
 
 // Workgroup b takes tile tile_order[b]: the hardware starts workgroups in index order, and the order array lists the
-// tiles with the longest lists first (k_tile_order), so the launch does not end on a few long tiles with the chip idle.
+// tiles with the longest lists first (k_tile_lists), so the launch does not end on a few long tiles with the chip idle.
 __device__ __forceinline__ TileCtx tile_ctx(const CamDev& cam, const uint32_t* __restrict__ ranges,
                                             const uint32_t* __restrict__ tile_order)
 {

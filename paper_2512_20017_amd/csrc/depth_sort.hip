@@ -1,0 +1,742 @@
+// Depth order inside each tile's list. The binning kernels leave every tile's list of (depth bits, point index) pairs in no
+// particular order, one that may differ from run to run; here each list is put into the order of the depth bits, equal ones by
+// point index. One launch of workgroups of eight wavefronts, every list on its own:
+//   - short lists (long_list_from(): how short depends on how many lists there are; k_tile_lists lists the tiles longest first and
+//     says how many are long): one WAVEFRONT per list, no workgroup barrier anywhere. Up to 64 entries by counting (every lane
+//     compares its key with all others through the scalar unit), else stable least-significant-digit radix passes with 10-bit
+//     digits. Keys and positions live in registers in list order; a pass scatters them into the wavefront's 6.5 KB of LDS and reads
+//     them back in the new order;
+//   - up to 5,632 entries: the same by a whole workgroup, each wavefront with its part of the list in registers;
+//   - up to 8,192: what moves is the permutation (16-bit positions, two copies in LDS); the keys are fetched through it;
+//   - longer lists: keys and values move between the global arrays and a second pair of them, each wavefront sweeping its
+//     part of the list once per pass (the first pass twice: count, then place; a placing sweep counts for the next pass).
+// A pass ranks its entries per wavefront and round of 64 by ballots (lanes with the same digit find each other), the first lane of
+// each group adds the group's size to the digit's counter in LDS (16 bits wide, two to a word) and gets back how many entries of
+// that digit came before (earlier rounds of the wavefront: LDS executes a wavefront's operations in order), and hands that to its
+// group through the LDS crossbar: equal digits keep their incoming order.
+//
+// Two passes, over the top 20 of the bits in which a list's depths differ (depths of one tile share sign and most exponent bits:
+// about 26 differ). That orders a list but for neighbours, some per thousand entries, that agree in those bits, and for equal
+// depths, which are in order only if they came in order. Neighbours out of order are looked for after the passes and put right by
+// swapping, over the even and the odd pairs of neighbours in turn, kTiePhases sweeps at most; if that does not do (many equal
+// depths), the list is sorted again by all bits: first by point index and then, which keeps that order, by depth.
+//
+// The work is a chain of dependent LDS and cross-lane steps per list, and what hides it is other lists in flight: three workgroups
+// per compute unit by LDS, 24 wavefronts, at most 80 registers. No scratch memory: a launch that has any is slower by tens of us.
+// Against three 9-bit passes with a branch around every round of 64, four wavefronts to a workgroup, one list alone (us): 100
+// entries 8.0 -> 3.2, 256 9.8 -> 4.6, 512 13.7 -> 8.1, 768 17.5 -> 5.7, 2,000 16.5 -> 10.2, 4,600 34.6 -> 21.0, 7,800 71.2 -> 33.9. All lists of
+// 1M points at 1920x1080 (8,160 tiles, 1.9 M pairs, the longest list 4,835): 38 -> 28; 4,096 points at 128x128 20.4 -> 8.3.
+// (Measured and dropped: each wavefront sorting its part and then finding every entry's place by binary search in the other parts:
+// 2,000 entries 18 us, 4,600 37.)
+#include "pbdr_internal.h"
+#include "wave_ops.h"
+
+#include <type_traits>
+
+namespace pbdr {
+
+constexpr int kTiePhases = 8;
+constexpr int kSortWaves = 8, kSortThreads = 64 * kSortWaves;      // a workgroup
+constexpr int kListBits = 10;                         // digit width of the list sorts
+constexpr int kListBins = 1 << kListBits;
+constexpr int kListWords = kListBins / 2;             // counters in LDS are 16 bits wide, two digits to a word (the LDS adds 32-bit words)
+constexpr int kPerLane = kListWords / 64;             // a wavefront's counter words, per lane
+constexpr int kFirstBits = 2 * kListBits;             // of the bits that differ, those the list is first sorted by
+constexpr int kLongBits = 9;                          // digit width of the lists too long for LDS: their counters are 32 bits wide
+constexpr int kLongBins = 1 << kLongBits;
+static_assert(kWaveListMax % 64 == 0, "whole rounds");
+constexpr int kWgKeyMax = 11 * kSortThreads;           // a workgroup's list with its keys in registers and LDS (11 rounds per wavefront)
+constexpr int kWgListMax = 16 * kSortThreads;          // a workgroup's list with its permutation in LDS (16 rounds per wavefront)
+
+struct WaveSortLds {      // a wavefront's share of the LDS when it sorts a list of its own
+    uint32_t key[kWaveListMax];
+    uint16_t idx[kWaveListMax];
+    uint32_t hist[kListWords];
+};
+struct WgSortLds {        // the workgroup's LDS when it sorts one list together
+    union {
+        struct { uint32_t key[kWgKeyMax]; uint16_t idx[kWgKeyMax]; };        // the list, keys and incoming positions
+        uint16_t perm[2][kWgListMax];                                        // the permutation alone, twice
+        uint32_t count[2][kSortWaves][kLongBins];                                     // two sets of full-width counters
+    };
+    uint32_t cnt[kSortWaves][kListWords];                             // per wavefront and digit: entries in the wavefront's part of the list, then where its first entry of that digit goes
+    uint32_t scan[kSortWaves];
+    uint32_t any[2][kSortWaves];
+    uint32_t mask;
+};
+union ListSortLds { WgSortLds wg; WaveSortLds wave[kSortWaves]; };
+static_assert(sizeof(ListSortLds) <= 53 * 1024, "three workgroups per compute unit");
+
+// The passes by kBits-bit digits over the top `bits` of the bit positions in which the keys differ: their number and the shift of
+// pass p (the topmost digit may reach past the highest of them into bits all keys share; it never reaches past bit 31).
+struct Passes { int lo, count; };
+__device__ __forceinline__ Passes list_passes(uint32_t diff, int bits, int digit)
+{
+    if (diff == 0u) return Passes{0, 0};
+    const int hi = 31 - __builtin_clz(diff), lo = max(__builtin_ctz(diff), hi + 1 - bits);
+    return Passes{lo, (hi - lo + digit) / digit};
+}
+__device__ __forceinline__ int list_shift(const Passes& p, int i, int digit) { return min(p.lo + digit * i, 32 - digit); }
+
+// Entries of this wavefront with the same digit as this lane's that come before it: earlier rounds (through the
+// digit's counter in `hist`, a row no other wavefront touches) plus lower lanes of this round. The lanes that share the
+// digit are found bit by bit: a lane differs from this one if, for some bit, its bit (one ballot per bit) is not this
+// lane's bit (sign-extended to a mask); both halves of the 64-lane sets are kept in 32-bit registers.
+// kPacked: the counters are 16 bits wide, digit d in half d & 1 of word d >> 1 (for lists of fewer than 65,536 entries:
+// no half ever carries into its neighbour); else one word per digit.
+__device__ __forceinline__ uint32_t packed_half(uint32_t word, uint32_t digit) { return (word >> ((digit & 1u) << 4)) & 0xffffu; }
+
+template <int kBits, bool kPacked>
+__device__ __forceinline__ uint32_t digit_prefix(uint32_t* hist, uint32_t digit, bool valid)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t dlo = 0u, dhi = 0u;
+#pragma unroll
+    for (int bit = 0; bit < kBits; ++bit) {
+        const uint32_t ext = (uint32_t)__builtin_amdgcn_sbfe((int)digit, bit, 1);      // 0 or ~0
+        const uint64_t m = __ballot(ext != 0u);
+        dlo |= (uint32_t)m ^ ext;
+        dhi |= (uint32_t)(m >> 32) ^ ext;
+    }
+    const uint64_t vm = __ballot(valid);
+    const uint32_t plo = ~dlo & (uint32_t)vm, phi = ~dhi & (uint32_t)(vm >> 32);       // valid lanes with this lane's digit
+    // lanes below this one among them
+    const uint32_t below_lo = lane < 32 ? (1u << lane) - 1u : ~0u, below_hi = lane < 32 ? 0u : (1u << (lane - 32)) - 1u;
+    const uint32_t rank = (uint32_t)__popc(plo & below_lo) + (uint32_t)__popc(phi & below_hi);
+    uint32_t before = 0u;
+    if (valid && rank == 0u) {
+        const uint32_t group = (uint32_t)__popc(plo) + (uint32_t)__popc(phi);
+        if (kPacked) before = packed_half(atomicAdd(&hist[digit >> 1], group << ((digit & 1u) << 4)), digit);
+        else before = atomicAdd(&hist[digit], group);
+    }
+    const int leader = !valid ? lane : (plo ? __builtin_ctz(plo) : 32 + __builtin_ctz(phi));
+    before = (uint32_t)__builtin_amdgcn_ds_bpermute(leader << 2, (int)before);
+    return before + rank;
+}
+
+// exclusive scan over a wavefront's packed digit counters, 2 * kPerLane consecutive digits per lane, in place
+__device__ __forceinline__ void wave_scan_digits(uint32_t* hist)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t c[2 * kPerLane], tot = 0u;
+#pragma unroll
+    for (int q = 0; q < kPerLane; ++q) {
+        const uint32_t w = hist[kPerLane * lane + q];
+        c[2 * q] = w & 0xffffu; c[2 * q + 1] = w >> 16;
+        tot += c[2 * q] + c[2 * q + 1];
+    }
+    uint32_t at = wave_inclusive_scan(tot, OpAdd{}) - tot;
+#pragma unroll
+    for (int q = 0; q < kPerLane; ++q) {
+        const uint32_t a0 = at, a1 = at + c[2 * q];
+        hist[kPerLane * lane + q] = a0 | (a1 << 16);
+        at = a1 + c[2 * q + 1];
+    }
+}
+
+__device__ __forceinline__ void wave_lds_sync()      // orders this wavefront's LDS writes before its later LDS reads
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// i < n - before, on the scalar side but for the comparison: "before + i < n" would keep a register for every before
+__device__ __forceinline__ bool within(int i, uint32_t n, int before) { return i < (int)n - before; }
+
+// The same value, as one that the compiler does not know: addresses and masks made of it are made where they stand. Else those of
+// all of a list's rounds are worked out ahead of everything, and there are not enough registers to keep them.
+__device__ __forceinline__ uint32_t anew_uniform(uint32_t v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ uint32_t anew(uint32_t v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// One wavefront sorts a list of at most 64 entries by counting: how many entries have a smaller key.
+__device__ __forceinline__ void wave_count_list(uint32_t L, const uint32_t* keys, uint32_t* vals)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t k = 0u, v = 0u, before = 0u;
+    if ((uint32_t)lane < L) { k = keys[lane]; v = vals[lane]; }
+    for (uint32_t j = 0; j < L; ++j) before += (uint32_t)__builtin_amdgcn_readlane((int)k, (int)j) < k ? 1u : 0u;
+    if ((uint32_t)lane >= L) before = 0u;
+    if (wave_reduce(before, OpAdd{}) != L * (L - 1u) / 2u) {      // some are equal: then by value
+        for (uint32_t j = 0; j < L; ++j)
+            before += ((uint32_t)__builtin_amdgcn_readlane((int)k, (int)j) == k && (uint32_t)__builtin_amdgcn_readlane((int)v, (int)j) < v) ? 1u : 0u;
+    }
+    if ((uint32_t)lane < L) vals[min(before, L - 1u)] = v;       // every lane read its entry above
+}
+
+// One wavefront sorts the list (keys, vals)[0 .. L), 64 < L <= 64 R, in place; the keys are spent. The rounds of 64 are all
+// walked, whatever the length: with a branch around every round none would overlap with the next, and each is a chain of LDS and
+// cross-lane steps.
+template <int R>
+__device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint32_t* keys, uint32_t* vals)
+{
+    const int lane = threadIdx.x & 63;
+    // the list in its current order: entry r * 64 + lane, with its incoming position. The places behind its end hold the largest
+    // key: their digits are all ones, so they stay behind, and a pass needs no bounds.
+    uint32_t key[R], id[R];      // id: the position, and during a pass its rank among equal digits above kIdBits
+    constexpr int kIdBits = 16;
+    const auto one_pass = [&](int shift) {
+#pragma unroll
+        for (int q = 0; q < kPerLane; ++q) W.hist[q * 64 + lane] = 0u;
+        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) id[r] |= digit_prefix<kListBits, true>(W.hist, (key[r] >> shift) & (kListBins - 1u), true) << kIdBits;
+        wave_lds_sync();
+        wave_scan_digits(W.hist);
+        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t digit = (anew(key[r]) >> shift) & (kListBins - 1u);
+            const uint32_t pos = min(packed_half(W.hist[digit >> 1], digit) + (id[r] >> kIdBits), (uint32_t)kWaveListMax - 1u);      // (always below)
+            W.key[pos] = key[r]; W.idx[pos] = (uint16_t)id[r];
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) { key[r] = W.key[r * 64u + lane]; id[r] = W.idx[r * 64u + lane]; }
+        wave_lds_sync();      // (the next pass, or the next list of this wavefront, writes the buffer again)
+    };
+    // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
+#pragma unroll 1
+    for (int stage = 0; stage < 3; ++stage) {
+        const uint32_t* const from = stage == 1 ? vals : keys;
+        const uint32_t k0 = from[0], at = anew(lane);
+        uint32_t diff = 0u;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            key[r] = 0xffffffffu;
+            id[r] = r * 64u + at;
+            if (within(lane, L, r * 64)) { key[r] = from[r * 64u + at]; diff |= key[r] ^ k0; }
+        }
+        diff = wave_reduce(diff, OpOr{});
+        const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
+        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
+        bool in_order = stage == 2;
+        if (stage == 0 && diff != 0u) {
+            bool tie = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane + 1, L, r * 64)) tie |= W.key[r * 64u + lane + 1u] <= key[r];
+            in_order = true;
+            if (__ballot(tie) != 0ull) {
+                int quiet = 0;      // sweeps in a row that found nothing to swap: over the even and over the odd neighbours
+                for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
+                    uint32_t suspect = 0u;      // a bit per pair of neighbours of this lane
+#pragma unroll
+                    for (int r = 0; r < (R + 1) / 2; ++r) {
+                        const uint32_t p = 2u * (r * 64u + lane) + (uint32_t)(sweep & 1);
+                        if (within(2 * lane + (sweep & 1) + 1, L, r * 128) && W.key[p] >= W.key[p + 1u]) suspect |= 1u << r;
+                    }
+                    bool swapped = false;
+                    for (; suspect; suspect &= suspect - 1u) {
+                        const uint32_t p = 2u * ((uint32_t)__builtin_ctz(suspect) * 64u + lane) + (uint32_t)(sweep & 1);
+                        const uint32_t ka = W.key[p], kb = W.key[p + 1u];
+                        const uint16_t a = W.idx[p], b = W.idx[p + 1u];
+                        if (ka > kb || vals[a] > vals[b]) {
+                            W.key[p] = kb; W.key[p + 1u] = ka;
+                            W.idx[p] = b; W.idx[p + 1u] = a;
+                            swapped = true;
+                        }
+                    }
+                    quiet = __ballot(swapped) != 0ull ? 0 : quiet + 1;
+                    wave_lds_sync();
+                }
+                in_order = quiet >= 2;
+#pragma unroll
+                for (int r = 0; r < R; ++r) id[r] = W.idx[r * 64u + lane];
+                wave_lds_sync();
+            }
+        }
+        if (stage == 0 && !in_order) continue;
+        // through the sorted positions; every entry is fetched before the first is stored
+        const auto put_in_order = [&](uint32_t* list) {
+            const uint32_t to = anew(lane);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, r * 64)) key[r] = list[id[r]];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, r * 64)) list[r * 64u + to] = key[r];
+        };
+        put_in_order(vals);
+        if (in_order) return;
+        put_in_order(keys);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // (read back by other lanes)
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// The wavefronts' digit counts, one row each, into where each wavefront's first entry of each digit goes: behind the smaller
+// digits, and the wavefronts before it. A thread takes a word of the counters, all rows of it. (Every wavefront adding the rows up
+// for itself reads all of them, eight words to a lane, eight lanes to a bank: 3 us a pass.) Starts and ends with a barrier.
+__device__ __forceinline__ void wg_scan_digits(WgSortLds& S)
+{
+    static_assert(kListWords == kSortThreads, "a word per thread");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __syncthreads();
+    uint32_t c[kSortWaves], all = 0u;      // two digits to a word: a digit's count over the list is below 65,536
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) { c[w] = S.cnt[w][threadIdx.x]; all += c[w]; }
+    const uint32_t tot = (all & 0xffffu) + (all >> 16), inc = wave_inclusive_scan(tot, OpAdd{});
+    if (lane == 63) S.scan[wave] = inc;
+    __syncthreads();
+    uint32_t at = inc - tot;
+#pragma unroll
+    for (int w = 0; w + 1 < kSortWaves; ++w) at += w < wave ? S.scan[w] : 0u;
+    uint32_t run = at | (at + (all & 0xffffu)) << 16;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) { S.cnt[w][threadIdx.x] = run; run += c[w]; }
+    __syncthreads();
+}
+
+// Does any thread of the workgroup say so? A barrier; calls in a row take turns with `turn` (0, 1, 0, ...).
+__device__ __forceinline__ bool wg_any(WgSortLds& S, int turn, bool v)
+{
+    const bool mine = __ballot(v) != 0ull;
+    if ((threadIdx.x & 63u) == 0u) S.any[turn & 1][threadIdx.x >> 6] = mine ? 1u : 0u;
+    __syncthreads();
+    uint32_t any = 0u;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) any |= S.any[turn & 1][w];
+    return any != 0u;
+}
+
+// The entries of the list are in order but for neighbours: sweeps over its even and its odd pairs of neighbours in turn. Returns
+// whether the list is in order now. Ends with a barrier.
+__device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint32_t* k, uint32_t* v)
+{
+    int quiet = 0;      // sweeps in a row that found nothing to swap
+    for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
+        bool swapped = false;
+        for (uint32_t i0 = 0; i0 + 1u < L; i0 += 16u * kSortThreads) {
+            uint32_t suspect = 0u;
+            const uint32_t first = i0 + 2u * threadIdx.x + (uint32_t)(sweep & 1);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {      // eight pairs of fetches in flight
+                const uint32_t p = first + r * 2u * kSortThreads;
+                if (p + 1u < L && k[p] >= k[p + 1u]) suspect |= 1u << r;
+            }
+            for (; suspect; suspect &= suspect - 1u) {
+                const uint32_t p = first + 2u * kSortThreads * (uint32_t)__builtin_ctz(suspect);
+                const uint32_t ka = k[p], kb = k[p + 1u], a = v[p], b = v[p + 1u];
+                if (ka > kb || a > b) { k[p] = kb; k[p + 1u] = ka; v[p] = b; v[p + 1u] = a; swapped = true; }
+            }
+        }
+        quiet = wg_any(S, sweep, swapped) ? 0 : quiet + 1;
+    }
+    return quiet >= 2;
+}
+
+// A workgroup sorts the list (keys, vals)[0 .. L), L <= kWgListMax, in place; the keys are spent. The permutation idx[c][i] =
+// incoming position of the entry now at i goes back and forth between its two copies in LDS; the keys are fetched through it.
+__device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint32_t* keys, uint32_t* vals)
+{
+    uint32_t L = L0;
+    constexpr int R = kWgListMax / kSortThreads;
+    static_assert(R % 4 == 0, "rounds are taken four at a time");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // each wavefront takes a contiguous quarter of the list, in rounds of 64
+    const uint32_t per_wave = ((L + kSortThreads - 1u) / kSortThreads) * 64u;
+    const int nr0 = (int)(per_wave / 64u);
+    const uint32_t wb = wave * per_wave, we0 = min(L, wb + per_wave);
+    uint16_t* src = S.perm[0];
+    uint16_t* dst = S.perm[1];
+    auto one_pass = [&](int shift, const uint32_t* from) {
+#pragma unroll
+        for (int q = 0; q < kPerLane; ++q) S.cnt[wave][q * 64 + lane] = 0u;
+        wave_lds_sync();
+        uint32_t we = anew_uniform(we0);
+        const int nr = nr0;
+        uint32_t dp[R];      // per entry of this lane: digit | (entries of that digit before it in this wavefront's part) << kListBits
+        const uint16_t* here = src + anew(wb + lane);
+#pragma unroll
+        for (int r0 = 0; r0 < R; r0 += 4) {       // four rounds at a time, no branch between them
+            if (r0 >= nr) break;
+            uint32_t k[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                k[j] = 0u;
+                if (within(lane, we, (int)wb + (r0 + j) * 64)) {
+                    const uint32_t i = here[(r0 + j) * 64];
+                    k[j] = from[i];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t digit = (k[j] >> shift) & (kListBins - 1u);
+                dp[r0 + j] = digit | (digit_prefix<kListBits, true>(S.cnt[wave], digit, within(lane, we, (int)wb + (r0 + j) * 64)) << kListBits);
+            }
+        }
+        wg_scan_digits(S);
+        we = anew_uniform(we0); L = anew_uniform(L0);
+        here = src + anew(wb + lane);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r % 8 == 0) asm volatile("" ::: "memory");      // (eight rounds in flight at a time)
+            if (within(lane, we, (int)wb + r * 64)) {
+                const uint32_t digit = dp[r] & (kListBins - 1u);
+                const uint32_t pos = min(packed_half(S.cnt[wave][digit >> 1], digit) + (dp[r] >> kListBits), L - 1u);
+                dst[pos] = here[r * 64];
+            }
+        }
+        __syncthreads();      // the pass is written; the other copy of the permutation may be overwritten
+        uint16_t* t = src; src = dst; dst = t;
+    };
+    // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
+#pragma unroll 1
+    for (int stage = 0; stage < 3; ++stage) {
+        const uint32_t* const from = stage == 1 ? vals : keys;
+        // the bit positions in which the keys differ
+        const uint32_t k0 = from[0];
+        uint32_t diff = 0u;
+        if (threadIdx.x == 0) S.mask = 0u;
+        for (uint32_t i0 = 0; i0 < L; i0 += 8u * kSortThreads) {      // eight independent fetches in flight
+            const uint32_t at = anew(threadIdx.x);
+            uint32_t t[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const uint32_t i = i0 + r * (uint32_t)kSortThreads + at;
+                t[r] = within((int)threadIdx.x, L, (int)i0 + r * kSortThreads) ? from[i] : k0;
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const uint32_t i = i0 + r * (uint32_t)kSortThreads + at;
+                diff |= t[r] ^ k0;
+                if (within((int)threadIdx.x, L, (int)i0 + r * kSortThreads)) {
+                    src[i] = (uint16_t)i;
+                }
+            }
+        }
+        diff = wave_reduce(diff, OpOr{});
+        __syncthreads();                               // S.mask is cleared; keys and permutation are in place
+        if (lane == 0 && diff) atomicOr(&S.mask, diff);
+        __syncthreads();
+        diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.mask);
+        const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
+        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits), from);
+        // through the sorted positions; every entry is fetched before the first is stored
+        const auto put_in_order = [&](uint32_t* list) {
+            uint32_t out[R];
+            const uint32_t to = anew(threadIdx.x);
+            L = anew_uniform(L0);
+#pragma unroll
+            for (int r0 = 0; r0 < R; r0 += 8) {      // (the addresses of eight rounds at a time)
+#pragma unroll
+                for (int r = r0; r < r0 + 8 && r < R; ++r) {
+                    out[r] = 0u;
+                    if (within((int)threadIdx.x, L, r * kSortThreads)) out[r] = list[src[r * kSortThreads + threadIdx.x]];
+                }
+                asm volatile("" ::: "memory");
+            }
+            __syncthreads();
+            L = anew_uniform(L0);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (within((int)threadIdx.x, L, r * kSortThreads)) list[r * kSortThreads + to] = out[r];
+            }
+        };
+        put_in_order(vals);
+        if (stage == 2) return;
+        put_in_order(keys);
+        __syncthreads();      // (also: the mask and the permutation may be written again)
+        if (stage == 0 && tie_sweeps(S, L, keys, vals)) return;
+    }
+}
+
+// A workgroup sorts the list (keys, vals)[0 .. L), L <= 4 * 64 R, in place; the keys are spent. As one wavefront does it, but for
+// the counters: each wavefront holds a quarter of the places, R rounds of 64, and counts for itself; where its entries of a digit
+// go then depends on the others' counts.
+template <int R>
+__device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t* keys, uint32_t* vals)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first = wave * 64 * R;
+    uint32_t* const hist = S.cnt[wave];
+    uint32_t key[R], id[R];      // id: the position, and during a pass its rank among the wavefront's equal digits above kIdBits
+    constexpr int kIdBits = 16;
+    const auto one_pass = [&](int shift) {
+        // (this wavefront's counters were last read by itself)
+#pragma unroll
+        for (int q = 0; q < kPerLane; ++q) hist[q * 64 + lane] = 0u;
+        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) id[r] |= digit_prefix<kListBits, true>(hist, (key[r] >> shift) & (kListBins - 1u), true) << kIdBits;
+        wg_scan_digits(S);      // (and every wavefront has fetched its entries of the pass before)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t digit = (anew(key[r]) >> shift) & (kListBins - 1u);
+            const uint32_t pos = min(packed_half(hist[digit >> 1], digit) + (id[r] >> kIdBits), (uint32_t)kWgKeyMax - 1u);      // (always below)
+            S.key[pos] = key[r]; S.idx[pos] = (uint16_t)id[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) { key[r] = S.key[first + r * 64 + lane]; id[r] = S.idx[first + r * 64 + lane]; }
+    };
+    // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
+#pragma unroll 1
+    for (int stage = 0; stage < 3; ++stage) {
+        const uint32_t* const from = stage == 1 ? vals : keys;
+        const uint32_t k0 = from[0], at = anew(first + lane);
+        uint32_t diff = 0u;
+        if (threadIdx.x == 0) S.mask = 0u;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            key[r] = 0xffffffffu;
+            id[r] = r * 64u + at;
+            if (within(lane, L, first + r * 64)) { key[r] = from[r * 64u + at]; diff |= key[r] ^ k0; }
+        }
+        diff = wave_reduce(diff, OpOr{});
+        __syncthreads();                               // S.mask is cleared
+        if (lane == 0 && diff) atomicOr(&S.mask, diff);
+        __syncthreads();
+        diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.mask);
+        const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
+        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
+        bool in_order = stage == 2;
+        if (stage == 0 && diff != 0u) {
+            bool tie = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane + 1, L, first + r * 64)) tie |= S.key[first + r * 64 + lane + 1] <= key[r];
+            in_order = true;
+            if (wg_any(S, 1, tie)) {
+                int quiet = 0;      // sweeps in a row that found nothing to swap: over the even and over the odd neighbours
+                for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
+                    const int base = 2 * (int)threadIdx.x + (sweep & 1);
+                    uint32_t suspect = 0u;      // a bit per pair of neighbours of this thread
+#pragma unroll
+                    for (int r = 0; r < (R + 1) / 2; ++r)
+                        if (within(base + 1, L, r * 2 * kSortThreads) && S.key[base + r * 2 * kSortThreads] >= S.key[base + r * 2 * kSortThreads + 1]) suspect |= 1u << r;
+                    bool swapped = false;
+                    for (; suspect; suspect &= suspect - 1u) {
+                        const int p = base + 2 * kSortThreads * __builtin_ctz(suspect);
+                        const uint32_t ka = S.key[p], kb = S.key[p + 1];
+                        const uint16_t a = S.idx[p], b = S.idx[p + 1];
+                        if (ka > kb || vals[a] > vals[b]) {
+                            S.key[p] = kb; S.key[p + 1] = ka;
+                            S.idx[p] = b; S.idx[p + 1] = a;
+                            swapped = true;
+                        }
+                    }
+                    quiet = wg_any(S, sweep, swapped) ? 0 : quiet + 1;
+                }
+                in_order = quiet >= 2;
+#pragma unroll
+                for (int r = 0; r < R; ++r) id[r] = S.idx[first + r * 64 + lane];
+            }
+        }
+        if (stage == 0 && !in_order) { __syncthreads(); continue; }
+        // through the sorted positions; every entry is fetched before the first is stored
+        const auto put_in_order = [&](uint32_t* list) {
+            const uint32_t to = anew(first + lane);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, first + r * 64)) key[r] = list[id[r]];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, first + r * 64)) list[r * 64u + to] = key[r];
+        };
+        put_in_order(vals);
+        if (in_order) return;
+        put_in_order(keys);
+        __syncthreads();      // (also: the mask may be written again)
+    }
+}
+
+// exclusive scan of one value per thread over the workgroup's threads
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sScan)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t inc = wave_inclusive_scan(v, OpAdd{});
+    if (lane == 63) sScan[wave] = inc;
+    __syncthreads();
+    uint32_t below = inc - v;
+#pragma unroll
+    for (int w = 0; w + 1 < kSortWaves; ++w) if (w < wave) below += sScan[w];
+    __syncthreads();
+    return below;
+}
+
+// Lists too long for LDS: one stable pass by the digit at `shift` from (kin, vin) to (kout, vout), all of length L
+// in global memory. Each wavefront takes a contiguous quarter of the list, in rounds of 64. `cur` holds, per wavefront
+// and digit, how many of its entries have that digit: counted here in a sweep of its own if `count_first`, else by
+// the previous pass, which knew where every entry went and so in whose quarter it would be (that is what `nxt` and
+// `next_shift` are for: pass a negative shift when no pass follows). The counters are then turned into where the
+// wavefront's first entry of each digit goes, and a sweep places the entries: digit_prefix() hands back the counter's
+// value before the round's entries were added plus the lane's rank among them, which now is the entry's position.
+// Nothing is kept per entry between the sweeps, so the list may be of any length.
+__device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLongBins], uint32_t (*nxt)[kLongBins], bool count_first, uint32_t L,
+                                               int shift, int next_shift, const uint32_t* __restrict__ kin,
+                                               const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout, uint32_t* __restrict__ vout)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t per_wave = ((L + kSortThreads - 1u) / kSortThreads) * 64u;
+    const uint32_t wb = min(L, wave * per_wave), we = min(L, wb + per_wave);
+    if (count_first) {
+#pragma unroll
+        for (int q = 0; q < kLongBins / 64; ++q) cur[wave][q * 64 + lane] = 0u;
+        wave_lds_sync();
+        for (uint32_t i0 = wb; i0 < we; i0 += 8u * 64u) {      // eight key fetches in flight at a time
+            uint32_t k[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t i = i0 + j * 64u + lane;
+                k[j] = i < we ? kin[i] : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (i0 + j * 64u < we) digit_prefix<kLongBits, false>(cur[wave], (k[j] >> shift) & (kLongBins - 1u), i0 + j * 64u + lane < we);
+        }
+    }
+    __syncthreads();      // every wavefront's counts are in
+    {   // a digit per thread: its run starts after all smaller digits; inside it the wavefronts follow each other
+        static_assert(kLongBins == kSortThreads, "one digit per thread");
+        uint32_t c[kSortWaves], tot = 0u;
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) { c[w] = cur[w][threadIdx.x]; tot += c[w]; }
+        uint32_t at = block_exclusive_scan(tot, S.scan);
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) { cur[w][threadIdx.x] = at; at += c[w]; nxt[w][threadIdx.x] = 0u; }
+    }
+    __syncthreads();
+    for (uint32_t i0 = wb; i0 < we; i0 += 8u * 64u) {
+        uint32_t k[8], v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t i = i0 + j * 64u + lane;
+            k[j] = 0u; v[j] = 0u;
+            if (i < we) { k[j] = kin[i]; v[j] = vin[i]; }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (i0 + j * 64u < we) {
+                const bool valid = i0 + j * 64u + lane < we;
+                const uint32_t pos = min(digit_prefix<kLongBits, false>(cur[wave], (k[j] >> shift) & (kLongBins - 1u), valid), L - 1u);      // < L for consistent counts
+                if (valid) {
+                    kout[pos] = k[j]; vout[pos] = v[j];
+                    if (next_shift >= 0) {      // the next pass finds this entry in the part of wavefront pos / per_wave
+                        uint32_t w2 = 0u;
+#pragma unroll
+                        for (uint32_t w = 1u; w < (uint32_t)kSortWaves; ++w) w2 += pos >= w * per_wave ? 1u : 0u;
+                        atomicAdd(&nxt[w2][(k[j] >> next_shift) & (kLongBins - 1u)], 1u);
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();      // the pass is written and the next pass's counts are complete
+}
+
+// One list too long for a wavefront, sorted by the whole workgroup (every exit is uniform for the workgroup).
+__device__ __forceinline__ void wg_sort_big(WgSortLds& S, uint32_t s, uint32_t e, const uint32_t* __restrict__ depth_bits,
+                                            uint32_t* __restrict__ keysA, uint32_t* __restrict__ valsA,
+                                            uint32_t* __restrict__ keysB, uint32_t* __restrict__ valsB)
+{
+    if (e <= s + 1u) return;
+    const uint32_t L = e - s;
+    if (L <= (uint32_t)kWgListMax) { wg_permute_list(S, L, keysA + s, valsA + s); return; }
+    // through global memory, from one pair of arrays to the other
+    const int lane = threadIdx.x & 63;
+    // the two sets of counters swap roles from pass to pass
+    uint32_t (*c0)[kLongBins] = S.count[0];
+    uint32_t (*c1)[kLongBins] = S.count[1];
+    uint32_t *k = keysA + s, *v = valsA + s, *k2 = keysB + s, *v2 = valsB + s;      // the list, and where the next pass puts it
+#pragma unroll 1
+    for (int stage = 0; stage < 3; ++stage) {
+        if (stage > 0) {
+            for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) k[i] = stage == 1 ? v[i] : depth_bits[v[i]];
+            __syncthreads();
+        }
+        const uint32_t k0 = k[0];
+        uint32_t diff = 0u;
+        if (threadIdx.x == 0) S.mask = 0u;
+        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) diff |= k[i] ^ k0;
+        diff = wave_reduce(diff, OpOr{});
+        __syncthreads();                               // S.mask is cleared
+        if (lane == 0 && diff) atomicOr(&S.mask, diff);
+        __syncthreads();
+        const uint32_t mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.mask);
+        const Passes ps = list_passes(mask, 32, kLongBits);
+        for (int p = 0; p < ps.count; ++p) {
+            const int next_shift = p + 1 < ps.count ? list_shift(ps, p + 1, kLongBits) : -1;
+            long_list_pass(S, (p & 1) ? c1 : c0, (p & 1) ? c0 : c1, p == 0, L, list_shift(ps, p, kLongBits), next_shift, k, v, k2, v2);
+            uint32_t* t = k; k = k2; k2 = t;
+            t = v; v = v2; v2 = t;
+        }
+        if (stage == 0 && tie_sweeps(S, L, k, v)) break;
+        __syncthreads();
+    }
+    if (v != valsA + s)
+        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) valsA[s + i] = v[i];
+}
+
+// Work items: tile_order lists the tiles longest first and its first `nbig` tiles are too long for one wavefront, so
+// workgroups 0 .. nbig - 1 take one such list each, and every later workgroup takes four shorter lists, one per
+// wavefront.
+__global__ __launch_bounds__(kSortThreads, 6) void k_tile_depth_sort(const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
+                                                            uint32_t ntiles, const uint32_t* __restrict__ status,
+                                                            const uint32_t* __restrict__ depth_bits, uint32_t cap,
+                                                            uint32_t* __restrict__ keysA, uint32_t* __restrict__ valsA,
+                                                            uint32_t* __restrict__ keysB, uint32_t* __restrict__ valsB)
+{
+    __shared__ ListSortLds U;
+    const uint32_t nbig = min(status[kStNumBig], ntiles);
+    if (blockIdx.x < nbig) {
+        const uint32_t tile = tile_order[blockIdx.x];
+        const uint32_t s = ranges[2 * tile], e = min(ranges[2 * tile + 1], cap), L = e > s ? e - s : 0u;
+        uint32_t *k = keysA + s, *v = valsA + s;
+        if (L > (uint32_t)kWgKeyMax) wg_sort_big(U.wg, s, e, depth_bits, keysA, valsA, keysB, valsB);
+        else if (L > 8u * kSortThreads) wg_sort_list<11>(U.wg, L, k, v);
+        else if (L > 6u * kSortThreads) wg_sort_list<8>(U.wg, L, k, v);
+        else if (L > 4u * kSortThreads) wg_sort_list<6>(U.wg, L, k, v);
+        else if (L > 3u * kSortThreads) wg_sort_list<4>(U.wg, L, k, v);
+        else if (L > 2u * kSortThreads) wg_sort_list<3>(U.wg, L, k, v);
+        else if (L > (uint32_t)kSortThreads) wg_sort_list<2>(U.wg, L, k, v);
+        else if (L > 1u) wg_sort_list<1>(U.wg, L, k, v);
+        return;
+    }
+    // (uniform per wavefront, which the compiler has to be told: then the rounds of a list are scalar branches)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t idx = nbig + (blockIdx.x - nbig) * (uint32_t)kSortWaves + (uint32_t)wave;
+    if (idx >= ntiles) return;
+    const uint32_t tile = tile_order[idx];
+    const uint32_t s = ranges[2 * tile], e = min(ranges[2 * tile + 1], cap);
+    if (e <= s + 1u) return;
+    // (a list of long_list_from() entries or more cannot come here: k_tile_lists counted it among the first nbig)
+    WaveSortLds& W = U.wave[wave];
+    const uint32_t L = e - s;
+    uint32_t *k = keysA + s, *v = valsA + s;
+    if (L <= 64u) wave_count_list(L, k, v);
+    else if (L <= 128u) wave_sort_list<2>(W, L, k, v);
+    else if (L <= 192u) wave_sort_list<3>(W, L, k, v);
+    else if (L <= 256u) wave_sort_list<4>(W, L, k, v);
+    else if (L <= 384u) wave_sort_list<6>(W, L, k, v);
+    else if (L <= 512u) wave_sort_list<8>(W, L, k, v);
+    else if (L <= (uint32_t)kWaveListMax) wave_sort_list<kWaveListMax / 64>(W, L, k, v);
+}
+
+hipError_t launch_tile_depth_sort(const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
+{
+    const auto u32 = [&](size_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
+    const uint32_t ntiles = (uint32_t)(cam.TX * cam.TY);
+    ProfScope prof(kKTileDepthSort, s);
+    // a list of the workgroup kind has at least long_list_from() entries, which bounds how many of them `cap` pairs can
+    // hold, and so how many workgroups can have work: the rest would only start and leave, which is not free on an
+    // image of 32,400 tiles
+    const uint32_t big_max = min(ntiles, L.cap / long_list_from(ntiles) + 1u);
+    const uint32_t items_max = min(ntiles, big_max + (ntiles + kSortWaves - 1u) / kSortWaves);
+    hipLaunchKernelGGL(k_tile_depth_sort, dim3(items_max), dim3(kSortThreads), 0, s, u32(L.off_ranges), u32(L.off_tile_order), ntiles, u32(L.off_status),
+                       u32(L.off_depth_bits), L.cap, u32(L.off_keys), u32(L.off_vals), u32(L.off_spare), u32(L.off_spare) + L.cap);
+    return hipGetLastError();
+}
+
+}  // namespace pbdr

@@ -150,7 +150,7 @@ struct Splat2DGradDev {
 
 // Status words at the head of the workspace.
 // pair count, overflow flag, visible-point count, number of tiles whose list is too long for one wavefront to sort
-// (written by k_tile_order): cleared by every binning. kStEpoch (two words) is never cleared by a call: the 64-bit
+// (written by k_tile_lists): cleared by every binning. kStEpoch (two words) is never cleared by a call: the 64-bit
 // number of backward passes this workspace has seen plus one, stamped into the per-pair records a pass writes (see
 // k_composite_bwd); it relies on the workspace having been zero-filled once before its first use.
 enum { kStNumDup = 0, kStOverflow = 1, kStNumVis = 2, kStNumBig = 3, kStCleared = 32, kStEpoch = 32, kStWords = 64 };
@@ -164,18 +164,21 @@ struct Layout {
     size_t record_bytes;      // raster record per point, 64 in both variants
     int partial_vec4;         // float4s of partial gradient sums per pair: 3 (3D) or 4 (2D)
     uint32_t cap;
-    int tile_bits, tile_passes;   // key bits / radix passes spent on the tile id
-    size_t off_status, off_packed, off_depth_bits, off_blk_vis, off_blk_pairs, off_blk_vis_at, off_blk_pairs_at, off_blk_order, off_touched, off_offsets, off_slot_base, off_order,
-        off_tkey0, off_tval0, off_tkey1, off_tval1, off_totals, off_tile_hist, off_ranges,
-        off_partial, off_keys64, off_chunk_rank, off_carry, off_grad_rec, off_reach, off_tile_order, total;
+    size_t off_status, off_packed, off_depth_bits, off_blk, off_sup, off_blk_at, off_blk_cells, off_touched, off_offsets, off_slot_base, off_order,
+        off_keys, off_vals, off_spare, off_tile_count, off_ranges, off_partial, off_keys64, off_chunk_rank, off_carry, off_grad_rec, off_reach,
+        off_tile_order, total;
 };
-constexpr int kSortItems = 2048;   // pairs per radix-sort block
-// A tile's list of fewer than kWaveListMax - 1 entries is put in depth order by one wavefront, a longer one by a whole
-// workgroup (radix_sort.hip); k_tile_order (binning.hip) counts the longer ones, so the value must be where two of its
-// length classes meet: a power of two or 1.5 times one.
-constexpr int kWaveListMax = 1024;
-constexpr int kRadixMaxBins = 256;   // widest digit: 8 bits
-int radix_pass_count(int key_bits);  // passes launch_radix_sort32 takes for this many key bits
+// A tile's list of fewer than long_list_from() entries is put in depth order by one wavefront, a longer one by a whole workgroup
+// of eight (depth_sort.hip). k_tile_lists (binning.hip) counts the longer ones, so the border lies where two of its length classes
+// meet: class code c starts at 2^(c / 2) entries less one, 1.5 times that where c is odd.
+// A workgroup sorts 768 entries in 5.7 us where a wavefront takes 10, with six times the wavefront time. So it is 767 entries
+// where there are more lists than the chip holds wavefronts at once (6,144), and the time of all lists counts (1M points, 8,160
+// tiles: 29 us; from 383 entries on 32). Below that the longest list counts: 255 (two views of 200k points, 3,600 tiles: 42 -> 30 us
+// for both; a 960 x 540 patch: 18 -> 13), and 127 where every list can have a workgroup at once, three per compute unit
+// (4,096 points, 64 tiles: 255 8.4 us, 127 8.3; 12,000 points, 475 tiles: 9.2, 6.9).
+constexpr int kWaveListMax = 768;
+inline int long_list_code(uint32_t ntiles) { return ntiles <= 768u ? 14 : ntiles <= 6144u ? 16 : 19; }
+inline uint32_t long_list_from(uint32_t ntiles) { const int c = long_list_code(ntiles); return (c & 1 ? 3u << (c / 2 - 1) : 1u << (c / 2)) - 1u; }
 bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L);
 
 // ---- launchers (each enqueues on `s` and returns the launch status) ----
@@ -212,8 +215,7 @@ struct BinInput {
 struct BinArrays;
 BinArrays bin_arrays(const Layout& L, char* ws);                                             // see binning_common.h
 hipError_t launch_bin_begin(const Layout& L, char* ws, hipStream_t s);                       // zero status / totals / ranges
-hipError_t launch_count_visible(const BinInput& in, const CamDev& cam, const Layout& L, char* ws, hipStream_t s);
-hipError_t launch_bin_finish(const BinInput& in, const CamDev& cam, const Layout& L, char* ws, hipStream_t s);
+hipError_t launch_bin_count(const BinInput& in, const CamDev& cam, const Layout& L, char* ws, hipStream_t s);
 hipError_t launch_bin_sort(const SplatsDev& sp, const CamDev& cam, const Layout& L, char* ws, hipStream_t s);
 hipError_t launch_composite_fwd(const CamDev& cam, const Layout& L, char* ws, const float bg[3], float* image,
                                 float* final_T, uint32_t* last_idx, hipStream_t s);
@@ -223,12 +225,9 @@ hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, in
 
 hipError_t launch_render_stats(const CamDev& cam, const Layout& L, char* ws, uint64_t* counters, hipStream_t s);
 
-// stable sort of every tile's list [ranges[2t], ranges[2t+1]) of (keysA, valsA) by depth_bits[val]; keysA's contents are
-// overwritten, (keysB, valsB) are scratch; the result is in valsA
-hipError_t launch_tile_depth_sort(const uint32_t* ranges, const uint32_t* tile_order, uint32_t ntiles, const uint32_t* status,
-                                  const uint32_t* depth_bits, uint32_t cap, uint32_t* keysA, uint32_t* valsA, uint32_t* keysB, uint32_t* valsB, hipStream_t s);
-hipError_t launch_radix_sort32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* count_ptr, uint32_t count_cap,
-                               int key_bits, uint32_t* totals, uint32_t* tile_hist, hipStream_t s);
+// every tile's list (keys = depth bits, vals = point indices, in any order) into the order of the depth bits, equal ones by
+// point index; the keys are spent
+hipError_t launch_tile_depth_sort(const CamDev& cam, const Layout& L, char* ws, hipStream_t s);
 hipError_t launch_make_keys64(const Layout& L, char* ws, hipStream_t s);
 
 // 2D Gaussian surfel variant (workspace laid out with kVariant2D)
@@ -276,9 +275,5 @@ hipError_t launch_mark_visible(int n, const int32_t* radius, uint8_t* visible, h
 hipError_t launch_adam_selective(int n, int planes, float* param, float* grad, float* exp_avg, float* exp_avg_sq,
                                  const uint8_t* visible, float lr, float beta1, float beta2, float eps, int step,
                                  int zero_grad, hipStream_t s);
-
-// final location of the sorted pair lists (depends on the parity of the tile pass count)
-inline size_t sorted_tkeys_off(const Layout& L) { return (L.tile_passes & 1) ? L.off_tkey1 : L.off_tkey0; }
-inline size_t sorted_vals_off(const Layout& L) { return (L.tile_passes & 1) ? L.off_tval1 : L.off_tval0; }
 
 }  // namespace pbdr

@@ -6,7 +6,7 @@
 namespace pbdr {
 
 enum KernelId {
-    kKPreprocess = 0, kKCountPack, kKScan, kKDuplicate, kKRadixHist, kKRadixScatter, kKTileRanges, kKFill,
+    kKPreprocess = 0, kKCountVisible, kKTileCount, kKTileLists, kKPack, kKFill,
     kKCompositeFwd, kKCompositeBwd, kKPreprocessBwd, kKStats, kKGather, kKGroupCull, kKLoss, kKAdam, kKTileDepthSort, kKernelCount
 };
 

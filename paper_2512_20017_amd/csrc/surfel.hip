@@ -273,23 +273,29 @@ __global__ __launch_bounds__(256) void k_preprocess2d_bwd(Scene2DDev sc, CamDev 
 
 // Surfels: the 64-byte raster record of a listed point, with centred rows (see binning_common.h for the rest of the
 // block's work: compaction and pair emission as for 3D Gaussians).
-__global__ __launch_bounds__(256) void k_pack_dup2d(Splats2DDev sp, CamDev cam, BinArrays A, Packed2D* __restrict__ packed)
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_pack2d(Splats2DDev sp, CamDev cam, BinArrays A, Packed2D* __restrict__ packed)
 {
     const size_t N = (size_t)sp.n;
-    pack_dup_block(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth, [&](int i) {
-        // (every load before the first store: the compiler cannot know that the record overlaps none of the planes)
-        const float mx = sp.mean2d[i], my = sp.mean2d[N + i];
-        float t[9];
+    struct Parts { float t[9], o, red, green, blue, mx, my; int radius; };
+    pack_block<kThreads>(BinInput{sp.n, sp.mean2d, sp.radius}, cam, A, sp.depth,
+        [&](int i, const PointExtent& e) {
+            Parts p;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) t[k] = sp.T[k * N + i];
-        const float o = sp.opacity[i], red = sp.color[i], green = sp.color[N + i], blue = sp.color[2 * N + i];
-        const int radius = sp.radius[i];
-        float4* dst = reinterpret_cast<float4*>(packed + i);
-        dst[0] = make_float4(fmaf(-mx, t[6], t[0]), fmaf(-mx, t[7], t[1]), fmaf(-my, t[6], t[3]), fmaf(-my, t[7], t[4]));
-        dst[1] = make_float4(t[6], t[7], t[8], o);
-        dst[2] = make_float4(mx, my, red, green);
-        dst[3] = make_float4(blue, __int_as_float(radius), fmaf(-mx, t[8], t[2]), fmaf(-my, t[8], t[5]));
-    });
+            for (int k = 0; k < 9; ++k) p.t[k] = sp.T[k * N + i];
+            p.o = sp.opacity[i]; p.red = sp.color[i]; p.green = sp.color[N + i]; p.blue = sp.color[2 * N + i];
+            p.mx = e.mx; p.my = e.my; p.radius = e.radius;
+            return p;
+        },
+        [&](int i, const Parts& p) {
+            float4* dst = reinterpret_cast<float4*>(packed + i);
+            const float* t = p.t;
+            const float mx = p.mx, my = p.my;
+            dst[0] = make_float4(fmaf(-mx, t[6], t[0]), fmaf(-mx, t[7], t[1]), fmaf(-my, t[6], t[3]), fmaf(-my, t[7], t[4]));
+            dst[1] = make_float4(t[6], t[7], t[8], p.o);
+            dst[2] = make_float4(mx, my, p.red, p.green);
+            dst[3] = make_float4(p.blue, __int_as_float(p.radius), fmaf(-mx, t[8], t[2]), fmaf(-my, t[8], t[5]));
+        });
 }
 
 constexpr int kAccStride2D = 15;   // floats between the LDS accumulators of consecutive surfels of a batch (odd)
@@ -915,16 +921,18 @@ hipError_t launch_preprocess2d_bwd_records(const Scene2DDev& sc, const CamDev& c
 hipError_t launch_bin_sort2d(const Splats2DDev& sp, const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
 {
     if (sp.n == 0) return launch_bin_begin(L, ws, s);      // nothing to count: only the cleared status words and ranges
-    hipError_t e = launch_count_visible(BinInput{sp.n, sp.mean2d, sp.radius}, cam, L, ws, s);
+    hipError_t e = launch_bin_count(BinInput{sp.n, sp.mean2d, sp.radius}, cam, L, ws, s);
     if (e != hipSuccess) return e;
     {
-        ProfScope prof(kKDuplicate, s);
-        hipLaunchKernelGGL(k_pack_dup2d, dim3((unsigned)((sp.n + 255) / 256)), dim3(256), 0, s, sp, cam, bin_arrays(L, ws),
-                           reinterpret_cast<Packed2D*>(ws + L.off_packed));
+        ProfScope prof(kKPack, s);
+        const unsigned nb = (unsigned)((sp.n + 255) / 256);
+        Packed2D* packed = reinterpret_cast<Packed2D*>(ws + L.off_packed);
+        if (block_threads(sp.n) == 256) hipLaunchKernelGGL(k_pack2d<256>, dim3(nb), dim3(256), 0, s, sp, cam, bin_arrays(L, ws), packed);
+        else hipLaunchKernelGGL(k_pack2d<1024>, dim3(nb), dim3(1024), 0, s, sp, cam, bin_arrays(L, ws), packed);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return launch_bin_finish(BinInput{sp.n, sp.mean2d, sp.radius}, cam, L, ws, s);
+    return launch_tile_depth_sort(cam, L, ws, s);
 }
 
 hipError_t launch_composite2d_fwd(const CamDev& cam, const Layout& L, char* ws, const float bg[3], float* image,
@@ -933,7 +941,7 @@ hipError_t launch_composite2d_fwd(const CamDev& cam, const Layout& L, char* ws, 
     ProfScope prof(kKCompositeFwd, s);
     hipLaunchKernelGGL(k_composite2d_fwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                        reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
-                       reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L)),
+                       reinterpret_cast<const uint32_t*>(ws + L.off_vals),
                        reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<uint32_t*>(ws + L.off_reach),
                        bg[0], bg[1], bg[2], image, final_T, last_idx);
     return hipGetLastError();
@@ -948,7 +956,7 @@ hipError_t launch_composite2d_bwd(const CamDev& cam, const Layout& L, char* ws, 
         ProfScope prof(kKCompositeBwd, s);
         hipLaunchKernelGGL(k_composite2d_bwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                            reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
-                       reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L)),
+                       reinterpret_cast<const uint32_t*>(ws + L.off_vals),
                            reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<const uint32_t*>(ws + L.off_reach),
                            reinterpret_cast<const uint32_t*>(ws + L.off_slot_base),
                            bg[0], bg[1], bg[2], final_T, last_idx, dL_dimage, L.cap, partial);
@@ -978,7 +986,7 @@ hipError_t launch_render_stats2d(const CamDev& cam, const Layout& L, char* ws, u
     hipLaunchKernelGGL(k_zero_counters2d, dim3(1), dim3(64), 0, s, reinterpret_cast<unsigned long long*>(counters));
     hipLaunchKernelGGL(k_render_stats2d, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                        reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
-                       reinterpret_cast<const uint32_t*>(ws + sorted_vals_off(L)),
+                       reinterpret_cast<const uint32_t*>(ws + L.off_vals),
                        reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<unsigned long long*>(counters));
     return hipGetLastError();
 }

@@ -1,6 +1,7 @@
 // C ABI of libpbdr: argument checks, workspace layout, camera conversion, kernel sequencing. No allocation here.
 #include "../../include/pbdr.h"
 #include "pbdr_internal.h"
+#include "pair_reduce.h"
 
 #include <cmath>
 #include <mutex>
@@ -80,8 +81,9 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->off_ranges = take((size_t)L->tiles * 2 * sizeof(uint32_t));
     L->off_partial = take((size_t)cap * L->partial_vec4 * 4 * sizeof(float));
     L->off_keys64 = take((size_t)cap * sizeof(uint64_t));
-    L->off_chunk_rank = take(((size_t)cap / 256 + 2) * sizeof(uint32_t));         // see pair_reduce.h
-    L->off_carry = take(((size_t)cap / 256 + 2) * 36 * sizeof(float));
+    const size_t chunks = ((size_t)cap >> gather_chunk_bits((uint32_t)cap)) + 2;  // see pair_reduce.h
+    L->off_chunk_rank = take(chunks * sizeof(uint32_t));
+    L->off_carry = take(chunks * kCarryFloats * sizeof(float));
     L->off_grad_rec = take((size_t)n * L->partial_vec4 * 4 * sizeof(float));      // per-point gradient records, by point index
     L->off_reach = take((size_t)(variant == kVariant2D ? 4 : 2) * cap);  // per sorted pair, forward -> backward: the tile's sixteen cells that the splat can reach (3D); a byte per quadrant, did it blend the splat (surfels)
     L->off_tile_order = take((size_t)L->tiles * sizeof(uint32_t));   // tiles in the order the compositing kernels take them

@@ -34,8 +34,9 @@ struct BinArrays {
     uint32_t* depth_bits;        // [n] bit pattern of the depth, by point index
     uint32_t* keys;              // [cap] depth bits of each pair, tile by tile
     uint32_t* vals;              // [cap] point index of each pair
-    uint32_t* chunk_rank;        // rank owning every 256th pair (pair_reduce.h)
+    uint32_t* chunk_rank;        // rank owning the first pair of every chunk (pair_reduce.h)
     uint32_t cap;
+    int chunk_bits;
     uint32_t* status;
 };
 
@@ -239,9 +240,9 @@ __device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam
         A.slot_base[i] = P.at;
         A.depth_bits[i] = bits;
         store(i, rec);
-        // which rank owns every 256th pair (for the pair-balanced gather of the backward pass)
+        // which rank owns the first pair of every chunk (for the pair-balanced gather of the backward pass)
         const uint32_t end = min(P.at + P.cnt, A.cap);
-        for (uint32_t c = (P.at + kChunkPairs - 1) / kChunkPairs; (uint64_t)c * kChunkPairs < end; ++c) A.chunk_rank[c] = P.slot_rank;
+        for (uint32_t c = (P.at + (1u << A.chunk_bits) - 1u) >> A.chunk_bits; (uint64_t)c << A.chunk_bits < end; ++c) A.chunk_rank[c] = P.slot_rank;
     }
     const uint32_t bx = box.y & 0xffffu, by = box.y >> 16, bw = box.z & 0xffffu, bh = box.z >> 16;
     if (box.x == 0u) return;                     // every pair lies beyond the capacity

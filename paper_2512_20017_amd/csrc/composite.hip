@@ -624,6 +624,7 @@ struct StoreSplatGrad {
     }
 };
 
+template <int kChunkBits>
 __global__ __launch_bounds__(256) void k_gather_splat_grads(int n, const uint32_t* __restrict__ status,
                                                             const uint32_t* __restrict__ order,
                                                             const uint32_t* __restrict__ offsets,
@@ -633,14 +634,14 @@ __global__ __launch_bounds__(256) void k_gather_splat_grads(int n, const uint32_
 {
     __shared__ uint32_t sEnd[4][64];
     const uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6);
-    gather_wave<3, 9, true>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplatGrad{rec, order});
+    gather_wave<3, 9, true, kChunkBits>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplatGrad{rec, order});
 }
 
 // also closes the backward call's epoch: the next call stamps its records with a new number
 __global__ __launch_bounds__(256) void k_gather_fixup(int n, uint32_t* __restrict__ status, const uint32_t* __restrict__ order,
-                                                      uint32_t cap, const float* __restrict__ carry, float4* __restrict__ rec)
+                                                      uint32_t cap, int chunk_bits, const float* __restrict__ carry, float4* __restrict__ rec)
 {
-    gather_fixup<9>(blockIdx.x * 256u + threadIdx.x, status, cap, carry, StoreSplatGrad{rec, order});
+    gather_fixup<9>(blockIdx.x * 256u + threadIdx.x, status, cap, chunk_bits, carry, StoreSplatGrad{rec, order});
     if (blockIdx.x == 0 && threadIdx.x == 0) {      // 64-bit count of backward calls on this workspace
         const uint32_t lo = status[kStEpoch] + 1u;
         status[kStEpoch] = lo;
@@ -732,7 +733,7 @@ hipError_t launch_composite_fwd(const CamDev& cam, const Layout& L, char* ws, co
 CarryFold carry_fold(const Layout& L, char* ws)
 {
     return CarryFold{reinterpret_cast<const float*>(ws + L.off_carry), reinterpret_cast<const uint32_t*>(ws + L.off_slot_base),
-                     reinterpret_cast<uint32_t*>(ws + L.off_status), L.cap};
+                     reinterpret_cast<uint32_t*>(ws + L.off_status), L.cap, gather_chunk_bits(L.cap)};
 }
 
 hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, int n, const float bg[3], const float* final_T, const uint32_t* last_idx, const float* dL_dimage,
@@ -757,12 +758,17 @@ hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, in
         ProfScope prof(kKGather, s);
         const uint32_t* chunk_rank = reinterpret_cast<const uint32_t*>(ws + L.off_chunk_rank);
         float* carry = reinterpret_cast<float*>(ws + L.off_carry);
-        const unsigned nwave = (unsigned)((L.cap + kChunkPairs - 1) / kChunkPairs);
+        const int bits = gather_chunk_bits(L.cap);
+        const unsigned nwave = (L.cap + (1u << bits) - 1u) >> bits;
         float4* rec = reinterpret_cast<float4*>(ws + L.off_grad_rec);
-        hipLaunchKernelGGL(k_gather_splat_grads, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank,
+        if (bits == 6)
+            hipLaunchKernelGGL(k_gather_splat_grads<6>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank,
+                           partial, L.cap, carry, rec);
+        else
+            hipLaunchKernelGGL(k_gather_splat_grads<8>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank,
                            partial, L.cap, carry, rec);
         if (g2.mean2d != nullptr) {
-            hipLaunchKernelGGL(k_gather_fixup, dim3((nwave + 255) / 256), dim3(256), 0, s, n, status, order, L.cap, carry, rec);
+            hipLaunchKernelGGL(k_gather_fixup, dim3((nwave + 255) / 256), dim3(256), 0, s, n, status, order, L.cap, bits, carry, rec);
             hipLaunchKernelGGL(k_grad_records_to_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
                                reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, g2);
         }

@@ -2,11 +2,11 @@
 //
 // The pairs of the listed point with rank r (its place among the listed points, in index order) occupy [offsets[r], offsets[r+1]) of the unsorted duplicate list, so the
 // records to add up for one point are contiguous, but their number varies from one to thousands. Work is therefore
-// cut by pairs, not by points: a wavefront owns 256 consecutive pairs (four steps of 64), finds the owning rank of
+// cut by pairs, not by points: a wavefront owns a chunk of consecutive pairs, 256 (four steps of 64) or 64, finds the owning rank of
 // each pair by binary search over a window of 64 range ends in LDS (64 pairs span at most 64 ranks: every visible
 // point has at least one pair), and runs a segmented inclusive scan over the 64 records with DPP row shifts and row
 // broadcasts (owners are sorted, so "same owner as the lane d below" is the whole segment test). A segment that
-// lies inside the wavefront's 256 pairs is stored directly. Segments cut by a wavefront boundary leave a left and /
+// lies inside the wavefront's chunk is stored directly. Segments cut by a wavefront boundary leave a left and /
 // or right piece in a small carry array, and a second kernel - one thread per boundary at which a segment starts -
 // adds the pieces in order. No atomics, no zero-filled outputs, same result on every run.
 #pragma once
@@ -14,14 +14,17 @@
 
 namespace pbdr {
 
-constexpr int kChunkPairs = 256;   // pairs per wavefront
+// Pairs per wavefront, as a power of two: 256, or 64 where that leaves the chip so empty that four steps in a row, each a round
+// trip to memory and a chain of LDS and DPP steps, are the launch (us, 256 / 64: 10,530 pairs 9.9 / 4.7, 102,000 9.8 / 5.0, 480,000 13.0 / 9.4). Beyond, the cut
+// points weigh as much as that gains (1.9 M pairs 28.7 / 26.6, the step the same). By the capacity, which the host knows.
+inline int gather_chunk_bits(uint32_t cap) { return cap <= (1u << 20) ? 6 : 8; }
 
 // carry record per wavefront: [0..15] left piece, [16..31] right piece, then {flags, left rank, right rank, -}
 constexpr int kCarryFloats = 36;
 enum { kCarryHasLeft = 1, kCarryLeftThrough = 2, kCarryHasRight = 4 };
 
-// chunk_rank[c] = rank that owns pair c * 256; written by the packing kernel (a rank writes one entry per 256 pairs it
-// spans).
+// chunk_rank[c] = rank that owns the first pair of chunk c; written by the packing kernel (a rank writes one entry per chunk it
+// reaches the start of).
 
 template <int kCtrl>
 __device__ __forceinline__ float dpp_shift0(float v)    // shifted-in lanes read 0
@@ -72,18 +75,19 @@ __device__ __forceinline__ void seg_scan_sorted(float (&v)[kVals], int owner)
     }
 }
 
-// One wavefront's 256 pairs. kVec4 float4 per record, of which the first kVals floats are summed. `store(rank, v)`
+// One wavefront's 2^kChunkBits pairs. kVec4 float4 per record, of which the first kVals floats are summed. `store(rank, v)`
 // writes a finished sum for rank `rank`. sEnd: 64 words of LDS private to the wavefront.
 // kTagged: the last two words of a record carry the 64-bit number of the backward call that wrote it (the workspace
 // counts its backward calls from one; it starts zero-filled, so no record of an earlier call, and no record never
 // written, carries the current number); a record with any other tag was not written by this call (its pair lies beyond
 // the last splat its tile blended) and counts as zero. That replaces clearing all records before every backward pass.
-template <int kVec4, int kVals, bool kTagged, class Store>
+template <int kVec4, int kVals, bool kTagged, int kChunkBits, class Store>
 __device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* __restrict__ status,
                                             const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ chunk_rank,
                                             const float4* __restrict__ partial, uint32_t cap, float* __restrict__ carry,
                                             uint32_t* sEnd, Store store)
 {
+    constexpr int kChunkPairs = 1 << kChunkBits;
     const int lane = threadIdx.x & 63;
     const uint32_t Pc = min(status[kStNumDup], cap);
     const uint32_t m = min(status[kStNumVis], (uint32_t)n);
@@ -189,11 +193,11 @@ __device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* _
 // One thread per wavefront boundary at which a cut segment starts: right piece of wavefront w, then the left pieces
 // of the following wavefronts up to and including the first that is not a through piece.
 template <int kVals, class Store>
-__device__ __forceinline__ void gather_fixup(uint32_t w, const uint32_t* __restrict__ status, uint32_t cap,
+__device__ __forceinline__ void gather_fixup(uint32_t w, const uint32_t* __restrict__ status, uint32_t cap, int chunk_bits,
                                              const float* __restrict__ carry, Store store)
 {
     const uint32_t Pc = min(status[kStNumDup], cap);
-    const uint32_t nw = (Pc + kChunkPairs - 1) / kChunkPairs;
+    const uint32_t nw = (Pc + (1u << chunk_bits) - 1u) >> chunk_bits;
     if (w >= nw) return;
     const float* c = carry + (size_t)w * kCarryFloats;
     const uint32_t* meta = reinterpret_cast<const uint32_t*>(c + 32);
@@ -216,7 +220,7 @@ __device__ __forceinline__ void gather_fixup(uint32_t w, const uint32_t* __restr
 
 // What k_gather_fixup does, from the side of the point: used by the kernels that read a point's record right after the
 // gather, so that the fixup launch (a few microseconds for ten thousand additions) can be left out. at, count: the
-// point's first pair and its number of pairs. Returns false if all of its pairs lie in one wavefront's 256 (the gather
+// point's first pair and its number of pairs. Returns false if all of its pairs lie in one wavefront's chunk (the gather
 // stored the record itself); else v = the right piece of the wavefront its first pair lies in, plus the left pieces of
 // the following wavefronts up to and including the first that is not a through piece - the pieces and the order of
 // gather_fixup, so the sum is bit for bit the record that kernel would store.
@@ -225,9 +229,9 @@ __device__ __forceinline__ bool record_from_carries(const CarryFold& cf, uint32_
 {
     const uint32_t Pc = min(cf.status[kStNumDup], cf.cap);
     const uint32_t beg = min(at, Pc), end = min(at + count, Pc);      // (at < 2^31, count <= 2^24)
-    const uint32_t w = beg / (uint32_t)kChunkPairs;
-    if (end <= (w + 1u) * (uint32_t)kChunkPairs) return false;
-    const uint32_t nw = (Pc + kChunkPairs - 1) / kChunkPairs;
+    const uint32_t w = beg >> cf.chunk_bits;
+    if (end <= (w + 1u) << cf.chunk_bits) return false;
+    const uint32_t nw = (Pc + (1u << cf.chunk_bits) - 1u) >> cf.chunk_bits;
     const float* c = cf.carry + (size_t)w * kCarryFloats;
     const uint32_t rank = reinterpret_cast<const uint32_t*>(c + 32)[2];
 #pragma unroll

@@ -39,7 +39,8 @@ struct StageRec {
     float4 a, b;                           // mx, my, A, B; C, L, red, green
     float c;                               // blue
     uint32_t pos;                          // place in the tile's list, from one
-    uint32_t pad[2];
+    uint32_t kind;                         // kSplatPlain, kSplatDefinite or 0
+    uint32_t pad;
 };
 
 // Which of the eight 4x4-pixel cells, two rows of four, whose first pixel centre lies at (lx, ly) from the splat's centre can
@@ -82,10 +83,11 @@ constexpr int kWalkPlain = 0, kWalkClamped = 1, kWalkGeneral = 2;
 template <int kKind>
 using WalkKind = std::integral_constant<int, kKind>;
 
-// Forward. The workgroup finds the cells of 256 list positions at a time, one per thread; most lists are not much longer.
-// Then the wavefronts go on by themselves: each compacts the positions that reach its quadrant, stages their records 64 at
-// a time (one per lane, in its own 3 KB of LDS) and writes the lists of its cells, LDS offsets of 16 bits; the entries
-// behind a list's end name a record that reaches nothing. A walk reads two entries per cell and trip: their alphas do not
+// Forward. The workgroup stages the records of 256 list positions at a time, one per thread, and finds their cells; most lists are
+// not much longer. Then the wavefronts go on by themselves: each compacts the positions that reach its quadrant, takes them 64 at
+// a time and writes the lists of its cells, LDS offsets of 16 bits; the entries behind a list's end name a record that reaches
+// nothing. (Each wavefront fetching the records of its own windows, twice as many in all and a round trip to memory per window:
+// 1M points 75.4 us instead of 71.5, 200k 42.3 instead of 40.3, 4,096 20.0 instead of 18.4.) A walk reads two entries per cell and trip: their alphas do not
 // depend on each other, which gives the vector ALU two independent chains; the blends stay in list order.
 // Against one splat a visit on the whole quadrant: the benchmark's view (1M points, 1920x1080, bench.py) 103.8 -> 88.9 us,
 // 77 -> 64 M vector instructions, its 4K street view (8M points) 326 -> 235; clusters and boxes as perf/cases.py draws them,
@@ -104,9 +106,8 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
 {
     constexpr int kGroups = 4, kPosBits = 12;
     static_assert(kFwdChunk <= 1 << kPosBits && kFwdChunk % 256 == 0, "a position and four cells in 16 bits");
-    __shared__ StageRec sRec[4][64 + 1];                       // the last one reaches nothing
+    __shared__ StageRec sRec[kFwdChunk + 1];                   // the last one reaches nothing
     __shared__ uint16_t sHits[4][kFwdChunk];                   // position in the chunk | the quadrant's cells << kPosBits
-    __shared__ uint32_t sId[kFwdChunk];
     __shared__ __align__(8) uint16_t sList[4][kGroups * 64 + 4];
     __shared__ uint16_t sCells[kFwdChunk];
     const int tile = (int)tile_order[blockIdx.x];
@@ -118,36 +119,37 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
     const int px = tx0 + (wave & 1) * 8 + (group & 1) * 4 + (lane & 3), py = ty0 + (wave >> 1) * 8 + (group >> 1) * 4 + ((lane >> 2) & 3);
     const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
     const bool inside = px >= cam.rx0 && px < cam.rx1 && py >= cam.ry0 && py < cam.ry1;
-    StageRec* const rec_w = sRec[wave];
     uint16_t* const list_w = sList[wave];
     uint16_t* const hits_w = sHits[wave];
-    constexpr uint32_t kNoRec = 64u * (uint32_t)sizeof(StageRec);
-    if (lane == 0) {
-        rec_w[64].a = make_float4(0.f, 0.f, 0.f, 0.f);
-        rec_w[64].b = make_float4(0.f, -1e30f, 0.f, 0.f);
-        rec_w[64].c = 0.f;
+    constexpr uint32_t kNoRec = (uint32_t)(kFwdChunk * sizeof(StageRec));
+    static_assert(kNoRec < 65536u, "offsets of 16 bits");
+    if (threadIdx.x == 0) {
+        sRec[kFwdChunk].a = make_float4(0.f, 0.f, 0.f, 0.f);
+        sRec[kFwdChunk].b = make_float4(0.f, -1e30f, 0.f, 0.f);
+        sRec[kFwdChunk].c = 0.f;
     }
+    static_assert(kFwdChunk == 256, "a position per thread");
+    uint32_t id = start + threadIdx.x < end ? vals[start + threadIdx.x] : 0u;      // of this thread's position in the next chunk
+    const auto rec_at = [&](uint32_t off) { return reinterpret_cast<const StageRec*>(reinterpret_cast<const char*>(sRec) + off); };
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
     uint32_t last = 0u;
     unsigned long long live = __ballot(inside);
     for (uint32_t base = start; base < end; base += kFwdChunk) {
         if (base != start && __syncthreads_or(live != 0ull) == 0) break;
         const int cnt = (int)min((uint32_t)kFwdChunk, end - base);
-#pragma unroll
-        for (int j = threadIdx.x; j < kFwdChunk; j += 256) {
-            uint32_t word = 0u;
-            if (j < cnt) {
-                const uint32_t id = vals[base + j];
-                sId[j] = id;
-                const float4* rec = reinterpret_cast<const float4*>(packed + id);
-                const float2 centre = *reinterpret_cast<const float2*>(rec);
-                const float4 ellipse = rec[3];
-                const float lx = (float)tx0 + 0.5f - centre.x, ly = (float)ty0 + 0.5f - centre.y;
-                word = by_quadrant(reached_cells(ellipse, lx, ly)) | (by_quadrant(reached_cells(ellipse, lx, ly + 8.f)) << 8);
-                cells[base + j] = (uint16_t)word;
-            }
-            sCells[j] = (uint16_t)word;
+        const int j = threadIdx.x;
+        uint32_t word = 0u;
+        if (j < cnt) {
+            const float4* rec = reinterpret_cast<const float4*>(packed + id);
+            const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2], ellipse = rec[3];
+            id = base + kFwdChunk + j < end ? vals[base + kFwdChunk + j] : 0u;
+            sRec[j].a = r0; sRec[j].b = r1;
+            *reinterpret_cast<float4*>(&sRec[j].c) = make_float4(r2.x, __uint_as_float(base - start + j + 1u), r2.w, 0.f);
+            const float lx = (float)tx0 + 0.5f - r0.x, ly = (float)ty0 + 0.5f - r0.y;
+            word = by_quadrant(reached_cells(ellipse, lx, ly)) | (by_quadrant(reached_cells(ellipse, lx, ly + 8.f)) << 8);
+            cells[base + j] = (uint16_t)word;
         }
+        sCells[j] = (uint16_t)word;
         __syncthreads();
         int nhit = 0;
 #pragma unroll
@@ -161,18 +163,14 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
         __builtin_amdgcn_wave_barrier();
         for (int w0 = 0; w0 < nhit; w0 += 64) {
             if (live == 0ull) break;
-            uint32_t m = 0u, kind = kSplatPlain;
+            uint32_t m = 0u, kind = kSplatPlain, mine = 0u;
             constexpr uint32_t kNone = kNoRec * 0x10001u;
             *reinterpret_cast<uint2*>(list_w + 4 * lane) = make_uint2(kNone, kNone);
             if (w0 + lane < nhit) {
                 const uint32_t h = hits_w[w0 + lane];
                 m = h >> kPosBits;
-                const uint32_t at = h & ((1u << kPosBits) - 1u);
-                const float4* rec = reinterpret_cast<const float4*>(packed + sId[at]);
-                const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2];
-                rec_w[lane].a = r0; rec_w[lane].b = r1; rec_w[lane].c = r2.x;
-                rec_w[lane].pos = base - start + at + 1u;
-                kind = __float_as_uint(r2.w);
+                mine = (h & ((1u << kPosBits) - 1u)) * (uint32_t)sizeof(StageRec);
+                kind = rec_at(mine)->kind;
             }
             const bool all_definite = __ballot((kind & kSplatDefinite) == 0u) == 0ull, all_plain = __ballot(kind != kSplatPlain) == 0ull;
             int n = 0;
@@ -180,7 +178,7 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
             for (int g = 0; g < kGroups; ++g) {
                 const bool on = (m & (1u << g)) != 0u && ((live >> (16 * g)) & 0xffffull) != 0ull;
                 const unsigned long long b = __ballot(on);
-                if (on) list_w[g * 64 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = (uint16_t)(lane * (int)sizeof(StageRec));
+                if (on) list_w[g * 64 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = (uint16_t)mine;
                 n = max(n, (int)__builtin_popcountll(b));
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -191,7 +189,7 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
                 constexpr bool kClamp = decltype(kind)::value >= kWalkClamped, kSign = decltype(kind)::value >= kWalkGeneral;
                 struct Visit { float alpha, r, g, b; bool ok; };
                 auto eval = [&](uint32_t off, Visit& v) {
-                    const StageRec* rec = reinterpret_cast<const StageRec*>(reinterpret_cast<const char*>(rec_w) + off);
+                    const StageRec* rec = rec_at(off);
                     const float4 a = rec->a, b = rec->b;
                     v.b = rec->c; v.r = b.z; v.g = b.w;
                     const float dx = fx - a.x, dy = fy - a.y;
@@ -224,9 +222,9 @@ __global__ __launch_bounds__(256) void k_composite_fwd(CamDev cam, const uint32_
             if (all_plain) walk(WalkKind<kWalkPlain>{});
             else if (all_definite) walk(WalkKind<kWalkClamped>{});
             else walk(WalkKind<kWalkGeneral>{});
-            if (last_off != ~0u) last = reinterpret_cast<const StageRec*>(reinterpret_cast<const char*>(rec_w) + last_off)->pos;
+            if (last_off != ~0u) last = rec_at(last_off)->pos;
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            __builtin_amdgcn_wave_barrier();             // the next window overwrites the staged records
+            __builtin_amdgcn_wave_barrier();             // the next window overwrites the lists
         }
     }
     if (inside) {

@@ -65,12 +65,6 @@ __device__ __forceinline__ uint32_t reached_cells(const float4& e, float lx, flo
     return cells;
 }
 
-// the cells of half a tile (reached_cells) in the order the kernels keep them: four bits per quadrant, its cells in row order
-__device__ __forceinline__ uint32_t by_quadrant(uint32_t m)
-{
-    return (m & 3u) | ((m >> 2) & 12u) | ((m << 2) & 0x30u) | (m & 0xc0u);
-}
-
 // The walks of both kernels come in three kinds, chosen per window or batch (uniform): without the clamp and the sign test,
 // neither of which can fire where every conic is safely definite and every opacity at most 0.98; with the clamp alone; and with
 // both, for the other states a caller may hand in. All are unrolled and ask for records ahead alike: one splat above 0.98 is

@@ -35,13 +35,6 @@ __device__ __forceinline__ TileCtx tile_ctx(const CamDev& cam, const uint32_t* _
     return c;
 }
 
-__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((unsigned long long)hi << 32) | lo;
-}
-
 // Asks for 16 bytes per active lane, from src to the wavefront's 16 * lane bytes behind dst (uniform) in LDS, without a
 // register in between. The issuing wavefront waits with wait_loads() before anybody reads them. (The builtin for this
 // instruction makes the compiler wait for the load before the next LDS read, whatever that reads.)
@@ -57,45 +50,6 @@ template <int kCtrl>
 __device__ __forceinline__ float dpp_move(float v)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
-}
-
-// Sums eight values over each row of 16 lanes at once by recursive halving: at each of three exchange steps a lane
-// keeps half of its values and adds its partner's copy of that half, then one more pairing finishes.
-//   step 1: partner lane ^ 8 (row_ror:8);           lanes with bit 3 clear keep values 0..3, the others 4..7
-//   step 2: partner lane ^ 7 (row_half_mirror);     lanes with bit 2 clear keep the first two of those, the others the rest
-//   step 3: partner lane ^ 3 (quad_perm [3,2,1,0]); lanes with bit 1 clear keep the first of those two
-//   last  : partner lane ^ 1 (quad_perm [1,0,3,2]); plain add
-// Each partner differs from the lane in exactly the bit that decides the step and in none of the bits that decided
-// earlier steps, so both hold the same values. Bits 3 and 2 are the quad a lane sits in, which is what a DPP bank
-// mask selects: steps 1 and 2 are two masked adds per output and no select (written as assembly because the compiler
-// has no form for a masked DPP write; the s_nop's cover the VALU-write -> DPP-read wait states inside and on both
-// sides of the block). 16 VALU instructions instead of 8 x 4. Every lane of the wavefront must be active.
-// On return the lane holds the row sum of value number (lane >> 1) & 7; lanes 2k and 2k+1 hold the same number.
-__device__ __forceinline__ float row_sum8(const float v[8], bool bit1)
-{
-    float a[4], c[2];
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %0, %6, %6 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %1, %7, %7 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %2, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %3, %9, %9 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %0, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %1, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %2, %12, %12 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %3, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %4, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %5, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "v_add_f32_dpp %4, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "v_add_f32_dpp %5, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-        "s_nop 1"
-        : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(c[0]), "=&v"(c[1])
-        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
-    const float keep = bit1 ? c[1] : c[0], send = bit1 ? c[0] : c[1];
-    float d = keep + dpp_move<0x1B>(send);         // quad_perm:[3,2,1,0]
-    d += dpp_move<0xB1>(d);                        // quad_perm:[1,0,3,2]
-    return d;
 }
 
 // Sums eight values over each quad of lanes: lane r of the quad is left with the sums of values 2 r and 2 r + 1.
@@ -122,25 +76,11 @@ __device__ __forceinline__ float quad_sum(float v)
     return v;
 }
 
-// ---- bookkeeping of the walks ----------------------------------------------------------------------------------------
-// The walks are bound by issue, scalar instructions included, so a visit's bookkeeping is spelled out: which pixels are still
-// open is a scalar lane mask and, in the surfel walks, the splats left in a wavefront's batch are a 64-bit scalar mask that
-// gives up one bit in one instruction (the 3D walks read lists, see composite.hip).
-
-// the lowest splat left in the mask, taken out of it (m != 0)
-__device__ __forceinline__ int take_lowest(unsigned long long& m)
+// The cells of half a tile, bit 4 r + c for row r and column c of its two rows of four, in the order the kernels keep them: four
+// bits per quadrant, its cells in row order.
+__device__ __forceinline__ uint32_t by_quadrant(uint32_t m)
 {
-    const int j = __builtin_ctzll(m);
-    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(j));
-    return j;
-}
-
-// the highest splat left in the mask, taken out of it (m != 0)
-__device__ __forceinline__ int take_highest(unsigned long long& m)
-{
-    const int j = 63 - __builtin_clzll(m);
-    asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(j));
-    return j;
+    return (m & 3u) | ((m >> 2) & 12u) | ((m << 2) & 0x30u) | (m & 0xc0u);
 }
 
 // One blend in list order. ok: lanes whose alpha counts; live: lanes whose pixel is still open, which is updated by the
@@ -150,18 +90,6 @@ __device__ __forceinline__ bool blend_decision(unsigned long long& live, bool ok
     const unsigned long long m = __ballot(ok);
     live &= ~(m & __ballot(Tn < kTStop));
     return __builtin_amdgcn_inverse_ballot_w64(live & m);
-}
-
-// Byte offset of a staged record, as a vector value: the address of the visit's LDS reads, and what a lane that blends
-// keeps as its last record (turned into a list position once a batch). Scalar multiply, one vector move; left to itself
-// the compiler forms the address with a 64-bit vector multiply-add, four times the issue slots.
-__device__ __forceinline__ uint32_t staged_offset(uint32_t wave_base, int j, uint32_t stride)
-{
-    uint32_t off = wave_base + (uint32_t)j * stride;
-    asm("" : "+s"(off));
-    uint32_t v;
-    asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(off));
-    return v;
 }
 
 }  // namespace pbdr

@@ -298,23 +298,11 @@ __global__ __launch_bounds__(kThreads) void k_pack2d(Splats2DDev sp, CamDev cam,
         });
 }
 
-constexpr int kAccStride2D = 15;   // floats between the LDS accumulators of consecutive surfels of a batch (odd)
-
-// LDS image of one staged batch of kB surfels (kB a multiple of 64, at most the workgroup size)
-template <int kB>
-struct Stage2D {
-    float4 a[kB];   // t0x, t0y, t1x, t1y
-    float4 b[kB];   // t2x, t2y, t2z, log2(opacity)
-    float4 c[kB];   // mx, my, red, green
-    float4 d[kB];   // blue, t0z, t1z, backward: list position + 1
-    unsigned long long mask[4][kB / 64];   // [quadrant][staging wavefront]: which of its 64 splats the quadrant visits
-};
-
-// Which quadrants of the tile whose first pixel centre is (x0, y0) can the splat with raster record r0..r3 (L = log2 of
-// its opacity) touch with alpha >= 1/255? Bit q for quadrant q. A quadrant is kept if the bounding box of the image of the
-// disk rim where alpha falls to 1/255 (rho^2 = 2 ln(255 o)), or of the low-pass support around the centre, meets its
-// pixel centres; taken conservatively, NaN keeps.
-__device__ __forceinline__ uint32_t tile_reach2d(const float4& r0, const float4& r1, const float4& r2, const float4& r3, float L,
+// Which of the sixteen 4x4 cells of the tile whose first pixel centre is (x0, y0) can the splat with raster record r0..r3 (L = log2
+// of its opacity) touch with alpha >= 1/255? Four bits per quadrant (by_quadrant()). A cell is kept if the bounding box of the
+// image of the disk rim where alpha falls to 1/255 (rho^2 = 2 ln(255 o)), or of the low-pass support around the centre, meets
+// its pixel centres; taken conservatively, NaN keeps.
+__device__ __forceinline__ uint32_t tile_cells2d(const float4& r0, const float4& r1, const float4& r2, const float4& r3, float L,
                                                  float x0, float y0)
 {
     const float tau = (L + kLog2_255) * 0.6931471805599453f;      // ln(255 o): alpha >= 1/255 <=> -ln G^ <= tau
@@ -323,19 +311,24 @@ __device__ __forceinline__ uint32_t tile_reach2d(const float4& r0, const float4&
     const float lp = sqrtf(fmaxf(tau, 0.f)) + 0.05f;           // radius of the low-pass part, with margin
     // image of the rim u^2 + v^2 = rho2, relative to the projected centre: rows T_0', T_1', T_2
     const float aa = rho2 * (r1.x * r1.x + r1.y * r1.y) - r1.z * r1.z;
-    if (!(aa < -0.02f * r1.z * r1.z)) return 15u;   // the rim at this level comes (almost) to the camera plane: keep
+    if (!(aa < -0.02f * r1.z * r1.z)) return 0xffffu;   // the rim at this level comes (almost) to the camera plane: keep
     const float ia = 1.0f / aa;
     const float bx = rho2 * (r0.x * r1.x + r0.y * r1.y) - r3.z * r1.z, by = rho2 * (r0.z * r1.x + r0.w * r1.y) - r3.w * r1.z;
     const float cx = rho2 * (r0.x * r0.x + r0.y * r0.y) - r3.z * r3.z, cy = rho2 * (r0.z * r0.z + r0.w * r0.w) - r3.w * r3.w;
     const float c0x = bx * ia, c0y = by * ia;
     const float hx = sqrtf(fmaxf(0.f, c0x * c0x - cx * ia)) * 1.001f + 0.01f;
     const float hy = sqrtf(fmaxf(0.f, c0y * c0y - cy * ia)) * 1.001f + 0.01f;
-    // a column or row of quadrants is out if it lies wholly beside it
-    const float qx0 = x0 - r2.x, qx1 = (x0 + 8.f) - r2.x, qy0 = y0 - r2.y, qy1 = (y0 + 8.f) - r2.y;
+    // a column or row of cells is out if it lies wholly beside it
     const float lo_x = fminf(-lp, c0x - hx), hi_x = fmaxf(lp, c0x + hx), lo_y = fminf(-lp, c0y - hy), hi_y = fmaxf(lp, c0y + hy);
-    const bool left = !(hi_x < qx0 || lo_x > qx0 + 7.f), right = !(hi_x < qx1 || lo_x > qx1 + 7.f);
-    const bool top = !(hi_y < qy0 || lo_y > qy0 + 7.f), bottom = !(hi_y < qy1 || lo_y > qy1 + 7.f);
-    return (left && top ? 1u : 0u) | (right && top ? 2u : 0u) | (left && bottom ? 4u : 0u) | (right && bottom ? 8u : 0u);
+    const float dx = x0 - r2.x, dy = y0 - r2.y;
+    uint32_t cols = 0u, rows = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        cols |= !(hi_x < dx + 4.f * k || lo_x > dx + (4.f * k + 3.f)) ? 1u << k : 0u;
+        rows |= !(hi_y < dy + 4.f * k || lo_y > dy + (4.f * k + 3.f)) ? 1u << k : 0u;
+    }
+    const auto half = [&](uint32_t r) { return by_quadrant(((r & 1u) ? cols : 0u) | ((r & 2u) ? cols << 4 : 0u)); };
+    return half(rows) | (half(rows >> 2) << 8);
 }
 
 // per-pair evaluation shared by forward and backward: exponent of G^ in log2 units and the pieces the backward needs
@@ -363,126 +356,175 @@ __device__ __forceinline__ void eval_pair2d(const float4& a, const float4& b, co
 // four times: 344 against 333 us at 2M disks on 2600x1463, 169 against 163 at 1M on 1920x1080; they gain
 // only where quadrants end far apart (390 against 424 us at 600k disks on 400x300).
 //
-// The walk also notes for the backward pass which splats its quadrant blended. Bound by instruction issue (92 % of it at
-// 1M disks, 1920x1080), it can spare little for that: the lane masks of a visit are kept as scalars, the instruction that
-// forms the mask of blending lanes leaves in the carry whether it is empty, and two additions with carry shift that bit
-// into a 64-bit history, one bit per visit (a ballot of the lane predicate, compare and select took two vector and five
-// scalar instructions a visit). LDS offsets and the last blended position are kept as staged_offset says. 1M disks at
-// 1920x1080, this kernel: 180.9 -> 162.4 us, and 167.7 for a walk in the compiler's own form that notes nothing.
+// As in the 3D kernel each row of 16 lanes is a 4x4 cell and a visit is one entry of each of the four cells' lists: 64 positions
+// that reach the quadrant at a time, LDS offsets of 16 bits, the entries behind a list's end name a record that reaches nothing.
+//
+// The walk also notes for the backward pass which cells blended which splats: lane i keeps the lane mask of visit i (two
+// instructions a visit and two scalar ones), and after a window the lane that stands for a splat asks the lanes of its places in the four lists.
+// Against one surfel a visit on the whole quadrant, 1M disks at 1920x1080 145.0 -> 131.0 us, 3,001 at 203x121 17.2 -> 15.4.
 constexpr int kFwdBatch2D = 256;
 
-__global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
+__global__ __launch_bounds__(256, 6) void k_composite2d_fwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
-                                                         uint32_t* __restrict__ blend_words, float bg0, float bg1, float bg2,
+                                                         uint16_t* __restrict__ blend_words, float bg0, float bg1, float bg2,
                                                          float* __restrict__ image, float* __restrict__ final_T,
                                                          uint32_t* __restrict__ last_idx)
 {
-    __shared__ Stage2D<kFwdBatch2D> S;
-    __shared__ unsigned long long sBlended[4][kFwdBatch2D / 64];     // [quadrant][64 positions of the batch]: blended by some pixel
-    const TileCtx c = tile_ctx(cam, ranges, tile_order);
+    constexpr int kPosBits = 12;
+    static_assert(kFwdBatch2D == 256, "a position per thread");
+    __shared__ float4 sA[kFwdBatch2D + 1];         // t0x, t0y, t1x, t1y (the last record of each part reaches nothing)
+    __shared__ float4 sB[kFwdBatch2D + 1];         // t2x, t2y, t2z, log2(opacity)
+    __shared__ float4 sC[kFwdBatch2D + 1];         // mx, my, red, green
+    __shared__ float4 sD[kFwdBatch2D + 1];         // blue, t0z, t1z, -
+    __shared__ uint16_t sHits[4][kFwdBatch2D];     // per quadrant: position in the batch | the quadrant's cells << kPosBits
+    __shared__ __align__(8) uint16_t sList[4][4 * 64 + 4];
+    __shared__ uint16_t sCells[kFwdBatch2D];
+    __shared__ uint8_t sBlended[4][kFwdBatch2D];   // [quadrant][position in the batch]: a bit per cell that blended it
+    const int tile = (int)tile_order[blockIdx.x];
+    const int tiy = tile / cam.TX, tix = tile - tiy * cam.TX;
+    const int tx0 = (cam.otx + tix) * kTile, ty0 = (cam.oty + tiy) * kTile;
+    const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const float fx = (float)c.px + 0.5f, fy = (float)c.py + 0.5f;
-    const float x0 = (float)c.tx0 + 0.5f, y0 = (float)c.ty0 + 0.5f;     // centre of the tile's first pixel
+    const int group = lane >> 4;
+    const int px = tx0 + (wave & 1) * 8 + (group & 1) * 4 + (lane & 3), py = ty0 + (wave >> 1) * 8 + (group >> 1) * 4 + ((lane >> 2) & 3);
+    const bool inside = px >= cam.rx0 && px < cam.rx1 && py >= cam.ry0 && py < cam.ry1;
+    const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
+    const float x0 = (float)tx0 + 0.5f, y0 = (float)ty0 + 0.5f;     // centre of the tile's first pixel
+    constexpr uint32_t kNone = (uint32_t)kFwdBatch2D * 16u * 0x10001u;
+    uint16_t* const list_w = sList[wave];
+    uint16_t* const hits_w = sHits[wave];
+    if (threadIdx.x == 0) {
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        sA[kFwdBatch2D] = zero; sB[kFwdBatch2D] = make_float4(0.f, 0.f, 0.f, -1e30f); sC[kFwdBatch2D] = zero; sD[kFwdBatch2D] = zero;
+    }
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
     uint32_t last = 0;
-    unsigned long long live = __ballot(c.inside);
-    for (uint32_t base = c.start; base < c.end; base += kFwdBatch2D) {
-        const int cnt = (int)min((uint32_t)kFwdBatch2D, c.end - base);
+    unsigned long long live = __ballot(inside);
+    uint32_t id = start + threadIdx.x < end ? vals[start + threadIdx.x] : 0u;      // of this thread's position in the next batch
+    for (uint32_t base = start; base < end; base += kFwdBatch2D) {
+        const int cnt = (int)min((uint32_t)kFwdBatch2D, end - base);
         uint32_t reach = 0u;
         if ((int)threadIdx.x < cnt) {
-            const uint32_t id = vals[base + threadIdx.x];
             const float4* rec = reinterpret_cast<const float4*>(packed + id);
             const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
+            id = base + kFwdBatch2D + threadIdx.x < end ? vals[base + kFwdBatch2D + threadIdx.x] : 0u;
             const float L = __log2f(r1.w);
-            S.a[threadIdx.x] = r0;
-            S.b[threadIdx.x] = make_float4(r1.x, r1.y, r1.z, L);
-            S.c[threadIdx.x] = r2;
-            S.d[threadIdx.x] = make_float4(r3.x, r3.z, r3.w, 0.f);
-            reach = tile_reach2d(r0, r1, r2, r3, L, x0, y0);
+            sA[threadIdx.x] = r0;
+            sB[threadIdx.x] = make_float4(r1.x, r1.y, r1.z, L);
+            sC[threadIdx.x] = r2;
+            sD[threadIdx.x] = make_float4(r3.x, r3.z, r3.w, 0.f);
+            reach = tile_cells2d(r0, r1, r2, r3, L, x0, y0);
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const unsigned long long m = __ballot(((reach >> q) & 1u) != 0u);
-            if (lane == 0) S.mask[q][wave] = m;
-        }
+        sCells[threadIdx.x] = (uint16_t)reach;
+        reinterpret_cast<uint32_t*>(sBlended)[threadIdx.x] = 0u;
         __syncthreads();
         uint32_t last_off = ~0u;                     // 16 * place in the batch of the splat the lane blended last
-        uint32_t used_lo = 0u, used_hi = 0u;         // a bit per visit, the newest lowest: some lane blended
-        // alpha of one visit: everything that does not depend on the pixel's running state. ok: lanes whose alpha counts
-        auto eval = [&](uint32_t off, float& alpha, unsigned long long& ok, float& r, float& g, float& bl) {
-            const auto at = [off](const float4* p) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) + off); };
-            const float4 a = at(S.a), b = at(S.b), cc = at(S.c), dd = at(S.d);
-            bl = dd.x; r = cc.z; g = cc.w;
-            Pair2D E;
-            eval_pair2d(a, b, cc, dd, fx, fy, E);
-            alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(b.w + fmaxf(E.e1, E.e2)));
-            ok = __builtin_amdgcn_ballot_w64(E.p2 != 0.f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
-        };
-        auto blend_one = [&](uint32_t off, float alpha, unsigned long long ok, float r, float g, float bl) {
-            const float aT = alpha * T;
-            const float Tn = T - aT;            // T (1 - alpha), with the product the weight needs anyway
-            const unsigned long long stop = __builtin_amdgcn_ballot_w64(Tn < kTStop);
-            const unsigned long long valid = live & ok;
-            unsigned long long blending;        // valid and not stop; SCC = any
-            asm("s_andn2_b64 %0, %3, %4\n\ts_addc_u32 %1, %1, %1\n\ts_addc_u32 %2, %2, %2"
-                : "=&s"(blending), "+s"(used_lo), "+s"(used_hi) : "s"(valid), "s"(stop) : "scc");
-            live &= ~(ok & stop);               // (a lane that is not live may be among these: it is not live anyway)
-            const bool blend = __builtin_amdgcn_inverse_ballot_w64(blending);
-            const float w = blend ? aT : 0.f;
-            C0 += r * w; C1 += g * w; C2 += bl * w;
-            T = blend ? Tn : T;
-            last_off = blend ? off : last_off;
-        };
-        for (int k = 0; k < kFwdBatch2D / 64; ++k) {
-            unsigned long long blended = 0ull;
-            if (live != 0ull) {
-                const unsigned long long reached = uniform_u64(S.mask[wave][k]);
-                unsigned long long m = reached;
-                used_lo = used_hi = 0u;
-                // two visits per trip while there are two (independent alphas, blends in list order)
-                int left = __builtin_popcountll(m);
-                for (; left >= 2; left -= 2) {
-                    const uint32_t o0 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
-                    const uint32_t o1 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
-                    float al0, red0, grn0, blu0, al1, red1, grn1, blu1;
-                    unsigned long long ok0, ok1;
-                    eval(o0, al0, ok0, red0, grn0, blu0);
-                    eval(o1, al1, ok1, red1, grn1, blu1);
-                    blend_one(o0, al0, ok0, red0, grn0, blu0);
-                    blend_one(o1, al1, ok1, red1, grn1, blu1);
-                }
-                if (left) {
-                    const uint32_t o0 = staged_offset(1024u * (uint32_t)k, take_lowest(m), sizeof(float4));
-                    float al0, red0, grn0, blu0;
-                    unsigned long long ok0;
-                    eval(o0, al0, ok0, red0, grn0, blu0);
-                    blend_one(o0, al0, ok0, red0, grn0, blu0);
-                }
-                // the history back to the visited splats' places: of v visits the one with r before it has bit v - 1 - r
-                const unsigned long long used = ((unsigned long long)used_hi << 32) | used_lo;
-                const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(reached >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)reached, 0u));
-                const int bit = (__builtin_popcountll(reached) - 1 - before) & 63;
-                blended = __ballot(((reached >> lane) & (used >> bit) & 1ull) != 0ull);
-            }
-            if (lane == 0) sBlended[wave][k] = blended;
+        int nhit = 0;
+#pragma unroll
+        for (int r = 0; r < kFwdBatch2D; r += 64) {      // (positions past the end have no cells)
+            const uint32_t m = ((uint32_t)sCells[r + lane] >> (4 * wave)) & 15u;
+            const unsigned long long b = __ballot(m != 0u);
+            if (m) hits_w[nhit + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = (uint16_t)((uint32_t)(r + lane) | (m << kPosBits));
+            nhit += __builtin_popcountll(b);
         }
-        if (last_off != ~0u) last = base - c.start + 1u + last_off / (uint32_t)sizeof(float4);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int w0 = 0; w0 < nhit; w0 += 64) {
+            if (live == 0ull) break;
+            uint32_t m = 0u, at = 0u;
+            *reinterpret_cast<uint2*>(list_w + 4 * lane) = make_uint2(kNone, kNone);
+            if (w0 + lane < nhit) {
+                const uint32_t h = hits_w[w0 + lane];
+                m = h >> kPosBits;
+                at = h & ((1u << kPosBits) - 1u);
+            }
+            int n = 0;
+            uint32_t places = 0u;      // of this lane's splat in the four lists, a byte each
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const bool on = (m & (1u << g)) != 0u && ((live >> (16 * g)) & 0xffffull) != 0ull;
+                const unsigned long long b = __ballot(on);
+                const int place = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                if (on) list_w[g * 64 + place] = (uint16_t)(at * 16u);
+                else m &= ~(1u << g);
+                places |= (uint32_t)place << (8 * g);
+                n = max(n, (int)__builtin_popcountll(b));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const uint16_t* const my_list = list_w + group * 64;
+            int used_lo = 0, used_hi = 0;                // lane i: the lanes that blended in visit i
+            // alpha of one visit: everything that does not depend on the pixel's running state. ok: lanes whose alpha counts
+            auto eval = [&](uint32_t off, float& alpha, unsigned long long& ok, float& r, float& g, float& bl) {
+                const auto from = [off](const float4* p) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) + off); };
+                const float4 a = from(sA), b = from(sB), cc = from(sC), dd = from(sD);
+                bl = dd.x; r = cc.z; g = cc.w;
+                Pair2D E;
+                eval_pair2d(a, b, cc, dd, fx, fy, E);
+                alpha = fminf(kAlphaMax, __builtin_amdgcn_exp2f(b.w + fmaxf(E.e1, E.e2)));
+                ok = __builtin_amdgcn_ballot_w64(E.p2 != 0.f) & __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
+            };
+            auto blend_one = [&](uint32_t off, float alpha, unsigned long long ok, float r, float g, float bl, unsigned long long& blending_now) {
+                const float aT = alpha * T;
+                const float Tn = T - aT;            // T (1 - alpha), with the product the weight needs anyway
+                const unsigned long long stop = __builtin_amdgcn_ballot_w64(Tn < kTStop);
+                const unsigned long long blending = live & ok & ~stop;
+                blending_now = blending;
+                live &= ~(ok & stop);               // (a lane that is not live may be among these: it is not live anyway)
+                const bool blend = __builtin_amdgcn_inverse_ballot_w64(blending);
+                // (chosen, not weighted with zero: a colour that is not finite reaches only the pixels that blend it)
+                C0 = blend ? fmaf(r, aT, C0) : C0; C1 = blend ? fmaf(g, aT, C1) : C1; C2 = blend ? fmaf(bl, aT, C2) : C2;
+                T = blend ? Tn : T;
+                last_off = blend ? off : last_off;
+            };
+            // two visits per trip (independent alphas, blends in list order)
+            uint32_t next = *reinterpret_cast<const uint32_t*>(my_list);
+            for (int i = 0; i < n; i += 2) {
+                const uint32_t o0 = next & 0xffffu, o1 = next >> 16;
+                next = *reinterpret_cast<const uint32_t*>(my_list + i + 2);      // (behind the last one: padding or the next list, not used)
+                asm volatile("" ::: "memory");                                   // asked for here, a trip ahead
+                float al0, red0, grn0, blu0, al1, red1, grn1, blu1;
+                unsigned long long ok0, ok1;
+                eval(o0, al0, ok0, red0, grn0, blu0);
+                eval(o1, al1, ok1, red1, grn1, blu1);
+                unsigned long long m0, m1;
+                blend_one(o0, al0, ok0, red0, grn0, blu0, m0);
+                blend_one(o1, al1, ok1, red1, grn1, blu1, m1);
+                uint32_t keep;
+                asm("s_mov_b32 %2, m0\n\ts_mov_b32 m0, %7\n\tv_writelane_b32 %0, %3, m0\n\tv_writelane_b32 %1, %4, m0\n\t"
+                    "s_add_u32 m0, m0, 1\n\tv_writelane_b32 %0, %5, m0\n\tv_writelane_b32 %1, %6, m0\n\ts_mov_b32 m0, %2"
+                    : "+v"(used_lo), "+v"(used_hi), "=&s"(keep)
+                    : "s"((uint32_t)m0), "s"((uint32_t)(m0 >> 32)), "s"((uint32_t)m1), "s"((uint32_t)(m1 >> 32)), "s"(i) : "scc");
+            }
+            // visit i's cells, in lane i; then each splat's, from its places
+            const uint32_t visit = ((uint32_t)used_lo & 0xffffu ? 1u : 0u) | ((uint32_t)used_lo >> 16 ? 2u : 0u) | ((uint32_t)used_hi & 0xffffu ? 4u : 0u) | ((uint32_t)used_hi >> 16 ? 8u : 0u);
+            uint32_t blended = 0u;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                blended |= (uint32_t)__builtin_amdgcn_ds_bpermute((int)((places >> (8 * g)) & 255u) << 2, (int)visit) & m & (1u << g);
+            if (blended) sBlended[wave][at] = (uint8_t)blended;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            __builtin_amdgcn_wave_barrier();             // the next window overwrites the lists
+        }
+        if (last_off != ~0u) last = base - start + 1u + last_off / (uint32_t)sizeof(float4);
         const int open = __syncthreads_count(live != 0ull);
         if ((int)threadIdx.x < cnt) {
             uint32_t word = 0u;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) word |= (uint32_t)((sBlended[q][wave] >> lane) & 1ull) << (8 * q);
-            blend_words[base + threadIdx.x] = word;
+            for (int q = 0; q < 4; ++q) word |= (uint32_t)sBlended[q][threadIdx.x] << (4 * q);
+            blend_words[base + threadIdx.x] = (uint16_t)word;
         }
         if (open == 0) break;                        // every pixel of the tile has ended
+        __syncthreads();                             // (the blended bits have been read)
     }
-    if (c.inside) {
+    if (inside) {
         const size_t HW = (size_t)cam.W * cam.H;
-        image[c.pix] = C0 + T * bg0;
-        image[HW + c.pix] = C1 + T * bg1;
-        image[2 * HW + c.pix] = C2 + T * bg2;
-        final_T[c.pix] = T;
-        last_idx[c.pix] = last;
+        const size_t pix = (size_t)(py - cam.ry0) * (size_t)cam.W + (size_t)(px - cam.rx0);
+        image[pix] = C0 + T * bg0;
+        image[HW + pix] = C1 + T * bg1;
+        image[2 * HW + pix] = C2 + T * bg2;
+        final_T[pix] = T;
+        last_idx[pix] = last;
     }
 }
 
@@ -494,60 +536,76 @@ __global__ __launch_bounds__(256) void k_composite2d_fwd(CamDev cam, const uint3
 // 64-byte record per (tile, splat) pair. dp and the low-pass sums leave out the factors o and, the latter, 2; the record
 // has them.
 //
-// The sums over pixels are taken four visits at a time, as in the 3D kernel: a visit stores five numbers per pixel (dp,
-// the blend weight, G^ dL/dalpha) as rows of 64 floats in LDS; after four visits each row of 16 lanes takes one of them, a
-// lane the numbers of four neighbouring pixels, whose dx, dy and dL/dcolour give its 15 weighted sums, and two row
-// butterflies finish all four visits at once: about 26 vector instructions a visit where every visit reducing its own 15
-// products took 55. Which pixels take the disk part is the sign of their weight, which is never negative itself: one
-// instruction a visit (as a ballot kept in the lanes that need it, five: 380 against 363 us). kRows2D rows, not six: the
-// LDS then holds four workgroups per compute unit. 1M disks at 1920x1080, this kernel: 454 -> 363 us, the blended splats
-// handed over by the forward pass included.
+// As in the 3D kernel a visit is one entry of each of the four cells' lists, and the sums over pixels are taken four visits at a
+// time: a visit stores five numbers per pixel (dp, the blend weight, G^ dL/dalpha) as rows of 64 floats in LDS; after four visits
+// each row of 16 lanes takes one of them and a quad of lanes each cell, a lane the numbers of four neighbouring pixels, a row of the
+// cell, whose dx, dy and dL/dcolour give its 15 weighted sums, and two exchanges inside the quad finish sixteen (splat, cell)
+// pairs at once. The sums are kept by visit and cell for kBwdVisits2D visits; then the lane that stands for a splat adds up those
+// of its places in the four lists. Which pixels take the disk part is the sign of their weight, which is never negative itself:
+// one instruction a visit (as a ballot kept in the lanes that need it, five). kRows2D rows, not six: the LDS then holds four
+// workgroups per compute unit.
 //
-// Only the entries that some quadrant blended are staged, 64 of them at a time wherever they stand in the list: 1M disks at
-// 1920x1080, mean step of eight scenes 718 -> 712 us (batches of 64 consecutive positions before), each of them faster.
-// Measured and dropped on top of it: the next batch's records asked for during the walk of the current one, no clearing of
-// the accumulators and a barrier less, at 30 registers more: 0.1 % of that step.
-constexpr int kBwdBatch2D = 64;    // surfels staged at a time by the backward kernel: what the per-quadrant accumulators leave room for
+// Only the cells that blended a splat list it, and only the entries that some cell blended are staged, 64 of them at a time
+// wherever they stand in the list.
+// Against one surfel a visit on the whole quadrant, 27 % of whose lanes blended it: 1M disks at 1920x1080 296.6 -> 250.8 us, 3,001 at
+// 203x121 36.8 -> 29.2; the errors against 64 bits are the same (mean2d 1.42e-7, opacity 1.75e-7, colour 1.78e-7, six scenes of 120k
+// disks at 960x540).
+constexpr int kBwdBatch2D = 64;    // surfels staged at a time by the backward kernel: one per lane
 constexpr uint32_t kBwdChunk2D = 256;      // list positions that are searched for blended entries at a time, one per thread
 constexpr int kSlots2D = 4;        // visits staged per reduction: one per row of 16 lanes
 constexpr int kRows2D = 5;         // rows a visit stores: dp (3), signed w, G^ dL/dalpha
+constexpr int kBwdVisits2D = 12;   // visits whose sums a wavefront keeps before it adds them up by splat (a multiple of kSlots2D)
 
 __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                          const uint32_t* __restrict__ vals, const Packed2D* __restrict__ packed,
-                                                         const uint32_t* __restrict__ blend_words, const uint32_t* __restrict__ slot_base,
+                                                         const uint16_t* __restrict__ blend_words, const uint32_t* __restrict__ slot_base,
                                                          float bg0, float bg1, float bg2,
                                                          const float* __restrict__ final_T, const uint32_t* __restrict__ last_idx,
                                                          const float* __restrict__ dL_dimage, uint32_t cap,
                                                          float4* __restrict__ partial)
 {
-    __shared__ Stage2D<kBwdBatch2D> S;
-    // [quadrant][splat of the batch][value], 15 floats apart (odd: the stores of one visit and the per-thread reads at
-    // the end of a batch spread over the LDS banks). A wavefront visits a splat at most once per batch, so it writes its
-    // quadrant's sums with plain stores and the thread that staged the splat adds the four up: no LDS float atomics,
-    // which cost the LDS about 2.5 cycles per active lane.
-    __shared__ float sAcc[4][kAccStride2D * kBwdBatch2D];
-    __shared__ __align__(16) float sV[4][kRows2D * kSlots2D * 64];   // per wavefront: visit slot s has rows kRows2D s ...
+    // the batch: t0x, t0y, t1x, t1y; t2x, t2y, t2z, log2(opacity); mx, my, red, green; blue, t0z, t1z, list position + 1. The last
+    // record of each part reaches nothing.
+    __shared__ float4 sA[kBwdBatch2D + 1], sB[kBwdBatch2D + 1], sC[kBwdBatch2D + 1], sD[kBwdBatch2D + 1];
+    __shared__ uint16_t sCells[kBwdBatch2D];
+    // per wavefront: visit slot s has rows kRows2D s ...; then, at the end of a batch, the wavefront's sums by splat, four parts of
+    // [splat] float4
+    __shared__ __align__(16) float sV[4][kRows2D * kSlots2D * 64];
+    __shared__ __align__(16) float sSum[4][kBwdVisits2D * 64];        // per wavefront: [visit][cell][16 sums]
+    __shared__ __align__(8) uint16_t sList[4][4 * kBwdBatch2D];
     __shared__ uint32_t sMax[4], sCount[4];
     __shared__ uint16_t sFound[kBwdBatch2D + kBwdChunk2D];
-    const TileCtx c = tile_ctx(cam, ranges, tile_order);
+    static_assert(kRows2D * kSlots2D * 64 >= 16 * kBwdBatch2D && kBwdVisits2D % kSlots2D == 0, "the sums by splat fit where the rows were");
+    const int tile = (int)tile_order[blockIdx.x];
+    const int tile_y = tile / cam.TX, tile_x = tile - tile_y * cam.TX;
+    const int tx0 = (cam.otx + tile_x) * kTile, ty0 = (cam.oty + tile_y) * kTile;
+    const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const float fx = (float)c.px + 0.5f, fy = (float)c.py + 0.5f;
+    const int group = lane >> 4;
+    const int px = tx0 + (wave & 1) * 8 + (group & 1) * 4 + (lane & 3), py = ty0 + (wave >> 1) * 8 + (group >> 1) * 4 + ((lane >> 2) & 3);
+    const bool inside = px >= cam.rx0 && px < cam.rx1 && py >= cam.ry0 && py < cam.ry1;
+    const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
     const size_t HW = (size_t)cam.W * cam.H;
     float T = 1.f, g0 = 0.f, g1 = 0.f, g2c = 0.f;
     uint32_t last = 0;
-    if (c.inside) {
-        T = final_T[c.pix];
-        last = min(last_idx[c.pix], c.end - c.start);
-        g0 = dL_dimage[c.pix]; g1 = dL_dimage[HW + c.pix]; g2c = dL_dimage[2 * HW + c.pix];
+    if (inside) {
+        const uint32_t pix = (uint32_t)(py - cam.ry0) * (uint32_t)cam.W + (uint32_t)(px - cam.rx0);
+        T = final_T[pix];
+        last = min(last_idx[pix], end - start);
+        g0 = dL_dimage[pix]; g1 = dL_dimage[HW + pix]; g2c = dL_dimage[2 * HW + pix];
     }
     float Sfx = T * (bg0 * g0 + bg1 * g1 + bg2 * g2c);
     uint32_t wmax = last;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, d, 64));
     if (lane == 0) sMax[wave] = wmax;     // the last list position any pixel of the quadrant blended
+    if (threadIdx.x == 0) {
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        sA[kBwdBatch2D] = zero; sB[kBwdBatch2D] = make_float4(0.f, 0.f, 0.f, -1e30f);
+        sC[kBwdBatch2D] = zero; sD[kBwdBatch2D] = make_float4(0.f, 0.f, 0.f, __uint_as_float(0xffffffffu));
+    }
     __syncthreads();
     const uint32_t tile_last = __builtin_amdgcn_readfirstlane(max(max(sMax[0], sMax[1]), max(sMax[2], sMax[3])));
-    const int tile_x = c.tix, tile_y = c.tiy;
     // Pairs that no pixel of the tile blended are never staged; the gather adds up the records of all pairs, so theirs are
     // written as zeros: those behind the last blended splat here, the others where the search below comes to them (every
     // pair is in exactly one tile's list: each record is written exactly once per call, and no fill of the whole array is
@@ -564,13 +622,14 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
             dst[0] = zero; dst[1] = zero; dst[2] = zero; dst[3] = zero;
         }
     };
-    for (uint32_t p = tile_last + threadIdx.x; p < c.end - c.start; p += 256u) write_zeros(vals[c.start + p]);
+    for (uint32_t p = tile_last + threadIdx.x; p < end - start; p += 256u) write_zeros(vals[start + p]);
     if (tile_last == 0) return;
-    float* const sAccW = sAcc[wave];
     float* const sVw = sV[wave];
+    float* const sSumW = sSum[wave];
+    uint16_t* const list_w = sList[wave];
     // In a reduction lane l takes visit slot l / 16 and the four pixels held by the wavefront's lanes 4 pg .. 4 pg + 3,
-    // pg = l % 16: half a pixel row of the quadrant. Their dL/dcolour come from those lanes, through LDS.
-    const int pg = lane & 15;
+    // pg = l % 16: a row of a 4x4 cell. Their dL/dcolour come from those lanes, through LDS.
+    const int pg = lane & 15, cell = pg >> 2, quad_lane = lane & 3;
     float4 G0, G1, G2;
     {
         sVw[lane] = g0; sVw[64 + lane] = g1; sVw[128 + lane] = g2c;
@@ -581,29 +640,24 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
         __builtin_amdgcn_wave_barrier();
     }
     // centre of the first of the four pixels; the others follow on the same row
-    const float rx = (float)(c.tx0 + (wave & 1) * 8 + 4 * (pg & 1)) + 0.5f, ry = (float)(c.ty0 + (wave >> 1) * 8 + (pg >> 1)) + 0.5f;
+    const float rx = (float)(tx0 + (wave & 1) * 8 + (cell & 1) * 4) + 0.5f, ry = (float)(ty0 + (wave >> 1) * 8 + (cell >> 1) * 4 + quad_lane) + 0.5f;
     const float* const rd_row = sVw + kRows2D * 64 * (lane >> 4) + 4 * pg;
     float* const wr_row = sVw + lane;
-    const bool bit1 = (lane & 2) != 0;
-    const int acc_slot = ((lane & 1) ? 8 : 0) + ((lane >> 1) & 7);     // see row_sum8: odd lanes take the second eight sums
-    int nslot = 0;                 // visits staged since the last reduction, and their surfels' positions in the batch,
-    uint32_t slot_pos = 0u;        // a byte each, the newest lowest: one instruction a visit
-    static_assert(kSlots2D == 4 && kBwdBatch2D <= 256, "four positions of eight bits");
-    const int slot_shift = 24 - 8 * (lane >> 4);      // of this lane's slot once four are staged
-    // Reduces the staged rows and stores the sums of the first `count` visit slots in their surfels' accumulators.
-    auto reduce_slots = [&](int count) {
+    float* const wr_sum = sSumW + 64 * (lane >> 4) + 16 * cell + 2 * quad_lane;
+    const uint16_t* const rd_list = list_w + cell * kBwdBatch2D + (lane >> 4);
+    // Reduces the staged rows, visits at .. at + 3 of the lists: the sums of slot s go to place i + s of the run.
+    auto reduce_slots = [&](int at, int i) {
         __builtin_amdgcn_wave_barrier();
-        const int j = (int)((slot_pos << (8 * (kSlots2D - count)) >> slot_shift) & 255u);
         const float4 d0 = *reinterpret_cast<const float4*>(rd_row);
         const float4 d1 = *reinterpret_cast<const float4*>(rd_row + 64);
         const float4 d2 = *reinterpret_cast<const float4*>(rd_row + 128);
         const float4 w = *reinterpret_cast<const float4*>(rd_row + 192);
         const float4 e = *reinterpret_cast<const float4*>(rd_row + 256);
-        const float4 cc = S.c[j];
+        const float2 centre = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(sC) + rd_list[at]);
         __builtin_amdgcn_wave_barrier();
         // each pixel's own offset (exact near the centre): dx of the first pixel times the sum, plus a ramp over the four,
         // cancels where the weight sits beside the centre
-        const float dx0 = rx - cc.x, dx1 = rx + 1.f - cc.x, dx2 = rx + 2.f - cc.x, dx3 = rx + 3.f - cc.x, dy = ry - cc.y;
+        const float dx0 = rx - centre.x, dx1 = rx + 1.f - centre.x, dx2 = rx + 2.f - centre.x, dx3 = rx + 3.f - centre.x, dy = ry - centre.y;
         const auto sum4 = [](const float4& v) { return (v.x + v.y) + (v.z + v.w); };
         const auto sum4x = [&](const float4& v) { return (v.x * dx0 + v.y * dx1) + (v.z * dx2 + v.w * dx3); };
         const float m0 = sum4(d0), m1 = sum4(d1), m2 = sum4(d2);
@@ -614,13 +668,14 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
         const float vb[8] = {dy * m2,
                              sumw(G0), sumw(G1), sumw(G2),
                              sum4(e), sum4x(l), dy * sum4(l), 0.f};
-        const float pa = row_sum8(va, bit1);
-        const float pb = row_sum8(vb, bit1);
-        // even lanes of a row keep the first eight sums, odd lanes (their copies) take the second eight
-        if (acc_slot < kAccStride2D && (lane >> 4) < count) sAccW[kAccStride2D * j + acc_slot] = (lane & 1) ? pb : pa;
+        float2 pa, pb;
+        quad_sum8(va, quad_lane, pa);
+        quad_sum8(vb, quad_lane, pb);
+        *reinterpret_cast<float2*>(wr_sum + 64 * i) = pa;
+        *reinterpret_cast<float2*>(wr_sum + 64 * i + 8) = pb;
     };
-    // The list is searched from its end for the entries that some quadrant blended, a chunk of 256 positions at a time;
-    // blend_words has a byte per quadrant, bit 0: some pixel of it blended the splat. The forward pass writes the words of
+    // The list is searched from its end for the entries that some cell blended, a chunk of 256 positions at a time;
+    // blend_words has four bits per quadrant, one per cell. The forward pass writes the words of
     // every position that its tile staged, and no pixel's last index lies behind those, so no word of an earlier call is
     // read here. What was found and not staged yet: sFound[head ..], nfound entries, positions falling. They are kept in
     // 16 bits, so that four workgroups still fit a compute unit; the upper 16 are `page`, and a chunk of another page
@@ -630,14 +685,14 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
     const auto ask_chunk = [&] {
         const uint32_t p = ((todo - 1u) & ~(kBwdChunk2D - 1u)) + (kBwdChunk2D - 1u) - threadIdx.x;
         chunk_bits = 0u;
-        if (todo > 0u && p < todo) { chunk_bits = blend_words[c.start + p]; chunk_id = vals[c.start + p]; }
+        if (todo > 0u && p < todo) { chunk_bits = blend_words[start + p]; chunk_id = vals[start + p]; }
     };
     ask_chunk();
     for (;;) {
         while (nfound < (uint32_t)kBwdBatch2D && todo > 0u && (nfound == 0u || (todo - 1u) >> 16 == page)) {
             const uint32_t chunk = (todo - 1u) & ~(kBwdChunk2D - 1u);
             const uint32_t p = chunk + (kBwdChunk2D - 1u) - threadIdx.x;
-            const bool blended = (chunk_bits & 0x01010101u) != 0u;
+            const bool blended = chunk_bits != 0u;
             const unsigned long long m = __ballot(blended);
             if (lane == 0) sCount[wave] = (uint32_t)__popcll(m);
             const uint16_t left = threadIdx.x < nfound ? sFound[head + threadIdx.x] : (uint16_t)0;
@@ -662,86 +717,129 @@ __global__ __launch_bounds__(256, 4) void k_composite2d_bwd(CamDev cam, const ui
         if (nfound == 0u) break;      // (then nothing is left to search either)
         const int cnt = (int)min((uint32_t)kBwdBatch2D, nfound);
         // stage the batch, one entry per lane of the first wavefront, list positions rising with the lane
-        uint32_t id = 0u, bits = 0u;
-        float4 q0, q1, q2, q3;
-        q0 = q1 = q2 = q3 = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t id = 0u;
+        float opacity = 0.f, radius_bits = 0.f;
         if ((int)threadIdx.x < cnt) {
             const uint32_t p = (page << 16) | sFound[head + (uint32_t)cnt - 1u - threadIdx.x];
-            id = vals[c.start + p];
-            bits = blend_words[c.start + p];
+            id = vals[start + p];
+            sCells[threadIdx.x] = blend_words[start + p];
             const float4* rec = reinterpret_cast<const float4*>(packed + id);
-            q0 = rec[0]; q1 = rec[1]; q2 = rec[2]; q3 = rec[3];
-            S.a[threadIdx.x] = q0;
-            S.b[threadIdx.x] = make_float4(q1.x, q1.y, q1.z, __log2f(q1.w));
-            S.c[threadIdx.x] = q2;
-            S.d[threadIdx.x] = make_float4(q3.x, q3.z, q3.w, __uint_as_float(p + 1u));
+            const float4 q0 = rec[0], q1 = rec[1], q2 = rec[2], q3 = rec[3];
+            opacity = q1.w; radius_bits = q3.y;
+            sA[threadIdx.x] = q0;
+            sB[threadIdx.x] = make_float4(q1.x, q1.y, q1.z, __log2f(q1.w));
+            sC[threadIdx.x] = q2;
+            sD[threadIdx.x] = make_float4(q3.x, q3.z, q3.w, __uint_as_float(p + 1u));
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const unsigned long long m = __ballot(((bits >> (8 * q)) & 1u) != 0u);
-            if (threadIdx.x == 0) S.mask[q][0] = m;
-        }
-#pragma unroll
-        for (int k = 0; k < 4 * kAccStride2D * kBwdBatch2D / 256; ++k) (&sAcc[0][0])[k * 256 + threadIdx.x] = 0.f;
         head += (uint32_t)cnt;
         nfound -= (uint32_t)cnt;
         __syncthreads();
-        unsigned long long m = uniform_u64(S.mask[wave][0]);
-        while (m) {
-            const int j = take_highest(m);
-            const float4 a = S.a[j], b = S.b[j], cc = S.c[j], dd = S.d[j];
-            const uint32_t pos = __float_as_uint(dd.w);      // list position + 1
-            const float blue = dd.x;
-            Pair2D E;
-            eval_pair2d(a, b, cc, dd, fx, fy, E);
-            const bool disk = E.e1 > E.e2;                         // which part of the max is active (false for NaN)
-            const float ex = disk ? E.e1 : E.e2;
-            const float araw = __builtin_amdgcn_exp2f(b.w + ex);   // o G^
-            const float alpha = fminf(kAlphaMax, araw);
-            const bool hit = (pos <= last) && (E.p2 != 0.f) && (alpha >= kAlphaMin);
-            const float ioma = __builtin_amdgcn_rcpf(1.f - alpha);
-            const float Tk = T * ioma;
-            const float w = hit ? alpha * Tk : 0.f;
-            const float cg = cc.z * g0 + cc.w * g1 + blue * g2c;
-            const float dL_dalpha = Tk * cg - Sfx * ioma;
-            const float da = (hit && araw < kAlphaMax) ? dL_dalpha : 0.f;     // zero where alpha was clamped
-            T = hit ? Tk : T;
-            Sfx += w * cg;
-            // G^ by an exponential of its own: the opacity's gradient is the sum of G^ dL/dalpha, and o G^ over o
-            // carries the rounding of log2(o). The sums below leave o out; the record multiplies them by it.
-            const float d_o = __builtin_amdgcn_exp2f(ex) * da;       // zero unless hit
-            // disk part: dL/du = -u o G dL/dalpha; low-pass part (the sums of the reduction): dL/dmx = 2 dx o G2 dL/dalpha.
-            // u, v, 1/p2 are finite wherever the disk part is the active one; elsewhere they are replaced by 0
-            // so that no 0 * inf reaches the sums.
-            const float us = disk ? E.u : 0.f, vs = disk ? E.v : 0.f, ips = disk ? E.ip2 : 0.f;
-            const float du = -us * d_o, dv = -vs * d_o;
-            float* const rows = wr_row + kRows2D * 64 * nslot;
-            rows[0] = du * ips;
-            rows[64] = dv * ips;
-            rows[128] = -(du * us + dv * vs) * ips;
-            rows[192] = disk ? -w : w;      // the sign marks the disk part
-            rows[256] = d_o;
-            slot_pos = (slot_pos << 8) | (uint32_t)j;
-            if (++nslot == kSlots2D) { reduce_slots(kSlots2D); nslot = 0; }
+        // the lists of the quadrant's cells, last splats first
+        constexpr uint32_t kNone = (uint32_t)kBwdBatch2D * 16u * 0x10001u;
+        *reinterpret_cast<uint2*>(list_w + 4 * lane) = make_uint2(kNone, kNone);
+        const uint32_t cells = lane < cnt ? ((uint32_t)sCells[lane] >> (4 * wave)) & 15u : 0u;
+        int n = 0;
+        uint32_t places = 0u;             // of this lane's splat in the lists
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const unsigned long long b = __ballot((cells & (1u << g)) != 0u);
+            const int c = __builtin_popcountll(b);
+            const int place = c - 1 - (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+            const bool on = (cells & (1u << g)) != 0u;
+            if (on) list_w[g * kBwdBatch2D + place] = (uint16_t)(lane * 16);
+            places |= (on ? (uint32_t)place : 255u) << (8 * g);
+            n = max(n, c);
         }
-        if (nslot) { reduce_slots(nslot); nslot = 0; }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // of the upper and of the lower two cells: two terms each, so that the sum does not depend on which run of visits has which
+        float4 acc[2][4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[0][k] = acc[1][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        const uint16_t* const my_list = list_w + group * kBwdBatch2D;
+        for (int first = 0; first < n; first += kBwdVisits2D) {
+            const int count = min(kBwdVisits2D, n - first);
+            const auto visit = [&](uint32_t off, float* rows) {
+                const auto from = [off](const float4* p) { return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p) + off); };
+                const float4 a = from(sA), b = from(sB), cc = from(sC), dd = from(sD);
+                const uint32_t pos = __float_as_uint(dd.w);      // list position + 1
+                const float blue = dd.x;
+                Pair2D E;
+                eval_pair2d(a, b, cc, dd, fx, fy, E);
+                const bool disk = E.e1 > E.e2;                         // which part of the max is active (false for NaN)
+                const float ex = disk ? E.e1 : E.e2;
+                const float araw = __builtin_amdgcn_exp2f(b.w + ex);   // o G^
+                const float alpha = fminf(kAlphaMax, araw);
+                const bool hit = (pos <= last) && (E.p2 != 0.f) && (alpha >= kAlphaMin);
+                const float ioma = __builtin_amdgcn_rcpf(1.f - alpha);
+                const float Tk = T * ioma;
+                const float w = hit ? alpha * Tk : 0.f;
+                const float cg = cc.z * g0 + cc.w * g1 + blue * g2c;
+                const float dL_dalpha = Tk * cg - Sfx * ioma;
+                const float da = (hit && araw < kAlphaMax) ? dL_dalpha : 0.f;     // zero where alpha was clamped
+                T = hit ? Tk : T;
+                Sfx += w * cg;
+                // G^ by an exponential of its own: the opacity's gradient is the sum of G^ dL/dalpha, and o G^ over o
+                // carries the rounding of log2(o). The sums below leave o out; the record multiplies them by it.
+                const float d_o = __builtin_amdgcn_exp2f(ex) * da;       // zero unless hit
+                // disk part: dL/du = -u o G dL/dalpha; low-pass part (the sums of the reduction): dL/dmx = 2 dx o G2 dL/dalpha.
+                // u, v, 1/p2 are finite wherever the disk part is the active one; elsewhere they are replaced by 0
+                // so that no 0 * inf reaches the sums.
+                const float us = disk ? E.u : 0.f, vs = disk ? E.v : 0.f, ips = disk ? E.ip2 : 0.f;
+                const float du = -us * d_o, dv = -vs * d_o;
+                rows[0] = du * ips;
+                rows[64] = dv * ips;
+                rows[128] = -(du * us + dv * vs) * ips;
+                rows[192] = disk ? -w : w;      // the sign marks the disk part
+                rows[256] = d_o;
+            };
+            const uint16_t* const run = my_list + first;
+            for (int i = 0; i < count; i += kSlots2D) {      // (behind the lists' ends: a record that reaches nothing)
+                const uint2 o = *reinterpret_cast<const uint2*>(run + i);
+                visit(o.x & 0xffffu, wr_row);
+                if (i + 1 < count) visit(o.x >> 16, wr_row + kRows2D * 64);
+                if (i + 2 < count) visit(o.y & 0xffffu, wr_row + 2 * kRows2D * 64);
+                if (i + 3 < count) visit(o.y >> 16, wr_row + 3 * kRows2D * 64);
+                reduce_slots(first + i, i);      // (what the rows of the slots behind the last visit hold goes to places that no splat has)
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const uint32_t at = ((places >> (8 * g)) & 255u) - (uint32_t)first;
+                if (at < (uint32_t)kBwdVisits2D) {
+                    const float4* v = reinterpret_cast<const float4*>(sSumW + 64 * at + 16 * g);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        float4& sum = acc[g >> 1][k];
+                        sum.x += v[k].x; sum.y += v[k].y; sum.z += v[k].z; sum.w += v[k].w;
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            reinterpret_cast<float4*>(sVw)[k * kBwdBatch2D + lane] = make_float4(acc[0][k].x + acc[1][k].x, acc[0][k].y + acc[1][k].y, acc[0][k].z + acc[1][k].z, acc[0][k].w + acc[1][k].w);
         __syncthreads();
         if ((int)threadIdx.x < cnt) {
+            const float4 q0 = sA[threadIdx.x], q1 = sB[threadIdx.x], q2 = sC[threadIdx.x];
+            const float2 q3 = make_float2(sD[threadIdx.x].y, sD[threadIdx.x].z);
             int x0, y0, x1, y1;
-            tile_rect(cam, q2.x, q2.y, __float_as_int(q3.y), x0, y0, x1, y1);
+            tile_rect(cam, q2.x, q2.y, __float_as_int(radius_bits), x0, y0, x1, y1);
             const uint32_t u = slot_base[id] + (uint32_t)((tile_y - y0) * (x1 - x0) + (tile_x - x0));
             if (u < cap && tile_x >= x0 && tile_x < x1 && tile_y >= y0 && tile_y < y1) {
                 float acc[15];
 #pragma unroll
                 for (int k = 0; k < 15; ++k) {
-                    const int e = kAccStride2D * (int)threadIdx.x + k;
-                    acc[k] = (sAcc[0][e] + sAcc[1][e]) + (sAcc[2][e] + sAcc[3][e]);
+                    const int e = 4 * ((k >> 2) * kBwdBatch2D + (int)threadIdx.x) + (k & 3);
+                    acc[k] = (sV[0][e] + sV[1][e]) + (sV[2][e] + sV[3][e]);
                 }
-                const float o = q1.w;
+                const float o = opacity;
                 const float s0[3] = {o * acc[0], o * acc[1], o * acc[2]};
                 const float sx[3] = {o * acc[3], o * acc[4], o * acc[5]};
                 const float sy[3] = {o * acc[6], o * acc[7], o * acc[8]};
-                const float t0[3] = {q0.x, q0.y, q3.z}, t1[3] = {q0.z, q0.w, q3.w}, t2[3] = {q1.x, q1.y, q1.z};
+                const float t0[3] = {q0.x, q0.y, q3.x}, t1[3] = {q0.z, q0.w, q3.y}, t2[3] = {q1.x, q1.y, q1.z};
                 const float mx = q2.x, my = q2.y;
                 float dhu[3], dhv[3], ex[3];
                 // sum dL/dh_u = T2 x Sy - T1' x S0
@@ -943,7 +1041,7 @@ hipError_t launch_composite2d_fwd(const CamDev& cam, const Layout& L, char* ws, 
     hipLaunchKernelGGL(k_composite2d_fwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                        reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
                        reinterpret_cast<const uint32_t*>(ws + L.off_vals),
-                       reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<uint32_t*>(ws + L.off_reach),
+                       reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<uint16_t*>(ws + L.off_reach),
                        bg[0], bg[1], bg[2], image, final_T, last_idx);
     return hipGetLastError();
 }
@@ -958,7 +1056,7 @@ hipError_t launch_composite2d_bwd(const CamDev& cam, const Layout& L, char* ws, 
         hipLaunchKernelGGL(k_composite2d_bwd, dim3((unsigned)(cam.TX * cam.TY)), dim3(256), 0, s, cam,
                            reinterpret_cast<const uint32_t*>(ws + L.off_ranges), reinterpret_cast<const uint32_t*>(ws + L.off_tile_order),
                        reinterpret_cast<const uint32_t*>(ws + L.off_vals),
-                           reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<const uint32_t*>(ws + L.off_reach),
+                           reinterpret_cast<const Packed2D*>(ws + L.off_packed), reinterpret_cast<const uint16_t*>(ws + L.off_reach),
                            reinterpret_cast<const uint32_t*>(ws + L.off_slot_base),
                            bg[0], bg[1], bg[2], final_T, last_idx, dL_dimage, L.cap, partial);
     }

@@ -629,30 +629,24 @@ __global__ __launch_bounds__(256) void k_gather_splat_grads(int n, const uint32_
     gather_wave<3, 9, true, kChunkBits>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplatGrad{rec, order});
 }
 
-// also closes the backward call's epoch: the next call stamps its records with a new number
-__global__ __launch_bounds__(256) void k_gather_fixup(int n, uint32_t* __restrict__ status, const uint32_t* __restrict__ order,
-                                                      uint32_t cap, int chunk_bits, const float* __restrict__ carry, float4* __restrict__ rec)
-{
-    gather_fixup<9>(blockIdx.x * 256u + threadIdx.x, status, cap, chunk_bits, carry, StoreSplatGrad{rec, order});
-    if (blockIdx.x == 0 && threadIdx.x == 0) {      // 64-bit count of backward calls on this workspace
-        const uint32_t lo = status[kStEpoch] + 1u;
-        status[kStEpoch] = lo;
-        if (lo == 0u) status[kStEpoch + 1] = status[kStEpoch + 1] + 1u;
-    }
-}
-
-// records -> planes, for the points binning listed (tiles_touched > 0)
+// records -> planes, for the points binning listed (tiles_touched > 0). A point whose pairs are cut by a boundary of the gather's
+// chunks is put together here (record_from_carries), and the call's epoch is closed: a launch of its own for that took 5 us.
 __global__ __launch_bounds__(256) void k_grad_records_to_planes(int n, const uint32_t* __restrict__ tiles_touched,
-                                                                const float4* __restrict__ rec, SplatGradDev g2)
+                                                                const float4* __restrict__ rec, CarryFold cf, SplatGradDev g2)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n || tiles_touched[i] == 0) return;
+    if (i == 0) close_backward_epoch(cf.status);
+    if (i >= n) return;
+    const uint32_t pairs = tiles_touched[i];
+    if (pairs == 0) return;
     const size_t N = (size_t)n;
     const float4 a = rec[(size_t)3 * i], b = rec[(size_t)3 * i + 1], c = rec[(size_t)3 * i + 2];
-    g2.mean2d[i] = a.x; g2.mean2d[N + i] = a.y;
-    g2.conic[i] = a.z; g2.conic[N + i] = a.w; g2.conic[2 * N + i] = b.x;
-    g2.opacity[i] = b.y;
-    g2.color[i] = b.z; g2.color[N + i] = b.w; g2.color[2 * N + i] = c.x;
+    float v[9] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x};
+    (void)record_from_carries<9>(cf, cf.slot_base[i], pairs, v);
+    g2.mean2d[i] = v[0]; g2.mean2d[N + i] = v[1];
+    g2.conic[i] = v[2]; g2.conic[N + i] = v[3]; g2.conic[2 * N + i] = v[4];
+    g2.opacity[i] = v[5];
+    g2.color[i] = v[6]; g2.color[N + i] = v[7]; g2.color[2 * N + i] = v[8];
 }
 
 // Measurement aid: the forward walk with counters instead of colours. counters[0] += list entries examined per pixel
@@ -759,11 +753,9 @@ hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, in
         else
             hipLaunchKernelGGL(k_gather_splat_grads<8>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank,
                            partial, L.cap, carry, rec);
-        if (g2.mean2d != nullptr) {
-            hipLaunchKernelGGL(k_gather_fixup, dim3((nwave + 255) / 256), dim3(256), 0, s, n, status, order, L.cap, bits, carry, rec);
+        if (g2.mean2d != nullptr)
             hipLaunchKernelGGL(k_grad_records_to_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
-                               reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, g2);
-        }
+                               reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, carry_fold(L, ws), g2);
         // else the caller goes on from the records with launch_preprocess_bwd_records, whose kernel puts the records cut
         // by wavefront boundaries together itself and closes the epoch (carry_fold below): one launch fewer
     }

@@ -7,7 +7,7 @@
 // point has at least one pair), and runs a segmented inclusive scan over the 64 records with DPP row shifts and row
 // broadcasts (owners are sorted, so "same owner as the lane d below" is the whole segment test). A segment that
 // lies inside the wavefront's chunk is stored directly. Segments cut by a wavefront boundary leave a left and /
-// or right piece in a small carry array, and a second kernel - one thread per boundary at which a segment starts -
+// or right piece in a small carry array, and the kernel that reads the points' records
 // adds the pieces in order. No atomics, no zero-filled outputs, same result on every run.
 #pragma once
 #include "pbdr_internal.h"
@@ -190,40 +190,10 @@ __device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* _
     }
 }
 
-// One thread per wavefront boundary at which a cut segment starts: right piece of wavefront w, then the left pieces
-// of the following wavefronts up to and including the first that is not a through piece.
-template <int kVals, class Store>
-__device__ __forceinline__ void gather_fixup(uint32_t w, const uint32_t* __restrict__ status, uint32_t cap, int chunk_bits,
-                                             const float* __restrict__ carry, Store store)
-{
-    const uint32_t Pc = min(status[kStNumDup], cap);
-    const uint32_t nw = (Pc + (1u << chunk_bits) - 1u) >> chunk_bits;
-    if (w >= nw) return;
-    const float* c = carry + (size_t)w * kCarryFloats;
-    const uint32_t* meta = reinterpret_cast<const uint32_t*>(c + 32);
-    if (!(meta[0] & kCarryHasRight)) return;
-    const uint32_t rank = meta[2];
-    float v[kVals];
-#pragma unroll
-    for (int k = 0; k < kVals; ++k) v[k] = c[16 + k];
-    for (uint32_t w2 = w + 1; w2 < nw; ++w2) {
-        const float* c2 = carry + (size_t)w2 * kCarryFloats;
-        const uint32_t* m2 = reinterpret_cast<const uint32_t*>(c2 + 32);
-        const uint32_t f2 = m2[0];
-        if (!(f2 & kCarryHasLeft) || m2[1] != rank) break;
-#pragma unroll
-        for (int k = 0; k < kVals; ++k) v[k] += c2[k];
-        if (!(f2 & kCarryLeftThrough)) break;
-    }
-    store(rank, v);
-}
-
-// What k_gather_fixup does, from the side of the point: used by the kernels that read a point's record right after the
-// gather, so that the fixup launch (a few microseconds for ten thousand additions) can be left out. at, count: the
+// For the kernels that read a point's record after the gather. at, count: the
 // point's first pair and its number of pairs. Returns false if all of its pairs lie in one wavefront's chunk (the gather
 // stored the record itself); else v = the right piece of the wavefront its first pair lies in, plus the left pieces of
-// the following wavefronts up to and including the first that is not a through piece - the pieces and the order of
-// gather_fixup, so the sum is bit for bit the record that kernel would store.
+// the following wavefronts up to and including the first that is not a through piece.
 template <int kVals>
 __device__ __forceinline__ bool record_from_carries(const CarryFold& cf, uint32_t at, uint32_t count, float (&v)[kVals])
 {
@@ -248,7 +218,7 @@ __device__ __forceinline__ bool record_from_carries(const CarryFold& cf, uint32_
     return true;
 }
 
-// the count of backward calls on this workspace goes up by one (k_gather_fixup does it when it runs)
+// the count of backward calls on this workspace goes up by one: the next call stamps its records with a new number
 __device__ __forceinline__ void close_backward_epoch(uint32_t* status)
 {
     const uint32_t lo = status[kStEpoch] + 1u;

@@ -187,10 +187,10 @@ hipError_t launch_preprocess(const SceneDev& sc, const CamDev& cam, const Splats
                              int group_size, hipStream_t s);
 hipError_t launch_group_bounds(const SceneDev& sc, int group_size, float* bounds, hipStream_t s);
 hipError_t launch_group_cull(const CamDev& cam, int n_groups, const float* bounds, uint8_t* keep, hipStream_t s);
-// For the kernels that read a point's gradient record straight after the gather and finish the records cut by
-// wavefront boundaries themselves (pair_reduce.h: record_from_carries), in place of the k_gather_fixup launch.
+// For the kernels that read a point's gradient record after the gather and finish the records cut by chunk boundaries
+// (pair_reduce.h: record_from_carries).
 struct CarryFold {
-    const float* carry;             // null: the records are complete (k_gather_fixup has run)
+    const float* carry;             // null: the gradients come from planes
     const uint32_t* slot_base;      // [n] first pair of each listed point
     uint32_t* status;
     uint32_t cap;

@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(SceneDev sc, CamDev cam,
 {
     const int n = sc.n;
     const int i = blockIdx.x * 256 + threadIdx.x;
-    // (with cf.carry this launch stands in for k_gather_fixup: it also closes the backward call's epoch)
+    // (with cf.carry this launch also closes the backward call's epoch)
     if (kFromRecords && cf.carry != nullptr && i == 0) close_backward_epoch(cf.status);
     if (i >= n) return;
     const size_t N = (size_t)n;

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void k_preprocess2d_bwd(Scene2DDev sc, CamDev 
 #pragma unroll
         for (int k = 0; k < 15; ++k) gs[k] = v[k];
         // a point whose pairs are cut by a wavefront boundary of the gather: its record is still in pieces (this launch
-        // stands in for k_gather2d_fixup, see pair_reduce.h)
+        // puts it together, see pair_reduce.h)
         if (cf.carry != nullptr) (void)record_from_carries<15>(cf, cf.slot_base[i], (uint32_t)radius[i], gs);
     } else {
 #pragma unroll
@@ -891,20 +891,17 @@ __global__ __launch_bounds__(256) void k_gather2d(int n, const uint32_t* __restr
     gather_wave<4, 15, false, kChunkBits>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplat2DGrad{rec, order});
 }
 
-__global__ __launch_bounds__(256) void k_gather2d_fixup(int n, const uint32_t* __restrict__ status, const uint32_t* __restrict__ order,
-                                                        uint32_t cap, int chunk_bits, const float* __restrict__ carry, float4* __restrict__ rec)
-{
-    gather_fixup<15>(blockIdx.x * 256u + threadIdx.x, status, cap, chunk_bits, carry, StoreSplat2DGrad{rec, order});
-}
-
 __global__ __launch_bounds__(256) void k_grad_records_to_planes2d(int n, const uint32_t* __restrict__ tiles_touched,
-                                                                  const float4* __restrict__ rec, Splat2DGradDev g2)
+                                                                  const float4* __restrict__ rec, CarryFold cf, Splat2DGradDev g2)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n || tiles_touched[i] == 0) return;
+    if (i >= n) return;
+    const uint32_t pairs = tiles_touched[i];
+    if (pairs == 0) return;
     const size_t N = (size_t)n;
     const float4 a = rec[(size_t)4 * i], b = rec[(size_t)4 * i + 1], c = rec[(size_t)4 * i + 2], d = rec[(size_t)4 * i + 3];
-    const float v[15] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w, d.x, d.y, d.z};
+    float v[15] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w, d.x, d.y, d.z};
+    (void)record_from_carries<15>(cf, cf.slot_base[i], pairs, v);      // (see the 3D variant)
 #pragma unroll
     for (int k = 0; k < 9; ++k) g2.T[(size_t)k * N + i] = v[k];
     g2.mean2d[i] = v[9]; g2.mean2d[N + i] = v[10];
@@ -1075,11 +1072,9 @@ hipError_t launch_composite2d_bwd(const CamDev& cam, const Layout& L, char* ws, 
         else
             hipLaunchKernelGGL(k_gather2d<8>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank, partial,
                            L.cap, carry, rec);
-        if (g2.mean2d != nullptr) {      // else the caller goes on from the records, pieces included (launch_preprocess2d_bwd_records)
-            hipLaunchKernelGGL(k_gather2d_fixup, dim3((nwave + 255) / 256), dim3(256), 0, s, n, status, order, L.cap, bits, carry, rec);
+        if (g2.mean2d != nullptr)      // else the caller goes on from the records, pieces included (launch_preprocess2d_bwd_records)
             hipLaunchKernelGGL(k_grad_records_to_planes2d, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
-                               reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, g2);
-        }
+                               reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, carry_fold(L, ws), g2);
     }
     return hipGetLastError();
 }

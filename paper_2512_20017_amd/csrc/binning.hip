@@ -122,13 +122,13 @@ __global__ __launch_bounds__(kThreads) void k_tile_count(BinInput in, CamDev cam
     __shared__ uint32_t sCount[kTableCells / 2];      // two to a word: a block has at most 256 pairs on a tile
     __shared__ uint2 sSum[kThreads / 64];
     __shared__ uint16_t sList[kTableCells];               // the cells of the table that are not zero
-    __shared__ uint32_t sCells, sListed;
+    __shared__ uint32_t sListed;
     const uint32_t blk = blockIdx.x;
     const uint2 mine = A.blk[blk];
     if (mine.x == 0u && blk + 1u != nb) return;
     const int i = (int)(blk * 256u + threadIdx.x);
     const PointExtent extent = point_extent(in, i);
-    if (threadIdx.x == 0) { sCells = 0u; sListed = 0u; }
+    if (threadIdx.x == 0) sListed = 0u;
     const uint2 before = blocks_before<kThreads>(A, blk, sSum);
     PointPairs P = point_pairs(cam, extent);
     if (blk + 1u == nb && threadIdx.x == 0) {
@@ -156,46 +156,45 @@ __global__ __launch_bounds__(kThreads) void k_tile_count(BinInput in, CamDev cam
     const uint32_t by = 0xffffu - __builtin_amdgcn_readfirstlane(max(max(q0.y, q1.y), max(q2.y, q3.y)));
     const uint32_t bw = __builtin_amdgcn_readfirstlane(max(max(q0.z, q1.z), max(q2.z, q3.z))) - bx;
     const uint32_t bh = __builtin_amdgcn_readfirstlane(max(max(q0.w, q1.w), max(q2.w, q3.w))) - by;
-    const uint32_t rows = kTableCells / bw;                       // of a band
-    for (uint32_t y0 = 0; y0 < bh; y0 += rows) {
-        const uint32_t cells = min(rows, bh - y0) * bw;
-        for (uint32_t c = threadIdx.x; 2u * c < cells; c += (uint32_t)kThreads) sCount[c] = 0u;
-        __syncthreads();
-        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) {
-            if (y - by - y0 < rows) {
-                const uint32_t c = (y - by - y0) * bw + x - bx;
-                atomicAdd(&sCount[c >> 1], 1u << ((c & 1u) << 4));
-            }
-        });
-        __syncthreads();
-        // (the cells are listed first: an atomic add of a cell as the search comes to it would be a round trip to memory each)
-        const auto count_of = [&](uint32_t c) { return (sCount[c >> 1] >> ((c & 1u) << 4)) & 0xffffu; };
-        for (uint32_t c = threadIdx.x; c < cells; c += (uint32_t)kThreads)
-            if (count_of(c)) sList[atomicAdd(&sListed, 1u)] = (uint16_t)c;
-        __syncthreads();
-        const uint32_t listed = __builtin_amdgcn_readfirstlane(sListed), out = before.y + __builtin_amdgcn_readfirstlane(sCells);
-        for (uint32_t j0 = 0; j0 < listed; j0 += 4u * (uint32_t)kThreads) {      // four adds in flight
-            uint32_t at[4], xy[4];
+    if (bw * bh > kTableCells) {
+        uint32_t* const rank = reinterpret_cast<uint32_t*>(A.cells) + before.y;      // (its pairs' slots hold two words each)
+        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) { return atomicAdd(&A.tile_count[y * (uint32_t)cam.TX + x], 1u); },
+                   [&](uint32_t r, uint32_t at, uint32_t) { rank[at] = r; });
+        if (threadIdx.x == 0) A.blk_cells[blk] = make_uint4(kDirect, 0u, 0u, 0u);
+        return;
+    }
+    const uint32_t cells = bw * bh;
+    for (uint32_t c = threadIdx.x; 2u * c < cells; c += (uint32_t)kThreads) sCount[c] = 0u;
+    __syncthreads();
+    walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) {
+        const uint32_t c = (y - by) * bw + x - bx;
+        return atomicAdd(&sCount[c >> 1], 1u << ((c & 1u) << 4));
+    }, [](uint32_t, uint32_t, uint32_t) {});
+    __syncthreads();
+    // (the cells are listed first: an atomic add of a cell as the search comes to it would be a round trip to memory each)
+    const auto count_of = [&](uint32_t c) { return (sCount[c >> 1] >> ((c & 1u) << 4)) & 0xffffu; };
+    for (uint32_t c = threadIdx.x; c < cells; c += (uint32_t)kThreads)
+        if (count_of(c)) sList[atomicAdd(&sListed, 1u)] = (uint16_t)c;
+    __syncthreads();
+    const uint32_t listed = __builtin_amdgcn_readfirstlane(sListed);
+    for (uint32_t j0 = 0; j0 < listed; j0 += 4u * (uint32_t)kThreads) {      // four adds in flight
+        uint32_t at[4], xy[4];
 #pragma unroll
-            for (uint32_t k = 0; k < 4u; ++k) {
-                const uint32_t j = j0 + k * (uint32_t)kThreads + threadIdx.x;
-                if (j < listed) {
-                    const uint32_t c = sList[j], row = c / bw, x = bx + c - row * bw, y = by + y0 + row;
-                    xy[k] = x | y << 16;
-                    at[k] = atomicAdd(&A.tile_count[y * (uint32_t)cam.TX + x], count_of(c));
-                }
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < 4u; ++k) {
-                const uint32_t j = j0 + k * (uint32_t)kThreads + threadIdx.x;
-                if (j < listed) A.cells[out + j] = make_uint2(xy[k], at[k]);      // (fewer tiles than pairs below the capacity)
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const uint32_t j = j0 + k * (uint32_t)kThreads + threadIdx.x;
+            if (j < listed) {
+                const uint32_t c = sList[j], row = c / bw, x = bx + c - row * bw, y = by + row;
+                xy[k] = x | y << 16;
+                at[k] = atomicAdd(&A.tile_count[y * (uint32_t)cam.TX + x], count_of(c));
             }
         }
-        __syncthreads();
-        if (threadIdx.x == 0) { sCells += listed; sListed = 0u; }
-        __syncthreads();      // the table is cleared for the next band
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const uint32_t j = j0 + k * (uint32_t)kThreads + threadIdx.x;
+            if (j < listed) A.cells[before.y + j] = make_uint2(xy[k], at[k]);      // (fewer tiles than pairs below the capacity)
+        }
     }
-    if (threadIdx.x == 0) A.blk_cells[blk] = make_uint4(sCells, bx | by << 16, bw | bh << 16, 0u);
+    if (threadIdx.x == 0) A.blk_cells[blk] = make_uint4(listed, bx | by << 16, bw, 0u);
 }
 
 // 3D Gaussians: the raster record (64 bytes) of a listed point (see binning_common.h for the rest of the block's work).

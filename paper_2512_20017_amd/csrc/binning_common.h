@@ -24,7 +24,7 @@ struct BinArrays {
     uint2* blk;                  // [blocks] listed points and their pairs (saturating)
     uint2* sup;                  // [blocks / kSuperBlocks] the same per kSuperBlocks blocks
     uint2* blk_at;               // [blocks] listed points and pairs in the blocks before this one (of blocks with a listed point)
-    uint4* blk_cells;            // [blocks] {tiles the block's pairs lie on, x | y << 16 of its rectangle of tiles, width | height << 16, -}
+    uint4* blk_cells;            // [blocks] {tiles the block's pairs lie on or kDirect, x | y << 16 of its rectangle of tiles, its width, -}
     uint2* cells;                // [cap] those tiles, from blk_at.y on: {x | y << 16, pairs of the blocks that counted the tile before}
     uint32_t* tile_count;        // [tiles] pairs
     const uint32_t* ranges;      // [tiles][2]
@@ -129,9 +129,10 @@ __device__ __forceinline__ uint32_t lay_out_pairs(PairLds<kThreads>& S, uint2 be
     return total;
 }
 
-// pair(x, y, place of its point in the block) for every pair of the block whose slot lies below the capacity
-template <int kThreads, class Pair>
-__device__ __forceinline__ void walk_pairs(PairLds<kThreads>& S, uint32_t total, uint32_t cap, Pair pair)
+// For every pair of the block whose slot lies below the capacity: done(pair(x, y, slot), slot, place of its point in the block).
+// Between the two lie up to four other pairs of the thread, so that what pair() fetches has time to arrive.
+template <int kThreads, class Pair, class Done>
+__device__ __forceinline__ void walk_pairs(PairLds<kThreads>& S, uint32_t total, uint32_t cap, Pair pair, Done done)
 {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     uint32_t st[4];
@@ -164,7 +165,7 @@ __device__ __forceinline__ void walk_pairs(PairLds<kThreads>& S, uint32_t total,
             if (S.at[own] + t < cap) {
                 // t / w for t, w < 256: the quotient of t + 1/2 stays 1 / (2 w) away from any whole number
                 const uint32_t row = (uint32_t)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)w));
-                pair((xy & 0xffffu) + t - row * w, (xy >> 16) + row, (uint32_t)own);
+                done(pair((xy & 0xffffu) + t - row * w, (xy >> 16) + row, S.at[own] + t), S.at[own] + t, (uint32_t)own);
             }
         }
     }
@@ -173,17 +174,32 @@ __device__ __forceinline__ void walk_pairs(PairLds<kThreads>& S, uint32_t total,
         const uint32_t own = S.wide[k], at = S.at[own], xy = S.xy[own], w = S.size[own] & 0xffffu, h = S.size[own] >> 16;
         const uint32_t dy = (uint32_t)kThreads / w, dx = (uint32_t)kThreads - dy * w;      // a step: rows and columns
         uint32_t ty = threadIdx.x / w, tx = threadIdx.x - ty * w;
-        for (uint32_t t = threadIdx.x; t < w * h && at + t < cap; t += (uint32_t)kThreads) {
-            pair((xy & 0xffffu) + tx, (xy >> 16) + ty, own);
-            tx += dx; ty += dy;
-            if (tx >= w) { tx -= w; ++ty; }
+        for (uint32_t t0 = threadIdx.x; t0 < w * h && at + t0 < cap; t0 += 4u * (uint32_t)kThreads) {
+            decltype(pair(0u, 0u, 0u)) p[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t t = t0 + q * (uint32_t)kThreads;
+                if (t < w * h && at + t < cap) p[q] = pair((xy & 0xffffu) + tx, (xy >> 16) + ty, at + t);
+                tx += dx; ty += dy;
+                if (tx >= w) { tx -= w; ++ty; }
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t t = t0 + q * (uint32_t)kThreads;
+                if (t < w * h && at + t < cap) done(p[q], at + t, own);
+            }
         }
     }
 }
 
-// A block's tiles are counted in a table of its rectangle of tiles in LDS, kTableCells at a time (bands of whole rows).
-// Points in Z-order make that rectangle small: a dozen tiles by a dozen on the benchmark's views.
-constexpr uint32_t kTableCells = 4096;      // at least one row of the widest grid
+// A block's pairs are counted per tile in a table of its rectangle of tiles in LDS. Points in Z-order make that rectangle small: a
+// dozen tiles by a dozen on the benchmark's views. The pairs of a block with a larger rectangle than the table (points beside the
+// camera, whose splats cover much of a 4K image; points in no spatial order) are counted one by one in memory instead, and the rank
+// each gets there is kept for k_pack: its tiles are many and have few pairs each, so the table would save little. (Taking the
+// rectangle in bands of the table's size walks all pairs once per band: one 4K street view of 8M points, counting 258 us and
+// packing 433; in memory 64 and 206.)
+constexpr uint32_t kTableCells = 4096;
+constexpr uint32_t kDirect = 0xffffffffu;      // blk_cells.x of such a block
 
 // Threads per block of 256 points, in k_tile_count and the packing kernels. A block's pairs may be thousands, and where the blocks
 // do not fill the chip the largest one is the launch: 1,024 threads (30k points at 1031x517, counting / packing 13.9 / 14.8 us with 256,
@@ -224,14 +240,14 @@ __device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam
     for (uint32_t k = 0; k < kPer; ++k) {
         const uint32_t j = k * (uint32_t)kThreads + threadIdx.x;
         cell[k] = make_uint2(0u, 0u);
-        if (j < box.x) cell[k] = A.cells[before.y + j];
+        if (j < box.x && box.x != kDirect) cell[k] = A.cells[before.y + j];
     }
     const auto tile_of = [&](const uint2& c) { return (c.x >> 16) * (uint32_t)cam.TX + (c.x & 0xffffu); };
     const uint32_t total = lay_out_pairs(S, before, P);
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) {
         start[k] = 0u;
-        if (k * (uint32_t)kThreads + threadIdx.x < box.x) start[k] = A.ranges[2u * tile_of(cell[k])];
+        if (k * (uint32_t)kThreads + threadIdx.x < box.x && box.x != kDirect) start[k] = A.ranges[2u * tile_of(cell[k])];
     }
     if (listed) {
         sDepth[threadIdx.x] = bits;
@@ -244,33 +260,32 @@ __device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam
         const uint32_t end = min(P.at + P.cnt, A.cap);
         for (uint32_t c = (P.at + (1u << A.chunk_bits) - 1u) >> A.chunk_bits; (uint64_t)c << A.chunk_bits < end; ++c) A.chunk_rank[c] = P.slot_rank;
     }
-    const uint32_t bx = box.y & 0xffffu, by = box.y >> 16, bw = box.z & 0xffffu, bh = box.z >> 16;
     if (box.x == 0u) return;                     // every pair lies beyond the capacity
-    const uint32_t rows = kTableCells / bw;      // of a band
-    for (uint32_t y0 = 0; y0 < bh; y0 += rows) {
-        if (y0) __syncthreads();                 // the band before has placed its pairs
-        const auto put = [&](const uint2& c, uint32_t at) {
-            const uint32_t x = c.x & 0xffffu, y = c.x >> 16;
-            if (y - by - y0 < rows) sNext[(y - by - y0) * bw + x - bx] = at + c.y;
-        };
-#pragma unroll
-        for (uint32_t k = 0; k < kPer; ++k)
-            if (k * (uint32_t)kThreads + threadIdx.x < box.x) put(cell[k], start[k]);
-        for (uint32_t j = 1024u + threadIdx.x; j < box.x; j += (uint32_t)kThreads) {
-            const uint2 c = A.cells[before.y + j];
-            put(c, A.ranges[2u * tile_of(c)]);
+    const auto place = [&](uint32_t pos, uint32_t own) {
+        if (pos < A.cap) {                       // always true for consistent inputs
+            A.keys[pos] = sDepth[own];
+            A.vals[pos] = blk * 256u + own;
         }
-        __syncthreads();
-        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t own) {
-            if (y - by - y0 < rows) {
-                const uint32_t pos = atomicAdd(&sNext[(y - by - y0) * bw + x - bx], 1u);
-                if (pos < A.cap) {               // always true for consistent inputs
-                    A.keys[pos] = sDepth[own];
-                    A.vals[pos] = blk * 256u + own;
-                }
-            }
-        });
+    };
+    if (box.x == kDirect) {
+        __syncthreads();                         // (the depths)
+        const uint32_t* const rank = reinterpret_cast<const uint32_t*>(A.cells) + before.y;
+        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t at) { return make_uint2(rank[at], A.ranges[2u * (y * (uint32_t)cam.TX + x)]); },
+                   [&](const uint2& p, uint32_t, uint32_t own) { place(p.x + p.y, own); });
+        return;
     }
+    const uint32_t bx = box.y & 0xffffu, by = box.y >> 16, bw = box.z;
+    const auto put = [&](const uint2& c, uint32_t at) { sNext[((c.x >> 16) - by) * bw + (c.x & 0xffffu) - bx] = at + c.y; };
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k)
+        if (k * (uint32_t)kThreads + threadIdx.x < box.x) put(cell[k], start[k]);
+    for (uint32_t j = 1024u + threadIdx.x; j < box.x; j += (uint32_t)kThreads) {
+        const uint2 c = A.cells[before.y + j];
+        put(c, A.ranges[2u * tile_of(c)]);
+    }
+    __syncthreads();
+    walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) { return atomicAdd(&sNext[(y - by) * bw + x - bx], 1u); },
+               [&](uint32_t pos, uint32_t, uint32_t own) { place(pos, own); });
 }
 
 }  // namespace pbdr

@@ -15,8 +15,10 @@
 // that digit came before (earlier rounds of the wavefront: LDS executes a wavefront's operations in order), and hands that to its
 // group through the LDS crossbar: equal digits keep their incoming order.
 //
-// Two passes, over the top 20 of the bits in which a list's depths differ (depths of one tile share sign and most exponent bits:
-// about 26 differ). That orders a list but for neighbours, some per thousand entries, that agree in those bits, and for equal
+// Two passes, over the top 20 bits of the depths less the list's smallest (whose range is 25 or 26 bits: a few octaves. The bits as
+// they are differ in 31 bits where a list has depths on both sides of 2.0, which every tile of a street has: 11 bits too coarse, and
+// most lists were sorted three times over, 192 us -> 134 for 7.3 M pairs at 3840x2160). That orders a list but for
+// neighbours, some per thousand entries, that agree in those bits, and for equal
 // depths, which are in order only if they came in order. Neighbours out of order are looked for after the passes and put right by
 // swapping, over the even and the odd pairs of neighbours in turn, kTiePhases sweeps at most; if that does not do (many equal
 // depths), the list is sorted again by all bits: first by point index and then, which keeps that order, by depth.
@@ -62,18 +64,18 @@ struct WgSortLds {        // the workgroup's LDS when it sorts one list together
     uint32_t cnt[kSortWaves][kListWords];                             // per wavefront and digit: entries in the wavefront's part of the list, then where its first entry of that digit goes
     uint32_t scan[kSortWaves];
     uint32_t any[2][kSortWaves];
-    uint32_t mask;
+    uint2 range[kSortWaves];
 };
 union ListSortLds { WgSortLds wg; WaveSortLds wave[kSortWaves]; };
 static_assert(sizeof(ListSortLds) <= 53 * 1024, "three workgroups per compute unit");
 
-// The passes by kBits-bit digits over the top `bits` of the bit positions in which the keys differ: their number and the shift of
-// pass p (the topmost digit may reach past the highest of them into bits all keys share; it never reaches past bit 31).
+// The passes by digits over the top `bits` bits of keys from 0 to `range`: their number and the shift of pass p (the topmost digit
+// may reach past the highest of those bits, never past bit 31).
 struct Passes { int lo, count; };
-__device__ __forceinline__ Passes list_passes(uint32_t diff, int bits, int digit)
+__device__ __forceinline__ Passes list_passes(uint32_t range, int bits, int digit)
 {
-    if (diff == 0u) return Passes{0, 0};
-    const int hi = 31 - __builtin_clz(diff), lo = max(__builtin_ctz(diff), hi + 1 - bits);
+    if (range == 0u) return Passes{0, 0};
+    const int hi = 31 - __builtin_clz(range), lo = max(0, hi + 1 - bits);
     return Passes{lo, (hi - lo + digit) / digit};
 }
 __device__ __forceinline__ int list_shift(const Passes& p, int i, int digit) { return min(p.lo + digit * i, 32 - digit); }
@@ -206,15 +208,19 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint3
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
         const uint32_t* const from = stage == 1 ? vals : keys;
-        const uint32_t k0 = from[0], at = anew(lane);
-        uint32_t diff = 0u;
+        const uint32_t at = anew(lane);
+        uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             key[r] = 0xffffffffu;
             id[r] = r * 64u + at;
-            if (within(lane, L, r * 64)) { key[r] = from[r * 64u + at]; diff |= key[r] ^ k0; }
+            if (within(lane, L, r * 64)) { key[r] = from[r * 64u + at]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
         }
-        diff = wave_reduce(diff, OpOr{});
+        lo = ~wave_reduce(lo, OpMax{});
+        const uint32_t diff = wave_reduce(hi, OpMax{}) - lo;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (within(lane, L, r * 64)) key[r] -= lo;
         const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
         for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
         bool in_order = stage == 2;
@@ -309,6 +315,20 @@ __device__ __forceinline__ bool wg_any(WgSortLds& S, int turn, bool v)
     return any != 0u;
 }
 
+// The keys' range over the workgroup: the threads' largest and smallest (inverted) key in, the smallest out and the difference
+// returned. One barrier; the next call is several barriers away.
+__device__ __forceinline__ uint32_t wg_key_range(WgSortLds& S, uint32_t& lo, uint32_t hi)
+{
+    const uint32_t l = wave_reduce(lo, OpMax{}), h = wave_reduce(hi, OpMax{});
+    if ((threadIdx.x & 63u) == 0u) S.range[threadIdx.x >> 6] = make_uint2(l, h);
+    __syncthreads();
+    uint2 all = S.range[0];
+#pragma unroll
+    for (int w = 1; w < kSortWaves; ++w) { const uint2 r = S.range[w]; all.x = max(all.x, r.x); all.y = max(all.y, r.y); }
+    lo = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)all.x);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)all.y) - lo;
+}
+
 // The entries of the list are in order but for neighbours: sweeps over its even and its odd pairs of neighbours in turn. Returns
 // whether the list is in order now. Ends with a barrier.
 __device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint32_t* k, uint32_t* v)
@@ -349,7 +369,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
     const uint32_t wb = wave * per_wave, we0 = min(L, wb + per_wave);
     uint16_t* src = S.perm[0];
     uint16_t* dst = S.perm[1];
-    auto one_pass = [&](int shift, const uint32_t* from) {
+    auto one_pass = [&](int shift, const uint32_t* from, uint32_t lo) {
 #pragma unroll
         for (int q = 0; q < kPerLane; ++q) S.cnt[wave][q * 64 + lane] = 0u;
         wave_lds_sync();
@@ -371,7 +391,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t digit = (k[j] >> shift) & (kListBins - 1u);
+                const uint32_t digit = ((k[j] - lo) >> shift) & (kListBins - 1u);
                 dp[r0 + j] = digit | (digit_prefix<kListBits, true>(S.cnt[wave], digit, within(lane, we, (int)wb + (r0 + j) * 64)) << kListBits);
             }
         }
@@ -394,10 +414,8 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
         const uint32_t* const from = stage == 1 ? vals : keys;
-        // the bit positions in which the keys differ
         const uint32_t k0 = from[0];
-        uint32_t diff = 0u;
-        if (threadIdx.x == 0) S.mask = 0u;
+        uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
         for (uint32_t i0 = 0; i0 < L; i0 += 8u * kSortThreads) {      // eight independent fetches in flight
             const uint32_t at = anew(threadIdx.x);
             uint32_t t[8];
@@ -409,19 +427,15 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 const uint32_t i = i0 + r * (uint32_t)kSortThreads + at;
-                diff |= t[r] ^ k0;
+                lo = max(lo, ~t[r]); hi = max(hi, t[r]);
                 if (within((int)threadIdx.x, L, (int)i0 + r * kSortThreads)) {
                     src[i] = (uint16_t)i;
                 }
             }
         }
-        diff = wave_reduce(diff, OpOr{});
-        __syncthreads();                               // S.mask is cleared; keys and permutation are in place
-        if (lane == 0 && diff) atomicOr(&S.mask, diff);
-        __syncthreads();
-        diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.mask);
+        const uint32_t diff = wg_key_range(S, lo, hi);      // (a barrier: keys and permutation are in place)
         const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
-        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits), from);
+        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits), from, lo);
         // through the sorted positions; every entry is fetched before the first is stored
         const auto put_in_order = [&](uint32_t* list) {
             uint32_t out[R];
@@ -446,7 +460,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
         put_in_order(vals);
         if (stage == 2) return;
         put_in_order(keys);
-        __syncthreads();      // (also: the mask and the permutation may be written again)
+        __syncthreads();      // (also: the permutation may be written again)
         if (stage == 0 && tie_sweeps(S, L, keys, vals)) return;
     }
 }
@@ -484,20 +498,18 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t*
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
         const uint32_t* const from = stage == 1 ? vals : keys;
-        const uint32_t k0 = from[0], at = anew(first + lane);
-        uint32_t diff = 0u;
-        if (threadIdx.x == 0) S.mask = 0u;
+        const uint32_t at = anew(first + lane);
+        uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             key[r] = 0xffffffffu;
             id[r] = r * 64u + at;
-            if (within(lane, L, first + r * 64)) { key[r] = from[r * 64u + at]; diff |= key[r] ^ k0; }
+            if (within(lane, L, first + r * 64)) { key[r] = from[r * 64u + at]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
         }
-        diff = wave_reduce(diff, OpOr{});
-        __syncthreads();                               // S.mask is cleared
-        if (lane == 0 && diff) atomicOr(&S.mask, diff);
-        __syncthreads();
-        diff = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.mask);
+        const uint32_t diff = wg_key_range(S, lo, hi);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (within(lane, L, first + r * 64)) key[r] -= lo;
         const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
         for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
         bool in_order = stage == 2;
@@ -548,7 +560,7 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t*
         put_in_order(vals);
         if (in_order) return;
         put_in_order(keys);
-        __syncthreads();      // (also: the mask may be written again)
+        __syncthreads();
     }
 }
 
@@ -574,7 +586,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 // wavefront's first entry of each digit goes, and a sweep places the entries: digit_prefix() hands back the counter's
 // value before the round's entries were added plus the lane's rank among them, which now is the entry's position.
 // Nothing is kept per entry between the sweeps, so the list may be of any length.
-__device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLongBins], uint32_t (*nxt)[kLongBins], bool count_first, uint32_t L,
+__device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLongBins], uint32_t (*nxt)[kLongBins], bool count_first, uint32_t L, uint32_t lo,
                                                int shift, int next_shift, const uint32_t* __restrict__ kin,
                                                const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout, uint32_t* __restrict__ vout)
 {
@@ -594,7 +606,7 @@ __device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLo
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-                if (i0 + j * 64u < we) digit_prefix<kLongBits, false>(cur[wave], (k[j] >> shift) & (kLongBins - 1u), i0 + j * 64u + lane < we);
+                if (i0 + j * 64u < we) digit_prefix<kLongBits, false>(cur[wave], ((k[j] - lo) >> shift) & (kLongBins - 1u), i0 + j * 64u + lane < we);
         }
     }
     __syncthreads();      // every wavefront's counts are in
@@ -620,14 +632,14 @@ __device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLo
         for (int j = 0; j < 8; ++j) {
             if (i0 + j * 64u < we) {
                 const bool valid = i0 + j * 64u + lane < we;
-                const uint32_t pos = min(digit_prefix<kLongBits, false>(cur[wave], (k[j] >> shift) & (kLongBins - 1u), valid), L - 1u);      // < L for consistent counts
+                const uint32_t pos = min(digit_prefix<kLongBits, false>(cur[wave], ((k[j] - lo) >> shift) & (kLongBins - 1u), valid), L - 1u);      // < L for consistent counts
                 if (valid) {
                     kout[pos] = k[j]; vout[pos] = v[j];
                     if (next_shift >= 0) {      // the next pass finds this entry in the part of wavefront pos / per_wave
                         uint32_t w2 = 0u;
 #pragma unroll
                         for (uint32_t w = 1u; w < (uint32_t)kSortWaves; ++w) w2 += pos >= w * per_wave ? 1u : 0u;
-                        atomicAdd(&nxt[w2][(k[j] >> next_shift) & (kLongBins - 1u)], 1u);
+                        atomicAdd(&nxt[w2][((k[j] - lo) >> next_shift) & (kLongBins - 1u)], 1u);
                     }
                 }
             }
@@ -645,7 +657,6 @@ __device__ __forceinline__ void wg_sort_big(WgSortLds& S, uint32_t s, uint32_t e
     const uint32_t L = e - s;
     if (L <= (uint32_t)kWgListMax) { wg_permute_list(S, L, keysA + s, valsA + s); return; }
     // through global memory, from one pair of arrays to the other
-    const int lane = threadIdx.x & 63;
     // the two sets of counters swap roles from pass to pass
     uint32_t (*c0)[kLongBins] = S.count[0];
     uint32_t (*c1)[kLongBins] = S.count[1];
@@ -656,19 +667,13 @@ __device__ __forceinline__ void wg_sort_big(WgSortLds& S, uint32_t s, uint32_t e
             for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) k[i] = stage == 1 ? v[i] : depth_bits[v[i]];
             __syncthreads();
         }
-        const uint32_t k0 = k[0];
-        uint32_t diff = 0u;
-        if (threadIdx.x == 0) S.mask = 0u;
-        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) diff |= k[i] ^ k0;
-        diff = wave_reduce(diff, OpOr{});
-        __syncthreads();                               // S.mask is cleared
-        if (lane == 0 && diff) atomicOr(&S.mask, diff);
-        __syncthreads();
-        const uint32_t mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.mask);
-        const Passes ps = list_passes(mask, 32, kLongBits);
+        uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
+        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) { lo = max(lo, ~k[i]); hi = max(hi, k[i]); }
+        const uint32_t diff = wg_key_range(S, lo, hi);
+        const Passes ps = list_passes(diff, 32, kLongBits);
         for (int p = 0; p < ps.count; ++p) {
             const int next_shift = p + 1 < ps.count ? list_shift(ps, p + 1, kLongBits) : -1;
-            long_list_pass(S, (p & 1) ? c1 : c0, (p & 1) ? c0 : c1, p == 0, L, list_shift(ps, p, kLongBits), next_shift, k, v, k2, v2);
+            long_list_pass(S, (p & 1) ? c1 : c0, (p & 1) ? c0 : c1, p == 0, L, lo, list_shift(ps, p, kLongBits), next_shift, k, v, k2, v2);
             uint32_t* t = k; k = k2; k2 = t;
             t = v; v = v2; v2 = t;
         }

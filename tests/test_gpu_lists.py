@@ -1,6 +1,6 @@
 """Tile lists where the binning kernels change their way of working: list lengths at the borders between the sorts of
 k_tile_depth_sort, which depend on how many tiles there are; blocks of 256 points whose rectangle of tiles is larger than the
-counting table; point counts at which a block gets another number of threads. Bit-exact against the oracle, which sorts by
+counting table, which go past it; point counts at which a block gets another number of threads. Bit-exact against the oracle, which sorts by
 (tile, depth bits, point index)."""
 import numpy as np
 import pytest
@@ -35,9 +35,9 @@ LENGTHS = [1, 2, 63, 64, 65, 126, 127, 128, 129, 192, 193, 254, 255, 256, 257, 3
 
 
 @pytest.mark.parametrize("w,h", [(320, 320), (1280, 720), (1936, 1040)])      # 400, 3,600 and 7,865 tiles
-@pytest.mark.parametrize("kind", ["uniform", "pairs", "runs", "one_depth"])
+@pytest.mark.parametrize("kind", ["uniform", "octaves", "pairs", "runs", "one_depth"])
 def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
-    """One tile per length, its points scattered over the point order. Depths: spread evenly; each value twice, as copied points
+    """One tile per length, its points scattered over the point order. Depths: spread evenly; over seven octaves on both sides of 2.0; each value twice, as copied points
     leave them (put right by swapping neighbours); in runs of a hundred equal ones and, in every tenth list, in the top bits alone
     (more than the swaps do: sorted again by point index); one for all."""
     rng = np.random.default_rng(w + len(kind))
@@ -47,6 +47,8 @@ def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
     centre = np.stack([(tile % tx) * 16 + rng.uniform(3, 13, n), (tile // tx) * 16 + rng.uniform(3, 13, n)], 1).astype(np.float32)
     if kind == "uniform":
         depth = rng.uniform(8, 20, n)
+    elif kind == "octaves":
+        depth = np.exp2(rng.uniform(-1.5, 5.5, n))
     elif kind == "pairs":
         depth = rng.uniform(8, 20, n)
         depth[1::2] = depth[:-1:2][:len(depth[1::2])]
@@ -67,11 +69,22 @@ def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
 @pytest.mark.parametrize("w,h", [(65536, 100), (3840, 2160), (48, 65536)])
 @pytest.mark.parametrize("n", [255, 600])
 def test_blocks_of_points_all_over_a_large_grid(w, h, n):
-    """Points in no spatial order: a block's rectangle of tiles is the whole grid, which its table takes in bands."""
+    """Points in no spatial order: a block's rectangle of tiles is the whole grid, and its pairs are counted in memory. Also with room
+    for less than half of the pairs: the first in point order, row by row, are kept."""
     rng = np.random.default_rng(w + n)
     st = _rand_state(rng, n, w, h, rmax=70)
-    st["radius"][rng.integers(0, n, 12)] = rng.integers(500, 5000, 12)      # points on hundreds of tiles that reach over bands
-    _check(st, rng.uniform(0.3, 50, n), w, h)
+    st["radius"][rng.integers(0, n, 12)] = rng.integers(500, 5000, 12)      # points on hundreds of tiles
+    depth = rng.uniform(0.3, 50, n)
+    ref = _check(st, depth, w, h)
+    cap = int(0.45 * ref["P"])
+    view = GpuView(n, _cam(w, h), cap)
+    view.splats = B.Splats.from_numpy(dict(st, depth=depth.astype(np.float32)))
+    B.pbdr_bin_sort(view.splats, view.cam, cap, view.ws)
+    got = view.lists()
+    assert B.pbdr_query_lists(view.ws, n, w, h, cap) == (ref["P"], True)
+    kept = np.sort(np.lexsort((ref["keys"] >> np.uint64(32), ref["vals"]))[:cap])
+    assert np.array_equal(got["keys"][:cap], ref["keys"][kept])
+    assert np.array_equal(got["vals"][:cap], ref["vals"][kept])
 
 
 @pytest.mark.parametrize("n", [1, 255, 256, 257, 4096, 4097, 262144 + 1, 300000])

@@ -85,7 +85,9 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->off_chunk_rank = take(chunks * sizeof(uint32_t));
     L->off_carry = take(chunks * kCarryFloats * sizeof(float));
     L->off_grad_rec = take((size_t)n * L->partial_vec4 * 4 * sizeof(float));      // per-point gradient records, by point index
-    L->off_reach = take((size_t)2 * cap);                            // per sorted pair, forward -> backward: the tile's sixteen cells that the splat can reach (3D), that blended it (surfels)
+    // per sorted pair, forward -> backward: the tile's sixteen cells that the splat can reach (3D), that blended it (surfels:
+    // their workspace keeps the size callers know, four bytes, of which the cells take two)
+    L->off_reach = take((size_t)(variant == kVariant2D ? 4 : 2) * cap);
     L->off_tile_order = take((size_t)L->tiles * sizeof(uint32_t));   // tiles in the order the compositing kernels take them
     L->total = off;
     return true;

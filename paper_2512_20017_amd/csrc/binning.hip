@@ -11,7 +11,8 @@
 // Five launches where a stable two-pass radix sort of the pairs by tile id took eleven; with the depth sort as it is now, us
 // before and now, in turn on one card: 1M points at 1920x1080 472 -> 438 a step, 225 -> 195 an evaluation; 30k at 1031x517 156 -> 129 a
 // step; 12,000 at 400x300 79 -> 49 an evaluation. The order of points matters more than before: where a block's points lie all
-// over the image, its pairs are on as many tiles, and each costs an atomic add.
+// over the image, its pairs are on as many tiles, and each costs an atomic add (1M points at 1920x1080, an evaluation: in Z-order
+// 218 -> 183 us, in random order 243 -> 318).
 #include "pbdr_internal.h"
 #include "binning_common.h"
 

@@ -77,7 +77,6 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->off_keys = take((size_t)cap * sizeof(uint32_t));
     L->off_vals = take((size_t)cap * sizeof(uint32_t));
     L->off_spare = take((size_t)cap * 2 * sizeof(uint32_t));             // the blocks' tiles, then the other half of a list too long for LDS
-    L->off_tile_count = take((size_t)L->tiles * sizeof(uint32_t));
     L->off_ranges = take((size_t)L->tiles * 2 * sizeof(uint32_t));
     L->off_partial = take((size_t)cap * L->partial_vec4 * 4 * sizeof(float));
     L->off_keys64 = take((size_t)cap * sizeof(uint64_t));

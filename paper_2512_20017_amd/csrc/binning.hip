@@ -25,17 +25,15 @@ namespace pbdr {
 // Four consecutive points per thread (one 16-byte load of the radii, one 16-byte store of the counts: with one point
 // per thread the launch did not keep enough bytes in flight, 2 TB/s at eight million points: 32 -> 21 us there), so a
 // wavefront covers exactly one block of 256 points and its two sums need no LDS and no barrier.
-__global__ __launch_bounds__(1024) void k_count_visible(BinInput in, CamDev cam, BinArrays A, uint32_t* __restrict__ ranges, uint32_t nranges,
-                                                        uint32_t ntiles)
+__global__ __launch_bounds__(1024) void k_count_visible(BinInput in, CamDev cam, BinArrays A, uint32_t nranges)
 {
     __shared__ uint2 sBlk[kSuperBlocks];
     const uint32_t gid = blockIdx.x * 1024u + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // first launch of a binning call: the status words, the tile ranges and the tiles' pair counts start at zero (every later
-    // kernel of the call comes after this one on the stream)
+    // first launch of a binning call: the status words and the tile ranges, which hold the tiles' pair counts first, start at zero
+    // (every later kernel of the call comes after this one on the stream)
     if (gid < (uint32_t)kStCleared) A.status[gid] = 0u;
-    for (uint32_t k = gid; k < nranges; k += gridDim.x * 1024u) ranges[k] = 0u;
-    for (uint32_t k = gid; k < ntiles; k += gridDim.x * 1024u) A.tile_count[k] = 0u;
+    for (uint32_t k = gid; k < nranges; k += gridDim.x * 1024u) A.ranges[k] = 0u;
     const size_t i0 = (size_t)gid * 4u;
     const size_t n = (size_t)in.n;
     int r[4] = {0, 0, 0, 0};
@@ -159,7 +157,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_count(BinInput in, CamDev cam
     const uint32_t bh = __builtin_amdgcn_readfirstlane(max(max(q0.w, q1.w), max(q2.w, q3.w))) - by;
     if (bw * bh > kTableCells) {
         uint32_t* const rank = reinterpret_cast<uint32_t*>(A.cells) + before.y;      // (its pairs' slots hold two words each)
-        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) { return atomicAdd(&A.tile_count[y * (uint32_t)cam.TX + x], 1u); },
+        walk_pairs(S, total, A.cap, [&](uint32_t x, uint32_t y, uint32_t) { return atomicAdd(&A.ranges[2u * (y * (uint32_t)cam.TX + x) + 1u], 1u); },
                    [&](uint32_t r, uint32_t at, uint32_t) { rank[at] = r; });
         if (threadIdx.x == 0) A.blk_cells[blk] = make_uint4(kDirect, 0u, 0u, 0u);
         return;
@@ -186,7 +184,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_count(BinInput in, CamDev cam
             if (j < listed) {
                 const uint32_t c = sList[j], row = c / bw, x = bx + c - row * bw, y = by + row;
                 xy[k] = x | y << 16;
-                at[k] = atomicAdd(&A.tile_count[y * (uint32_t)cam.TX + x], count_of(c));
+                at[k] = atomicAdd(&A.ranges[2u * (y * (uint32_t)cam.TX + x) + 1u], count_of(c));
             }
         }
 #pragma unroll
@@ -261,11 +259,14 @@ __device__ __forceinline__ uint64_t lanes_of_my_class(uint32_t cls)
 
 // Workgroup g takes the kOrderChunk tiles from g * kOrderChunk on. Where they go also depends on the other workgroups' tiles:
 // how many of each class lie in earlier chunks, and in later ones, and how many pairs in earlier ones. Every workgroup counts
-// those for itself, so none waits for another.
+// those for itself, so none waits for another. A tile's entry is {0, pairs} until its workgroup makes it {start, end}, in one store of
+// eight bytes; whichever of the two another workgroup finds there in one load, the difference is the number of pairs.
 template <bool kMulti>                      // more than one chunk
-__global__ __launch_bounds__(1024) void k_tile_lists(const uint32_t* __restrict__ tile_count, uint32_t ntiles, uint32_t* __restrict__ ranges,
-                                                     uint32_t* __restrict__ tile_order, uint32_t* __restrict__ status, int long_code)
+__global__ __launch_bounds__(1024) void k_tile_lists(uint64_t* ranges, uint32_t ntiles, uint32_t* __restrict__ tile_order, uint32_t* __restrict__ status,
+                                                     int long_code)
 {
+    const auto entry = [&](uint32_t t) { return __hip_atomic_load(ranges + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    const auto pairs_of = [](uint64_t r) { return (uint32_t)(r >> 32) - (uint32_t)r; };
     // per class: (earlier chunks,) the 16 wavefronts of this one(, later chunks)
     constexpr uint32_t kOrderSlots = kMulti ? 18u : 16u, kFirst = kMulti ? 1u : 0u;
     constexpr int kPer = (kOrderClasses * kOrderSlots + 63) / 64;
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(1024) void k_tile_lists(const uint32_t* __restrict_
     const uint32_t c0 = blockIdx.x * kOrderChunk, c1 = min(ntiles, c0 + kOrderChunk);
     const uint32_t t = c0 + threadIdx.x;
     const uint64_t below = (1ull << lane) - 1ull;
-    const uint32_t len = t < c1 ? tile_count[t] : 0u;
+    const uint32_t len = t < c1 ? pairs_of(entry(t)) : 0u;
     for (uint32_t i = threadIdx.x; i < 64u * kOrderSlots; i += 1024u) count[i] = 0u;
     if (kMulti)
         for (uint32_t i = threadIdx.x; i < 2u * kOrderClasses * 16u; i += 1024u) other[i] = 0u;
@@ -289,18 +290,17 @@ __global__ __launch_bounds__(1024) void k_tile_lists(const uint32_t* __restrict_
         // (one of 16 counters per side and class, by lane: a wavefront's tiles are mostly of one class, and additions to
         // one LDS address take their turns)
         for (uint32_t ib = threadIdx.x; ib < ntiles; ib += 4u * 1024u) {
-            uint32_t r[4];
+            uint64_t r[4];
 #pragma unroll
             for (uint32_t k = 0; k < 4u; ++k) {
-                const uint32_t i = ib + k * 1024u;
-                r[k] = i < ntiles ? tile_count[i] : 0u;
+                r[k] = entry(min(ib + k * 1024u, ntiles - 1u));
             }
 #pragma unroll
             for (uint32_t k = 0; k < 4u; ++k) {
                 const uint32_t i = ib + k * 1024u;
-                if (i < c0) earlier += r[k];      // (all lists together stay below the capacity, 2^30)
+                if (i < c0) earlier += pairs_of(r[k]);      // (all lists together stay below the capacity, 2^30)
                 if (i < ntiles && (i < c0 || i >= c1))
-                    atomicAdd(&other[((i < c0 ? 0u : (uint32_t)kOrderClasses) + order_class(r[k])) * 16u + (lane & 15u)], 1u);
+                    atomicAdd(&other[((i < c0 ? 0u : (uint32_t)kOrderClasses) + order_class(pairs_of(r[k]))) * 16u + (lane & 15u)], 1u);
             }
         }
 #pragma unroll
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(1024) void k_tile_lists(const uint32_t* __restrict_
         if (k < w) start += sPairs[0][k];
         if (kMulti) start += sPairs[1][k];
     }
-    if (t < c1) reinterpret_cast<uint2*>(ranges)[t] = len ? make_uint2(start, start + len) : make_uint2(0u, 0u);
+    if (t < c1 && len) __hip_atomic_store(ranges + t, (uint64_t)(start + len) << 32 | start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // (an empty one stays {0, 0})
     __syncthreads();
     // how many tiles hold 2^(long_code / 2) - 1 entries (1.5 times that if odd) or more: they come first in the order, and the depth sort gives each a whole
     // workgroup (where a class starts)
@@ -391,7 +391,6 @@ BinArrays bin_arrays(const Layout& L, char* ws)
     A.blk_at = reinterpret_cast<uint2*>(ws + L.off_blk_at);
     A.blk_cells = reinterpret_cast<uint4*>(ws + L.off_blk_cells);
     A.cells = reinterpret_cast<uint2*>(ws + L.off_spare);
-    A.tile_count = u32(L.off_tile_count);
     A.ranges = u32(L.off_ranges);
     A.order = u32(L.off_order);
     A.offsets = u32(L.off_offsets);
@@ -412,13 +411,12 @@ hipError_t launch_bin_count(const BinInput& in, const CamDev& cam, const Layout&
 {
     if (in.n == 0) return hipSuccess;
     const BinArrays A = bin_arrays(L, ws);
-    uint32_t* ranges = reinterpret_cast<uint32_t*>(ws + L.off_ranges);
     const unsigned nb = (unsigned)((in.n + 255) / 256);
     const uint32_t ntiles = (uint32_t)(cam.TX * cam.TY);      // the call's tile grid (a patch covers fewer tiles than the image the workspace is sized for)
     {
         ProfScope prof(kKCountVisible, s);
-        hipLaunchKernelGGL(k_count_visible, dim3((nb + kSuperBlocks - 1u) / kSuperBlocks), dim3(1024), 0, s, in, cam, A, ranges,
-                           (uint32_t)(2 * (size_t)L.tiles), ntiles);
+        hipLaunchKernelGGL(k_count_visible, dim3((nb + kSuperBlocks - 1u) / kSuperBlocks), dim3(1024), 0, s, in, cam, A,
+                           (uint32_t)(2 * (size_t)L.tiles));
     }
     {
         ProfScope prof(kKTileCount, s);
@@ -426,9 +424,10 @@ hipError_t launch_bin_count(const BinInput& in, const CamDev& cam, const Layout&
         else hipLaunchKernelGGL(k_tile_count<1024>, dim3(nb), dim3(1024), 0, s, in, cam, A, nb);
     }
     ProfScope prof(kKTileLists, s);
+    uint64_t* ranges = reinterpret_cast<uint64_t*>(ws + L.off_ranges);
     uint32_t* tile_order = reinterpret_cast<uint32_t*>(ws + L.off_tile_order);
-    if (ntiles <= kOrderChunk) hipLaunchKernelGGL(k_tile_lists<false>, dim3(1), dim3(1024), 0, s, A.tile_count, ntiles, ranges, tile_order, A.status, long_list_code(ntiles));
-    else hipLaunchKernelGGL(k_tile_lists<true>, dim3((ntiles + kOrderChunk - 1u) / kOrderChunk), dim3(1024), 0, s, A.tile_count, ntiles, ranges, tile_order, A.status, long_list_code(ntiles));
+    if (ntiles <= kOrderChunk) hipLaunchKernelGGL(k_tile_lists<false>, dim3(1), dim3(1024), 0, s, ranges, ntiles, tile_order, A.status, long_list_code(ntiles));
+    else hipLaunchKernelGGL(k_tile_lists<true>, dim3((ntiles + kOrderChunk - 1u) / kOrderChunk), dim3(1024), 0, s, ranges, ntiles, tile_order, A.status, long_list_code(ntiles));
     return hipGetLastError();
 }
 

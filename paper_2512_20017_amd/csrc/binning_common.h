@@ -26,8 +26,7 @@ struct BinArrays {
     uint2* blk_at;               // [blocks] listed points and pairs in the blocks before this one (of blocks with a listed point)
     uint4* blk_cells;            // [blocks] {tiles the block's pairs lie on or kDirect, x | y << 16 of its rectangle of tiles, its width, -}
     uint2* cells;                // [cap] those tiles, from blk_at.y on: {x | y << 16, pairs of the blocks that counted the tile before}
-    uint32_t* tile_count;        // [tiles] pairs
-    const uint32_t* ranges;      // [tiles][2]
+    uint32_t* ranges;            // [tiles][2] {0, pairs} from k_tile_count, {start, end} from k_tile_lists on
     uint32_t* order;             // [n] listed points in index order ("rank" -> point)
     uint32_t* offsets;           // [n + 1] first pair of each rank; offsets[listed] = pair total
     uint32_t* slot_base;         // [n] first pair of each listed point, by point index

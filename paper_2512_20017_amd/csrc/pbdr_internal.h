@@ -165,7 +165,7 @@ struct Layout {
     int partial_vec4;         // float4s of partial gradient sums per pair: 3 (3D) or 4 (2D)
     uint32_t cap;
     size_t off_status, off_packed, off_depth_bits, off_blk, off_sup, off_blk_at, off_blk_cells, off_touched, off_offsets, off_slot_base, off_order,
-        off_keys, off_vals, off_spare, off_tile_count, off_ranges, off_partial, off_keys64, off_chunk_rank, off_carry, off_grad_rec, off_reach,
+        off_keys, off_vals, off_spare, off_ranges, off_partial, off_keys64, off_chunk_rank, off_carry, off_grad_rec, off_reach,
         off_tile_order, total;
 };
 // A tile's list of fewer than long_list_from() entries is put in depth order by one wavefront, a longer one by a whole workgroup

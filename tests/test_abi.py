@@ -47,6 +47,15 @@ def test_workspace_bytes():
         B.pbdr_workspace_bytes(10, 128, 128, 1 << 40)
 
 
+@pytest.mark.parametrize("size", [B.pbdr_workspace_bytes, B.pbdr2d_workspace_bytes])
+def test_workspace_of_a_large_grid(size):
+    """Twelve bytes a tile: where its list starts and ends, and its place in the order."""
+    one_tile = size(1000, 16, 16, 400_000)
+    for w, h in ((65536, 65536), (65536, 100), (3840, 2160)):
+        tiles = (w + 15) // 16 * ((h + 15) // 16)
+        assert size(1000, w, h, 400_000) - one_tile <= 12 * tiles + 1024
+
+
 def test_invalid_arguments_are_rejected_on_the_host():
     L = B.lib()
     cam = B.camera_struct(dict(width=64, height=64, fx=50, fy=50, cx=32, cy=32, R=[1, 0, 0, 0, 1, 0, 0, 0, 1], t=[0, 0, 3]))

@@ -193,12 +193,18 @@ __device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* _
 // For the kernels that read a point's record after the gather. at, count: the
 // point's first pair and its number of pairs. Returns false if all of its pairs lie in one wavefront's chunk (the gather
 // stored the record itself); else v = the right piece of the wavefront its first pair lies in, plus the left pieces of
-// the following wavefronts up to and including the first that is not a through piece.
+// the following wavefronts up to and including the first that is not a through piece; zero if the point has no pair below the
+// capacity (its record holds whatever was there).
 template <int kVals>
 __device__ __forceinline__ bool record_from_carries(const CarryFold& cf, uint32_t at, uint32_t count, float (&v)[kVals])
 {
     const uint32_t Pc = min(cf.status[kStNumDup], cf.cap);
     const uint32_t beg = min(at, Pc), end = min(at + count, Pc);      // (at < 2^31, count <= 2^24)
+    if (beg == end) {      // all of them beyond the capacity: nothing was added up
+#pragma unroll
+        for (int k = 0; k < kVals; ++k) v[k] = 0.f;
+        return true;
+    }
     const uint32_t w = beg >> cf.chunk_bits;
     if (end <= (w + 1u) << cf.chunk_bits) return false;
     const uint32_t nw = (Pc + (1u << cf.chunk_bits) - 1u) >> cf.chunk_bits;

@@ -65,25 +65,29 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->off_status = take(kStWords * sizeof(uint32_t));
     L->off_packed = take((size_t)n * L->record_bytes);
     L->off_depth_bits = take((size_t)n * sizeof(uint32_t));
-    const size_t nb = ((size_t)n + 255) / 256;                           // blocks of 256 points
-    L->off_blk = take(nb * sizeof(uint2));
-    L->off_sup = take((nb / 16 + 1) * sizeof(uint2));
-    L->off_blk_at = take(nb * sizeof(uint2));
-    L->off_blk_cells = take(nb * sizeof(uint4));
     L->off_touched = take((size_t)n * sizeof(uint32_t));
     L->off_offsets = take(((size_t)n + 1) * sizeof(uint32_t));
     L->off_slot_base = take((size_t)n * sizeof(uint32_t));
     L->off_order = take((size_t)n * sizeof(uint32_t));       // listed points in index order ("rank" -> point)
     L->off_keys = take((size_t)cap * sizeof(uint32_t));
     L->off_vals = take((size_t)cap * sizeof(uint32_t));
-    L->off_spare = take((size_t)cap * 2 * sizeof(uint32_t));             // the blocks' tiles, then the other half of a list too long for LDS
+    // the blocks' tiles, then the other half of a list too long for LDS, then the gather's cut pieces
+    L->off_spare = take((size_t)cap * 2 * sizeof(uint32_t));
+    L->off_carry = L->off_spare;
+    static_assert(kCarryFloats * sizeof(float) <= 256 && kCarryFloats * sizeof(float) + 64 * 2 * sizeof(uint32_t) <= 2 * 64 * 2 * sizeof(uint32_t),
+                  "a piece per 64 pairs fits: one in the 256 bytes of the smallest array, each further one in its own 64 pairs' part");
     L->off_ranges = take((size_t)L->tiles * 2 * sizeof(uint32_t));
     L->off_partial = take((size_t)cap * L->partial_vec4 * 4 * sizeof(float));
     L->off_keys64 = take((size_t)cap * sizeof(uint64_t));
-    const size_t chunks = ((size_t)cap >> gather_chunk_bits((uint32_t)cap)) + 2;  // see pair_reduce.h
-    L->off_chunk_rank = take(chunks * sizeof(uint32_t));
-    L->off_carry = take(chunks * kCarryFloats * sizeof(float));
+    L->off_chunk_rank = take((gather_chunks_max((uint32_t)cap) + 1) * sizeof(uint32_t));
     L->off_grad_rec = take((size_t)n * L->partial_vec4 * 4 * sizeof(float));      // per-point gradient records, by point index
+    // what binning keeps per block of 256 points lies there too: it is done with before the backward pass starts (40 bytes a block
+    // at most, and a record has 48)
+    const size_t nb = ((size_t)n + 255) / 256;
+    L->off_blk_cells = L->off_grad_rec;
+    L->off_blk = L->off_blk_cells + nb * sizeof(uint4);
+    L->off_blk_at = L->off_blk + nb * sizeof(uint2);
+    L->off_sup = L->off_blk_at + nb * sizeof(uint2);
     // per sorted pair, forward -> backward: the tile's sixteen cells that the splat can reach (3D), that blended it (surfels:
     // their workspace keeps the size callers know, four bytes, of which the cells take two)
     L->off_reach = take((size_t)(variant == kVariant2D ? 4 : 2) * cap);

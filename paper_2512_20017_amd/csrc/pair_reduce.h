@@ -18,6 +18,14 @@ namespace pbdr {
 // trip to memory and a chain of LDS and DPP steps, are the launch (us, 256 / 64: 10,530 pairs 9.9 / 4.7, 102,000 9.8 / 5.0, 480,000 13.0 / 9.4). Beyond, the cut
 // points weigh as much as that gains (1.9 M pairs 28.7 / 26.6, the step the same). By the capacity, which the host knows.
 inline int gather_chunk_bits(uint32_t cap) { return cap <= (1u << 20) ? 6 : 8; }
+// The chunks of any number of pairs up to the capacity are at most so many: what a workspace has room for, so that one of some
+// capacity serves every smaller one too.
+inline size_t gather_chunks_max(uint32_t cap)
+{
+    const size_t shorter = cap < (1u << 20) ? cap : 1u << 20;
+    const size_t a = (shorter + 63) / 64, b = ((size_t)cap + 255) / 256;
+    return a > b ? a : b;
+}
 
 // carry record per wavefront: [0..15] left piece, [16..31] right piece, then {flags, left rank, right rank, -}
 constexpr int kCarryFloats = 36;

@@ -56,6 +56,28 @@ def test_workspace_of_a_large_grid(size):
         assert size(1000, w, h, 400_000) - one_tile <= 12 * tiles + 1024
 
 
+# (points, width, height, pairs): bytes of the 3D and of the surfel workspace that calls of these sizes have been served with
+SERVED = {(30_011, 1031, 517, 400_000): (34_024_192, 41_704_192), (1000, 65536, 65536, 400_000): (231_494_144, 238_710_016),
+          (100_000, 1280, 720, 1 << 20): (91_980_288, 112_454_656), (4096, 128, 128, 20_000): (2_047_232, 2_472_704),
+          (1, 1, 1, 1): (8448, 8448), (7_722_898, 4772, 16, 28_794): (1_022_196_480, 1_146_281_216),
+          (1_000_000, 1920, 1080, 8_000_000): (732_805_376, 892_805_376)}
+
+
+@pytest.mark.parametrize("args", SERVED)
+def test_a_workspace_that_served_a_call_still_does(args):
+    assert B.pbdr_workspace_bytes(*args) <= SERVED[args][0]
+    assert B.pbdr2d_workspace_bytes(*args) <= SERVED[args][1]
+
+
+@pytest.mark.parametrize("size", [B.pbdr_workspace_bytes, B.pbdr2d_workspace_bytes])
+def test_a_workspace_serves_every_smaller_capacity(size):
+    """Also around 2^20 pairs, where the sums over a point's pairs change their way of working."""
+    for n, w, h in ((100_000, 1280, 720), (1, 16, 16)):
+        caps = [0, 1, 2, 63, 64, 65, 255, 256, 257, 1_040_000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, 1_050_000, 1 << 21, (1 << 22) - 1, 1 << 22, (1 << 22) + 1, 1 << 24]
+        sizes = [size(n, w, h, c) for c in caps]
+        assert sizes == sorted(sizes)
+
+
 def test_invalid_arguments_are_rejected_on_the_host():
     L = B.lib()
     cam = B.camera_struct(dict(width=64, height=64, fx=50, fy=50, cx=32, cy=32, R=[1, 0, 0, 0, 1, 0, 0, 0, 1], t=[0, 0, 3]))

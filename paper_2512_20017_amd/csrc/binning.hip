@@ -400,7 +400,6 @@ BinArrays bin_arrays(const Layout& L, char* ws)
     A.vals = u32(L.off_vals);
     A.chunk_rank = u32(L.off_chunk_rank);
     A.cap = L.cap;
-    A.chunk_bits = gather_chunk_bits(L.cap);
     A.status = u32(L.off_status);
     return A;
 }

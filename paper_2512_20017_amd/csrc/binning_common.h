@@ -35,7 +35,6 @@ struct BinArrays {
     uint32_t* vals;              // [cap] point index of each pair
     uint32_t* chunk_rank;        // rank owning the first pair of every chunk (pair_reduce.h)
     uint32_t cap;
-    int chunk_bits;
     uint32_t* status;
 };
 
@@ -223,6 +222,7 @@ __device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam
     const int i = (int)(blk * 256u + threadIdx.x);
     const uint2 before = A.blk_at[blk];
     const uint4 box = A.blk_cells[blk];
+    const int chunk_bits = gather_chunk_bits(min(A.status[kStNumDup], A.cap));
     // a block none of whose points is listed has nothing to write (most blocks, when the view sees a tenth of a large cloud)
     if (A.blk[blk].x == 0u) return;
     const PointExtent extent = point_extent(in, i);
@@ -257,7 +257,7 @@ __device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam
         store(i, rec);
         // which rank owns the first pair of every chunk (for the pair-balanced gather of the backward pass)
         const uint32_t end = min(P.at + P.cnt, A.cap);
-        for (uint32_t c = (P.at + (1u << A.chunk_bits) - 1u) >> A.chunk_bits; (uint64_t)c << A.chunk_bits < end; ++c) A.chunk_rank[c] = P.slot_rank;
+        for (uint32_t c = (P.at + (1u << chunk_bits) - 1u) >> chunk_bits; (uint64_t)c << chunk_bits < end; ++c) A.chunk_rank[c] = P.slot_rank;
     }
     if (box.x == 0u) return;                     // every pair lies beyond the capacity
     const auto place = [&](uint32_t pos, uint32_t own) {

@@ -616,7 +616,6 @@ struct StoreSplatGrad {
     }
 };
 
-template <int kChunkBits>
 __global__ __launch_bounds__(256) void k_gather_splat_grads(int n, const uint32_t* __restrict__ status,
                                                             const uint32_t* __restrict__ order,
                                                             const uint32_t* __restrict__ offsets,
@@ -626,7 +625,7 @@ __global__ __launch_bounds__(256) void k_gather_splat_grads(int n, const uint32_
 {
     __shared__ uint32_t sEnd[4][64];
     const uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6);
-    gather_wave<3, 9, true, kChunkBits>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplatGrad{rec, order});
+    gather_wave<3, 9, true>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplatGrad{rec, order});
 }
 
 // records -> planes, for the points binning listed (tiles_touched > 0). A point whose pairs are cut by a boundary of the gather's
@@ -719,7 +718,7 @@ hipError_t launch_composite_fwd(const CamDev& cam, const Layout& L, char* ws, co
 CarryFold carry_fold(const Layout& L, char* ws)
 {
     return CarryFold{reinterpret_cast<const float*>(ws + L.off_carry), reinterpret_cast<const uint32_t*>(ws + L.off_slot_base),
-                     reinterpret_cast<uint32_t*>(ws + L.off_status), L.cap, gather_chunk_bits(L.cap)};
+                     reinterpret_cast<uint32_t*>(ws + L.off_status), L.cap};
 }
 
 hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, int n, const float bg[3], const float* final_T, const uint32_t* last_idx, const float* dL_dimage,
@@ -744,15 +743,10 @@ hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, in
         ProfScope prof(kKGather, s);
         const uint32_t* chunk_rank = reinterpret_cast<const uint32_t*>(ws + L.off_chunk_rank);
         float* carry = reinterpret_cast<float*>(ws + L.off_carry);
-        const int bits = gather_chunk_bits(L.cap);
-        const unsigned nwave = (L.cap + (1u << bits) - 1u) >> bits;
+        const unsigned nwave = (unsigned)gather_chunks_max(L.cap);
         float4* rec = reinterpret_cast<float4*>(ws + L.off_grad_rec);
-        if (bits == 6)
-            hipLaunchKernelGGL(k_gather_splat_grads<6>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank,
-                           partial, L.cap, carry, rec);
-        else
-            hipLaunchKernelGGL(k_gather_splat_grads<8>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank,
-                           partial, L.cap, carry, rec);
+        hipLaunchKernelGGL(k_gather_splat_grads, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank, partial,
+                           L.cap, carry, rec);
         if (g2.mean2d != nullptr)
             hipLaunchKernelGGL(k_grad_records_to_planes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
                                reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, carry_fold(L, ws), g2);

@@ -16,10 +16,11 @@ namespace pbdr {
 
 // Pairs per wavefront, as a power of two: 256, or 64 where that leaves the chip so empty that four steps in a row, each a round
 // trip to memory and a chain of LDS and DPP steps, are the launch (us, 256 / 64: 10,530 pairs 9.9 / 4.7, 102,000 9.8 / 5.0, 480,000 13.0 / 9.4). Beyond, the cut
-// points weigh as much as that gains (1.9 M pairs 28.7 / 26.6, the step the same). By the capacity, which the host knows.
-inline int gather_chunk_bits(uint32_t cap) { return cap <= (1u << 20) ? 6 : 8; }
-// The chunks of any number of pairs up to the capacity are at most so many: what a workspace has room for, so that one of some
-// capacity serves every smaller one too.
+// points weigh as much as that gains (1.9 M pairs 28.7 / 26.6, the step the same). By the number of pairs, not by the room for them:
+// the order of the additions, and so the last bits of a gradient, do not depend on dup_capacity.
+__host__ __device__ inline int gather_chunk_bits(uint32_t pairs) { return pairs <= (1u << 20) ? 6 : 8; }
+// The chunks of any number of pairs up to the capacity are at most so many: what is launched, and what a workspace has room for, so
+// that one of some capacity serves every smaller one too.
 inline size_t gather_chunks_max(uint32_t cap)
 {
     const size_t shorter = cap < (1u << 20) ? cap : 1u << 20;
@@ -90,14 +91,13 @@ __device__ __forceinline__ void seg_scan_sorted(float (&v)[kVals], int owner)
 // written, carries the current number); a record with any other tag was not written by this call (its pair lies beyond
 // the last splat its tile blended) and counts as zero. That replaces clearing all records before every backward pass.
 template <int kVec4, int kVals, bool kTagged, int kChunkBits, class Store>
-__device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* __restrict__ status,
+__device__ __forceinline__ void gather_chunk(uint32_t w, uint32_t Pc, int n, const uint32_t* __restrict__ status,
                                             const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ chunk_rank,
                                             const float4* __restrict__ partial, uint32_t cap, float* __restrict__ carry,
                                             uint32_t* sEnd, Store store)
 {
     constexpr int kChunkPairs = 1 << kChunkBits;
     const int lane = threadIdx.x & 63;
-    const uint32_t Pc = min(status[kStNumDup], cap);
     const uint32_t m = min(status[kStNumVis], (uint32_t)n);
     const uint32_t epoch_lo = status[kStEpoch] + 1u, epoch_hi = status[kStEpoch + 1] + (epoch_lo == 0u ? 1u : 0u);
     const uint32_t wbeg = w * (uint32_t)kChunkPairs;
@@ -198,6 +198,16 @@ __device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* _
     }
 }
 
+template <int kVec4, int kVals, bool kTagged, class Store>
+__device__ __forceinline__ void gather_wave(uint32_t w, int n, const uint32_t* __restrict__ status, const uint32_t* __restrict__ offsets,
+                                            const uint32_t* __restrict__ chunk_rank, const float4* __restrict__ partial, uint32_t cap,
+                                            float* __restrict__ carry, uint32_t* sEnd, Store store)
+{
+    const uint32_t Pc = min(status[kStNumDup], cap);
+    if (gather_chunk_bits(Pc) == 6) gather_chunk<kVec4, kVals, kTagged, 6>(w, Pc, n, status, offsets, chunk_rank, partial, cap, carry, sEnd, store);
+    else gather_chunk<kVec4, kVals, kTagged, 8>(w, Pc, n, status, offsets, chunk_rank, partial, cap, carry, sEnd, store);
+}
+
 // For the kernels that read a point's record after the gather. at, count: the
 // point's first pair and its number of pairs. Returns false if all of its pairs lie in one wavefront's chunk (the gather
 // stored the record itself); else v = the right piece of the wavefront its first pair lies in, plus the left pieces of
@@ -213,9 +223,10 @@ __device__ __forceinline__ bool record_from_carries(const CarryFold& cf, uint32_
         for (int k = 0; k < kVals; ++k) v[k] = 0.f;
         return true;
     }
-    const uint32_t w = beg >> cf.chunk_bits;
-    if (end <= (w + 1u) << cf.chunk_bits) return false;
-    const uint32_t nw = (Pc + (1u << cf.chunk_bits) - 1u) >> cf.chunk_bits;
+    const int bits = gather_chunk_bits(Pc);
+    const uint32_t w = beg >> bits;
+    if (end <= (w + 1u) << bits) return false;
+    const uint32_t nw = (Pc + (1u << bits) - 1u) >> bits;
     const float* c = cf.carry + (size_t)w * kCarryFloats;
     const uint32_t rank = reinterpret_cast<const uint32_t*>(c + 32)[2];
 #pragma unroll

@@ -194,7 +194,6 @@ struct CarryFold {
     const uint32_t* slot_base;      // [n] first pair of each listed point
     uint32_t* status;
     uint32_t cap;
-    int chunk_bits;                 // pair_reduce.h
 };
 CarryFold carry_fold(const Layout& L, char* ws);
 

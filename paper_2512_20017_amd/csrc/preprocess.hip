@@ -596,7 +596,7 @@ hipError_t launch_preprocess_bwd(const SceneDev& sc, const CamDev& cam, const in
     if (sc.n == 0) return hipSuccess;
     const unsigned blocks = (unsigned)((sc.n + 255) / 256);
     ProfScope prof(kKPreprocessBwd, s);
-    const CarryFold none{nullptr, nullptr, nullptr, 0u, 0};
+    const CarryFold none{nullptr, nullptr, nullptr, 0u};
     if (first_view) launch_preprocess_bwd_t<true, false>(sc, cam, radius, g2, nullptr, none, g, blocks, s);
     else launch_preprocess_bwd_t<false, false>(sc, cam, radius, g2, nullptr, none, g, blocks, s);
     return hipGetLastError();

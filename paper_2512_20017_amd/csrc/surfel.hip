@@ -880,7 +880,6 @@ struct StoreSplat2DGrad {      // one 64-byte record per point, by point index (
     }
 };
 
-template <int kChunkBits>
 __global__ __launch_bounds__(256) void k_gather2d(int n, const uint32_t* __restrict__ status, const uint32_t* __restrict__ order,
                                                   const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ chunk_rank,
                                                   const float4* __restrict__ partial, uint32_t cap, float* __restrict__ carry,
@@ -888,7 +887,7 @@ __global__ __launch_bounds__(256) void k_gather2d(int n, const uint32_t* __restr
 {
     __shared__ uint32_t sEnd[4][64];
     const uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6);
-    gather_wave<4, 15, false, kChunkBits>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplat2DGrad{rec, order});
+    gather_wave<4, 15, false>(w, n, status, offsets, chunk_rank, partial, cap, carry, sEnd[threadIdx.x >> 6], StoreSplat2DGrad{rec, order});
 }
 
 __global__ __launch_bounds__(256) void k_grad_records_to_planes2d(int n, const uint32_t* __restrict__ tiles_touched,
@@ -994,7 +993,7 @@ hipError_t launch_preprocess2d_bwd(const Scene2DDev& sc, const CamDev& cam, cons
     if (sc.n == 0) return hipSuccess;
     const unsigned blocks = (unsigned)((sc.n + 255) / 256);
     ProfScope prof(kKPreprocessBwd, s);
-    const CarryFold no_fold{nullptr, nullptr, nullptr, 0u, 0};
+    const CarryFold no_fold{nullptr, nullptr, nullptr, 0u};
     if (first_view) launch_preprocess2d_bwd_t<true, false>(sc, cam, sp.radius, sp.T, g2, nullptr, no_fold, g, blocks, s);
     else launch_preprocess2d_bwd_t<false, false>(sc, cam, sp.radius, sp.T, g2, nullptr, no_fold, g, blocks, s);
     return hipGetLastError();
@@ -1063,15 +1062,9 @@ hipError_t launch_composite2d_bwd(const CamDev& cam, const Layout& L, char* ws, 
         const uint32_t* offsets = reinterpret_cast<const uint32_t*>(ws + L.off_offsets);
         const uint32_t* chunk_rank = reinterpret_cast<const uint32_t*>(ws + L.off_chunk_rank);
         float* carry = reinterpret_cast<float*>(ws + L.off_carry);
-        const int bits = gather_chunk_bits(L.cap);
-        const unsigned nwave = (L.cap + (1u << bits) - 1u) >> bits;
+        const unsigned nwave = (unsigned)gather_chunks_max(L.cap);
         float4* rec = reinterpret_cast<float4*>(ws + L.off_grad_rec);
-        if (bits == 6)
-            hipLaunchKernelGGL(k_gather2d<6>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank, partial,
-                           L.cap, carry, rec);
-        else
-            hipLaunchKernelGGL(k_gather2d<8>, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank, partial,
-                           L.cap, carry, rec);
+        hipLaunchKernelGGL(k_gather2d, dim3((nwave + 3) / 4), dim3(256), 0, s, n, status, order, offsets, chunk_rank, partial, L.cap, carry, rec);
         if (g2.mean2d != nullptr)      // else the caller goes on from the records, pieces included (launch_preprocess2d_bwd_records)
             hipLaunchKernelGGL(k_grad_records_to_planes2d, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
                                reinterpret_cast<const uint32_t*>(ws + L.off_touched), rec, carry_fold(L, ws), g2);

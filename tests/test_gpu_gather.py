@@ -92,3 +92,42 @@ def test_room_for_fewer_pairs_than_there_are(model, seed):
     for k in KEYS[model]:
         grad_close(f"{model} cut {k}", got[k], ref[k])
         assert not got[k][dropped].any()
+
+
+@pytest.mark.parametrize("model", ["gauss", "surfel"])
+@pytest.mark.parametrize("seed", [0, 1])
+def test_borders_of_the_sums(model, seed):
+    """Every point against the oracle; and the same bits whatever the room, on both sides of 2^20 pairs of it."""
+    cam, st, P = _strip(model, seed)
+    lists = oracle.bin_sort(st["mean2d"].astype(np.float64), st["radius"], st["depth"], W, H)
+    assert lists["P"] == P
+    G = _loss_gradient(model, st, lists, seed)
+    ref, got = _reference(model, st, lists, G), []
+    for cap in (P, 1 << 20, (1 << 20) + 1):
+        view = _view(model, cam, st, cap)
+        view.render_fwd(BG)
+        got.append(view.render_bwd(BG, G))
+    for k in KEYS[model]:
+        grad_close(f"{model} {k}", got[0][k], ref[k])
+        for g in got[1:]:
+            assert np.array_equal(g[k], got[0][k]), k
+
+
+@pytest.mark.parametrize("model", ["gauss", "surfel"])
+def test_borders_of_the_long_chunks(model):
+    """More than 2^20 pairs, in points of 1 to 640 of them: 256 pairs a wavefront, a segment open from one step of 64 to the next.
+    Three of four points are too faint to blend: the lists are 1,640 splats deep, and 410 blended ones keep the rounding of the
+    walk over them, which is not the subject, as small as in a usual scene."""
+    cam, st, P = _strip(model, 5)
+    copies = (1 << 20) // P + 2
+    n1 = len(st["opacity"])
+    big = {k: np.concatenate([v] * copies) for k, v in st.items()}
+    big["opacity"] = np.where(np.arange(n1 * copies) // n1 % 4 == 0, 0.02, 0.003).astype(np.float32)
+    lists = oracle.bin_sort(big["mean2d"].astype(np.float64), big["radius"], big["depth"], W, H)
+    assert lists["P"] == P * copies > 1 << 20
+    G = _loss_gradient(model, big, lists, 5)
+    view = _view(model, cam, big, lists["P"])
+    view.render_fwd(BG)
+    got, ref = view.render_bwd(BG, G), _reference(model, big, lists, G)
+    for k in KEYS[model]:
+        grad_close(f"{model} long {k}", got[k], ref[k])

@@ -379,7 +379,8 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_fwd(CamDev cam, const ui
     __shared__ uint16_t sHits[4][kFwdBatch2D];     // per quadrant: position in the batch | the quadrant's cells << kPosBits
     __shared__ __align__(8) uint16_t sList[4][4 * 64 + 4];
     __shared__ uint16_t sCells[kFwdBatch2D];
-    __shared__ uint8_t sBlended[4][kFwdBatch2D];   // [quadrant][position in the batch]: a bit per cell that blended it
+    __shared__ uint32_t sBlendedWords[kFwdBatch2D];      // as bytes [quadrant][position in the batch]: a bit per cell that blended it
+    uint8_t* const sBlended = reinterpret_cast<uint8_t*>(sBlendedWords);
     const int tile = (int)tile_order[blockIdx.x];
     const int tiy = tile / cam.TX, tix = tile - tiy * cam.TX;
     const int tx0 = (cam.otx + tix) * kTile, ty0 = (cam.oty + tiy) * kTile;
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_fwd(CamDev cam, const ui
             reach = tile_cells2d(r0, r1, r2, r3, L, x0, y0);
         }
         sCells[threadIdx.x] = (uint16_t)reach;
-        reinterpret_cast<uint32_t*>(sBlended)[threadIdx.x] = 0u;
+        sBlendedWords[threadIdx.x] = 0u;
         __syncthreads();
         uint32_t last_off = ~0u;                     // 16 * place in the batch of the splat the lane blended last
         int nhit = 0;
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_fwd(CamDev cam, const ui
 #pragma unroll
             for (int g = 0; g < 4; ++g)
                 blended |= (uint32_t)__builtin_amdgcn_ds_bpermute((int)((places >> (8 * g)) & 255u) << 2, (int)visit) & m & (1u << g);
-            if (blended) sBlended[wave][at] = (uint8_t)blended;
+            if (blended) sBlended[wave * kFwdBatch2D + at] = (uint8_t)blended;
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             __builtin_amdgcn_wave_barrier();             // the next window overwrites the lists
         }
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(256, 6) void k_composite2d_fwd(CamDev cam, const ui
         if ((int)threadIdx.x < cnt) {
             uint32_t word = 0u;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) word |= (uint32_t)sBlended[q][threadIdx.x] << (4 * q);
+            for (int q = 0; q < 4; ++q) word |= (uint32_t)sBlended[q * kFwdBatch2D + threadIdx.x] << (4 * q);
             blend_words[base + threadIdx.x] = (uint16_t)word;
         }
         if (open == 0) break;                        // every pixel of the tile has ended

@@ -88,9 +88,8 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->off_blk = L->off_blk_cells + nb * sizeof(uint4);
     L->off_blk_at = L->off_blk + nb * sizeof(uint2);
     L->off_sup = L->off_blk_at + nb * sizeof(uint2);
-    // per sorted pair, forward -> backward: the tile's sixteen cells that the splat can reach (3D), that blended it (surfels:
-    // their workspace keeps the size callers know, four bytes, of which the cells take two)
-    L->off_reach = take((size_t)(variant == kVariant2D ? 4 : 2) * cap);
+    // per sorted pair, forward -> backward: a bit for each of the tile's sixteen cells that the splat can reach (3D), that blended it (surfels)
+    L->off_reach = take((size_t)cap * sizeof(uint16_t));
     L->off_tile_order = take((size_t)L->tiles * sizeof(uint32_t));   // tiles in the order the compositing kernels take them
     L->total = off;
     return true;
@@ -257,7 +256,8 @@ int pbdr_status_view(void* workspace, size_t workspace_bytes, int32_t n, int32_t
 {
     Layout L;
     if (!status_words) return PBDR_ERR_INVALID_ARG;
-    // the status block heads both kinds of workspace; the 3D layout is the smaller one, so its size check serves both
+    // the status block heads both kinds of workspace; the 3D layout is the smaller one (records of 48 bytes, not 64), so its size
+    // check serves both
     const int st = workspace_ok(workspace, workspace_bytes, n, width, height, dup_capacity, &L);
     if (st != PBDR_OK) return st;
     *status_words = reinterpret_cast<const uint32_t*>((char*)workspace + L.off_status);

@@ -32,13 +32,15 @@ def test_workspace_bytes():
     big = B.pbdr_workspace_bytes(1_000_000, 1920, 1080, 8_000_000)
     assert 0 < small < big
     assert big % 256 == 0
-    # dominated by 116 B/point (raster record, tile count, offset, slot base, rank -> point, depth bits, 48-byte
-    # gradient record) + 77.1 B/pair (tile keys, values, their ping-pong copies, 48 B of partial gradient sums, 8 B of
-    # inspection keys, per-2048-pair digit counts, per-256-pair chunk data, four bytes of quadrant bits)
-    assert abs(big - (116e6 + 77.1 * 8e6)) < 0.02 * big
-    # surfels: 32 B more per point (64-byte raster and gradient records) and 16 B more per pair (64 B of partial sums)
-    big2 = B.pbdr2d_workspace_bytes(1_000_000, 1920, 1080, 8_000_000)
-    assert abs((big2 - big) - (32e6 + 16 * 8e6)) < 1e5
+    # 132 B/point (64-byte raster record, depth bits, tile count, offset, slot base, rank -> point, 48-byte gradient record) + 74 B/pair
+    # (depth bits, point index, 8 B that the sort and the gather use in turn, 48 B of partial gradient sums, 8 B of inspection
+    # keys, two bytes of cell bits; chunk owners are four bytes per 256 pairs) + 12 B/tile
+    for n, cap in ((1_000_000, 8_000_000), (3_000_000, 2_500_000)):
+        big = B.pbdr_workspace_bytes(n, 1920, 1080, cap)
+        assert abs(big - (132 * n + (74 + 4 / 256) * cap + 12 * 8160)) < 1e5
+        # surfels: 16 B more per point (64-byte gradient records) and 16 B more per pair (64 B of partial sums)
+        big2 = B.pbdr2d_workspace_bytes(n, 1920, 1080, cap)
+        assert abs((big2 - big) - (16 * n + 16 * cap)) < 1e4
     with pytest.raises(B.PbdrError):
         B.pbdr_workspace_bytes(-1, 128, 128, 10)
     with pytest.raises(B.PbdrError):

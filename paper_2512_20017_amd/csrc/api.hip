@@ -69,16 +69,15 @@ bool make_layout(int n, int W, int H, uint64_t cap, int variant, Layout* L)
     L->off_offsets = take(((size_t)n + 1) * sizeof(uint32_t));
     L->off_slot_base = take((size_t)n * sizeof(uint32_t));
     L->off_order = take((size_t)n * sizeof(uint32_t));       // listed points in index order ("rank" -> point)
-    L->off_keys = take((size_t)cap * sizeof(uint32_t));
     L->off_vals = take((size_t)cap * sizeof(uint32_t));
+    L->off_pairs = take((size_t)cap * sizeof(uint2));                    // the lists before they are sorted; the keys that pbdr_lists_view shows
     // the blocks' tiles, then the other half of a list too long for LDS, then the gather's cut pieces
-    L->off_spare = take((size_t)cap * 2 * sizeof(uint32_t));
+    L->off_spare = take((size_t)cap * sizeof(uint2));
     L->off_carry = L->off_spare;
-    static_assert(kCarryFloats * sizeof(float) <= 256 && kCarryFloats * sizeof(float) + 64 * 2 * sizeof(uint32_t) <= 2 * 64 * 2 * sizeof(uint32_t),
+    static_assert(kCarryFloats * sizeof(float) <= 256 && kCarryFloats * sizeof(float) <= 64 * sizeof(uint2),
                   "a piece per 64 pairs fits: one in the 256 bytes of the smallest array, each further one in its own 64 pairs' part");
     L->off_ranges = take((size_t)L->tiles * 2 * sizeof(uint32_t));
     L->off_partial = take((size_t)cap * L->partial_vec4 * 4 * sizeof(float));
-    L->off_keys64 = take((size_t)cap * sizeof(uint64_t));
     L->off_chunk_rank = take((gather_chunks_max((uint32_t)cap) + 1) * sizeof(uint32_t));
     L->off_grad_rec = take((size_t)n * L->partial_vec4 * 4 * sizeof(float));      // per-point gradient records, by point index
     // what binning keeps per block of 256 points lies there too: it is done with before the backward pass starts (40 bytes a block
@@ -529,7 +528,7 @@ static int lists_view(int variant, void* workspace, size_t workspace_bytes, int3
             const hipError_t e = launch_make_keys64(L, ws, (hipStream_t)hip_stream);
             if (e != hipSuccess) return hip_result(e);
         }
-        *keys = reinterpret_cast<const uint64_t*>(ws + L.off_keys64);
+        *keys = reinterpret_cast<const uint64_t*>(ws + L.off_pairs);
     }
     if (vals) *vals = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     if (ranges) *ranges = reinterpret_cast<const uint32_t*>(ws + L.off_ranges);

@@ -366,7 +366,7 @@ hipError_t launch_make_keys64(const Layout& L, char* ws, hipStream_t s)
 {
     const uint32_t* tv = reinterpret_cast<const uint32_t*>(ws + L.off_vals);
     hipLaunchKernelGGL(k_make_keys64, dim3((unsigned)L.tiles), dim3(256), 0, s, reinterpret_cast<const uint32_t*>(ws + L.off_ranges), tv,
-                       reinterpret_cast<const uint32_t*>(ws + L.off_depth_bits), L.cap, reinterpret_cast<uint64_t*>(ws + L.off_keys64));
+                       reinterpret_cast<const uint32_t*>(ws + L.off_depth_bits), L.cap, reinterpret_cast<uint64_t*>(ws + L.off_pairs));
     return hipGetLastError();
 }
 
@@ -396,8 +396,7 @@ BinArrays bin_arrays(const Layout& L, char* ws)
     A.offsets = u32(L.off_offsets);
     A.slot_base = u32(L.off_slot_base);
     A.depth_bits = u32(L.off_depth_bits);
-    A.keys = u32(L.off_keys);
-    A.vals = u32(L.off_vals);
+    A.pairs = reinterpret_cast<uint2*>(ws + L.off_pairs);
     A.chunk_rank = u32(L.off_chunk_rank);
     A.cap = L.cap;
     A.status = u32(L.off_status);

@@ -31,8 +31,7 @@ struct BinArrays {
     uint32_t* offsets;           // [n + 1] first pair of each rank; offsets[listed] = pair total
     uint32_t* slot_base;         // [n] first pair of each listed point, by point index
     uint32_t* depth_bits;        // [n] bit pattern of the depth, by point index
-    uint32_t* keys;              // [cap] depth bits of each pair, tile by tile
-    uint32_t* vals;              // [cap] point index of each pair
+    uint2* pairs;                // [cap] {depth bits, point index}, tile by tile
     uint32_t* chunk_rank;        // rank owning the first pair of every chunk (pair_reduce.h)
     uint32_t cap;
     uint32_t* status;
@@ -261,10 +260,7 @@ __device__ __forceinline__ void pack_block(const BinInput& in, const CamDev& cam
     }
     if (box.x == 0u) return;                     // every pair lies beyond the capacity
     const auto place = [&](uint32_t pos, uint32_t own) {
-        if (pos < A.cap) {                       // always true for consistent inputs
-            A.keys[pos] = sDepth[own];
-            A.vals[pos] = blk * 256u + own;
-        }
+        if (pos < A.cap) A.pairs[pos] = make_uint2(sDepth[own], blk * 256u + own);      // (always, for consistent inputs)
     };
     if (box.x == kDirect) {
         __syncthreads();                         // (the depths)

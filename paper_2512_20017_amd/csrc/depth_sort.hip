@@ -1,6 +1,6 @@
 // Depth order inside each tile's list. The binning kernels leave every tile's list of (depth bits, point index) pairs in no
-// particular order, one that may differ from run to run; here each list is put into the order of the depth bits, equal ones by
-// point index. One launch of workgroups of eight wavefronts, every list on its own:
+// particular order, one that may differ from run to run; here the point indices of each list are put into the order of the depth bits,
+// equal ones by point index. One launch of workgroups of eight wavefronts, every list on its own:
 //   - short lists (long_list_from(): how short depends on how many lists there are; k_tile_lists lists the tiles longest first and
 //     says how many are long): one WAVEFRONT per list, no workgroup barrier anywhere. Up to 64 entries by counting (every lane
 //     compares its key with all others through the scalar unit), else stable least-significant-digit radix passes with 10-bit
@@ -8,7 +8,7 @@
 //     them back in the new order;
 //   - up to 5,632 entries: the same by a whole workgroup, each wavefront with its part of the list in registers;
 //   - up to 8,192: what moves is the permutation (16-bit positions, two copies in LDS); the keys are fetched through it;
-//   - longer lists: keys and values move between the global arrays and a second pair of them, each wavefront sweeping its
+//   - longer lists: the pairs move between the global array and a second one, each wavefront sweeping its
 //     part of the list once per pass (the first pass twice: count, then place; a placing sweep counts for the next pass).
 // A pass ranks its entries per wavefront and round of 64 by ballots (lanes with the same digit find each other), the first lane of
 // each group adds the group's size to the digit's counter in LDS (16 bits wide, two to a word) and gets back how many entries of
@@ -159,25 +159,25 @@ __device__ __forceinline__ uint32_t anew(uint32_t v)
 }
 
 // One wavefront sorts a list of at most 64 entries by counting: how many entries have a smaller key.
-__device__ __forceinline__ void wave_count_list(uint32_t L, const uint32_t* keys, uint32_t* vals)
+__device__ __forceinline__ void wave_count_list(uint32_t L, const uint2* pairs, uint32_t* vals)
 {
     const int lane = threadIdx.x & 63;
     uint32_t k = 0u, v = 0u, before = 0u;
-    if ((uint32_t)lane < L) { k = keys[lane]; v = vals[lane]; }
+    if ((uint32_t)lane < L) { const uint2 p = pairs[lane]; k = p.x; v = p.y; }
     for (uint32_t j = 0; j < L; ++j) before += (uint32_t)__builtin_amdgcn_readlane((int)k, (int)j) < k ? 1u : 0u;
     if ((uint32_t)lane >= L) before = 0u;
     if (wave_reduce(before, OpAdd{}) != L * (L - 1u) / 2u) {      // some are equal: then by value
         for (uint32_t j = 0; j < L; ++j)
             before += ((uint32_t)__builtin_amdgcn_readlane((int)k, (int)j) == k && (uint32_t)__builtin_amdgcn_readlane((int)v, (int)j) < v) ? 1u : 0u;
     }
-    if ((uint32_t)lane < L) vals[min(before, L - 1u)] = v;       // every lane read its entry above
+    if ((uint32_t)lane < L) vals[min(before, L - 1u)] = v;
 }
 
-// One wavefront sorts the list (keys, vals)[0 .. L), 64 < L <= 64 R, in place; the keys are spent. The rounds of 64 are all
+// One wavefront sorts the list pairs[0 .. L), 64 < L <= 64 R, into vals; the pairs are spent. The rounds of 64 are all
 // walked, whatever the length: with a branch around every round none would overlap with the next, and each is a chain of LDS and
 // cross-lane steps.
 template <int R>
-__device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint32_t* keys, uint32_t* vals)
+__device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint2* pairs, uint32_t* vals)
 {
     const int lane = threadIdx.x & 63;
     // the list in its current order: entry r * 64 + lane, with its incoming position. The places behind its end hold the largest
@@ -207,14 +207,15 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint3
     // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
-        const uint32_t* const from = stage == 1 ? vals : keys;
+        uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
+        const uint32_t* const from = words + (stage == 1 ? 1 : 0);      // (every other word)
         const uint32_t at = anew(lane);
         uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             key[r] = 0xffffffffu;
             id[r] = r * 64u + at;
-            if (within(lane, L, r * 64)) { key[r] = from[r * 64u + at]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
+            if (within(lane, L, r * 64)) { key[r] = from[2u * (r * 64u + at)]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
         }
         lo = ~wave_reduce(lo, OpMax{});
         const uint32_t diff = wave_reduce(hi, OpMax{}) - lo;
@@ -244,7 +245,7 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint3
                         const uint32_t p = 2u * ((uint32_t)__builtin_ctz(suspect) * 64u + lane) + (uint32_t)(sweep & 1);
                         const uint32_t ka = W.key[p], kb = W.key[p + 1u];
                         const uint16_t a = W.idx[p], b = W.idx[p + 1u];
-                        if (ka > kb || vals[a] > vals[b]) {
+                        if (ka > kb || pairs[a].y > pairs[b].y) {
                             W.key[p] = kb; W.key[p + 1u] = ka;
                             W.idx[p] = b; W.idx[p + 1u] = a;
                             swapped = true;
@@ -260,23 +261,30 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint3
             }
         }
         if (stage == 0 && !in_order) continue;
-        // through the sorted positions; every entry is fetched before the first is stored
-        const auto put_in_order = [&](uint32_t* list) {
-            const uint32_t to = anew(lane);
+        // through the sorted positions
+        const uint32_t to = anew(lane);
+        if (in_order) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (within(lane, L, r * 64)) key[r] = list[id[r]];
+                if (within(lane, L, r * 64)) key[r] = words[2u * id[r] + 1u];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, r * 64)) vals[r * 64u + to] = key[r];
+            return;
+        }
+#pragma unroll
+        for (uint32_t half = 0; half < 2u; ++half) {      // (every entry is fetched before the first is stored)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, r * 64)) key[r] = words[2u * id[r] + half];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (within(lane, L, r * 64)) list[r * 64u + to] = key[r];
-        };
-        put_in_order(vals);
-        if (in_order) return;
-        put_in_order(keys);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // (read back by other lanes)
-        __builtin_amdgcn_wave_barrier();
+                if (within(lane, L, r * 64)) words[2u * (r * 64u + to) + half] = key[r];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // (read back by other lanes)
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 }
 
@@ -331,7 +339,7 @@ __device__ __forceinline__ uint32_t wg_key_range(WgSortLds& S, uint32_t& lo, uin
 
 // The entries of the list are in order but for neighbours: sweeps over its even and its odd pairs of neighbours in turn. Returns
 // whether the list is in order now. Ends with a barrier.
-__device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint32_t* k, uint32_t* v)
+__device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint2* p)
 {
     int quiet = 0;      // sweeps in a row that found nothing to swap
     for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
@@ -341,13 +349,13 @@ __device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint32_t* k
             const uint32_t first = i0 + 2u * threadIdx.x + (uint32_t)(sweep & 1);
 #pragma unroll
             for (int r = 0; r < 8; ++r) {      // eight pairs of fetches in flight
-                const uint32_t p = first + r * 2u * kSortThreads;
-                if (p + 1u < L && k[p] >= k[p + 1u]) suspect |= 1u << r;
+                const uint32_t i = first + r * 2u * kSortThreads;
+                if (i + 1u < L && p[i].x >= p[i + 1u].x) suspect |= 1u << r;
             }
             for (; suspect; suspect &= suspect - 1u) {
-                const uint32_t p = first + 2u * kSortThreads * (uint32_t)__builtin_ctz(suspect);
-                const uint32_t ka = k[p], kb = k[p + 1u], a = v[p], b = v[p + 1u];
-                if (ka > kb || a > b) { k[p] = kb; k[p + 1u] = ka; v[p] = b; v[p + 1u] = a; swapped = true; }
+                const uint32_t i = first + 2u * kSortThreads * (uint32_t)__builtin_ctz(suspect);
+                const uint2 a = p[i], b = p[i + 1u];
+                if (a.x > b.x || a.y > b.y) { p[i] = b; p[i + 1u] = a; swapped = true; }
             }
         }
         quiet = wg_any(S, sweep, swapped) ? 0 : quiet + 1;
@@ -355,15 +363,15 @@ __device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint32_t* k
     return quiet >= 2;
 }
 
-// A workgroup sorts the list (keys, vals)[0 .. L), L <= kWgListMax, in place; the keys are spent. The permutation idx[c][i] =
+// A workgroup sorts the list pairs[0 .. L), L <= kWgListMax, into vals; the pairs are spent. The permutation perm[c][i] =
 // incoming position of the entry now at i goes back and forth between its two copies in LDS; the keys are fetched through it.
-__device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint32_t* keys, uint32_t* vals)
+__device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint2* pairs, uint32_t* vals)
 {
     uint32_t L = L0;
     constexpr int R = kWgListMax / kSortThreads;
     static_assert(R % 4 == 0, "rounds are taken four at a time");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // each wavefront takes a contiguous quarter of the list, in rounds of 64
+    // each wavefront takes a contiguous eighth of the list, in rounds of 64
     const uint32_t per_wave = ((L + kSortThreads - 1u) / kSortThreads) * 64u;
     const int nr0 = (int)(per_wave / 64u);
     const uint32_t wb = wave * per_wave, we0 = min(L, wb + per_wave);
@@ -386,7 +394,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
                 k[j] = 0u;
                 if (within(lane, we, (int)wb + (r0 + j) * 64)) {
                     const uint32_t i = here[(r0 + j) * 64];
-                    k[j] = from[i];
+                    k[j] = from[2u * i];
                 }
             }
 #pragma unroll
@@ -413,7 +421,8 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
     // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
-        const uint32_t* const from = stage == 1 ? vals : keys;
+        uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
+        const uint32_t* const from = words + (stage == 1 ? 1 : 0);      // (every other word)
         const uint32_t k0 = from[0];
         uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
         for (uint32_t i0 = 0; i0 < L; i0 += 8u * kSortThreads) {      // eight independent fetches in flight
@@ -422,7 +431,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
                 const uint32_t i = i0 + r * (uint32_t)kSortThreads + at;
-                t[r] = within((int)threadIdx.x, L, (int)i0 + r * kSortThreads) ? from[i] : k0;
+                t[r] = within((int)threadIdx.x, L, (int)i0 + r * kSortThreads) ? from[2u * i] : k0;
             }
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
@@ -437,7 +446,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
         const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
         for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits), from, lo);
         // through the sorted positions; every entry is fetched before the first is stored
-        const auto put_in_order = [&](uint32_t* list) {
+        const auto put_in_order = [&](const uint32_t* in, uint32_t* list, uint32_t step) {      // words step apart
             uint32_t out[R];
             const uint32_t to = anew(threadIdx.x);
             L = anew_uniform(L0);
@@ -446,7 +455,7 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
 #pragma unroll
                 for (int r = r0; r < r0 + 8 && r < R; ++r) {
                     out[r] = 0u;
-                    if (within((int)threadIdx.x, L, r * kSortThreads)) out[r] = list[src[r * kSortThreads + threadIdx.x]];
+                    if (within((int)threadIdx.x, L, r * kSortThreads)) out[r] = in[2u * src[r * kSortThreads + threadIdx.x]];
                 }
                 asm volatile("" ::: "memory");
             }
@@ -454,22 +463,25 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint3
             L = anew_uniform(L0);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if (within((int)threadIdx.x, L, r * kSortThreads)) list[r * kSortThreads + to] = out[r];
+                if (within((int)threadIdx.x, L, r * kSortThreads)) list[step * (r * kSortThreads + to)] = out[r];
             }
         };
-        put_in_order(vals);
-        if (stage == 2) return;
-        put_in_order(keys);
+        if (stage == 2) { put_in_order(words + 1, vals, 1u); return; }
+        put_in_order(words + 1, words + 1, 2u);
+        put_in_order(words, words, 2u);
         __syncthreads();      // (also: the permutation may be written again)
-        if (stage == 0 && tie_sweeps(S, L, keys, vals)) return;
+        if (stage == 0 && tie_sweeps(S, L, pairs)) {
+            for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) vals[i] = pairs[i].y;
+            return;
+        }
     }
 }
 
-// A workgroup sorts the list (keys, vals)[0 .. L), L <= 4 * 64 R, in place; the keys are spent. As one wavefront does it, but for
-// the counters: each wavefront holds a quarter of the places, R rounds of 64, and counts for itself; where its entries of a digit
+// A workgroup sorts the list pairs[0 .. L), L <= 8 * 64 R, into vals; the pairs are spent. As one wavefront does it, but for
+// the counters: each wavefront holds an eighth of the places, R rounds of 64, and counts for itself; where its entries of a digit
 // go then depends on the others' counts.
 template <int R>
-__device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t* keys, uint32_t* vals)
+__device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint2* pairs, uint32_t* vals)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int first = wave * 64 * R;
@@ -497,14 +509,15 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t*
     // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
-        const uint32_t* const from = stage == 1 ? vals : keys;
+        uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
+        const uint32_t* const from = words + (stage == 1 ? 1 : 0);      // (every other word)
         const uint32_t at = anew(first + lane);
         uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             key[r] = 0xffffffffu;
             id[r] = r * 64u + at;
-            if (within(lane, L, first + r * 64)) { key[r] = from[r * 64u + at]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
+            if (within(lane, L, first + r * 64)) { key[r] = from[2u * (r * 64u + at)]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
         }
         const uint32_t diff = wg_key_range(S, lo, hi);
 #pragma unroll
@@ -532,7 +545,7 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t*
                         const int p = base + 2 * kSortThreads * __builtin_ctz(suspect);
                         const uint32_t ka = S.key[p], kb = S.key[p + 1];
                         const uint16_t a = S.idx[p], b = S.idx[p + 1];
-                        if (ka > kb || vals[a] > vals[b]) {
+                        if (ka > kb || pairs[a].y > pairs[b].y) {
                             S.key[p] = kb; S.key[p + 1] = ka;
                             S.idx[p] = b; S.idx[p + 1] = a;
                             swapped = true;
@@ -546,20 +559,27 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint32_t*
             }
         }
         if (stage == 0 && !in_order) { __syncthreads(); continue; }
-        // through the sorted positions; every entry is fetched before the first is stored
-        const auto put_in_order = [&](uint32_t* list) {
-            const uint32_t to = anew(first + lane);
+        // through the sorted positions
+        const uint32_t to = anew(first + lane);
+        if (in_order) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (within(lane, L, first + r * 64)) key[r] = list[id[r]];
+                if (within(lane, L, first + r * 64)) key[r] = words[2u * id[r] + 1u];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, first + r * 64)) vals[r * 64u + to] = key[r];
+            return;
+        }
+#pragma unroll
+        for (uint32_t half = 0; half < 2u; ++half) {      // (every entry is fetched before the first is stored)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, first + r * 64)) key[r] = words[2u * id[r] + half];
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (within(lane, L, first + r * 64)) list[r * 64u + to] = key[r];
-        };
-        put_in_order(vals);
-        if (in_order) return;
-        put_in_order(keys);
+                if (within(lane, L, first + r * 64)) words[2u * (r * 64u + to) + half] = key[r];
+        }
         __syncthreads();
     }
 }
@@ -578,17 +598,16 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
     return below;
 }
 
-// Lists too long for LDS: one stable pass by the digit at `shift` from (kin, vin) to (kout, vout), all of length L
-// in global memory. Each wavefront takes a contiguous quarter of the list, in rounds of 64. `cur` holds, per wavefront
+// Lists too long for LDS: one stable pass by the digit at `shift` of the depth bits, or of the point indices, from in to out, both of
+// length L in global memory. Each wavefront takes a contiguous eighth of the list, in rounds of 64. `cur` holds, per wavefront
 // and digit, how many of its entries have that digit: counted here in a sweep of its own if `count_first`, else by
-// the previous pass, which knew where every entry went and so in whose quarter it would be (that is what `nxt` and
+// the previous pass, which knew where every entry went and so in whose eighth it would be (that is what `nxt` and
 // `next_shift` are for: pass a negative shift when no pass follows). The counters are then turned into where the
 // wavefront's first entry of each digit goes, and a sweep places the entries: digit_prefix() hands back the counter's
 // value before the round's entries were added plus the lane's rank among them, which now is the entry's position.
 // Nothing is kept per entry between the sweeps, so the list may be of any length.
 __device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLongBins], uint32_t (*nxt)[kLongBins], bool count_first, uint32_t L, uint32_t lo,
-                                               int shift, int next_shift, const uint32_t* __restrict__ kin,
-                                               const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout, uint32_t* __restrict__ vout)
+                                               int shift, int next_shift, bool by_index, const uint2* __restrict__ in, uint2* __restrict__ out)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t per_wave = ((L + kSortThreads - 1u) / kSortThreads) * 64u;
@@ -602,7 +621,7 @@ __device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLo
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const uint32_t i = i0 + j * 64u + lane;
-                k[j] = i < we ? kin[i] : 0u;
+                k[j] = i < we ? (by_index ? in[i].y : in[i].x) : 0u;
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j)
@@ -621,25 +640,25 @@ __device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLo
     }
     __syncthreads();
     for (uint32_t i0 = wb; i0 < we; i0 += 8u * 64u) {
-        uint32_t k[8], v[8];
+        uint2 p[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const uint32_t i = i0 + j * 64u + lane;
-            k[j] = 0u; v[j] = 0u;
-            if (i < we) { k[j] = kin[i]; v[j] = vin[i]; }
+            p[j] = i < we ? in[i] : make_uint2(0u, 0u);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             if (i0 + j * 64u < we) {
                 const bool valid = i0 + j * 64u + lane < we;
-                const uint32_t pos = min(digit_prefix<kLongBits, false>(cur[wave], ((k[j] - lo) >> shift) & (kLongBins - 1u), valid), L - 1u);      // < L for consistent counts
+                const uint32_t k = (by_index ? p[j].y : p[j].x) - lo;
+                const uint32_t pos = min(digit_prefix<kLongBits, false>(cur[wave], (k >> shift) & (kLongBins - 1u), valid), L - 1u);      // < L for consistent counts
                 if (valid) {
-                    kout[pos] = k[j]; vout[pos] = v[j];
+                    out[pos] = p[j];
                     if (next_shift >= 0) {      // the next pass finds this entry in the part of wavefront pos / per_wave
                         uint32_t w2 = 0u;
 #pragma unroll
                         for (uint32_t w = 1u; w < (uint32_t)kSortWaves; ++w) w2 += pos >= w * per_wave ? 1u : 0u;
-                        atomicAdd(&nxt[w2][((k[j] - lo) >> next_shift) & (kLongBins - 1u)], 1u);
+                        atomicAdd(&nxt[w2][(k >> next_shift) & (kLongBins - 1u)], 1u);
                     }
                 }
             }
@@ -648,65 +667,58 @@ __device__ __forceinline__ void long_list_pass(WgSortLds& S, uint32_t (*cur)[kLo
     __syncthreads();      // the pass is written and the next pass's counts are complete
 }
 
-// One list too long for a wavefront, sorted by the whole workgroup (every exit is uniform for the workgroup).
-__device__ __forceinline__ void wg_sort_big(WgSortLds& S, uint32_t s, uint32_t e, const uint32_t* __restrict__ depth_bits,
-                                            uint32_t* __restrict__ keysA, uint32_t* __restrict__ valsA,
-                                            uint32_t* __restrict__ keysB, uint32_t* __restrict__ valsB)
+// A workgroup sorts a list of any length, pairs[0 .. L), into vals, from one array to the other and back.
+__device__ __forceinline__ void wg_sort_long(WgSortLds& S, uint32_t L, uint2* pairs, uint2* spare, uint32_t* vals)
 {
-    if (e <= s + 1u) return;
-    const uint32_t L = e - s;
-    if (L <= (uint32_t)kWgListMax) { wg_permute_list(S, L, keysA + s, valsA + s); return; }
-    // through global memory, from one pair of arrays to the other
     // the two sets of counters swap roles from pass to pass
     uint32_t (*c0)[kLongBins] = S.count[0];
     uint32_t (*c1)[kLongBins] = S.count[1];
-    uint32_t *k = keysA + s, *v = valsA + s, *k2 = keysB + s, *v2 = valsB + s;      // the list, and where the next pass puts it
+    uint2 *here = pairs, *there = spare;      // the list, and where the next pass puts it
+    // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
 #pragma unroll 1
     for (int stage = 0; stage < 3; ++stage) {
-        if (stage > 0) {
-            for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) k[i] = stage == 1 ? v[i] : depth_bits[v[i]];
-            __syncthreads();
-        }
         uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
-        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) { lo = max(lo, ~k[i]); hi = max(hi, k[i]); }
+        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) {
+            const uint32_t k = stage == 1 ? here[i].y : here[i].x;
+            lo = max(lo, ~k); hi = max(hi, k);
+        }
         const uint32_t diff = wg_key_range(S, lo, hi);
         const Passes ps = list_passes(diff, 32, kLongBits);
         for (int p = 0; p < ps.count; ++p) {
             const int next_shift = p + 1 < ps.count ? list_shift(ps, p + 1, kLongBits) : -1;
-            long_list_pass(S, (p & 1) ? c1 : c0, (p & 1) ? c0 : c1, p == 0, L, lo, list_shift(ps, p, kLongBits), next_shift, k, v, k2, v2);
-            uint32_t* t = k; k = k2; k2 = t;
-            t = v; v = v2; v2 = t;
+            long_list_pass(S, (p & 1) ? c1 : c0, (p & 1) ? c0 : c1, p == 0, L, lo, list_shift(ps, p, kLongBits), next_shift, stage == 1, here, there);
+            uint2* t = here; here = there; there = t;
         }
-        if (stage == 0 && tie_sweeps(S, L, k, v)) break;
+        if (stage == 0 && tie_sweeps(S, L, here)) break;
         __syncthreads();
     }
-    if (v != valsA + s)
-        for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) valsA[s + i] = v[i];
+    for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) vals[i] = here[i].y;
 }
 
 // Work items: tile_order lists the tiles longest first and its first `nbig` tiles are too long for one wavefront, so
-// workgroups 0 .. nbig - 1 take one such list each, and every later workgroup takes four shorter lists, one per
+// workgroups 0 .. nbig - 1 take one such list each, and every later workgroup takes eight shorter lists, one per
 // wavefront.
 __global__ __launch_bounds__(kSortThreads, 6) void k_tile_depth_sort(const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
                                                             uint32_t ntiles, const uint32_t* __restrict__ status,
-                                                            const uint32_t* __restrict__ depth_bits, uint32_t cap,
-                                                            uint32_t* __restrict__ keysA, uint32_t* __restrict__ valsA,
-                                                            uint32_t* __restrict__ keysB, uint32_t* __restrict__ valsB)
+                                                            uint32_t cap, uint2* __restrict__ pairs, uint32_t* __restrict__ vals,
+                                                            uint2* __restrict__ spare)
 {
     __shared__ ListSortLds U;
     const uint32_t nbig = min(status[kStNumBig], ntiles);
     if (blockIdx.x < nbig) {
         const uint32_t tile = tile_order[blockIdx.x];
         const uint32_t s = ranges[2 * tile], e = min(ranges[2 * tile + 1], cap), L = e > s ? e - s : 0u;
-        uint32_t *k = keysA + s, *v = valsA + s;
-        if (L > (uint32_t)kWgKeyMax) wg_sort_big(U.wg, s, e, depth_bits, keysA, valsA, keysB, valsB);
-        else if (L > 8u * kSortThreads) wg_sort_list<11>(U.wg, L, k, v);
-        else if (L > 6u * kSortThreads) wg_sort_list<8>(U.wg, L, k, v);
-        else if (L > 4u * kSortThreads) wg_sort_list<6>(U.wg, L, k, v);
-        else if (L > 3u * kSortThreads) wg_sort_list<4>(U.wg, L, k, v);
-        else if (L > 2u * kSortThreads) wg_sort_list<3>(U.wg, L, k, v);
-        else if (L > (uint32_t)kSortThreads) wg_sort_list<2>(U.wg, L, k, v);
-        else if (L > 1u) wg_sort_list<1>(U.wg, L, k, v);
+        uint2* const p = pairs + s;
+        uint32_t* const v = vals + s;
+        if (L > (uint32_t)kWgListMax) wg_sort_long(U.wg, L, p, spare + s, v);
+        else if (L > (uint32_t)kWgKeyMax) wg_permute_list(U.wg, L, p, v);
+        else if (L > 8u * kSortThreads) wg_sort_list<11>(U.wg, L, p, v);
+        else if (L > 6u * kSortThreads) wg_sort_list<8>(U.wg, L, p, v);
+        else if (L > 4u * kSortThreads) wg_sort_list<6>(U.wg, L, p, v);
+        else if (L > 3u * kSortThreads) wg_sort_list<4>(U.wg, L, p, v);
+        else if (L > 2u * kSortThreads) wg_sort_list<3>(U.wg, L, p, v);
+        else if (L > (uint32_t)kSortThreads) wg_sort_list<2>(U.wg, L, p, v);
+        else if (L > 0u) wg_sort_list<1>(U.wg, L, p, v);
         return;
     }
     // (uniform per wavefront, which the compiler has to be told: then the rounds of a list are scalar branches)
@@ -715,18 +727,19 @@ __global__ __launch_bounds__(kSortThreads, 6) void k_tile_depth_sort(const uint3
     if (idx >= ntiles) return;
     const uint32_t tile = tile_order[idx];
     const uint32_t s = ranges[2 * tile], e = min(ranges[2 * tile + 1], cap);
-    if (e <= s + 1u) return;
+    if (e <= s) return;
     // (a list of long_list_from() entries or more cannot come here: k_tile_lists counted it among the first nbig)
     WaveSortLds& W = U.wave[wave];
     const uint32_t L = e - s;
-    uint32_t *k = keysA + s, *v = valsA + s;
-    if (L <= 64u) wave_count_list(L, k, v);
-    else if (L <= 128u) wave_sort_list<2>(W, L, k, v);
-    else if (L <= 192u) wave_sort_list<3>(W, L, k, v);
-    else if (L <= 256u) wave_sort_list<4>(W, L, k, v);
-    else if (L <= 384u) wave_sort_list<6>(W, L, k, v);
-    else if (L <= 512u) wave_sort_list<8>(W, L, k, v);
-    else if (L <= (uint32_t)kWaveListMax) wave_sort_list<kWaveListMax / 64>(W, L, k, v);
+    uint2* const p = pairs + s;
+    uint32_t* const v = vals + s;
+    if (L <= 64u) wave_count_list(L, p, v);
+    else if (L <= 128u) wave_sort_list<2>(W, L, p, v);
+    else if (L <= 192u) wave_sort_list<3>(W, L, p, v);
+    else if (L <= 256u) wave_sort_list<4>(W, L, p, v);
+    else if (L <= 384u) wave_sort_list<6>(W, L, p, v);
+    else if (L <= 512u) wave_sort_list<8>(W, L, p, v);
+    else if (L <= (uint32_t)kWaveListMax) wave_sort_list<kWaveListMax / 64>(W, L, p, v);
 }
 
 hipError_t launch_tile_depth_sort(const CamDev& cam, const Layout& L, char* ws, hipStream_t s)
@@ -740,7 +753,7 @@ hipError_t launch_tile_depth_sort(const CamDev& cam, const Layout& L, char* ws, 
     const uint32_t big_max = min(ntiles, L.cap / long_list_from(ntiles) + 1u);
     const uint32_t items_max = min(ntiles, big_max + (ntiles + kSortWaves - 1u) / kSortWaves);
     hipLaunchKernelGGL(k_tile_depth_sort, dim3(items_max), dim3(kSortThreads), 0, s, u32(L.off_ranges), u32(L.off_tile_order), ntiles, u32(L.off_status),
-                       u32(L.off_depth_bits), L.cap, u32(L.off_keys), u32(L.off_vals), u32(L.off_spare), u32(L.off_spare) + L.cap);
+                       L.cap, reinterpret_cast<uint2*>(ws + L.off_pairs), u32(L.off_vals), reinterpret_cast<uint2*>(ws + L.off_spare));
     return hipGetLastError();
 }
 

@@ -165,7 +165,7 @@ struct Layout {
     int partial_vec4;         // float4s of partial gradient sums per pair: 3 (3D) or 4 (2D)
     uint32_t cap;
     size_t off_status, off_packed, off_depth_bits, off_blk, off_sup, off_blk_at, off_blk_cells, off_touched, off_offsets, off_slot_base, off_order,
-        off_keys, off_vals, off_spare, off_ranges, off_partial, off_keys64, off_chunk_rank, off_carry, off_grad_rec, off_reach,
+        off_vals, off_pairs, off_spare, off_ranges, off_partial, off_chunk_rank, off_carry, off_grad_rec, off_reach,
         off_tile_order, total;
 };
 // A tile's list of fewer than long_list_from() entries is put in depth order by one wavefront, a longer one by a whole workgroup
@@ -225,8 +225,8 @@ hipError_t launch_composite_bwd(const CamDev& cam, const Layout& L, char* ws, in
 
 hipError_t launch_render_stats(const CamDev& cam, const Layout& L, char* ws, uint64_t* counters, hipStream_t s);
 
-// every tile's list (keys = depth bits, vals = point indices, in any order) into the order of the depth bits, equal ones by
-// point index; the keys are spent
+// every tile's list (pairs of depth bits and point index, in any order) into vals, the point indices in the order of the depth
+// bits, equal ones by point index; the pairs are spent
 hipError_t launch_tile_depth_sort(const CamDev& cam, const Layout& L, char* ws, hipStream_t s);
 hipError_t launch_make_keys64(const Layout& L, char* ws, hipStream_t s);
 

@@ -32,12 +32,12 @@ def test_workspace_bytes():
     big = B.pbdr_workspace_bytes(1_000_000, 1920, 1080, 8_000_000)
     assert 0 < small < big
     assert big % 256 == 0
-    # 132 B/point (64-byte raster record, depth bits, tile count, offset, slot base, rank -> point, 48-byte gradient record) + 74 B/pair
-    # (depth bits, point index, 8 B that the sort and the gather use in turn, 48 B of partial gradient sums, 8 B of inspection
-    # keys, two bytes of cell bits; chunk owners are four bytes per 256 pairs) + 12 B/tile
+    # 132 B/point (64-byte raster record, depth bits, tile count, offset, slot base, rank -> point, 48-byte gradient record) + 70 B/pair
+    # (point index, the unsorted {depth bits, point index} or inspection keys, 8 B that the sort and the gather use in turn, 48 B of
+    # partial gradient sums, two bytes of cell bits; chunk owners are four bytes per 256 pairs) + 12 B/tile
     for n, cap in ((1_000_000, 8_000_000), (3_000_000, 2_500_000)):
         big = B.pbdr_workspace_bytes(n, 1920, 1080, cap)
-        assert abs(big - (132 * n + (74 + 4 / 256) * cap + 12 * 8160)) < 1e5
+        assert abs(big - (132 * n + (70 + 4 / 256) * cap + 12 * 8160)) < 1e5
         # surfels: 16 B more per point (64-byte gradient records) and 16 B more per pair (64 B of partial sums)
         big2 = B.pbdr2d_workspace_bytes(n, 1920, 1080, cap)
         assert abs((big2 - big) - (16 * n + 16 * cap)) < 1e4

@@ -19,14 +19,18 @@
 // they are differ in 31 bits where a list has depths on both sides of 2.0, which every tile of a street has: 11 bits too coarse, and
 // most lists were sorted three times over, 192 us -> 134 for 7.3 M pairs at 3840x2160). That orders a list but for
 // neighbours, some per thousand entries, that agree in those bits, and for equal
-// depths, which are in order only if they came in order. Neighbours out of order are looked for after the passes and put right by
-// swapping, over the even and the odd pairs of neighbours in turn, kTiePhases sweeps at most; if that does not do (many equal
-// depths), the list is sorted again by all bits: first by point index and then, which keeps that order, by depth.
+// depths, which are in order only if they came in order. Such runs of equal bits are put right by counting: every entry of a run
+// compares its depth and point index with the others' and goes to its rank. Where a run is longer than kCountRun entries (whole walls
+// at one depth), the runs are numbered and the list is sorted again by number and point index in one key; where such a list also has
+// depths that agree in the top bits and differ below, or where the key would not fit a word, by point index and then, which keeps
+// that order, by all bits of the depths. All lists of 1M points at 1920x1080, binning included, with the depths rounded to 4, to 0.5 and to
+// 0.03 (of 10 to 20 units), and each value four times, against sweeps that swapped neighbours, eight of them before all three sorts:
+// 141 -> 106, 142 -> 109, 138 -> 104, 124 -> 90; as they are 80.
 //
 // The work is a chain of dependent LDS and cross-lane steps per list, and what hides it is other lists in flight: three workgroups
 // per compute unit by LDS, 24 wavefronts, at most 80 registers. No scratch memory: a launch that has any is slower by tens of us.
 // Against three 9-bit passes with a branch around every round of 64, four wavefronts to a workgroup, one list alone (us): 100
-// entries 8.0 -> 3.2, 256 9.8 -> 4.6, 512 13.7 -> 8.1, 768 17.5 -> 5.7, 2,000 16.5 -> 10.2, 4,600 34.6 -> 21.0, 7,800 71.2 -> 33.9. All lists of
+// entries 8.0 -> 3.7, 256 9.8 -> 4.4, 512 13.7 -> 4.6, 768 17.5 -> 5.9, 2,000 16.5 -> 11.5, 4,600 34.6 -> 22.6, 7,800 71.2 -> 35.6. All lists of
 // 1M points at 1920x1080 (8,160 tiles, 1.9 M pairs, the longest list 4,835): 38 -> 28; 4,096 points at 128x128 20.4 -> 8.3.
 // (Measured and dropped: each wavefront sorting its part and then finding every entry's place by binary search in the other parts:
 // 2,000 entries 18 us, 4,600 37.)
@@ -37,7 +41,6 @@
 
 namespace pbdr {
 
-constexpr int kTiePhases = 8;
 constexpr int kSortWaves = 8, kSortThreads = 64 * kSortWaves;      // a workgroup
 constexpr int kListBits = 10;                         // digit width of the list sorts
 constexpr int kListBins = 1 << kListBits;
@@ -50,22 +53,32 @@ static_assert(kWaveListMax % 64 == 0, "whole rounds");
 constexpr int kWgKeyMax = 11 * kSortThreads;           // a workgroup's list with its keys in registers and LDS (11 rounds per wavefront)
 constexpr int kWgListMax = 16 * kSortThreads;          // a workgroup's list with its permutation in LDS (16 rounds per wavefront)
 
+// Runs of more entries with equal bits are not put right by counting, whose time grows with the run (64 instead of 32: depths rounded to
+// 4 units 104 -> 109 us; 16: each value four times 90 -> 102).
+constexpr uint32_t kCountRun = 32;
+constexpr uint32_t kCountRunInMemory = 16;      // for the lists that do not fit the LDS, whose entries are fetched from memory each time
+
 struct WaveSortLds {      // a wavefront's share of the LDS when it sorts a list of its own
     uint32_t key[kWaveListMax];
-    uint16_t idx[kWaveListMax];
-    uint32_t hist[kListWords];
+    union {
+        struct { uint16_t idx[kWaveListMax]; uint32_t hist[kListWords]; };
+        uint32_t val[kWaveListMax];      // (once the passes are done)
+    };
 };
 struct WgSortLds {        // the workgroup's LDS when it sorts one list together
     union {
         struct { uint32_t key[kWgKeyMax]; uint16_t idx[kWgKeyMax]; };        // the list, keys and incoming positions
+        struct { uint32_t key_[kWgKeyMax]; uint32_t val[kWgKeyMax]; };       // keys and point indices, once the passes are done
         uint16_t perm[2][kWgListMax];                                        // the permutation alone, twice
         uint32_t count[2][kSortWaves][kLongBins];                                     // two sets of full-width counters
+        // per wavefront and digit: entries in the wavefront's part of the list, then where its first entry of that digit goes
+        struct { uint32_t first_[kWgKeyMax + kWgKeyMax / 2]; uint32_t cnt[kSortWaves][kListWords]; };
     };
-    uint32_t cnt[kSortWaves][kListWords];                             // per wavefront and digit: entries in the wavefront's part of the list, then where its first entry of that digit goes
     uint32_t scan[kSortWaves];
     uint32_t any[2][kSortWaves];
     uint2 range[kSortWaves];
 };
+static_assert(sizeof(WgSortLds::perm) <= sizeof(WgSortLds::first_), "the permutation and the counters at the same time");
 union ListSortLds { WgSortLds wg; WaveSortLds wave[kSortWaves]; };
 static_assert(sizeof(ListSortLds) <= 53 * 1024, "three workgroups per compute unit");
 
@@ -79,6 +92,10 @@ __device__ __forceinline__ Passes list_passes(uint32_t range, int bits, int digi
     return Passes{lo, (hi - lo + digit) / digit};
 }
 __device__ __forceinline__ int list_shift(const Passes& p, int i, int digit) { return min(p.lo + digit * i, 32 - digit); }
+
+// What a list in LDS is being sorted by: the top bits of the depths; the number of the run of equal depths, above the point index;
+// where those two do not fit a word, the point index and then, which keeps that order, all bits of the depths.
+enum class SortBy { kDepthTop, kRun, kIndex, kDepth };
 
 // Entries of this wavefront with the same digit as this lane's that come before it: earlier rounds (through the
 // digit's counter in `hist`, a row no other wavefront touches) plus lower lanes of this round. The lanes that share the
@@ -145,6 +162,9 @@ __device__ __forceinline__ void wave_lds_sync()      // orders this wavefront's 
 // i < n - before, on the scalar side but for the comparison: "before + i < n" would keep a register for every before
 __device__ __forceinline__ bool within(int i, uint32_t n, int before) { return i < (int)n - before; }
 
+// how many lanes of the set lie below this one
+__device__ __forceinline__ uint32_t lanes_below(uint64_t set) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0u)); }
+
 // The same value, as one that the compiler does not know: addresses and masks made of it are made where they stand. Else those of
 // all of a list's rounds are worked out ahead of everything, and there are not enough registers to keep them.
 __device__ __forceinline__ uint32_t anew_uniform(uint32_t v)
@@ -156,6 +176,87 @@ __device__ __forceinline__ uint32_t anew(uint32_t v)
 {
     asm volatile("" : "+v"(v));
     return v;
+}
+
+// The list keys[0 .. L), values[0 .. L) in LDS is in order but for the runs of entries that agree in the bits from `shift` on. Puts the
+// values of places `base` .. base + 63 where they belong: each entry of a run counts how many of the run come before it. One
+// wavefront; the LDS holds whole rounds of 64 places.
+__device__ __forceinline__ void rank_round(const uint32_t* keys, const uint32_t* values, uint32_t L, int shift, uint32_t base, uint32_t* out)
+{
+    const uint32_t lane = anew(threadIdx.x) & 63u, place = base + lane;
+    // where runs start, a bit per place of a round (each place behind the end is a run of its own)
+    const auto starts = [&](uint32_t b) {
+        const uint32_t p = b + lane;
+        return __ballot(p >= L || p == 0u || (keys[p] >> shift) != (keys[max(p, 1u) - 1u] >> shift));
+    };
+    const uint64_t here = starts(base), upto = ~0ull >> (63u - lane);
+    uint32_t before = base, behind = base + 64u;      // the last start before the round's places, the first one behind them
+    if ((here & 1ull) == 0ull) {
+        uint64_t h;
+        do { before -= 64u; h = starts(before); } while (h == 0ull);      // (place 0 is a start)
+        before += 63u - (uint32_t)__builtin_clzll(h);
+    }
+    while (behind < L) {
+        const uint64_t h = starts(behind);
+        if (h) { behind += (uint32_t)__builtin_ctzll(h); break; }
+        behind += 64u;
+    }
+    const uint64_t lo = here & upto, hi = here & ~upto;
+    const uint32_t s = lo ? base + 63u - (uint32_t)__builtin_clzll(lo) : before;
+    const uint32_t n = (hi ? base + (uint32_t)__builtin_ctzll(hi) : behind) - s;      // of the run: one or more
+    const uint32_t value = values[place];
+    const uint64_t mine = (uint64_t)keys[place] << 32 | value;
+    uint32_t rank = 0u;
+    if (__ballot(n > 1u) != 0ull) {
+        for (uint32_t d = 0; __ballot(d < n) != 0ull; d += 4u) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t j = s + min(d + q, n - 1u);
+                rank += (d + q < n && ((uint64_t)keys[j] << 32 | values[j]) < mine) ? 1u : 0u;
+            }
+        }
+    }
+    if (place < L) out[min(s + rank, L - 1u)] = value;      // (always below)
+}
+
+// Which of the wavefront's R rounds hold an entry of a run of two or more? agree: a bit per round, this lane's entry agrees with the next place's.
+__device__ __forceinline__ uint32_t rounds_of(uint32_t agree, int R)
+{
+    uint32_t rounds = 0u;
+    for (int r = 0; r < R; ++r) {
+        const uint64_t b = __ballot((agree >> r) & 1u);
+        if (b) rounds |= (1u << r) | (uint32_t)(b >> 63) << (r + 1);
+    }
+    return rounds & ((1u << R) - 1u);
+}
+
+// Of a list in LDS in order of the bits from `shift` on, in the rounds of 64 places from `first` on that `rounds` names: does a run of entries
+// that agree in those bits have more than kCountRun? One wavefront.
+__device__ __forceinline__ bool long_runs(const uint32_t* keys, uint32_t L, int shift, uint32_t first, uint32_t rounds)
+{
+    bool any = false;
+    for (; rounds != 0u; rounds &= rounds - 1u) {
+        const uint32_t p = first + 64u * (uint32_t)__builtin_ctz(rounds) + (anew(threadIdx.x) & 63u);
+        any |= p + kCountRun < L && keys[p + kCountRun] >> shift == keys[p] >> shift;
+    }
+    return __ballot(any) != 0ull;
+}
+
+// Do neighbours that agree in those bits differ below? Of the places from `place` on, `step` apart.
+__device__ __forceinline__ bool mixed_runs(const uint32_t* keys, uint32_t L, int shift, uint32_t place, uint32_t step)
+{
+    bool any = false;
+    for (uint32_t p = place; p + 1u < L; p += step) any |= keys[p] != keys[p + 1u] && keys[p] >> shift == keys[p + 1u] >> shift;
+    return any;
+}
+
+// Keys of the number of an entry's run, 0 .. last_run, above its point index less the list's smallest, 0 .. values.
+struct RunKey { bool fits; int bits; uint32_t mask, range; };
+__device__ __forceinline__ RunKey run_key(uint32_t last_run, uint32_t values)
+{
+    const int bits = 32 - __builtin_clz(values | 1u), run_bits = last_run ? 32 - __builtin_clz(last_run) : 0;
+    const uint32_t mask = (1u << (bits & 31)) - 1u;
+    return RunKey{bits + run_bits <= 32 && bits < 32, bits & 31, mask, last_run << (bits & 31) | mask};
 }
 
 // One wavefront sorts a list of at most 64 entries by counting: how many entries have a smaller key.
@@ -204,66 +305,102 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint2
         for (int r = 0; r < R; ++r) { key[r] = W.key[r * 64u + lane]; id[r] = W.idx[r * 64u + lane]; }
         wave_lds_sync();      // (the next pass, or the next list of this wavefront, writes the buffer again)
     };
-    // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
+    uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
+    SortBy by = SortBy::kDepthTop;
+    uint32_t range = 0u, value_base = 0u, value_mask = 0u;
 #pragma unroll 1
-    for (int stage = 0; stage < 3; ++stage) {
-        uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
-        const uint32_t* const from = words + (stage == 1 ? 1 : 0);      // (every other word)
-        const uint32_t at = anew(lane);
-        uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
+    for (;;) {
+        if (by != SortBy::kRun) {
+            const uint32_t* const from = words + (by == SortBy::kIndex ? 1 : 0);      // (every other word)
+            const uint32_t at = anew(lane);
+            uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            key[r] = 0xffffffffu;
-            id[r] = r * 64u + at;
-            if (within(lane, L, r * 64)) { key[r] = from[2u * (r * 64u + at)]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
-        }
-        lo = ~wave_reduce(lo, OpMax{});
-        const uint32_t diff = wave_reduce(hi, OpMax{}) - lo;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (within(lane, L, r * 64)) key[r] -= lo;
-        const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
-        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
-        bool in_order = stage == 2;
-        if (stage == 0 && diff != 0u) {
-            bool tie = false;
+            for (int r = 0; r < R; ++r) {
+                key[r] = 0xffffffffu;
+                id[r] = r * 64u + at;
+                if (within(lane, L, r * 64)) { key[r] = from[2u * (r * 64u + at)]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
+            }
+            lo = ~wave_reduce(lo, OpMax{});
+            range = wave_reduce(hi, OpMax{}) - lo;
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (within(lane + 1, L, r * 64)) tie |= W.key[r * 64u + lane + 1u] <= key[r];
-            in_order = true;
+                if (within(lane, L, r * 64)) key[r] -= lo;
+        }
+        const Passes ps = list_passes(range, by == SortBy::kDepthTop ? kFirstBits : 32, kListBits);
+        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
+        if (by == SortBy::kRun) {      // (no two keys are equal; a key holds its point index)
+            const uint32_t to = anew(lane);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, r * 64)) vals[r * 64u + to] = (key[r] & value_mask) + value_base;
+            return;
+        }
+        if (by == SortBy::kDepthTop) {
+            bool tie = false;
+            uint32_t rounds = 0u;      // with entries to be put right, a bit each
+            if (range != 0u) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane + 1, L, r * 64)) tie |= W.key[r * 64u + lane + 1u] <= key[r];
+            }
             if (__ballot(tie) != 0ull) {
-                int quiet = 0;      // sweeps in a row that found nothing to swap: over the even and over the odd neighbours
-                for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
-                    uint32_t suspect = 0u;      // a bit per pair of neighbours of this lane
+                uint32_t agree = 0u;
+                const uint32_t at = anew(lane);
 #pragma unroll
-                    for (int r = 0; r < (R + 1) / 2; ++r) {
-                        const uint32_t p = 2u * (r * 64u + lane) + (uint32_t)(sweep & 1);
-                        if (within(2 * lane + (sweep & 1) + 1, L, r * 128) && W.key[p] >= W.key[p + 1u]) suspect |= 1u << r;
+                for (int r = 0; r < R; ++r)
+                    if (within(lane + 1, L, r * 64)) agree |= W.key[r * 64u + at + 1u] >> ps.lo == key[r] >> ps.lo ? 1u << r : 0u;
+                rounds = rounds_of(agree, R);
+            }
+            if (range != 0u && (rounds == 0u || !long_runs(W.key, L, ps.lo, 0u, rounds))) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane, L, r * 64)) id[r] = words[2u * id[r] + 1u];
+                const uint32_t to = anew(lane);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (((rounds >> r) & 1u) == 0u && within(lane, L, r * 64)) vals[r * 64u + to] = id[r];
+                if (rounds == 0u) return;
+#pragma unroll
+                for (int r = 0; r < R; ++r) W.val[r * 64u + lane] = id[r];
+                wave_lds_sync();
+                for (; rounds != 0u; rounds &= rounds - 1u) rank_round(W.key, W.val, L, ps.lo, 64u * (uint32_t)__builtin_ctz(rounds), vals);
+                return;
+            }
+            // runs of equal depth, numbered, above the point indices less the list's smallest
+            bool fits = false;
+            if (range == 0u || __ballot(mixed_runs(W.key, L, ps.lo, lane, 64u)) == 0ull) {
+                uint32_t lo = 0u, hi = 0u, count = 0u, last = 0u;
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane, L, r * 64)) { id[r] = words[2u * id[r] + 1u]; lo = max(lo, ~id[r]); hi = max(hi, id[r]); }
+                if (range != 0u) {
+                    for (uint32_t p = lane; p - lane < L; p += 64u) {      // (place 0 and those behind the end start no run)
+                        const uint32_t k = W.key[p], up = (uint32_t)__shfl_up((int)k, 1, 64);
+                        const bool starts = p < L && p != 0u && k != (lane == 0 ? last : up);
+                        const uint64_t b = __ballot(starts);
+                        last = (uint32_t)__builtin_amdgcn_readlane((int)k, 63);
+                        W.key[p] = count + lanes_below(b) + (starts ? 1u : 0u);
+                        count += (uint32_t)__popcll(b);
                     }
-                    bool swapped = false;
-                    for (; suspect; suspect &= suspect - 1u) {
-                        const uint32_t p = 2u * ((uint32_t)__builtin_ctz(suspect) * 64u + lane) + (uint32_t)(sweep & 1);
-                        const uint32_t ka = W.key[p], kb = W.key[p + 1u];
-                        const uint16_t a = W.idx[p], b = W.idx[p + 1u];
-                        if (ka > kb || pairs[a].y > pairs[b].y) {
-                            W.key[p] = kb; W.key[p + 1u] = ka;
-                            W.idx[p] = b; W.idx[p + 1u] = a;
-                            swapped = true;
-                        }
-                    }
-                    quiet = __ballot(swapped) != 0ull ? 0 : quiet + 1;
-                    wave_lds_sync();
                 }
-                in_order = quiet >= 2;
+                value_base = ~wave_reduce(lo, OpMax{});
+                const RunKey rk = run_key(count, wave_reduce(hi, OpMax{}) - value_base);
+                fits = rk.fits;
+                value_mask = rk.mask;
 #pragma unroll
-                for (int r = 0; r < R; ++r) id[r] = W.idx[r * 64u + lane];
+                for (int r = 0; r < R; ++r) {
+                    key[r] = within(lane, L, r * 64) ? (range != 0u ? W.key[r * 64u + lane] << rk.bits : 0u) | (id[r] - value_base) : 0xffffffffu;
+                    id[r] = 0u;
+                }
+                range = rk.range;
                 wave_lds_sync();
             }
+            by = fits ? SortBy::kRun : SortBy::kIndex;
+            continue;
         }
-        if (stage == 0 && !in_order) continue;
         // through the sorted positions
         const uint32_t to = anew(lane);
-        if (in_order) {
+        if (by == SortBy::kDepth) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if (within(lane, L, r * 64)) key[r] = words[2u * id[r] + 1u];
@@ -285,6 +422,7 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint2
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");      // (read back by other lanes)
             __builtin_amdgcn_wave_barrier();
         }
+        by = SortBy::kDepth;
     }
 }
 
@@ -320,7 +458,7 @@ __device__ __forceinline__ bool wg_any(WgSortLds& S, int turn, bool v)
     uint32_t any = 0u;
 #pragma unroll
     for (int w = 0; w < kSortWaves; ++w) any |= S.any[turn & 1][w];
-    return any != 0u;
+    return __builtin_amdgcn_readfirstlane(any) != 0u;
 }
 
 // The keys' range over the workgroup: the threads' largest and smallest (inverted) key in, the smallest out and the difference
@@ -337,30 +475,30 @@ __device__ __forceinline__ uint32_t wg_key_range(WgSortLds& S, uint32_t& lo, uin
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)all.y) - lo;
 }
 
-// The entries of the list are in order but for neighbours: sweeps over its even and its odd pairs of neighbours in turn. Returns
-// whether the list is in order now. Ends with a barrier.
-__device__ __forceinline__ bool tie_sweeps(WgSortLds& S, uint32_t L, uint2* p)
+// The list is in order but for the runs of entries that agree in the bits from `shift` on of the keys less lo: puts the point indices in
+// order, each entry of a run by its rank. Returns false if a run is too long for that (vals is then written in part).
+__device__ __forceinline__ bool rank_ties(WgSortLds& S, uint32_t L, uint32_t lo, int shift, const uint2* p, uint32_t* vals)
 {
-    int quiet = 0;      // sweeps in a row that found nothing to swap
-    for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
-        bool swapped = false;
-        for (uint32_t i0 = 0; i0 + 1u < L; i0 += 16u * kSortThreads) {
-            uint32_t suspect = 0u;
-            const uint32_t first = i0 + 2u * threadIdx.x + (uint32_t)(sweep & 1);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {      // eight pairs of fetches in flight
-                const uint32_t i = first + r * 2u * kSortThreads;
-                if (i + 1u < L && p[i].x >= p[i + 1u].x) suspect |= 1u << r;
-            }
-            for (; suspect; suspect &= suspect - 1u) {
-                const uint32_t i = first + 2u * kSortThreads * (uint32_t)__builtin_ctz(suspect);
-                const uint2 a = p[i], b = p[i + 1u];
-                if (a.x > b.x || a.y > b.y) { p[i] = b; p[i + 1u] = a; swapped = true; }
-            }
+    bool fits = true;
+    for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) {
+        const uint2 mine = p[i];
+        const uint32_t top = (mine.x - lo) >> shift;
+        uint32_t pos = i, d = 1u;
+        for (; d <= kCountRunInMemory && d <= i; ++d) {
+            const uint2 o = p[i - d];
+            if ((o.x - lo) >> shift != top) break;
+            if (mine.x < o.x || (mine.x == o.x && mine.y < o.y)) --pos;
         }
-        quiet = wg_any(S, sweep, swapped) ? 0 : quiet + 1;
+        fits &= d <= kCountRunInMemory;
+        for (d = 1u; d <= kCountRunInMemory && i + d < L; ++d) {
+            const uint2 o = p[i + d];
+            if ((o.x - lo) >> shift != top) break;
+            if (o.x < mine.x || (o.x == mine.x && o.y < mine.y)) ++pos;
+        }
+        fits &= d <= kCountRunInMemory;
+        vals[pos] = mine.y;
     }
-    return quiet >= 2;
+    return !wg_any(S, 0, !fits);
 }
 
 // A workgroup sorts the list pairs[0 .. L), L <= kWgListMax, into vals; the pairs are spent. The permutation perm[c][i] =
@@ -446,34 +584,30 @@ __device__ __forceinline__ void wg_permute_list(WgSortLds& S, uint32_t L0, uint2
         const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
         for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits), from, lo);
         // through the sorted positions; every entry is fetched before the first is stored
-        const auto put_in_order = [&](const uint32_t* in, uint32_t* list, uint32_t step) {      // words step apart
-            uint32_t out[R];
-            const uint32_t to = anew(threadIdx.x);
-            L = anew_uniform(L0);
+        uint2 out[R];
+        const uint32_t to = anew(threadIdx.x);
+        L = anew_uniform(L0);
 #pragma unroll
-            for (int r0 = 0; r0 < R; r0 += 8) {      // (the addresses of eight rounds at a time)
+        for (int r0 = 0; r0 < R; r0 += 8) {      // (the addresses of eight rounds at a time)
 #pragma unroll
-                for (int r = r0; r < r0 + 8 && r < R; ++r) {
-                    out[r] = 0u;
-                    if (within((int)threadIdx.x, L, r * kSortThreads)) out[r] = in[2u * src[r * kSortThreads + threadIdx.x]];
-                }
-                asm volatile("" ::: "memory");
+            for (int r = r0; r < r0 + 8 && r < R; ++r) {
+                out[r] = make_uint2(0u, 0u);
+                if (within((int)threadIdx.x, L, r * kSortThreads)) out[r] = pairs[src[r * kSortThreads + threadIdx.x]];
             }
-            __syncthreads();
-            L = anew_uniform(L0);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (within((int)threadIdx.x, L, r * kSortThreads)) list[step * (r * kSortThreads + to)] = out[r];
-            }
-        };
-        if (stage == 2) { put_in_order(words + 1, vals, 1u); return; }
-        put_in_order(words + 1, words + 1, 2u);
-        put_in_order(words, words, 2u);
-        __syncthreads();      // (also: the permutation may be written again)
-        if (stage == 0 && tie_sweeps(S, L, pairs)) {
-            for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) vals[i] = pairs[i].y;
-            return;
+            asm volatile("" ::: "memory");
         }
+        __syncthreads();
+        L = anew_uniform(L0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (within((int)threadIdx.x, L, r * kSortThreads)) {
+                if (stage == 2) vals[r * kSortThreads + to] = out[r].y;
+                else pairs[r * kSortThreads + to] = out[r];
+            }
+        }
+        if (stage == 2) return;
+        __syncthreads();      // (also: the permutation may be written again)
+        if (stage == 0 && rank_ties(S, L, lo, ps.lo, pairs, vals)) return;
     }
 }
 
@@ -506,62 +640,120 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint2* pa
 #pragma unroll
         for (int r = 0; r < R; ++r) { key[r] = S.key[first + r * 64 + lane]; id[r] = S.idx[first + r * 64 + lane]; }
     };
-    // by depth bits; where that leaves equal ones out of order, by point index and then, which keeps that order, by depth bits again
+    uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
+    SortBy by = SortBy::kDepthTop;
+    uint32_t range = 0u, value_base = 0u, value_mask = 0u;
 #pragma unroll 1
-    for (int stage = 0; stage < 3; ++stage) {
-        uint32_t* const words = reinterpret_cast<uint32_t*>(pairs);
-        const uint32_t* const from = words + (stage == 1 ? 1 : 0);      // (every other word)
-        const uint32_t at = anew(first + lane);
-        uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
+    for (;;) {
+        if (by != SortBy::kRun) {
+            const uint32_t* const from = words + (by == SortBy::kIndex ? 1 : 0);      // (every other word)
+            const uint32_t at = anew(first + lane);
+            uint32_t lo = 0u, hi = 0u;      // (the smallest key, inverted)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            key[r] = 0xffffffffu;
-            id[r] = r * 64u + at;
-            if (within(lane, L, first + r * 64)) { key[r] = from[2u * (r * 64u + at)]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
-        }
-        const uint32_t diff = wg_key_range(S, lo, hi);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (within(lane, L, first + r * 64)) key[r] -= lo;
-        const Passes ps = list_passes(diff, stage == 0 ? kFirstBits : 32, kListBits);
-        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
-        bool in_order = stage == 2;
-        if (stage == 0 && diff != 0u) {
-            bool tie = false;
+            for (int r = 0; r < R; ++r) {
+                key[r] = 0xffffffffu;
+                id[r] = r * 64u + at;
+                if (within(lane, L, first + r * 64)) { key[r] = from[2u * (r * 64u + at)]; lo = max(lo, ~key[r]); hi = max(hi, key[r]); }
+            }
+            range = wg_key_range(S, lo, hi);
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (within(lane + 1, L, first + r * 64)) tie |= S.key[first + r * 64 + lane + 1] <= key[r];
-            in_order = true;
-            if (wg_any(S, 1, tie)) {
-                int quiet = 0;      // sweeps in a row that found nothing to swap: over the even and over the odd neighbours
-                for (int sweep = 0; sweep < kTiePhases && quiet < 2; ++sweep) {
-                    const int base = 2 * (int)threadIdx.x + (sweep & 1);
-                    uint32_t suspect = 0u;      // a bit per pair of neighbours of this thread
-#pragma unroll
-                    for (int r = 0; r < (R + 1) / 2; ++r)
-                        if (within(base + 1, L, r * 2 * kSortThreads) && S.key[base + r * 2 * kSortThreads] >= S.key[base + r * 2 * kSortThreads + 1]) suspect |= 1u << r;
-                    bool swapped = false;
-                    for (; suspect; suspect &= suspect - 1u) {
-                        const int p = base + 2 * kSortThreads * __builtin_ctz(suspect);
-                        const uint32_t ka = S.key[p], kb = S.key[p + 1];
-                        const uint16_t a = S.idx[p], b = S.idx[p + 1];
-                        if (ka > kb || pairs[a].y > pairs[b].y) {
-                            S.key[p] = kb; S.key[p + 1] = ka;
-                            S.idx[p] = b; S.idx[p + 1] = a;
-                            swapped = true;
-                        }
-                    }
-                    quiet = wg_any(S, sweep, swapped) ? 0 : quiet + 1;
-                }
-                in_order = quiet >= 2;
-#pragma unroll
-                for (int r = 0; r < R; ++r) id[r] = S.idx[first + r * 64 + lane];
-            }
+                if (within(lane, L, first + r * 64)) key[r] -= lo;
         }
-        if (stage == 0 && !in_order) { __syncthreads(); continue; }
+        const Passes ps = list_passes(range, by == SortBy::kDepthTop ? kFirstBits : 32, kListBits);
+        for (int p = 0; p < ps.count; ++p) one_pass(list_shift(ps, p, kListBits));
+        if (by == SortBy::kRun) {      // (as in a wavefront's list, this and what follows)
+            const uint32_t to = anew(first + lane);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (within(lane, L, first + r * 64)) vals[r * 64u + to] = (key[r] & value_mask) + value_base;
+            return;
+        }
+        if (by == SortBy::kDepthTop) {
+            bool tie = false;
+            if (range != 0u) {
+                const uint32_t at = anew(first + lane);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane + 1, L, first + r * 64)) tie |= S.key[at + r * 64 + 1] <= key[r];
+            }
+            const bool ties = wg_any(S, 0, tie);
+            bool long_run = range == 0u;
+            uint32_t rounds = 0u;      // of this wavefront's
+            if (ties) {
+                uint32_t agree = 0u;
+                const uint32_t at = anew(first + lane);
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane + 1, L, first + r * 64)) agree |= S.key[at + r * 64 + 1] >> ps.lo == key[r] >> ps.lo ? 1u << r : 0u;
+                rounds = rounds_of(agree, R);
+                if (first != 0 && first < (int)L && S.key[first - 1] >> ps.lo == S.key[first] >> ps.lo) rounds |= 1u;
+                rounds = __builtin_amdgcn_readfirstlane(rounds);
+                long_run = wg_any(S, 1, long_runs(S.key, L, ps.lo, first, rounds));
+            }
+            if (!long_run) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane, L, first + r * 64)) id[r] = words[2u * id[r] + 1u];
+                const uint32_t to = anew(first + lane);
+                if (ties) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) S.val[to + r * 64] = id[r];
+                    __syncthreads();      // (before the stores to memory, which it would wait for)
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (((rounds >> r) & 1u) == 0u && within(lane, L, first + r * 64)) vals[r * 64u + to] = id[r];
+                for (; rounds != 0u; rounds &= rounds - 1u) rank_round(S.key, S.val, L, ps.lo, (uint32_t)first + 64u * (uint32_t)__builtin_ctz(rounds), vals);
+                return;
+            }
+            bool fits = false;
+            if (range == 0u || !wg_any(S, 0, mixed_runs(S.key, L, ps.lo, anew(threadIdx.x), kSortThreads))) {
+                uint32_t lo = 0u, hi = 0u, count = 0u;
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane, L, first + r * 64)) { id[r] = words[2u * id[r] + 1u]; lo = max(lo, ~id[r]); hi = max(hi, id[r]); }
+                if (range != 0u) {
+                    const uint32_t ln = anew(threadIdx.x) & 63u;
+                    uint32_t last = first != 0 ? S.key[first - 1] : 0u;
+                    __syncthreads();      // (the runs' numbers take the keys' places)
+                    for (uint32_t p = first + ln; p - ln < min(L, (uint32_t)first + 64u * R); p += 64u) {
+                        const uint32_t k = S.key[p], up = (uint32_t)__shfl_up((int)k, 1, 64);
+                        const bool starts = p < L && p != 0u && k != (ln == 0u ? last : up);
+                        const uint64_t b = __ballot(starts);
+                        last = (uint32_t)__builtin_amdgcn_readlane((int)k, 63);
+                        S.key[p] = count + lanes_below(b) + (starts ? 1u : 0u);
+                        count += (uint32_t)__popcll(b);
+                    }
+                }
+                if ((anew(threadIdx.x) & 63u) == 0u) S.scan[wave] = count;
+                hi = wg_key_range(S, lo, hi);      // (a barrier)
+                value_base = lo;
+                uint32_t before = 0u;
+                count = 0u;
+                for (int w = 0; w < kSortWaves; ++w) {
+                    const uint32_t n = __builtin_amdgcn_readfirstlane(S.scan[w]);
+                    before += w < wave ? n : 0u;
+                    count += n;
+                }
+                const RunKey rk = run_key(count, hi);
+                fits = rk.fits;
+                value_mask = rk.mask;
+                const uint32_t to = anew(first + lane);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    key[r] = within(lane, L, first + r * 64) ? (range != 0u ? (before + S.key[to + r * 64]) << rk.bits : 0u) | (id[r] - value_base) : 0xffffffffu;
+                    id[r] = 0u;
+                }
+                range = rk.range;
+                __syncthreads();      // (S.scan is written again by the passes)
+            }
+            by = fits ? SortBy::kRun : SortBy::kIndex;
+            continue;
+        }
         // through the sorted positions
         const uint32_t to = anew(first + lane);
-        if (in_order) {
+        if (by == SortBy::kDepth) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if (within(lane, L, first + r * 64)) key[r] = words[2u * id[r] + 1u];
@@ -581,6 +773,7 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint2* pa
                 if (within(lane, L, first + r * 64)) words[2u * (r * 64u + to) + half] = key[r];
         }
         __syncthreads();
+        by = SortBy::kDepth;
     }
 }
 
@@ -689,8 +882,7 @@ __device__ __forceinline__ void wg_sort_long(WgSortLds& S, uint32_t L, uint2* pa
             long_list_pass(S, (p & 1) ? c1 : c0, (p & 1) ? c0 : c1, p == 0, L, lo, list_shift(ps, p, kLongBits), next_shift, stage == 1, here, there);
             uint2* t = here; here = there; there = t;
         }
-        if (stage == 0 && tie_sweeps(S, L, here)) break;
-        __syncthreads();
+        if (stage == 0 && rank_ties(S, L, 0u, 0, here, vals)) return;
     }
     for (uint32_t i = threadIdx.x; i < L; i += kSortThreads) vals[i] = here[i].y;
 }

@@ -29,7 +29,6 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t v, Op op)      // unifo
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v, op), 63);
 }
 struct OpAdd { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; } };
-struct OpOr { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a | b; } };
 struct OpMax { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return max(a, b); } };
 
 }  // namespace pbdr

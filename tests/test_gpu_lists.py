@@ -35,11 +35,11 @@ LENGTHS = [1, 2, 63, 64, 65, 126, 127, 128, 129, 192, 193, 254, 255, 256, 257, 3
 
 
 @pytest.mark.parametrize("w,h", [(320, 320), (1280, 720), (1936, 1040)])      # 400, 3,600 and 7,865 tiles
-@pytest.mark.parametrize("kind", ["uniform", "octaves", "pairs", "runs", "one_depth"])
+@pytest.mark.parametrize("kind", ["uniform", "octaves", "pairs", "runs", "walls", "one_depth"])
 def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
     """One tile per length, its points scattered over the point order. Depths: spread evenly; over seven octaves on both sides of 2.0; each value twice, as copied points
-    leave them (put right by swapping neighbours); in runs of a hundred equal ones and, in every tenth list, in the top bits alone
-    (more than the swaps do: sorted again by point index); one for all."""
+    leave them; in runs of a hundred equal ones and, in every tenth list, in the top bits alone; in walls of 1 to 257 points at
+    nearly one depth, on both sides of the lengths up to which equal ones are put right by counting; one for all."""
     rng = np.random.default_rng(w + len(kind))
     tx = (w + 15) // 16
     tile = np.repeat(np.arange(len(LENGTHS)) * 7 + tx + 3, LENGTHS)
@@ -56,6 +56,15 @@ def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
         depth = 3 + (rng.permutation(n) // 100) * 0.01
         steep = tile % 10 == 0
         depth[steep] = 2.0 + rng.integers(0, 5, steep.sum()) * 2.0 ** -22 + (rng.random(steep.sum()) < 0.01) * 1e6
+    elif kind == "walls":
+        depth = np.empty(n, dtype=np.float32)
+        for t in np.unique(tile):
+            at = np.flatnonzero(tile == t)
+            walls = rng.permutation([1, 2, 15, 16, 17, 18, 63, 64, 65, 255, 256, 257] if t % 3 else [1, 2, 3, 15, 16])
+            wall = np.repeat(np.arange(len(at)), np.resize(walls, len(at)))[:len(at)]
+            depth[at] = 8 + 0.25 * (wall % 4000)
+        near = rng.random(n) < 0.3      # a few last places away
+        depth[near] = (depth[near].view(np.uint32) + rng.integers(1, 4, near.sum(), dtype=np.uint32)).view(np.float32)
     else:
         depth = np.full(n, 4.25)
     order = rng.permutation(n)
@@ -98,3 +107,19 @@ def test_dense_blocks_on_few_tiles(n):
               color=np.zeros((n, 3)), radius=np.zeros(n, dtype=np.int32))
     st["radius"][n - m:] = rng.integers(1, 40, m)
     _check(st, rng.uniform(0.3, 50, n), w, h)
+
+
+@pytest.mark.parametrize("length", [700, 5600, 5700])
+def test_many_depths_and_one_wall_far_apart_in_the_point_order(length):
+    """A wall of 40 points among points of their own depths, 2^24 points from the first to the last: the number of a run of equal
+    depths and the distance in the point order together take more than a word, and the list is sorted by point index and depth."""
+    rng = np.random.default_rng(length)
+    n, w, h = (1 << 24) + 1, 32, 32
+    at = np.concatenate([[0], np.sort(rng.choice(n - 2, length - 2, replace=False) + 1), [n - 1]])
+    st = dict(mean2d=np.full((n, 2), 8.0, dtype=np.float32), conic=np.tile(np.float32([0.1, 0, 0.1]), (n, 1)), opacity=np.full(n, 0.01, dtype=np.float32),
+              color=np.zeros((n, 3), dtype=np.float32), radius=np.zeros(n, dtype=np.int32))
+    st["radius"][at] = 1
+    depth = np.ones(n, dtype=np.float32)
+    depth[at] = 1 + rng.permutation(length) / 64
+    depth[rng.choice(at, 40, replace=False)] = 3.0
+    _check(st, depth, w, h)

@@ -18,63 +18,68 @@
 
 namespace pbdr {
 
-// Tiles touched by every point (0 for culled points) and, per block of 256 consecutive points and per kSuperBlocks of them,
+// Tiles touched by every point (0 for culled points) and, per block of 256 consecutive points and per 2^super_shift of them,
 // the number of points that touch at least one tile - those are the points binning lists ("visible" below) - and the number of
 // their pairs. A state made by the preprocessing calls has radius == 0 for every point without a tile; a caller-made state with
 // radius > 0 and an empty tile rectangle is treated as culled here, so every listed point owns at least one pair.
 // Four consecutive points per thread (one 16-byte load of the radii, one 16-byte store of the counts: with one point
 // per thread the launch did not keep enough bytes in flight, 2 TB/s at eight million points: 32 -> 21 us there), so a
 // wavefront covers exactly one block of 256 points and its two sums need no LDS and no barrier.
+template <uint32_t kSuper>
 __global__ __launch_bounds__(1024) void k_count_visible(BinInput in, CamDev cam, BinArrays A, uint32_t nranges)
 {
-    __shared__ uint2 sBlk[kSuperBlocks];
+    __shared__ uint2 sBlk[16];
     const uint32_t gid = blockIdx.x * 1024u + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // first launch of a binning call: the status words and the tile ranges, which hold the tiles' pair counts first, start at zero
     // (every later kernel of the call comes after this one on the stream)
     if (gid < (uint32_t)kStCleared) A.status[gid] = 0u;
     for (uint32_t k = gid; k < nranges; k += gridDim.x * 1024u) A.ranges[k] = 0u;
-    const size_t i0 = (size_t)gid * 4u;
     const size_t n = (size_t)in.n;
-    int r[4] = {0, 0, 0, 0};
-    if (i0 + 4u <= n && (reinterpret_cast<uintptr_t>(in.radius) & 15u) == 0u) {
-        const int4 v = *reinterpret_cast<const int4*>(in.radius + i0);
-        r[0] = v.x; r[1] = v.y; r[2] = v.z; r[3] = v.w;
-    } else {
+    uint2 sum = make_uint2(0u, 0u);      // of the wavefront's blocks
+#pragma unroll 1
+    for (uint32_t q = 0; q < kSuper / 16u; ++q) {
+        const size_t blk = (size_t)blockIdx.x * kSuper + q * 16u + wave;      // the wavefront's 256 points
+        if (kSuper > 16u && blk * 256u >= n) break;
+        const size_t i0 = blk * 256u + (size_t)lane * 4u;
+        int r[4] = {0, 0, 0, 0};
+        if (i0 + 4u <= n && (reinterpret_cast<uintptr_t>(in.radius) & 15u) == 0u) {
+            const int4 v = *reinterpret_cast<const int4*>(in.radius + i0);
+            r[0] = v.x; r[1] = v.y; r[2] = v.z; r[3] = v.w;
+        } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) if (i0 + k < n) r[k] = in.radius[i0 + k];
-    }
-    uint32_t t[4];
-    uint32_t vis = 0u, pairs = 0u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        t[k] = 0u;
-        if (r[k] > 0) {      // (r[k] is 0 past the end)
-            int x0, y0, x1, y1;
-            tile_rect(cam, in.mean2d[i0 + k], in.mean2d[n + i0 + k], r[k], x0, y0, x1, y1);
-            t[k] = (uint32_t)(max(x1 - x0, 0) * max(y1 - y0, 0));       // <= 2^24: the grid has at most 4096 x 4096 tiles
+            for (int k = 0; k < 4; ++k) if (i0 + k < n) r[k] = in.radius[i0 + k];
         }
-        vis += t[k] > 0u ? 1u : 0u;
-        pairs = sat_add(pairs, t[k]);
-    }
-    if (i0 + 4u <= n) {
-        *reinterpret_cast<uint4*>(A.touched + i0) = make_uint4(t[0], t[1], t[2], t[3]);      // (the array starts on a 256-byte boundary)
-    } else {
+        uint32_t t[4];
+        uint32_t vis = 0u, pairs = 0u;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) if (i0 + k < n) A.touched[i0 + k] = t[k];
+        for (int k = 0; k < 4; ++k) {
+            t[k] = 0u;
+            if (r[k] > 0) {      // (r[k] is 0 past the end)
+                int x0, y0, x1, y1;
+                tile_rect(cam, in.mean2d[i0 + k], in.mean2d[n + i0 + k], r[k], x0, y0, x1, y1);
+                t[k] = (uint32_t)(max(x1 - x0, 0) * max(y1 - y0, 0));       // <= 2^24: the grid has at most 4096 x 4096 tiles
+            }
+            vis += t[k] > 0u ? 1u : 0u;
+            pairs = sat_add(pairs, t[k]);
+        }
+        if (i0 + 4u <= n) {
+            *reinterpret_cast<uint4*>(A.touched + i0) = make_uint4(t[0], t[1], t[2], t[3]);      // (the array starts on a 256-byte boundary)
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) if (i0 + k < n) A.touched[i0 + k] = t[k];
+        }
+        vis = wave_reduce(vis, OpAdd{});
+        pairs = wave_reduce(pairs, OpSatAdd{});
+        if (lane == 0 && blk * 256u < n) A.blk[blk] = make_uint2(vis, pairs);
+        sum.x += vis; sum.y = sat_add(sum.y, pairs);
     }
-    vis = wave_reduce(vis, OpAdd{});
-    pairs = wave_reduce(pairs, OpSatAdd{});
-    const size_t blk = (size_t)blockIdx.x * kSuperBlocks + wave;      // the wavefront's 256 points
-    if (lane == 0) {
-        sBlk[wave] = make_uint2(vis, pairs);
-        if (blk * 256u < n) A.blk[blk] = make_uint2(vis, pairs);
-    }
+    if (lane == 0) sBlk[wave] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint2 s = make_uint2(0u, 0u);
 #pragma unroll
-        for (uint32_t w = 0; w < kSuperBlocks; ++w) { s.x += sBlk[w].x; s.y = sat_add(s.y, sBlk[w].y); }
+        for (uint32_t w = 0; w < 16u; ++w) { s.x += sBlk[w].x; s.y = sat_add(s.y, sBlk[w].y); }
         A.sup[blockIdx.x] = s;
     }
 }
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(1024) void k_count_visible(BinInput in, CamDev cam,
 template <int kThreads>
 __device__ __forceinline__ uint2 blocks_before(const BinArrays& A, uint32_t b, uint2* sSum)
 {
-    const uint32_t s = b / kSuperBlocks;
+    const uint32_t s = b >> A.super_shift;
     uint32_t v = 0u, p = 0u;
     for (uint32_t i0 = 0; i0 < s; i0 += 4u * (uint32_t)kThreads) {      // four loads in flight
         uint2 x[4];
@@ -95,8 +100,8 @@ __device__ __forceinline__ uint2 blocks_before(const BinArrays& A, uint32_t b, u
 #pragma unroll
         for (uint32_t k = 0; k < 4u; ++k) { v += x[k].x; p = sat_add(p, x[k].y); }
     }
-    const uint32_t i = s * kSuperBlocks + threadIdx.x;
-    if (threadIdx.x < kSuperBlocks && i < b) {
+    const uint32_t i = (s << A.super_shift) + threadIdx.x;      // (at most 128 blocks in a part, and a workgroup has 256 threads)
+    if (i < b) {
         const uint2 x = A.blk[i];
         v += x.x; p = sat_add(p, x.y);
     }
@@ -398,6 +403,7 @@ BinArrays bin_arrays(const Layout& L, char* ws)
     A.depth_bits = u32(L.off_depth_bits);
     A.pairs = reinterpret_cast<uint2*>(ws + L.off_pairs);
     A.chunk_rank = u32(L.off_chunk_rank);
+    A.super_shift = super_shift(L.n);
     A.cap = L.cap;
     A.status = u32(L.off_status);
     return A;
@@ -413,8 +419,10 @@ hipError_t launch_bin_count(const BinInput& in, const CamDev& cam, const Layout&
     const uint32_t ntiles = (uint32_t)(cam.TX * cam.TY);      // the call's tile grid (a patch covers fewer tiles than the image the workspace is sized for)
     {
         ProfScope prof(kKCountVisible, s);
-        hipLaunchKernelGGL(k_count_visible, dim3((nb + kSuperBlocks - 1u) / kSuperBlocks), dim3(1024), 0, s, in, cam, A,
-                           (uint32_t)(2 * (size_t)L.tiles));
+        const dim3 grid(((nb - 1u) >> A.super_shift) + 1u);
+        const uint32_t nranges = (uint32_t)(2 * (size_t)L.tiles);
+        if (A.super_shift == 4u) hipLaunchKernelGGL(k_count_visible<16>, grid, dim3(1024), 0, s, in, cam, A, nranges);
+        else hipLaunchKernelGGL(k_count_visible<128>, grid, dim3(1024), 0, s, in, cam, A, nranges);
     }
     {
         ProfScope prof(kKTileCount, s);

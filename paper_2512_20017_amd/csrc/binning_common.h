@@ -18,11 +18,14 @@ __device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b)      // a, b
 struct OpSatAdd { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return sat_add(a, b); } };
 
 // What the binning kernels keep per block of 256 points, per tile and per pair (device pointers into the workspace).
-constexpr uint32_t kSuperBlocks = 16;      // blocks of points per workgroup of k_count_visible
+// Blocks of points per workgroup of k_count_visible, as a power of two: 16, one a wavefront, or 128 where that still makes 512
+// workgroups. Every block with a listed point adds up the sums of all workgroups before its own, which grows as the square of the number
+// of points (binning of 100M points, a tenth of them seen: 1,061 us with 16, 945 with 128; of 32M 319 and 317).
+inline uint32_t super_shift(int n) { return n > 1 << 24 ? 7u : 4u; }
 struct BinArrays {
     uint32_t* touched;           // [n] tiles per point, 0 = not listed
     uint2* blk;                  // [blocks] listed points and their pairs (saturating)
-    uint2* sup;                  // [blocks / kSuperBlocks] the same per kSuperBlocks blocks
+    uint2* sup;                  // [blocks >> super_shift] the same per 2^super_shift blocks
     uint2* blk_at;               // [blocks] listed points and pairs in the blocks before this one (of blocks with a listed point)
     uint4* blk_cells;            // [blocks] {tiles the block's pairs lie on or kDirect, x | y << 16 of its rectangle of tiles, its width, -}
     uint2* cells;                // [cap] those tiles, from blk_at.y on: {x | y << 16, pairs of the blocks that counted the tile before}
@@ -33,6 +36,7 @@ struct BinArrays {
     uint32_t* depth_bits;        // [n] bit pattern of the depth, by point index
     uint2* pairs;                // [cap] {depth bits, point index}, tile by tile
     uint32_t* chunk_rank;        // rank owning the first pair of every chunk (pair_reduce.h)
+    uint32_t super_shift;
     uint32_t cap;
     uint32_t* status;
 };

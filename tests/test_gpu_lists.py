@@ -123,3 +123,20 @@ def test_many_depths_and_one_wall_far_apart_in_the_point_order(length):
     depth[at] = 1 + rng.permutation(length) / 64
     depth[rng.choice(at, 40, replace=False)] = 3.0
     _check(st, depth, w, h)
+
+
+@pytest.mark.parametrize("n", [1 << 24, (1 << 24) + 1, (1 << 24) + 3 * 32768 + 257])
+def test_sums_over_many_blocks(n):
+    """On both sides of the point count from which the sums that a block adds up are those of 128 blocks, not of 16: listed points in the
+    blocks on both sides of such parts, in the first and last block, and in every block of one part."""
+    rng = np.random.default_rng(n)
+    w, h = 320, 200
+    parts = rng.choice(n // 32768 - 1, 60, replace=False) * 32768
+    at = np.unique(np.concatenate([[0, n - 1], parts, parts + 32767, parts + 32768, parts[0] + np.arange(0, 32768, 100), rng.choice(n, 500, replace=False)]))
+    st = dict(mean2d=np.full((n, 2), 8.0, dtype=np.float32), conic=np.tile(np.float32([0.1, 0, 0.1]), (n, 1)), opacity=np.full(n, 0.01, dtype=np.float32),
+              color=np.zeros((n, 3), dtype=np.float32), radius=np.zeros(n, dtype=np.int32))
+    st["mean2d"][at] = np.stack([rng.uniform(0, w, len(at)), rng.uniform(0, h, len(at))], 1)
+    st["radius"][at] = rng.integers(1, 30, len(at))
+    depth = np.ones(n, dtype=np.float32)
+    depth[at] = rng.uniform(0.3, 50, len(at))
+    _check(st, depth, w, h)

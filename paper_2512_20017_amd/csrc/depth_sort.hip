@@ -19,7 +19,8 @@
 // they are differ in 31 bits where a list has depths on both sides of 2.0, which every tile of a street has: 11 bits too coarse, and
 // most lists were sorted three times over, 192 us -> 134 for 7.3 M pairs at 3840x2160). That orders a list but for
 // neighbours, some per thousand entries, that agree in those bits, and for equal
-// depths, which are in order only if they came in order. Such runs of equal bits are put right by counting: every entry of a run
+// depths, which are in order only if they came in order. Where all such runs are of two entries and no depths are equal, as in nearly every
+// list of a few hundred, the two change places on their way out. Else the runs are put right by counting: every entry of a run
 // compares its depth and point index with the others' and goes to its rank. Where a run is longer than kCountRun entries (whole walls
 // at one depth), the runs are numbered and the list is sorted again by number and point index in one key; where such a list also has
 // depths that agree in the top bits and differ below, or where the key would not fit a word, by point index and then, which keeps
@@ -219,6 +220,13 @@ __device__ __forceinline__ void rank_round(const uint32_t* keys, const uint32_t*
     if (place < L) out[min(s + rank, L - 1u)] = value;      // (always below)
 }
 
+// Of a list in rounds of 64, a bit a round and lane: the bits of the entries before. first: that of the entry before the first.
+__device__ __forceinline__ uint32_t of_entries_before(uint32_t bits, uint32_t first)
+{
+    const uint32_t wrapped = (uint32_t)__builtin_amdgcn_readlane((int)bits, 63) << 1 | first;      // lane 0's: the last lane's of the round before
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)wrapped, (int)bits, 0x138, 0xf, 0xf, false);      // wave_shr:1
+}
+
 // Which of the wavefront's R rounds hold an entry of a run of two or more? agree: a bit per round, this lane's entry agrees with the next place's.
 __device__ __forceinline__ uint32_t rounds_of(uint32_t agree, int R)
 {
@@ -336,22 +344,32 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint2
             return;
         }
         if (by == SortBy::kDepthTop) {
-            bool tie = false;
-            uint32_t rounds = 0u;      // with entries to be put right, a bit each
+            // a bit a round: the entry agrees with the next one, and is the larger of the two
+            uint32_t agree = 0u, larger = 0u;
+            bool more = range == 0u;      // are there equal ones, or more than two that agree?
             if (range != 0u) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    if (within(lane + 1, L, r * 64)) tie |= W.key[r * 64u + lane + 1u] <= key[r];
+                    if (within(lane + 1, L, r * 64)) {
+                        const uint32_t next = W.key[r * 64u + lane + 1u];
+                        agree |= (next ^ key[r]) >> ps.lo == 0u ? 1u << r : 0u;
+                        larger |= next < key[r] ? 1u << r : 0u;
+                        more |= next == key[r];
+                    }
+                more |= (agree & of_entries_before(agree, 0u)) != 0u;
             }
-            if (__ballot(tie) != 0ull) {
-                uint32_t agree = 0u;
-                const uint32_t at = anew(lane);
+            if (__ballot(more) == 0ull) {      // two that agree change places here if they have to
+                const uint32_t smaller = of_entries_before(larger, 0u), to = anew(lane);
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    if (within(lane + 1, L, r * 64)) agree |= W.key[r * 64u + at + 1u] >> ps.lo == key[r] >> ps.lo ? 1u << r : 0u;
-                rounds = rounds_of(agree, R);
+                    if (within(lane, L, r * 64)) id[r] = words[2u * id[r] + 1u];
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane, L, r * 64)) vals[r * 64u + to + ((larger >> r) & 1u) - ((smaller >> r) & 1u)] = id[r];
+                return;
             }
-            if (range != 0u && (rounds == 0u || !long_runs(W.key, L, ps.lo, 0u, rounds))) {
+            uint32_t rounds = range != 0u ? rounds_of(agree, R) : 0u;      // with entries to be put right, a bit each
+            if (range != 0u && !long_runs(W.key, L, ps.lo, 0u, rounds)) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     if (within(lane, L, r * 64)) id[r] = words[2u * id[r] + 1u];
@@ -359,7 +377,6 @@ __device__ __forceinline__ void wave_sort_list(WaveSortLds& W, uint32_t L, uint2
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     if (((rounds >> r) & 1u) == 0u && within(lane, L, r * 64)) vals[r * 64u + to] = id[r];
-                if (rounds == 0u) return;
 #pragma unroll
                 for (int r = 0; r < R; ++r) W.val[r * 64u + lane] = id[r];
                 wave_lds_sync();
@@ -670,25 +687,40 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint2* pa
             return;
         }
         if (by == SortBy::kDepthTop) {
-            bool tie = false;
+            uint32_t agree = 0u, larger = 0u;
+            uint32_t agree0 = 0u, larger0 = 0u;      // the same of the entry before this wavefront's
+            bool more = range == 0u;
             if (range != 0u) {
                 const uint32_t at = anew(first + lane);
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    if (within(lane + 1, L, first + r * 64)) tie |= S.key[at + r * 64 + 1] <= key[r];
+                    if (within(lane + 1, L, first + r * 64)) {
+                        const uint32_t next = S.key[at + r * 64 + 1];
+                        agree |= (next ^ key[r]) >> ps.lo == 0u ? 1u << r : 0u;
+                        larger |= next < key[r] ? 1u << r : 0u;
+                        more |= next == key[r];
+                    }
+                if (first != 0 && first < (int)L) {
+                    const uint32_t before = S.key[first - 1], own = S.key[first];
+                    agree0 = (before ^ own) >> ps.lo == 0u ? 1u : 0u;
+                    larger0 = own < before ? 1u : 0u;
+                }
+                more |= (agree & of_entries_before(agree, agree0)) != 0u;
             }
-            const bool ties = wg_any(S, 0, tie);
-            bool long_run = range == 0u;
-            uint32_t rounds = 0u;      // of this wavefront's
-            if (ties) {
-                uint32_t agree = 0u;
-                const uint32_t at = anew(first + lane);
+            if (!wg_any(S, 0, more)) {
+                const uint32_t smaller = of_entries_before(larger, larger0), to = anew(first + lane);
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    if (within(lane + 1, L, first + r * 64)) agree |= S.key[at + r * 64 + 1] >> ps.lo == key[r] >> ps.lo ? 1u << r : 0u;
-                rounds = rounds_of(agree, R);
-                if (first != 0 && first < (int)L && S.key[first - 1] >> ps.lo == S.key[first] >> ps.lo) rounds |= 1u;
-                rounds = __builtin_amdgcn_readfirstlane(rounds);
+                    if (within(lane, L, first + r * 64)) id[r] = words[2u * id[r] + 1u];
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (within(lane, L, first + r * 64)) vals[r * 64u + to + ((larger >> r) & 1u) - ((smaller >> r) & 1u)] = id[r];
+                return;
+            }
+            bool long_run = range == 0u;
+            uint32_t rounds = 0u;      // of this wavefront's
+            if (!long_run) {
+                rounds = __builtin_amdgcn_readfirstlane(rounds_of(agree, R) | agree0);
                 long_run = wg_any(S, 1, long_runs(S.key, L, ps.lo, first, rounds));
             }
             if (!long_run) {
@@ -696,11 +728,9 @@ __device__ __forceinline__ void wg_sort_list(WgSortLds& S, uint32_t L, uint2* pa
                 for (int r = 0; r < R; ++r)
                     if (within(lane, L, first + r * 64)) id[r] = words[2u * id[r] + 1u];
                 const uint32_t to = anew(first + lane);
-                if (ties) {
 #pragma unroll
-                    for (int r = 0; r < R; ++r) S.val[to + r * 64] = id[r];
-                    __syncthreads();      // (before the stores to memory, which it would wait for)
-                }
+                for (int r = 0; r < R; ++r) S.val[to + r * 64] = id[r];
+                __syncthreads();      // (before the stores to memory, which it would wait for)
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     if (((rounds >> r) & 1u) == 0u && within(lane, L, first + r * 64)) vals[r * 64u + to] = id[r];

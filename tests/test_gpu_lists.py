@@ -35,10 +35,11 @@ LENGTHS = [1, 2, 63, 64, 65, 126, 127, 128, 129, 192, 193, 254, 255, 256, 257, 3
 
 
 @pytest.mark.parametrize("w,h", [(320, 320), (1280, 720), (1936, 1040)])      # 400, 3,600 and 7,865 tiles
-@pytest.mark.parametrize("kind", ["uniform", "octaves", "pairs", "runs", "walls", "one_depth"])
+@pytest.mark.parametrize("kind", ["uniform", "octaves", "pairs", "twos", "runs", "walls", "one_depth"])
 def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
     """One tile per length, its points scattered over the point order. Depths: spread evenly; over seven octaves on both sides of 2.0; each value twice, as copied points
-    leave them; in runs of a hundred equal ones and, in every tenth list, in the top bits alone; in walls of 1 to 257 points at
+    leave them; in twos that differ in the last place, at even or at odd places of the list, so that in half of the lists such a two lies
+    across every border between rounds of 64 entries; in runs of a hundred equal ones and, in every tenth list, in the top bits alone; in walls of 1 to 257 points at
     nearly one depth, on both sides of the lengths up to which equal ones are put right by counting; one for all."""
     rng = np.random.default_rng(w + len(kind))
     tx = (w + 15) // 16
@@ -52,6 +53,12 @@ def test_list_lengths_at_the_borders_of_the_sorts(w, h, kind):
     elif kind == "pairs":
         depth = rng.uniform(8, 20, n)
         depth[1::2] = depth[:-1:2][:len(depth[1::2])]
+    elif kind == "twos":
+        depth = np.empty(n, dtype=np.float32)
+        for t in np.unique(tile):
+            at = np.flatnonzero(tile == t)
+            i = np.arange(len(at)) + (t // 7) % 2
+            depth[at] = ((8 + 12 * (i // 2) / len(at)).astype(np.float32).view(np.uint32) + (i % 2).astype(np.uint32)).view(np.float32)
     elif kind == "runs":
         depth = 3 + (rng.permutation(n) // 100) * 0.01
         steep = tile % 10 == 0

@@ -506,6 +506,8 @@ def bench_view(args, workload, headline):
     target = torch.from_numpy(np.ascontiguousarray(synth.target_image(args.seed, W, H).transpose(2, 0, 1))).cuda()
     dL = (torch.sign(image - target) / float(3 * W * H)).contiguous()
     n_vis = int((splats.radius > 0).sum().item())
+    # points of the blocks of 256 that have a visible one: binning reads radius and mean2d of all of them
+    n_blocks = 256 * int(torch.nn.functional.pad((splats.radius > 0).to(torch.int32), (0, -n % 256)).view(-1, 256).amax(1).sum().item())
     if args.group_size > 0 and not surfels:
         kept_groups = float(g_keep[:ng].float().mean().item())
     examined, blended = f_stats(cam, n, cap, ws)
@@ -619,8 +621,8 @@ def bench_view(args, workload, headline):
     hbm_bytes = {   # algorithmic bytes per step
         "k_preprocess": 16.0 * n + (32.0 + 12.0 * K + 40.0) * n_vis,
         "k_count_visible": 8.0 * n + 8.0 * n_vis,
-        "k_tile_count": 4.0 * n + 8.0 * n_vis,
-        "k_pack": 4.0 * n + (44.0 + 64.0) * n_vis + 8.0 * P,
+        "k_tile_count": 12.0 * n_blocks,
+        "k_pack": 12.0 * n_blocks + (32.0 + 64.0 + 16.0) * n_vis + 8.0 * P,
         "k_tile_depth_sort": 12.0 * P,
         "k_gather_splat_grads": 8.0 * n + 48.0 * P + 36.0 * n,
         # accumulate: read + write of the visible points' gradient entries; first view: one write of every point's

@@ -10,9 +10,10 @@
 // equal ones, by point index (k_tile_depth_sort, depth_sort.hip), so the result is the same on every run.
 // Five launches where a stable two-pass radix sort of the pairs by tile id took eleven; with the depth sort as it is now, us
 // before and now, in turn on one card: 1M points at 1920x1080 472 -> 438 a step, 225 -> 195 an evaluation; 30k at 1031x517 156 -> 129 a
-// step; 12,000 at 400x300 79 -> 49 an evaluation. The order of points matters more than before: where a block's points lie all
-// over the image, its pairs are on as many tiles, and each costs an atomic add (1M points at 1920x1080, an evaluation: in Z-order
-// 218 -> 183 us, in random order 243 -> 318).
+// step; 12,000 at 400x300 79 -> 48 an evaluation. The order of points matters more than before: where a block's points lie all
+// over the image, its pairs are on as many tiles, and each costs an atomic add, 26 G/s wherever they go (1M points at 1920x1080, an
+// evaluation: in Z-order 213 -> 178 us, in random order 242 -> 300, a tenth of them in random order 214 -> 183). Counting sixteen such blocks
+// together in LDS is no faster (k_tile_count 104 -> 145 us): they have one or two pairs a tile, so the adds hardly become fewer.
 #include "pbdr_internal.h"
 #include "binning_common.h"
 

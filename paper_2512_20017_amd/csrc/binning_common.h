@@ -198,7 +198,7 @@ __device__ __forceinline__ void walk_pairs(PairLds<kThreads>& S, uint32_t total,
 // camera, whose splats cover much of a 4K image; points in no spatial order) are counted one by one in memory instead, and the rank
 // each gets there is kept for k_pack: its tiles are many and have few pairs each, so the table would save little. (Taking the
 // rectangle in bands of the table's size walks all pairs once per band: one 4K street view of 8M points, counting 258 us and
-// packing 433; in memory 64 and 206.)
+// packing 433; in memory 62 and 181.)
 constexpr uint32_t kTableCells = 4096;
 constexpr uint32_t kDirect = 0xffffffffu;      // blk_cells.x of such a block
 
